@@ -14,16 +14,11 @@
 //   * The four wavefronts of a workgroup split K; their partial tiles are added through LDS in a fixed order,
 //     then an epilogue functor consumes the 32x64 tile (rotary + cache append, SwiGLU, split-K partials, or the
 //     running softmax statistics of the LM head). Everything is deterministic.
-#include "tr_internal.h"
+#include "mfma_common.h"
 #include <algorithm>
 #include <type_traits>
 
 namespace tr {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 constexpr int NWAVES = 4;  // wavefronts per workgroup (one per SIMD, 512 registers each); they split K
 constexpr int MAXKW = 14;  // k-steps a wavefront keeps resident (4 wavefronts x 14 x 16 = 896 columns of K per workgroup)
@@ -42,34 +37,6 @@ __device__ __forceinline__ bf16_t m_f32_to_bf16(float f)
 }
 __device__ __forceinline__ float m_bf16_to_f32(bf16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// value = hi + lo with hi = bf16(value), lo = bf16(value - hi), both rounded to nearest even by the hardware's packed
-// conversion (two values per instruction)
-__device__ __forceinline__ void split_hi_lo(const float (&v)[8], uint4 &hi, uint4 &lo)
-{
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const f32x2 x = {v[2 * p], v[2 * p + 1]};
-        h[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
-        const f32x2 rest = {v[2 * p] - __uint_as_float(h[p] << 16), v[2 * p + 1] - __uint_as_float(h[p] & 0xffff0000u)};
-        l[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
-    }
-    hi = make_uint4(h[0], h[1], h[2], h[3]);
-    lo = make_uint4(l[0], l[1], l[2], l[3]);
-}
-
-// Packed activations of one group of up to 64 rows: [k-step][column block][lane] of 16 bytes, column blocks =
-// {hi rows 0-31, (hi rows 32-63), lo rows 0-31, (lo rows 32-63)}; lane = row%32 + 32*(k%16 / 8).
-__device__ __forceinline__ void store_packed(uint4 *pack, int ncb, int row_in_group, int k8 /* index of the 8-column chunk */,
-                                             const float (&v)[8])
-{
-    uint4 hi, lo;
-    split_hi_lo(v, hi, lo);
-    const int ks = k8 >> 1, lane = (row_in_group & 31) + 32 * (k8 & 1), cb = row_in_group >> 5;
-    pack[((size_t)ks * ncb + cb) * 64 + lane] = hi;
-    pack[((size_t)ks * ncb + (ncb >> 1) + cb) * 64 + lane] = lo;
-}
-
 // ------------------------------------------------------------------ one-time weight repack
 
 // pair_dh > 0 (q, k, v matrices, pair_dh = head dim): the rows of a head are reordered so that tile row 2p holds dim
@@ -79,16 +46,6 @@ __device__ __forceinline__ int paired_row(int t, int i, int pair_dh)
 {
     const int tph = pair_dh >> 5, head = t / tph, sub = t % tph;
     return head * pair_dh + sub * 16 + (i >> 1) + (i & 1) * (pair_dh >> 1);
-}
-
-// MFMA row rho of a tile (the accumulator holds rows 8*qd + 4*hf + e in register 4*qd + e of the lanes with lane/32 = hf)
-// carries the tile's feature tile_feature(rho): features are placed so that the accumulator registers {8a .. 8a+7} of
-// one lane, a = 0 or 1, are 8 CONSECUTIVE features 16a + 8hf .. + 7. A wavefront can then hand half of its accumulator
-// to another wavefront and keep, per lane, whole runs of 8 features.
-__host__ __device__ __forceinline__ int tile_feature(int rho)
-{
-    const int qd = rho >> 3, hf = (rho >> 2) & 1, e = rho & 3;
-    return 16 * (qd >> 1) + 8 * hf + 4 * (qd & 1) + e;
 }
 
 __global__ void repack_kernel(const bf16_t *W, int N, int K, uint4 *Wt, int KS, int dst_tile0, int dst_tile_stride, int n_tiles, int pair_dh)
@@ -841,12 +798,9 @@ struct EpiPartial {   // split-K partial sums: part[split][m][n]
 template <typename KT>
 struct EpiQkv {       // bias, rotary embedding, q out, cache append; tiles hold rotary pairs next to each other (see repack_kernel)
     static constexpr bool half_only = true;   // launched with GemmArgs::half = 1: 32-row workgroups only
-    const float *bias;        // concatenated [qw + 2 kvw], natural feature order
-    const float2 *rope;
+    QkvOut<KT> out;
     const int *slot, *pos;
-    float *q;
-    KT *kc, *vc;
-    int M, Hq, Hkv, dh, max_seq, qw, vts;   // max_seq, vts: positions per storage unit of the cache (a slot or a page)
+    int M;
     const int *ptab;          // paged cache: page table [slot][maxp] and page length; page = 0: the unit is the slot
     int page, maxp;
     int rpos, runit, rupos;   // position of this thread's batch row (for the rotation) and where its key and value go:
@@ -861,56 +815,9 @@ struct EpiQkv {       // bias, rotary embedding, q out, cache append; tiles hold
         if (live) M = min(M, *live);
     }
     __device__ void row_ready(float *, int, int) {}
-    // v: tile rows i0..i0+7 = the pairs (j, j + dh/2), j = 16*sub + i0/2 .. +3, as (first, partner) x 4
     template <int PAR> __device__ void tile(int t, int m, int i0, const float (&v)[8])
     {
-        if (m >= M) return;
-        const int tph = dh >> 5, half = dh >> 1, hh = t / tph, j0 = (t % tph) * 16 + (i0 >> 1), p = rpos;
-        const float4 ba = *reinterpret_cast<const float4 *>(bias + hh * dh + j0), bb = *reinterpret_cast<const float4 *>(bias + hh * dh + half + j0);
-        const float a[4] = {v[0] + ba.x, v[2] + ba.y, v[4] + ba.z, v[6] + ba.w}, b[4] = {v[1] + bb.x, v[3] + bb.y, v[5] + bb.z, v[7] + bb.w};
-        float lo[4], hi[4];
-        if (hh < Hq + Hkv) {
-            const float4 *rp = reinterpret_cast<const float4 *>(rope + (size_t)p * half + j0);   // 4 (cos, sin) pairs, 32 bytes, aligned
-            const float4 c0 = rp[0], c1 = rp[1];
-            const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sy[4] = {c0.y, c0.w, c1.y, c1.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                lo[e] = a[e] * cx[e] - b[e] * sy[e];
-                hi[e] = b[e] * cx[e] + a[e] * sy[e];
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { lo[e] = a[e]; hi[e] = b[e]; }
-        }
-        if (hh < Hq) {
-            float *dst = q + (size_t)m * qw + hh * dh + j0;
-            *reinterpret_cast<float4 *>(dst) = make_float4(lo[0], lo[1], lo[2], lo[3]);
-            *reinterpret_cast<float4 *>(dst + half) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-        } else {
-            const int head = hh < Hq + Hkv ? hh - Hq : hh - Hq - Hkv;
-            if (hh < Hq + Hkv || vts == 0) {
-                KT *dst = (hh < Hq + Hkv ? kc : vc) + (((size_t)runit * Hkv + head) * max_seq + rupos) * dh + j0;
-                store4(dst, lo);
-                store4(dst + half, hi);
-            } else {   // block-transposed V: one position of 8 dim rows
-                KT *dst = vc + ((((size_t)runit * Hkv + head) * (vts >> 5) + (rupos >> 5)) * dh + j0) * 32 + (rupos & 31);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) { store1(dst + e * 32, lo[e]); store1(dst + (half + e) * 32, hi[e]); }
-            }
-        }
-    }
-    __device__ static void store4(float *dst, const float (&v)[4]) { *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]); }
-    __device__ static void store4(bf16_t *dst, const float (&v)[4])
-    {
-        const f32x2 x0 = {v[0], v[1]}, x1 = {v[2], v[3]};
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(x0, bf16x2)),
-                                                     __builtin_bit_cast(uint32_t, __builtin_convertvector(x1, bf16x2)));
-    }
-    __device__ static void store1(float *dst, float v) { *dst = v; }
-    __device__ static void store1(bf16_t *dst, float v)
-    {
-        const f32x2 x = {v, 0.f};
-        *dst = (bf16_t)__builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+        if (m < M) qkv_emit<false>(out, t, m, i0, v, rpos, runit, rupos);
     }
     __device__ void end(float *, int, int) {}
 };
@@ -1461,12 +1368,12 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(Dims D, const float *pa
             q[(size_t)m * D.qw + n2] = y2;
         } else if (hh < D.Hq + D.Hkv) {
             KT *dst = kc + k_offset(D, at.unit, hh - D.Hq, at.pos, 0);
-            EpiQkv<KT>::store1(dst + j, y1);
-            EpiQkv<KT>::store1(dst + j + half, y2);
+            kv_store1(dst + j, y1);
+            kv_store1(dst + j + half, y2);
         } else {
             const int head = hh - D.Hq - D.Hkv;
-            EpiQkv<KT>::store1(vc + v_offset(D, at.unit, head, at.pos, j), y1);
-            EpiQkv<KT>::store1(vc + v_offset(D, at.unit, head, at.pos, j + half), y2);
+            kv_store1(vc + v_offset(D, at.unit, head, at.pos, j), y1);
+            kv_store1(vc + v_offset(D, at.unit, head, at.pos, j + half), y2);
         }
     }
 }
@@ -1588,6 +1495,15 @@ void plan_partial(int KS, int n_tiles, int groups, int *nsplit, int *ksw, int *t
     *tiles_per_wg = tiles_per_workgroup(n_tiles, S * groups, 1);
 }
 
+int gemm_split_steps(int K, int N, int M)
+{
+    int S, ksw, tpw;
+    plan_partial(K / 16, (N + 31) / 32, (M + 63) / 64, &S, &ksw, &tpw);
+    return ksw;
+}
+
+int oproj_tiles_per_range(const Dims &D, int M) { return tiles_per_workgroup((D.d + 31) / 32, M > 32 ? 2 * ((M + 63) / 64) : 1, 1); }
+
 int gemm_partial_splits(int K, int N)
 {
     int S, ksw, tpw;
@@ -1628,15 +1544,13 @@ void launch_gemm_qkv(hipStream_t s, int kdt, const Dims &D, const void *Wt, cons
     a.tiles_per_wg = tiles_per_workgroup(a.n_tiles, rows.n > 32 ? 2 * ((rows.n + 63) / 64) : 1, 1);
     a.half = 1;
     a.live = rows.live;
-    if (kdt == DT_F32) {
-        EpiQkv<float> e{bias, rope, rows.slot, rows.pos, q, (float *)kc, (float *)vc, rows.n, D.Hq, D.Hkv, D.dh, kv_unit_len(D), D.qw, kv_unit_vts(D),
-                        D.ptab, D.page, D.maxp, 0, 0, 0, rows.live};
+    auto go = [&](auto kt) {
+        using KT = decltype(kt);
+        EpiQkv<KT> e{{bias, rope, q, (KT *)kc, (KT *)vc, D.Hq, D.Hkv, D.dh, kv_unit_len(D), D.qw, kv_unit_vts(D)},
+                     rows.slot, rows.pos, rows.n, D.ptab, D.page, D.maxp, 0, 0, 0, rows.live};
         launch_gemm(s, a, 1, e);
-    } else {
-        EpiQkv<bf16_t> e{bias, rope, rows.slot, rows.pos, q, (bf16_t *)kc, (bf16_t *)vc, rows.n, D.Hq, D.Hkv, D.dh, kv_unit_len(D), D.qw, kv_unit_vts(D),
-                         D.ptab, D.page, D.maxp, 0, 0, 0, rows.live};
-        launch_gemm(s, a, 1, e);
-    }
+    };
+    if (kdt == DT_F32) go(float{}); else go(bf16_t{});
 }
 
 void launch_gemm_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, void *hpack, const int *live, const float *sumsq,
@@ -1659,7 +1573,7 @@ int launch_gemm_oproj_residual(hipStream_t s, const Dims &D, const void *Wt, con
 {
     GemmArgs a{};
     a.Wt = (const uint4 *)Wt; a.pack = (const uint4 *)pack_a; a.KS = D.qw / 16; a.ksw = a.KS; a.n_tiles = (D.d + 31) / 32; a.M = M; a.live = live;
-    a.tiles_per_wg = tiles_per_workgroup(a.n_tiles, M > 32 ? 2 * ((M + 63) / 64) : 1, 1);
+    a.tiles_per_wg = oproj_tiles_per_range(D, M);
     a.half = 1;
     EpiResidualNorm e{x, (const bf16_t *)gain, (uint4 *)pack_out, sumsq, M, D.d, mfma_ncb(M), ss_stride, 0, 0, 0.f};
     launch_gemm(s, a, 1, e);

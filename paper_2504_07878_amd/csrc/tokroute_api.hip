@@ -353,6 +353,62 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
             launch_attention(s, ctx->c.kv_dtype, D, q_, ctx->kc_layer(l), ctx->vc_layer(l), rows_, max_ctx_, part_, part_floats_, cnt_, att_, pack_, ncb_, defer_);
         }
     };
+    // Many rows: block products (tile_kernels.hip) whose epilogues finish the layer, with the bits of the kernels below. Measured per layer, 0.5B-class
+    // at 1024 / 2048 / 8192 rows: 131 / 190 / 598 us against 119 / 201 / 697; 7B-class at 128 / 256 / 512 / 1152 rows: 230 / 420 / 640 / 1090 against
+    // 229 / 483 / 836 / 1690.
+    if (!live && ((L.mfma && R >= 1536) || (L.split && R >= 160))) {
+        float *rstd = ctx->at<float>(L.sumsq), *part = ctx->at<float>(L.part);
+        const bool defer = L.mfma && gemm_oproj_residual_supported(D);   // the output projection packs the FFN input itself
+        const int steps_d = D.d / 16, n_qkv = D.qw + 2 * D.kvw, n_gu = 2 * ((D.F + 31) / 32) * 32;
+        const int k_qkv = L.mfma ? steps_d : gemm_split_steps(D.d, n_qkv, R), k_gu = L.mfma ? steps_d : gemm_split_steps(D.d, n_gu, R);
+        const int k_o = defer ? D.qw / 16 : gemm_split_steps(D.qw, D.d, R), k_d = gemm_split_steps(D.F, D.d, R);
+        // a wide model's products with few blocks keep their K splits apart (7B-class at 512 / 768 / 1152 rows, down projection with the partials' share of the
+        // next launch 181 / 253 / 371 us, in one piece 188 / 277 / 317; q|k|v 44 blocks of 128 features: in one piece from 320 rows on)
+        const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = L.mfma || tile_fills_chip(D.d, R, 448);
+        PrepArgs p{};
+        p.x = x; p.M = R; p.d = D.d; p.eps = D.eps; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = 4; p.part = part; p.part_M = R;
+        int pending = 0, ns = 0;
+        for (int l = 0; l < D.L; ++l) {
+            const LayerW &w = ctx->layers[(size_t)l];
+            p.gain = (const bf16_t *)w.ln1; p.nsplit = pending;
+            { Bracket br(ctx, s, TR_KERNEL_PREP); launch_prep(s, p); }
+            {
+                Bracket br(ctx, s, TR_KERNEL_QKV);
+                if (whole_qkv)
+                    launch_tile_qkv(s, ctx->c.kv_dtype, D, ctx->wt(l, L.wt_qkv), ctx->at<uint4>(L.pack_d), ctx->bias(l), rows, ctx->at<float2>(L.rope), q, ctx->kc_layer(l),
+                                    ctx->vc_layer(l), k_qkv);
+                else {
+                    launch_gemm_partial(s, ctx->wt(l, L.wt_qkv), ctx->at<uint4>(L.pack_d), D.d, n_qkv, R, part, &ns);
+                    launch_qkv_finish(s, ctx->c.kv_dtype, D, part, ns, ctx->bias(l), rows, ctx->at<float2>(L.rope), q, ctx->kc_layer(l), ctx->vc_layer(l));
+                }
+            }
+            attend(l, q, rows, max_ctx, ctx->at<float>(L.attn_part), attn_part_floats, ctx->at<int>(L.attn_cnt), att, ctx->at<uint4>(L.pack_a), 4, nullptr);
+            p.nsplit = 0;
+            {
+                Bracket br(ctx, s, TR_KERNEL_OPROJ);
+                if (defer || whole_d)
+                    launch_tile_residual(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, x, w.ln2, defer ? ctx->at<uint4>(L.pack_d) : nullptr, k_o);
+                else launch_tile_partial(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, part, &p.nsplit);
+                if (defer) launch_row_rstd(s, x, R, D.d, oproj_tiles_per_range(D, R), D.eps, rstd);
+            }
+            if (!defer) {
+                p.gain = (const bf16_t *)w.ln2;
+                Bracket br(ctx, s, TR_KERNEL_PREP);
+                launch_prep(s, p);
+            }
+            {
+                Bracket br(ctx, s, TR_KERNEL_GATEUP);
+                launch_tile_swiglu(s, D, ctx->wt(l, L.wt_gu), ctx->at<uint4>(L.pack_d), R, ctx->at<uint4>(L.pack_h), defer ? rstd : nullptr, k_gu);
+            }
+            {
+                Bracket br(ctx, s, TR_KERNEL_DOWN);
+                pending = 0;
+                if (whole_d) launch_tile_residual(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, x, nullptr, nullptr, k_d);
+                else launch_tile_partial(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, part, &pending);
+            }
+        }
+        return pending;
+    }
     // Wide model, 3 and 4 rows whose count the host knows: the streaming kernels that keep the rows in registers (the last branch below)
     // take fewer launches than the matrix-core path with its partials and finishing kernels (7B-class step at 3 rows: 3.9 -> 3.5 ms).
     const bool rows_kernels = !live && ffn_rows_supported(ctx->c.dtype, D, R);

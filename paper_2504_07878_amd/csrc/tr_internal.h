@@ -185,6 +185,20 @@ void launch_gemm_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void
 bool gemm_oproj_residual_supported(const Dims &D);
 int launch_gemm_oproj_residual(hipStream_t s, const Dims &D, const void *Wt, const void *pack_a, int M, float *x, const void *gain, void *pack_out,
                                float *sumsq, int ss_stride, const int *live = nullptr);
+// ---- many rows (tile_kernels.hip): packed activations with 4 column blocks per 64-row group (more than 32 rows)
+// ksw: k-steps of 16 per split of the sum, as planned for the skinny kernels (gemm_split_steps); K / 16: one split
+int gemm_split_steps(int K, int N, int M);
+bool tile_fills_chip(int N, int M, int blocks);   // whether M rows x N features make at least that many blocks of 64 x 128
+void launch_tile_qkv(hipStream_t s, int kdt, const Dims &D, const void *Wt, const void *pack, const float *bias, Rows rows, const float2 *rope, float *q,
+                     void *kc, void *vc, int ksw);
+void launch_tile_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, void *hpack, const float *rstd, int ksw);
+// x[M][N] += W . A; pack_out != NULL: also the next layer's packed input x * gain
+void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, int ksw);
+// split-K partials of the same sums (see launch_gemm_partial)
+void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit);
+// tile ranges of the skinny output projection over M rows (see launch_gemm_oproj_residual): tiles per range
+int oproj_tiles_per_range(const Dims &D, int M);
+void launch_row_rstd(hipStream_t s, const float *x, int M, int d, int tiles_per_range, float eps, float *rstd);
 // Wide models (K beyond what one workgroup keeps resident): every linear layer goes through split-K partials, and the
 // layers with a non-linear epilogue are finished by a small kernel of their own.
 // number of partial buffers launch_gemm_partial will produce for a K x N layer
