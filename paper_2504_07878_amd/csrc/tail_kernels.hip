@@ -39,8 +39,28 @@ __device__ __forceinline__ float t_wave_sum(float v)
     return v;
 }
 
-constexpr int SLICE_ROWS = 128;  // vocabulary rows per workgroup (32 per wavefront)
-int tail_slice_rows() { return SLICE_ROWS; }
+template <typename WT> struct TRaw8;
+template <> struct TRaw8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void load(const float *p) { a = *reinterpret_cast<const float4 *>(p); b = *reinterpret_cast<const float4 *>(p + 4); }
+    __device__ __forceinline__ void widen(float (&w)[8]) const { w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w; }
+};
+template <> struct TRaw8<bf16_t> {
+    uint4 v;
+    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
+    __device__ __forceinline__ void widen(float (&w)[8]) const
+    {
+        w[0] = __uint_as_float(v.x << 16); w[1] = __uint_as_float(v.x & 0xffff0000u);
+        w[2] = __uint_as_float(v.y << 16); w[3] = __uint_as_float(v.y & 0xffff0000u);
+        w[4] = __uint_as_float(v.z << 16); w[5] = __uint_as_float(v.z & 0xffff0000u);
+        w[6] = __uint_as_float(v.w << 16); w[7] = __uint_as_float(v.w & 0xffff0000u);
+    }
+};
+
+// Vocabulary rows per workgroup (a quarter per wavefront, four at a time): 128, fewer when that would leave compute units without a
+// workgroup (4096 rows of 256 fp32 columns: 32 workgroups of 128 rows 24.6 us, 256 of 16 rows, with the norm, 5.7 us).
+constexpr int SLICE_ROWS = 128;
+int tail_slice_rows(int V) { return std::min(SLICE_ROWS, (V + 4095) / 4096 * 16); }
 
 // ------------------------------------------------------------------ final RMSNorm; exposes the hidden state
 
@@ -66,10 +86,28 @@ __global__ __launch_bounds__(256) void tail_norm_kernel(int d, float eps, const 
 
 // ------------------------------------------------------------------ LM head slice: running softmax statistics
 
-// part[slice][row] = {max, argmax (as int bits), sum exp(z - max), unused}
-template <typename WT, int MB>
-__global__ __launch_bounds__(256) void lmhead_kernel(const WT *head, int V, int d, const float *hn, int n, float4 *part, float *logits)
+// the four wavefronts' triples of row m (they hold increasing vocabulary ranges) -> out[m]
+template <int MB> __device__ __forceinline__ void merge_wavefronts(const float4 (&wpart)[4][MB], int m, float4 *out)
 {
+    float M = -INFINITY; int I = 0x7fffffff;
+    for (int w = 0; w < 4; ++w) {
+        const float4 p = wpart[w][m];
+        if (p.x > M) { M = p.x; I = __float_as_int(p.y); }
+    }
+    float S = 0.f;
+    for (int w = 0; w < 4; ++w) {
+        const float4 p = wpart[w][m];
+        if (p.x > -INFINITY) S += p.z * expf(p.x - M);
+    }
+    out[m] = make_float4(M, __int_as_float(I), S, 0.f);
+}
+
+// part[slice][row] = {max, argmax (as int bits), sum exp(z - max), unused}
+// ROWS: vocabulary rows of a slice where the launcher can fix them (a loop of known length), 0: slice_rows.
+template <typename WT, int MB, int ROWS>
+__global__ __launch_bounds__(256) void lmhead_kernel(const WT *head, int V, int d, const float *hn, int n, int slice_rows, float4 *part, float *logits)
+{
+    if (ROWS) slice_rows = ROWS;
     __shared__ float4 wpart[4][MB];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int r0 = blockIdx.y * MB;
@@ -81,8 +119,8 @@ __global__ __launch_bounds__(256) void lmhead_kernel(const WT *head, int V, int 
 #pragma unroll
     for (int m = 0; m < MB; ++m) { mx[m] = -INFINITY; sum[m] = 0.f; idx[m] = 0x7fffffff; }
 
-    const int v_begin = blockIdx.x * SLICE_ROWS + wave * (SLICE_ROWS / 4);
-    for (int v0 = v_begin; v0 < v_begin + SLICE_ROWS / 4 && v0 < V; v0 += 4) {
+    const int v_begin = blockIdx.x * slice_rows + wave * (slice_rows / 4);
+    for (int v0 = v_begin; v0 < v_begin + slice_rows / 4 && v0 < V; v0 += 4) {
         float acc[4][MB];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
@@ -125,20 +163,120 @@ __global__ __launch_bounds__(256) void lmhead_kernel(const WT *head, int V, int 
         for (int m = 0; m < MB; ++m) wpart[wave][m] = make_float4(mx[m], __int_as_float(idx[m]), sum[m], 0.f);
     }
     __syncthreads();
-    if (threadIdx.x < MB && r0 + threadIdx.x < n) {
-        const int m = threadIdx.x;
-        float M = -INFINITY; int I = 0x7fffffff;
-        for (int w = 0; w < 4; ++w) {      // wavefronts hold increasing vocabulary ranges
-            const float4 p = wpart[w][m];
-            if (p.x > M) { M = p.x; I = __float_as_int(p.y); }
-        }
-        float S = 0.f;
-        for (int w = 0; w < 4; ++w) {
-            const float4 p = wpart[w][m];
-            if (p.x > -INFINITY) S += p.z * expf(p.x - M);
-        }
-        part[(size_t)blockIdx.x * n + r0 + m] = make_float4(M, __int_as_float(I), S, 0.f);
+    if (threadIdx.x < MB && r0 + threadIdx.x < n) merge_wavefronts<MB>(wpart, threadIdx.x, part + (size_t)blockIdx.x * n + r0);
+}
+
+// The same slice for a small model (d <= SMALL_HEAD_D) whose head gives a compute unit one workgroup at most: the launch is a chain of latencies,
+// so the final norm joins it. Every workgroup requests its first weights, then normalises the MB rows into LDS (workgroup 0 of a row also
+// leaves them in hn and hidden), and the cross-lane sums of the four vocabulary rows run side by side. Sums of squares in tail_norm_kernel's order.
+constexpr int SMALL_HEAD_D = 1024;
+
+template <typename WT, int MB>
+__global__ __launch_bounds__(256) void lmhead_norm_kernel(const WT *head, int V, int d, float eps, const WT *gain, const float *x, const int *gather, int n,
+                                                          int slice_rows, float4 *part, float *logits, float *hn, float *hidden, int hidden_tap)
+{
+    __shared__ float4 wpart[4][MB];
+    __shared__ __attribute__((aligned(16))) float s_x[MB][SMALL_HEAD_D];
+    __shared__ float red[MB][4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r0 = blockIdx.y * MB;
+    const int v_begin = blockIdx.x * slice_rows + wave * (slice_rows / 4), v_end = min(v_begin + slice_rows / 4, V);
+    TRaw8<WT> w[2][4];
+    // vocabulary rows v .. v + 3, columns lane*8 and 512 + lane*8 (both clamped: what lies past the end is not used)
+    auto request = [&](int v) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (h == 0 || d > 512)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) w[h][r].load(head + (size_t)min(v + r, V - 1) * d + min(h * 512 + lane * 8, d - 8));
+    };
+    request(v_begin);
+    float xv[MB][4], gv[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) gv[i] = t_widen(gain, min((int)threadIdx.x + 256 * i, d - 1));
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const int row = min(r0 + m, n - 1);
+        const float *xr = x + (size_t)(gather ? gather[row] : row) * d;
+        float ss = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xv[m][i] = xr[min((int)threadIdx.x + 256 * i, d - 1)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ss = threadIdx.x + 256 * i < d ? fmaf(xv[m][i], xv[m][i], ss) : ss;
+        ss = t_wave_sum(ss);
+        if (lane == 0) red[m][wave] = ss;
     }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+        const float rstd = 1.0f / sqrtf((red[m][0] + red[m][1] + red[m][2] + red[m][3]) / (float)d + eps);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = threadIdx.x + 256 * i;
+            if (j >= d) continue;
+            const float v = xv[m][i] * rstd * gv[i];
+            s_x[m][j] = v;
+            if (blockIdx.x == 0 && r0 + m < n) {
+                hn[(size_t)(r0 + m) * d + j] = v;
+                if (hidden) hidden[(size_t)(r0 + m) * d + j] = hidden_tap == 0 ? v : xv[m][i];
+            }
+        }
+    }
+    __syncthreads();
+    float mx[MB], sum[MB];
+    int idx[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m) { mx[m] = -INFINITY; sum[m] = 0.f; idx[m] = 0x7fffffff; }
+    for (int v0 = v_begin; v0 < v_end; v0 += 4) {
+        if (v0 != v_begin) request(v0);
+        float z[4][MB];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int m = 0; m < MB; ++m) z[r][m] = 0.f;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = h * 512 + lane * 8;
+            if (k >= d) continue;
+            float wv[4][8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) w[h][r].widen(wv[r]);
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                float xe[8];
+                t_load8(&s_x[m][k], xe);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) z[r][m] = fmaf(wv[r][e], xe[e], z[r][m]);
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int m = 0; m < MB; ++m) z[r][m] += __shfl_xor(z[r][m], o, 64);
+#pragma unroll
+        for (int m = 0; m < MB; ++m) {
+            float top = mx[m];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (v0 + r >= V) continue;
+                if (logits && lane == 0 && r0 + m < n) logits[(size_t)(r0 + m) * V + v0 + r] = z[r][m];
+                if (z[r][m] > top) { top = z[r][m]; idx[m] = v0 + r; }   // strict: the lowest index wins ties
+            }
+            if (top > mx[m]) { sum[m] *= expf(mx[m] - top); mx[m] = top; }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (v0 + r < V) sum[m] += expf(z[r][m] - mx[m]);
+        }
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int m = 0; m < MB; ++m) wpart[wave][m] = make_float4(mx[m], __int_as_float(idx[m]), sum[m], 0.f);
+    }
+    __syncthreads();
+    if (threadIdx.x < MB && r0 + threadIdx.x < n) merge_wavefronts<MB>(wpart, threadIdx.x, part + (size_t)blockIdx.x * n + r0);
 }
 
 // ------------------------------------------------------------------ merge the slices, run the router, set the flag
@@ -154,24 +292,6 @@ __global__ __launch_bounds__(256) void lmhead_kernel(const WT *head, int V, int 
 constexpr int TF_WAVES = 16;
 constexpr int TF_THREADS = 64 * TF_WAVES;
 constexpr int RQ = 4;   // hidden units of the router per wavefront and batch of requests (8 requests in flight per lane)
-
-template <typename WT> struct TRaw8;
-template <> struct TRaw8<float> {
-    float4 a, b;
-    __device__ __forceinline__ void load(const float *p) { a = *reinterpret_cast<const float4 *>(p); b = *reinterpret_cast<const float4 *>(p + 4); }
-    __device__ __forceinline__ void widen(float (&w)[8]) const { w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w; w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w; }
-};
-template <> struct TRaw8<bf16_t> {
-    uint4 v;
-    __device__ __forceinline__ void load(const bf16_t *p) { v = *reinterpret_cast<const uint4 *>(p); }
-    __device__ __forceinline__ void widen(float (&w)[8]) const
-    {
-        w[0] = __uint_as_float(v.x << 16); w[1] = __uint_as_float(v.x & 0xffff0000u);
-        w[2] = __uint_as_float(v.y << 16); w[3] = __uint_as_float(v.y & 0xffff0000u);
-        w[4] = __uint_as_float(v.z << 16); w[5] = __uint_as_float(v.z & 0xffff0000u);
-        w[6] = __uint_as_float(v.w << 16); w[7] = __uint_as_float(v.w & 0xffff0000u);
-    }
-};
 
 template <typename WT>
 __global__ __launch_bounds__(TF_THREADS) void tail_final_kernel(int d, int rh, TailArgs t)
@@ -340,21 +460,50 @@ __global__ __launch_bounds__(TF_THREADS) void tail_final_kernel(int d, int rh, T
 template <typename WT>
 static void launch_lmhead_gemv_t(hipStream_t s, const Dims &D, const TailArgs &t)
 {
-    if (t.n == 1)
-        hipLaunchKernelGGL((lmhead_kernel<WT, 1>), dim3(t.nslices, 1), dim3(256), 0, s, (const WT *)t.head, D.V, D.d, t.hn, t.n,
+    auto go = [&](auto kern, int mb) {
+        hipLaunchKernelGGL(kern, dim3(t.nslices, (t.n + mb - 1) / mb), dim3(256), 0, s, (const WT *)t.head, D.V, D.d, t.hn, t.n, tail_slice_rows(D.V),
                            (float4 *)t.part, t.logits);
-    else if (t.n == 2)
-        hipLaunchKernelGGL((lmhead_kernel<WT, 2>), dim3(t.nslices, 1), dim3(256), 0, s, (const WT *)t.head, D.V, D.d, t.hn, t.n,
-                           (float4 *)t.part, t.logits);
-    else
-        hipLaunchKernelGGL((lmhead_kernel<WT, 4>), dim3(t.nslices, (t.n + 3) / 4), dim3(256), 0, s, (const WT *)t.head, D.V, D.d, t.hn, t.n,
-                           (float4 *)t.part, t.logits);
+    };
+    if (tail_slice_rows(D.V) == SLICE_ROWS) {
+        if (t.n == 1) go(lmhead_kernel<WT, 1, SLICE_ROWS>, 1);
+        else if (t.n == 2) go(lmhead_kernel<WT, 2, SLICE_ROWS>, 2);
+        else go(lmhead_kernel<WT, 4, SLICE_ROWS>, 4);
+    } else {
+        if (t.n == 1) go(lmhead_kernel<WT, 1, 0>, 1);
+        else if (t.n == 2) go(lmhead_kernel<WT, 2, 0>, 2);
+        else go(lmhead_kernel<WT, 4, 0>, 4);
+    }
+}
+
+template <typename WT>
+static void launch_lmhead_norm_t(hipStream_t s, const Dims &D, const TailArgs &t)
+{
+    auto go = [&](auto kern, int mb) {
+        hipLaunchKernelGGL(kern, dim3(t.nslices, (t.n + mb - 1) / mb), dim3(256), 0, s, (const WT *)t.head, D.V, D.d, D.eps, (const WT *)t.final_norm, t.x,
+                           t.gather, t.n, tail_slice_rows(D.V), (float4 *)t.part, t.logits, t.hn, t.hidden, t.hidden_tap);
+    };
+    if (t.n == 1) go(lmhead_norm_kernel<WT, 1>, 1);
+    else if (t.n == 2) go(lmhead_norm_kernel<WT, 2>, 2);
+    else go(lmhead_norm_kernel<WT, 4>, 4);
+}
+
+// Final norm and LM head. In one launch where the norm, repeated by every workgroup, costs less than a launch of its own: one slice per compute
+// unit (fewer than SLICE_ROWS vocabulary rows each), rows that fit a workgroup's LDS, and few of them. (A hidden state that replaces x in place
+// keeps the launch of its own: here every workgroup reads x.)
+static bool lmhead_takes_norm(const Dims &D, const TailArgs &t)
+{
+    return D.d <= SMALL_HEAD_D && tail_slice_rows(D.V) < SLICE_ROWS && t.n <= 8 && t.hidden != t.x;
 }
 
 void launch_lmhead_gemv(hipStream_t s, int wdt, const Dims &D, const TailArgs &t)
 {
-    if (wdt == DT_F32) launch_lmhead_gemv_t<float>(s, D, t);
-    else launch_lmhead_gemv_t<bf16_t>(s, D, t);
+    if (lmhead_takes_norm(D, t)) {
+        if (wdt == DT_F32) launch_lmhead_norm_t<float>(s, D, t);
+        else launch_lmhead_norm_t<bf16_t>(s, D, t);
+    } else {
+        if (wdt == DT_F32) launch_lmhead_gemv_t<float>(s, D, t);
+        else launch_lmhead_gemv_t<bf16_t>(s, D, t);
+    }
 }
 
 void launch_tail_final(hipStream_t s, int wdt, const Dims &D, const TailArgs &t)
@@ -369,6 +518,7 @@ void launch_tail_final(hipStream_t s, int wdt, const Dims &D, const TailArgs &t)
 
 void launch_tail_norm(hipStream_t s, int wdt, const Dims &D, const TailArgs &t)
 {
+    if (lmhead_takes_norm(D, t)) return;
     if (wdt == DT_F32)
         hipLaunchKernelGGL(tail_norm_kernel<float>, dim3(t.n), dim3(256), 0, s, D.d, D.eps, (const float *)t.final_norm, t.x, t.gather, t.hn,
                            t.hidden, t.hidden_tap);

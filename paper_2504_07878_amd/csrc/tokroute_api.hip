@@ -119,7 +119,7 @@ Layout make_layout(const tr_config *c)
     // rows of one pass over the weights: a decode batch, one whole prompt, and room to pack several prompts or catch-up
     // segments into a pass (more 64-row groups per launch: the activations a workgroup keeps are reused for more tiles)
     L.max_rows = std::max({c->max_batch, c->max_seq, std::min(8192, c->max_batch * c->max_seq)});
-    L.nslices = (c->vocab + tail_slice_rows() - 1) / tail_slice_rows();
+    L.nslices = (c->vocab + tail_slice_rows(c->vocab) - 1) / tail_slice_rows(c->vocab);
     const size_t R = (size_t)L.max_rows;
     // room for up to 32 context splits of a full decode batch
     L.attn_part_floats = (size_t)c->max_batch * c->n_q_heads * 32 * (c->head_dim + 4);
@@ -565,7 +565,7 @@ TailArgs tail_args(tr_ctx *ctx, const tr_out *out, int out_offset, int n)
     t.n = n;
     t.hn = ctx->at<float>(L.hn);
     t.part = ctx->at<float>(L.tail_part);
-    t.nslices = L.nslices; t.slice_rows = tail_slice_rows();
+    t.nslices = L.nslices;
     t.token = out->token + out_offset; t.conf = out->conf + out_offset; t.score = out->score + out_offset; t.flag = out->flag + out_offset;
     t.hidden = out->hidden ? out->hidden + (size_t)out_offset * ctx->D.d : nullptr;
     t.logits = out->logits ? out->logits + (size_t)out_offset * ctx->D.V : nullptr;
@@ -1017,7 +1017,7 @@ int tr_tail_noalloc(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, co
     if (!ctx) return TR_ERR_INVALID_ARG;
     if (!x || !check_out(out)) return fail(ctx, TR_ERR_INVALID_ARG, "tr_tail_noalloc: null argument");
     if ((uintptr_t)x % 16) return fail(ctx, TR_ERR_INVALID_ARG, "tr_tail_noalloc: x must be 16-byte aligned");
-    const int nslices = (ctx->c.vocab + tail_slice_rows() - 1) / tail_slice_rows();
+    const int nslices = ctx->lay.nslices;
     if (n < 1 || n > NOALLOC_MAX_ROWS) return fail(ctx, TR_ERR_CAPACITY, "tr_tail_noalloc: n outside [1, 64]");
     if (ctx->c.d_model > NOALLOC_MAX_D || nslices > NOALLOC_MAX_SLICES)
         return fail(ctx, TR_ERR_CAPACITY, "tr_tail_noalloc: d_model above 4096 or vocabulary above 262144");

@@ -100,7 +100,7 @@ struct TailArgs {
     int n;
     float *hn;               // scratch [n][d]: normalised rows
     float *part;             // scratch [nslices][n][4]: slice max, argmax, sum-exp
-    int nslices, slice_rows;
+    int nslices;
     int32_t *token; float *conf, *score; int32_t *flag; float *hidden, *logits;
     long long *counters;     // [max_batch][2] or NULL
     int counter_mode;        // 0 none, 1 add (decode), 2 set (prefill)
@@ -160,8 +160,8 @@ void launch_fill_int(hipStream_t s, int *p, int n, int value);   // p[0..n) = va
 void launch_active_setup(hipStream_t s, int n, const int *cand_slot, const int *host_len, const int *flags_dev, const int *tokens_dev, int n_max,
                          int vocab, int *dev_len, int *d_slot, int *d_tok, int *d_pos, int *active);
 
-int tail_slice_rows();
-void launch_tail_norm(hipStream_t s, int wdt, const Dims &D, const TailArgs &t);   // final RMSNorm of the streaming tail: t.x -> t.hn (and t.hidden)
+int tail_slice_rows(int V);   // vocabulary rows per workgroup of the streaming head
+void launch_tail_norm(hipStream_t s, int wdt, const Dims &D, const TailArgs &t);   // final RMSNorm of the streaming tail: t.x -> t.hn (and t.hidden); no launch where launch_lmhead_gemv does it itself
 void launch_tail_final(hipStream_t s, int wdt, const Dims &D, const TailArgs &t);
 void launch_lmhead_gemv(hipStream_t s, int wdt, const Dims &D, const TailArgs &t);
 
