@@ -41,6 +41,7 @@ struct Layout {
     size_t r1;         // sums of the router's first layer, [max_batch][router_tiles * 32], written by the LM-head launch
     int router_tiles;  // tiles of router weight rows appended to the repacked head matrix (0: the merge kernel computes the router itself)
     size_t qblock;     // query-row blocks of a pass (prompts, catch-up segments): first row * 8 + rows
+    size_t pack8;      // FFN activations of a step of few rows as matrix operands
     size_t kvn;        // new keys and values of up to two decode rows, [row][2][kv width] floats (fused q|k|v + attention kernel)
     size_t dev_len;    // device-side sequence lengths [max_batch], used by the steps whose rows are selected on the device
     size_t sumsq;      // rows' sums of squares per tile range of the output projection, [max_rows][ss_stride] floats (deferred RMSNorm)
@@ -174,6 +175,7 @@ Layout make_layout(const tr_config *c)
         L.part = take(part_bytes);
     }
     L.qblock = take(R * 4);
+    L.pack8 = take((size_t)((c->d_ffn + 31) / 32) * 1024);
     L.kvn = take(2 * 2 * kvw * 4);
     L.dev_len = take((size_t)c->max_batch * 4);
     L.ss_stride = 32;
@@ -409,9 +411,21 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
         }
         return pending;
     }
-    // Wide model, 3 and 4 rows whose count the host knows: the streaming kernels that keep the rows in registers (the last branch below)
-    // take fewer launches than the matrix-core path with its partials and finishing kernels (7B-class step at 3 rows: 3.9 -> 3.5 ms).
+    // Wide model, 2 to 4 rows whose count the host knows: the streaming kernels that keep the rows in registers (the last branch below)
     const bool rows_kernels = !live && ffn_rows_supported(ctx->c.dtype, D, R);
+    // A decode step of 3 to 8 rows (one or two: the streaming kernels, four launches a layer): every product on kernels that take and leave fp32 rows.
+    // 7B-class at 3 / 4 / 8 rows 3.64 / 3.62 / 3.77 ms, the streaming kernels 3.54 / 3.50 ms up to 4 rows, the split-K path below 3.97 ms at 8.
+    if ((L.mfma || L.split) && (live || distinct_slots) && R >= 3 && R <= FEW_MAX_ROWS && !rows_kernels && few_supported(D)) {
+        for (int l = 0; l < D.L; ++l) {
+            const LayerW &w = ctx->layers[(size_t)l];
+            { Bracket br(ctx, s, TR_KERNEL_QKV); launch_few_qkv(s, ctx->c.kv_dtype, D, ctx->wt(l, L.wt_qkv), x, w.ln1, ctx->bias(l), rows, ctx->at<float2>(L.rope), q, ctx->kc_layer(l), ctx->vc_layer(l)); }
+            attend(l, q, rows, max_ctx, ctx->at<float>(L.attn_part), attn_part_floats, ctx->at<int>(L.attn_cnt), att, nullptr, 0, nullptr);
+            { Bracket br(ctx, s, TR_KERNEL_OPROJ); launch_few_oproj(s, D, ctx->wt(l, L.wt_o), att, R, x, live); }
+            { Bracket br(ctx, s, TR_KERNEL_GATEUP); launch_few_swiglu(s, D, ctx->wt(l, L.wt_gu), x, w.ln2, R, ctx->at<uint4>(L.pack8), live); }
+            { Bracket br(ctx, s, TR_KERNEL_DOWN); launch_few_down(s, D, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack8), R, x, live); }
+        }
+        return 0;
+    }
     if (ctx->use_split(R) && !rows_kernels) {
         // wide model: every linear layer leaves split-K partials; rotary/cache append and SwiGLU are finished by kernels of their own
         const int ncb = mfma_ncb(R);

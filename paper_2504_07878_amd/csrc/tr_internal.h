@@ -199,6 +199,15 @@ void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K,
 // tile ranges of the skinny output projection over M rows (see launch_gemm_oproj_residual): tiles per range
 int oproj_tiles_per_range(const Dims &D, int M);
 void launch_row_rstd(hipStream_t s, const float *x, int M, int d, int tiles_per_range, float eps, float *rstd);
+// ---- decode steps of 3 to 8 rows (few_kernels.hip): fp32 rows in and out, no packing, no partials
+constexpr int FEW_MAX_ROWS = 8;
+bool few_supported(const Dims &D);
+void launch_few_qkv(hipStream_t s, int kdt, const Dims &D, const void *Wt, const float *x, const void *gain, const float *bias, Rows rows, const float2 *rope,
+                    float *q, void *kc, void *vc);
+void launch_few_oproj(hipStream_t s, const Dims &D, const void *Wt, const float *att, int R, float *x, const int *live);
+void launch_few_swiglu(hipStream_t s, const Dims &D, const void *Wt, const float *x, const void *gain, int R, void *hpack, const int *live);
+void launch_few_down(hipStream_t s, const Dims &D, const void *Wt, const void *hpack, int R, float *x, const int *live);
+
 // Wide models (K beyond what one workgroup keeps resident): every linear layer goes through split-K partials, and the
 // layers with a non-linear epilogue are finished by a small kernel of their own.
 // number of partial buffers launch_gemm_partial will produce for a K x N layer
