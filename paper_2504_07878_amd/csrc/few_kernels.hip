@@ -45,17 +45,6 @@ template <typename T> __device__ __forceinline__ T few_load(const void *base, ui
     return *reinterpret_cast<const T *>(p + off);
 }
 
-// A buffer of `bytes` bytes and a lane's 16 bytes of it: lanes whose own offset lies beyond the buffer get zeros
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t few_buffer(const void *p, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
-}
-__device__ __forceinline__ uint4 few_buffer_load(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t uniform)
-{
-    typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-    return __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)uniform, 0));
-}
-
 // The rows of a workgroup: an even share of all pairs, neighbouring shares on one XCD, walked in units of 8 pairs (the 16 rows of a matrix operand).
 struct FewShare {
     int lo, hi;   // pairs lo .. hi - 1
@@ -349,12 +338,12 @@ __global__ __launch_bounds__(64 * FEW_WAVES, 2) void few_long_kernel(FewArgs a, 
     const int n32 = a.KS / 2, ns = n32 > wave ? (n32 - wave + FEW_WAVES - 1) / FEW_WAVES : 0;
     uint4 w[D], x[D];
     const uint32_t w_off = few_weight_offset(lane, share.lo, share.hi, a.KS, 1), x_off = lane * 16;
-    const auto W = few_buffer(a.Wt, (uint32_t)((2 * a.pairs + 31) / 32) * a.KS * 1024), X = few_buffer(act, n32 * 1024);
+    const auto W = buffer_of(a.Wt, (uint32_t)((2 * a.pairs + 31) / 32) * a.KS * 1024), X = buffer_of(act, n32 * 1024);
     auto load = [&](int i, int s) {   // past the wavefront's last step: beyond the buffers, which costs no memory access (and counts like any load)
         const bool past = s >= ns;
         const int step = past ? 0 : wave + FEW_WAVES * s;
-        w[i] = few_buffer_load(W, past ? ~15u : w_off, step * 2048);
-        x[i] = few_buffer_load(X, past ? ~15u : x_off, step * 1024);
+        w[i] = buffer_load16(W, past ? BUFFER_NOWHERE : w_off, step * 2048);
+        x[i] = buffer_load16(X, past ? BUFFER_NOWHERE : x_off, step * 1024);
     };
 #pragma unroll
     for (int i = 0; i < D; ++i) load(i, i);

@@ -47,6 +47,19 @@ __host__ __device__ __forceinline__ int tile_feature(int rho)
     return 16 * (qd >> 1) + 8 * hf + 4 * (qd & 1) + e;
 }
 
+// A buffer of `bytes` bytes and a lane's 16 bytes of it, `off` bytes in (plus `uniform`): where off lies beyond the buffer the lane gets zeros and no
+// memory is touched, but the load counts like any other, so that the number in flight stays known at compile time.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+constexpr uint32_t BUFFER_NOWHERE = 0x80000000u;   // (buffers are smaller)
+__device__ __forceinline__ uint4 buffer_load16(__amdgpu_buffer_rsrc_t b, uint32_t off, uint32_t uniform)
+{
+    typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
+    return __builtin_bit_cast(uint4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(b, (int)off, (int)uniform, 0));
+}
+
 // four / one cache elements, rounded to nearest even where the cache is bf16
 __device__ __forceinline__ void kv_store4(float *dst, const float (&v)[4]) { *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]); }
 __device__ __forceinline__ void kv_store4(bf16_t *dst, const float (&v)[4])

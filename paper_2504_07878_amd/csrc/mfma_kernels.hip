@@ -336,7 +336,6 @@ struct AttnWave {
                                         int t_begin, int t_step, int j1, int nq = 1)
     {
         const int ulen = PAGED ? D.page : D.max_seq, uvts = PAGED ? D.page : D.vts;   // positions per storage unit
-        const bf16_t *Kb = kc + ((size_t)slot * D.Hkv + g) * (size_t)ulen * DH, *Vb = vt + ((size_t)slot * D.Hkv + g) * (size_t)DH * uvts;   // contiguous cache
         [[maybe_unused]] const int t_last = (j1 - 1) & ~31;   // last block of 32 keys that holds a key of this row
         const int lane = threadIdx.x & 63, j = lane & 31, hf = lane >> 5, G = D.G;
         const int rq = MULTI ? j / G : 0, hq = MULTI ? j % G : j;          // query row and head of this lane's column
@@ -364,40 +363,44 @@ struct AttnWave {
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) o[db][rr] = 0.f;
 
-        // NB blocks of 32 keys are requested together (64-wide heads: 64 keys in flight at once; three or four at once measured no faster:
-        // a compute unit's requests in flight are limited well below what one wavefront can ask for)
+        // NB blocks of 32 keys are in flight (64-wide heads: 64 keys; three or four measured no faster: a compute unit's requests in flight are limited
+        // well below what one wavefront can ask for). Rows on their own (one or two wavefronts per SIMD): a block's registers take the block NB further on
+        // as soon as the products have read them (64 rows of 760 keys, 64-wide: 11.9 -> 11.0 us; 63 rows of up to 937 keys, 128-wide: 20.1 -> 16.8 us).
+        // Blocks of rows leave that to the other wavefronts of the SIMD: the registers it takes cost one of three (4600 prompt rows: 90 -> 104 us).
         constexpr int NB = NBLK;
-        for (int t0 = t_begin; t0 < j1; t0 += NB * t_step) {
-            uint4 ka[NB][KSQ], va[NB][2][DB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                int t = t0 + nb * t_step;   // may start past j1 in the last trip
-                const bf16_t *kp;
-                int tv;                     // start of the block of V^T rows inside its storage unit
-                if constexpr (PAGED) {
-                    t = min(t, t_last);     // such a block's requests are redirected to the row's last block and unused
-                    const int unit = D.ptab[(size_t)slot * D.maxp + t / D.page];
-                    Kb = kc + ((size_t)unit * D.Hkv + g) * (size_t)ulen * DH;
-                    Vb = vt + ((size_t)unit * D.Hkv + g) * (size_t)DH * uvts;
-                    tv = t % D.page;
-                    kp = Kb + (size_t)(tv + min(krow, j1 - 1 - t)) * DH + hf * 8;
-                } else {                    // rows are clamped, V^T rows are padded to 32
-                    t = min(t, t_last);     // a block past the context: its requests repeat the row's last block and are not used
-                    kp = Kb + (size_t)min(t + krow, j1 - 1) * DH + hf * 8;
-                    tv = min(t, D.vts - 32);
-                }
-#pragma unroll
-                for (int ks = 0; ks < KSQ; ++ks) ka[nb][ks] = *reinterpret_cast<const uint4 *>(kp + ks * 16);
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-                    for (int db = 0; db < DB; ++db)
-                        va[nb][kk][db] = *reinterpret_cast<const uint4 *>(Vb + ((size_t)(tv >> 5) * DH + db * 32 + j) * 32 + 16 * kk + 8 * hf);
+        constexpr bool AHEAD = !MULTI;
+        uint4 ka[NB][KSQ], va[NB][2][DB];
+        int unit[NB], tv[NB];   // where a block lies: storage unit, first position in it
+        auto request_k = [&](int nb, int t) {   // a block past the context is requested from beyond the buffer
+            unit[nb] = slot; tv[nb] = t;
+            if constexpr (PAGED) {
+                const int tc = min(t, t_last), pg = tc / D.page;
+                unit[nb] = D.ptab[(size_t)slot * D.maxp + pg];
+                tv[nb] = tc - pg * D.page;
             }
+            const auto buf = buffer_of(kc + ((size_t)unit[nb] * D.Hkv + g) * (size_t)ulen * DH, (uint32_t)ulen * DH * 2);
+            const uint32_t off = t < j1 ? (uint32_t)(tv[nb] + min(krow, j1 - 1 - t)) * (DH * 2) + hf * 16 : BUFFER_NOWHERE;   // keys past the context repeat its last
+#pragma unroll
+            for (int ks = 0; ks < KSQ; ++ks) ka[nb][ks] = buffer_load16(buf, off + ks * 32, 0);
+        };
+        auto request_v = [&](int nb, int t) {   // after request_k of the block; rows of V^T are padded to 32 positions
+            const auto buf = buffer_of(vt + ((size_t)unit[nb] * D.Hkv + g) * (size_t)DH * uvts, (uint32_t)uvts * DH * 2);
+            const uint32_t off = t < j1 ? (uint32_t)(tv[nb] >> 5) * (DH * 64) + j * 64 + hf * 16 : BUFFER_NOWHERE;
+#pragma unroll
+            for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) va[nb][kk][db] = buffer_load16(buf, off + db * 2048 + kk * 32, 0);
+        };
+        auto request = [&](int t0) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) { request_k(nb, t0 + nb * t_step); request_v(nb, t0 + nb * t_step); }
+        };
+        auto trip = [&](int t0, auto more) {
+            if (!AHEAD) request(t0);
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
                 const int t = t0 + nb * t_step;
-                if (t >= j1) break;   // uniform over the wavefront
+                if (!more && t >= j1) break;   // uniform over the wavefront
                 f32x16 sacc;
 #pragma unroll
                 for (int rr = 0; rr < 16; ++rr) sacc[rr] = 0.f;
@@ -407,6 +410,7 @@ struct AttnWave {
                     sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, qh[ks], sacc, 0, 0, 0);
                     sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kv, ql[ks], sacc, 0, 0, 0);
                 }
+                if (more) request_k(nb, t + NB * t_step);
                 // register rr of this lane is key t + 16*(rr/8) + 8*hf + rr%8 of head j
                 if (t + 32 > j1min) {   // the last block of a row's context may be ragged
 #pragma unroll
@@ -442,7 +446,18 @@ struct AttnWave {
                         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, pl, o[db], 0, 0, 0);
                     }
                 }
+                if (more) request_v(nb, t + NB * t_step);
             }
+        };
+        int t0 = t_begin;
+        if constexpr (AHEAD) {
+            request(t0);
+#pragma unroll 1
+            for (; t0 + NB * t_step < j1; t0 += NB * t_step) trip(t0, std::true_type{});
+            trip(t0, std::false_type{});
+        } else {
+#pragma unroll 1
+            for (; t0 < j1; t0 += NB * t_step) trip(t0, std::false_type{});
         }
     }
 };
