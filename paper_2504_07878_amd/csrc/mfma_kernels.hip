@@ -781,7 +781,6 @@ struct GemmArgs {
     int tiles_per_wg;
     int M;              // rows in total (groups of 64 along gridDim.z)
     int half;           // 1: every 64-row group is served by two workgroups of 32 rows each (more workgroups for short tile ranges)
-    int remap_groups;   // > 0: 1-D grid; the row groups of one tile range are placed on the same XCD, next to each other in time
     const int *live;    // device-side row count or NULL: with zero live rows the whole launch returns at once
 };
 
@@ -791,7 +790,7 @@ struct GemmArgs {
 // MFMAs of the next tile, which the matrix pipe executes while the vector ALUs do the epilogue.
 
 struct EpiPartial {   // split-K partial sums: part[split][m][n]
-    static constexpr bool half_only = false;
+    static constexpr bool half_only = false, one_group = false;
     float *part;
     int N, M;
     __device__ void block(int, int) {}
@@ -845,7 +844,7 @@ struct EpiQkv {       // bias, rotary embedding, q out, cache append; tiles hold
 // them through LDS in band order: 8 registers per thread while the resident activations are being requested, not 32.
 template <bool RAGGED, bool DEFER>
 struct EpiSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written as packed activations of the down projection
-    static constexpr bool half_only = false;
+    static constexpr bool half_only = false, one_group = false;
     uint4 *hpack;     // [group][F/16][NCB][64]
     int M, F, ncb;
     float hold[8];
@@ -946,19 +945,19 @@ struct EpiResidualNorm {
 // DUMP = false keeps every vector-memory store out of the tile loop, so that the wait counters of the weight stream stay exact.
 // RAGGED: the vocabulary is not a multiple of 32.
 template <bool DUMP, bool RAGGED>
-struct EpiLmHead {    // running softmax statistics per batch row; logits optionally dumped
-    static constexpr bool half_only = false;
+struct EpiLmHead {    // running softmax statistics per batch row (one 64-row group at most); logits optionally dumped
+    static constexpr bool half_only = false, one_group = true;
     float4 *part;     // [gridDim.x][M]
     float *logits;
     int M, V;
     float mx, sum;
-    int idx, bx, grp, nwg;   // nwg: workgroups that own tiles (the grid may be padded)
+    int idx, bx;
     // The tiles from index vt on are not vocabulary rows but the hidden units of the router's first layer (its weight
     // rows are appended to the head matrix: same activations, so the product comes for free inside this launch): their
     // raw sums go to r1[row][unit] and are kept out of the softmax statistics. vt = INT_MAX: no such tiles.
     float *r1;
     int vt, r1_stride;
-    __device__ void block(int b, int g) { bx = b; grp = g; }
+    __device__ void block(int b, int) { bx = b; }
     __device__ void begin() { mx = -INFINITY; sum = 0.f; idx = 0x7fffffff; }
     __device__ void row(int, int) {}
     __device__ void row_ready(float *, int, int) {}
@@ -1003,8 +1002,7 @@ struct EpiLmHead {    // running softmax statistics per batch row; logits option
         s[band * 64 + row_local] = make_float4(mx, __int_as_float(idx), sum, 0.f);
         __syncthreads();
         const int j = threadIdx.x;
-        const int m = grp * 64 + j;
-        if (j < 64 && m < M && bx < nwg) {
+        if (j < 64 && j < M) {
             float Mx = -INFINITY; int I = 0x7fffffff;
             for (int b = 0; b < 4; ++b) {
                 const float4 p = s[b * 64 + j];
@@ -1016,7 +1014,7 @@ struct EpiLmHead {    // running softmax statistics per batch row; logits option
                 const float4 p = s[b * 64 + j];
                 if (p.x > -INFINITY) S += p.z * expf(p.x - Mx);
             }
-            part[(size_t)bx * M + m] = make_float4(Mx, __int_as_float(I), S, 0.f);
+            part[(size_t)bx * M + j] = make_float4(Mx, __int_as_float(I), S, 0.f);
         }
     }
 };
@@ -1040,12 +1038,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int per = (ks1 - ks0 + NWAVES - 1) / NWAVES;   // <= KW
     const int wk0 = ks0 + wave * per;
     const int nk = max(0, min(ks1, wk0 + per) - wk0);
-    int bx = blockIdx.x, group = blockIdx.z;
-    if (a.remap_groups > 0) {   // workgroups are dealt to the 8 XCDs round-robin: keep the groups of a tile range on one XCD
-        const int xcd = bx & 7, slot = bx >> 3;
-        group = slot % a.remap_groups;
-        bx = (slot / a.remap_groups) * 8 + xcd;
-    }
+    const int bx = blockIdx.x, group = blockIdx.z;
     epi.block(bx, group);
     // half mode: the packed activations hold 4 column blocks per 64-row group; this workgroup takes {h, 2 + h}
     const int pgroup = a.half ? group >> 1 : group, hsel = a.half ? group & 1 : 0, pncb = a.half ? 4 : NCB;
@@ -1200,12 +1193,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int per = (ks1 - ks0 + 1) / 2;   // <= KW2
     const int wk0 = ks0 + kh * per;
     const int nk = max(0, min(ks1, wk0 + per) - wk0);
-    int bx = blockIdx.x, group = blockIdx.z;
-    if (a.remap_groups > 0) {   // workgroups are dealt to the 8 XCDs round-robin: keep the groups of a tile range on one XCD
-        const int xcd = bx & 7, slot = bx >> 3;
-        group = slot % a.remap_groups;
-        bx = (slot / a.remap_groups) * 8 + xcd;
-    }
+    const int bx = blockIdx.x, group = blockIdx.z;
     epi.block(bx, group);
     const int m = group * 64 + rh * 32 + (lane & 31), i0 = 16 * kh + 8 * hf;
     epi.row(m, 2 * kh + hf);   // per-row inputs of the epilogue: requested first, so that they are the oldest requests in flight
@@ -1330,7 +1318,6 @@ static void launch_gemm(hipStream_t s, const GemmArgs &a, int nsplit, const Epi 
 {
     const int groups = (a.M + 63) / 64;
     dim3 grid((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg, nsplit, groups);
-    if (a.remap_groups > 0) grid = dim3((grid.x + 7) / 8 * 8 * groups, 1, 1);
     if (a.half && a.M > 32) { grid.z = 2 * groups; launch_gemm_kw<2>(s, a, grid, epi); return; }
     GemmArgs b = a;
     b.half = 0;
@@ -1340,7 +1327,7 @@ static void launch_gemm(hipStream_t s, const GemmArgs &a, int nsplit, const Epi 
         // split two ways each. Several groups re-read the weights from L2, where loading every tile twice per
         // workgroup costs more than the smaller reduction saves: they keep the four-way K split.
         if (groups == 1) launch_gemm22_kw(s, b, grid, epi);
-        else launch_gemm_kw<4>(s, b, grid, epi);
+        else if constexpr (!Epi::one_group) launch_gemm_kw<4>(s, b, grid, epi);
     }
 }
 
@@ -1597,17 +1584,13 @@ int launch_gemm_oproj_residual(hipStream_t s, const Dims &D, const void *Wt, con
 
 bool gemm_oproj_residual_supported(const Dims &D) { return D.qw / 16 <= NWAVES * MAXKW && (D.d + 31) / 32 <= 32; }   // one workgroup spans K; at most 32 tile ranges per row
 
-// tiles per workgroup of the LM-head launch: the whole launch (every 64-row group over every tile) is one round of at most 256 workgroups
-static int lmhead_tiles_per_wg(int n_tiles, int M)
-{
-    const int groups = (M + 63) / 64, per_group = groups >= 256 ? 1 : 256 / groups;
-    return (n_tiles + per_group - 1) / per_group;
-}
+// tiles per workgroup of the LM-head launch: one round of at most 256 workgroups
+static int lmhead_tiles_per_wg(int n_tiles) { return (n_tiles + 255) / 256; }
 
-int lmhead_mfma_wgs(int V, int router_tiles, int M)
+int lmhead_mfma_wgs(int V, int router_tiles)
 {
     const int n_tiles = (V + 31) / 32 + router_tiles;
-    const int tpw = lmhead_tiles_per_wg(n_tiles, M);
+    const int tpw = lmhead_tiles_per_wg(n_tiles);
     return (n_tiles + tpw - 1) / tpw;
 }
 
@@ -1618,10 +1601,9 @@ void launch_gemm_lmhead(hipStream_t s, const Dims &D, const void *Wt, const void
     a.live = live;
     const int vt = (D.V + 31) / 32;
     a.Wt = (const uint4 *)Wt; a.pack = (const uint4 *)pack; a.KS = D.d / 16; a.ksw = a.KS; a.n_tiles = vt + router_tiles; a.M = M;
-    a.tiles_per_wg = lmhead_tiles_per_wg(a.n_tiles, M);
-    a.remap_groups = M > 64 ? (M + 63) / 64 : 0;
+    a.tiles_per_wg = lmhead_tiles_per_wg(a.n_tiles);
     auto go = [&](auto e) {
-        e.part = (float4 *)part; e.logits = logits; e.M = M; e.V = D.V; e.nwg = lmhead_mfma_wgs(D.V, router_tiles, M);
+        e.part = (float4 *)part; e.logits = logits; e.M = M; e.V = D.V;
         e.r1 = r1; e.vt = router_tiles > 0 ? vt : 0x7fffffff; e.r1_stride = router_tiles * 32;
         launch_gemm(s, a, 1, e);
     };

@@ -170,6 +170,66 @@ struct TileResidual {
     }
 };
 
+// LM head over more than 64 rows (0.14 PFLOP of bf16 work at 256 rows and 152 k features: 142 -> 129 us with the norm and the final kernel;
+// below that one 64-row group streams the weights at HBM speed). Softmax statistics of a block's features per row: part[feature block][m] = {max, lowest index that attains it, sum exp(z - max)}. The tiles from vt on are
+// the router's first layer: their sums go to r1 and stay out of the statistics (see EpiLmHead). logits: also written, or NULL.
+struct TileHead {
+    static constexpr bool pairs = false;
+    float4 *part;
+    float *logits, *r1;
+    const int *live;   // device-side row count or NULL: with zero live rows the launch returns at once
+    int M, V, vt, r1_stride, n_tiles;
+    template <int WM> struct State { __device__ void init(const TileHead &, const int (&)[WM], int) {} };
+    template <int GM, int GN, int WM, int WN>
+    __device__ __forceinline__ void whole(const f32x16 (&acc)[WM][WN], const int (&m)[WM], int t0, int nb, int wm, int wn, float4 *lds) const
+    {
+        const int lane = threadIdx.x & 63, hf = lane >> 5;
+#pragma unroll
+        for (int mi = 0; mi < WM; ++mi) {
+            float mx = -INFINITY, sum = 0.f;
+            int idx = 0x7fffffff;
+            auto each = [&](auto f) {   // the lane's features of the vocabulary, ascending
+#pragma unroll
+                for (int ni = 0; ni < WN; ++ni)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) f(ni, (t0 + ni) * 32 + 16 * (r >> 3) + 8 * hf + (r & 7), acc[mi][ni][r]);
+            };
+            each([&](int ni, int n, float z) {
+                if (t0 + ni < vt && n < V && z > mx) { mx = z; idx = n; }   // strict: the lowest index wins ties
+            });
+            const float ref = mx == -INFINITY ? 0.f : mx;
+            each([&](int ni, int n, float z) { sum += t0 + ni < vt && n < V ? __expf(z - ref) : 0.f; });
+            if (logits && m[mi] < M)
+                each([&](int ni, int n, float z) { if (t0 + ni < vt && n < V) logits[(size_t)m[mi] * V + n] = z; });
+            if (m[mi] < M)
+                each([&](int ni, int n, float z) { if (t0 + ni >= vt && t0 + ni < n_tiles) r1[(size_t)m[mi] * r1_stride + n - vt * 32] = z; });
+            const float mo = __shfl_xor(mx, 32, 64), so = __shfl_xor(sum, 32, 64);
+            const int io = __shfl_xor(idx, 32, 64);
+            const float top = fmaxf(mx, mo), rt = top == -INFINITY ? 0.f : top;
+            const int it = mx > mo || (mx == mo && idx < io) ? idx : io;
+            if (hf == 0) lds[wn * (GM * WM * 32) + (wm * WM + mi) * 32 + lane] = make_float4(top, __int_as_float(it), sum * __expf(mx - rt) + so * __expf(mo - rt), 0.f);
+        }
+        __syncthreads();
+        const int row = threadIdx.x;                                       // a row of the block; its waves' shares in ascending feature order
+        const int r0 = m[0] - ((wm * WM) * 32 + (lane & 31)) + row;        // the block's first row, plus row
+        if (row < GM * WM * 32 && r0 < M) {
+            float top = -INFINITY, sum = 0.f;
+            int idx = 0x7fffffff;
+#pragma unroll
+            for (int w = 0; w < GN; ++w) {
+                const float4 p = lds[w * (GM * WM * 32) + row];
+                if (p.x > top) { top = p.x; idx = __float_as_int(p.y); }
+            }
+#pragma unroll
+            for (int w = 0; w < GN; ++w) {
+                const float4 p = lds[w * (GM * WM * 32) + row];
+                if (p.x > -INFINITY) sum += p.z * __expf(p.x - top);
+            }
+            part[(size_t)nb * M + r0] = make_float4(top, __int_as_float(idx), sum, 0.f);
+        }
+    }
+};
+
 // ------------------------------------------------------------------ the kernel
 
 // GM x GN wavefronts of WM x WN accumulators; ST: stages of one k-step in the ring; OCC: wavefronts per SIMD the registers must leave room for.
@@ -180,6 +240,9 @@ struct TileResidual {
 template <int GM, int GN, int WM, int WN, int ST, int OCC, bool SPLITS, class Epi>
 __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a, Epi epi)
 {
+    constexpr bool PLAIN = std::is_same_v<Epi, TileHead>;   // nothing depends on the order of the sum: one run
+    if constexpr (PLAIN)
+        if (epi.live && *epi.live == 0) return;   // uniform over the launch
     constexpr int NWV = GM * GN, BT = GN * WN, RB = GM * WM, CH = BT + 2 * RB;   // wavefronts, weight tiles, 32-row blocks, 1 KiB operands per k-step
     constexpr int L = CH / NWV, STG = CH * 64, P = ST - 1;
     static_assert(CH % NWV == 0 && (P - 1) * L < 64, "every wavefront copies the same number of operands; the wait counter has 6 bits");
@@ -283,6 +346,18 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
     issue();                                                    // the ring is full
     fetch(even);
     int left = nstep;
+    if constexpr (PLAIN) {
+        clear(acc);
+#pragma unroll 1
+        for (; left >= 2; left -= 2) {
+            step(even, odd);
+            step(odd, even);
+        }
+        if (left) step(even, odd);
+        wait_and_barrier<0>();                                  // no load may be in flight into LDS when it is used otherwise
+        epi.template whole<GM, GN, WM, WN>(acc, m, t0, nb, wm, wn, reinterpret_cast<float4 *>(sm));
+        return;
+    }
 #pragma unroll 1
     while (left > 0) {                                          // one split
         int in_split = min(left, a.ksw);
@@ -315,6 +390,8 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
             });
     }
     wait_and_barrier<0>();                                      // no load may be in flight into LDS when the workgroup ends
+    if constexpr (PLAIN) return;
+    else {
     // one split: the starting value joins last (the same sum)
     auto value = [&](int mi, int ni, int h, float (&v)[8]) {
         if constexpr (SPLITS) run8(tot[mi][ni], h, v);
@@ -347,6 +424,7 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
                 epi.store(st, mi, m[mi], t0 + ni, 16 * h + 8 * hf, v);
             }
         });
+    }
     }
 }
 
@@ -423,6 +501,26 @@ void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K,
     a.kwg = ksw;
     *nsplit = (a.KS + ksw - 1) / ksw;
     launch_tile<false>(s, a, *nsplit, TilePartial{part, N, M});
+}
+
+int tile_head_blocks(int V, int router_tiles) { return ((V + 31) / 32 + router_tiles + 7) / 8; }
+
+// 128 x 256 blocks by 8 wavefronts, two workgroups per compute unit; where that leaves half a block of rows empty, 64 x 256 blocks by 4, three per
+// compute unit. Whole tail of the 0.5B-class model at 256 / 160 / 100 rows: large blocks 130 / 118 / 76 us, small ones 137 / 99 / 74 us; at 256 rows with
+// 4 wavefronts of 64 x 128 a block 131 us (one workgroup per compute unit: 168 us), with 256 x 256 blocks 163 us.
+void launch_tile_head(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, float *part, float *logits, float *r1, int router_tiles,
+                      const int *live)
+{
+    const int vt = (D.V + 31) / 32;
+    TileArgs a = tile_args(Wt, pack, D.d, vt + router_tiles, M, D.d / 16);
+    const TileHead e{(float4 *)part, logits, r1, live, M, D.V, router_tiles > 0 ? vt : 0x7fffffff, router_tiles * 32, a.n_tiles};
+    a.groups = (M + 63) / 64;
+    const bool large = a.groups % 2 == 0;
+    a.n_mblk = large ? a.groups / 2 : a.groups; a.n_nblk = tile_head_blocks(D.V, router_tiles);
+    a.gm = a.n_mblk;   // the row blocks of a feature block next to each other: its weights come from HBM once
+    a.items = a.n_mblk * a.n_nblk; a.per_xcd = (a.items + 7) / 8;
+    if (large) hipLaunchKernelGGL((tile_gemm_kernel<2, 4, 2, 2, 5, 2, false, TileHead>), dim3(a.per_xcd * 8), dim3(512), 0, s, a, e);
+    else hipLaunchKernelGGL((tile_gemm_kernel<1, 4, 2, 2, 4, 3, false, TileHead>), dim3(a.per_xcd * 8), dim3(256), 0, s, a, e);
 }
 
 // 1/rms of the rows of x, with the sum of squares in the order of the skinny output projection's epilogue and its consumer: a row is cut into ranges

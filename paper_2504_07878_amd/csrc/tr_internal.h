@@ -196,6 +196,10 @@ void launch_tile_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void
 void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, int ksw);
 // split-K partials of the same sums (see launch_gemm_partial)
 void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit);
+// LM head over more than 64 rows: softmax statistics per row and block of 256 features (tile_head_blocks of them), see TileHead
+int tile_head_blocks(int V, int router_tiles);
+void launch_tile_head(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, float *part, float *logits, float *r1, int router_tiles,
+                      const int *live);
 // tile ranges of the skinny output projection over M rows (see launch_gemm_oproj_residual): tiles per range
 int oproj_tiles_per_range(const Dims &D, int M);
 void launch_row_rstd(hipStream_t s, const float *x, int M, int d, int tiles_per_range, float eps, float *rstd);
@@ -223,7 +227,7 @@ void launch_swiglu_finish(hipStream_t s, const Dims &D, const float *part, int n
 // writes slice_part[slice][m] = {max, lowest argmax, sum-exp} (what the tail's final kernel merges) and, when asked, the logits.
 constexpr int LMHEAD_FINISH_COLS = 2048;
 void launch_lmhead_finish(hipStream_t s, const float *part, int nsplit, int M, int V, float *slice_part, float *logits);
-int lmhead_mfma_wgs(int V, int router_tiles, int M);   // workgroups per 64-row group that own tiles, for M rows (most at M <= 64)
+int lmhead_mfma_wgs(int V, int router_tiles);   // workgroups that own tiles, up to 64 rows
 // router_tiles > 0: the matrix holds that many extra tiles after the vocabulary (the router's first layer); their raw sums go to r1[row][router_tiles * 32]
 void launch_gemm_lmhead(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, float *part, float *logits, float *r1, int router_tiles,
                         const int *live = nullptr);
