@@ -108,7 +108,7 @@ struct TileQkv {       // bias, rotary embedding, q out, cache append
 
 struct TileSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written as packed activations of the down projection
     static constexpr bool pairs = true;
-    const float *rstd; // [row] factor on gate and up (deferred RMSNorm), or NULL
+    const float *rstd; // rstd[row * SS_STRIDE]: factor on gate and up (deferred RMSNorm), or NULL
     uint4 *hpack;      // [group][F/16][4][64]
     int M, F;
     template <int WM> struct State {
@@ -116,7 +116,7 @@ struct TileSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written
         __device__ void init(const TileSwiglu &e, const int (&m)[WM], int)
         {
 #pragma unroll
-            for (int mi = 0; mi < WM; ++mi) rs[mi] = e.rstd ? e.rstd[min(m[mi], e.M - 1)] : 1.0f;
+            for (int mi = 0; mi < WM; ++mi) rs[mi] = e.rstd ? e.rstd[(size_t)min(m[mi], e.M - 1) * SS_STRIDE] : 1.0f;
         }
     };
     template <int WM> __device__ __forceinline__ void start(State<WM> &, int, int, int, float (&v)[8]) const
@@ -138,23 +138,39 @@ struct TileSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written
     }
 };
 
-// x += tile; with `pack` the input of the next linear layer is written as x * gain (hi/lo split, no 1/rms).
+// x += tile; with `pack` the input of the next linear layer is written as x * gain (hi/lo split, no 1/rms) and the rows' sums of squares over each
+// tile of 32 features as sumsq[row][tile] (a tile's four bands of 8 features, each summed in order, added pairwise): the consumer applies 1/rms.
 struct TileResidual {
     static constexpr bool pairs = false;
     float *x;              // residual stream [M][d], updated in place
     const bf16_t *gain;    // gain of the norm that follows
     uint4 *pack;           // packed activations of the next linear layer [group][d/16][4][64], or NULL
+    float *sumsq;
     int M, d;
-    template <int WM> struct State { __device__ void init(const TileResidual &, const int (&)[WM], int) {} };
+    template <int WM> struct State {
+        float first;       // sum of squares of the tile's lower band of this lane
+        __device__ void init(const TileResidual &, const int (&)[WM], int) {}
+    };
     template <int WM> __device__ __forceinline__ void start(State<WM> &, int, int m, int n0, float (&v)[8]) const
     {
         const float *xr = x + (size_t)min(m, M - 1) * d + min(n0, d - 8);
         const float4 p = *reinterpret_cast<const float4 *>(xr), q = *reinterpret_cast<const float4 *>(xr + 4);
         v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w; v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
     }
-    template <int WM> __device__ __forceinline__ void store(State<WM> &, int, int m, int t, int i0, const float (&xn)[8]) const
+    template <int WM> __device__ __forceinline__ void store(State<WM> &st, int, int m, int t, int i0, const float (&xn)[8]) const
     {
         const int n0 = t * 32 + i0;
+        if (pack) {   // the lanes l and l + 32 hold the same row
+            float ss = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss = fmaf(xn[e], xn[e], ss);
+            if (n0 >= d) ss = 0.f;
+            if (i0 < 16) st.first = ss;
+            else {
+                const float a = st.first + __shfl_xor(st.first, 32, 64), b = ss + __shfl_xor(ss, 32, 64);
+                if (i0 == 16 && m < M && t * 32 < d) sumsq[(size_t)m * SS_STRIDE + t] = a + b;
+            }
+        }
         if (m >= M || n0 >= d) return;
         float *xr = x + (size_t)m * d + n0;
         *reinterpret_cast<float4 *>(xr) = make_float4(xn[0], xn[1], xn[2], xn[3]);
@@ -235,8 +251,9 @@ struct TileHead {
 // GM x GN wavefronts of WM x WN accumulators; ST: stages of one k-step in the ring; OCC: wavefronts per SIMD the registers must leave room for.
 // Sums are formed in the order of the skinny kernels: the k-steps of a split (ksw of them) fall into four runs of `per` = ksw / 4 rounded up, each
 // accumulated from zero by the matrix instructions (hi product, then lo product, k-step by k-step); the four runs of a split are added in order,
-// and the splits are added in order to the epilogue's starting value. A pass over many rows then leaves the same bits in the cache as one over
-// few. SPLITS: more than one split is walked (or the start is not zero), which takes a third set of sums.
+// and the splits are added in order to the epilogue's starting value. A product in one piece then has the bits of its skinny kernel, and one in parts
+// (TilePartial) the same depth of sums.
+// SPLITS: more than one split is walked (or the start is not zero), which takes a third set of sums.
 template <int GM, int GN, int WM, int WN, int ST, int OCC, bool SPLITS, class Epi>
 __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a, Epi epi)
 {
@@ -486,20 +503,39 @@ void launch_tile_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void
     else launch_tile<true>(s, a, 1, e);
 }
 
-void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, int ksw)
+void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, float *sumsq, int ksw)
 {
     const TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, ksw);
-    const TileResidual e{x, (const bf16_t *)gain, (uint4 *)pack_out, M, N};
+    const TileResidual e{x, (const bf16_t *)gain, (uint4 *)pack_out, sumsq, M, N};
     if (ksw >= a.KS) launch_tile<false>(s, a, 1, e);
     else launch_tile<true>(s, a, 1, e);
 }
 
+// Parts of K for a product whose blocks leave compute units idle: as many as keep every block of 64 x 128 on a unit of its own, two blocks a unit where
+// the blocks of one part fill more than half of them. (What counts is the busiest unit: 111 rows of the 7B-class model with 2 x 28 x 4 blocks 6.5 ms, with
+// 2 x 28 x 7 6.9 ms; 300 rows with 5 x 28 blocks 12.4 ms, with 5 x 28 x 3 11.1 ms.) A part has at least 256 columns.
+static int tile_splits(int K, int N, int M)
+{
+    const int whole = (M + 63) / 64 * ((N + 127) / 128), steps = K / 16;
+    const int want = std::max(1, (whole > 128 ? 512 : 256) / whole), S = std::min({want, 16, std::max(1, steps / 16)}), per = (steps + S - 1) / S;
+    return (steps + per - 1) / per;
+}
+
+size_t tile_partial_floats(int K, int N, int max_rows)
+{
+    size_t most = 0;
+    for (int groups = 1; groups <= (max_rows + 63) / 64; ++groups) {
+        const int M = std::min(max_rows, 64 * groups);
+        most = std::max(most, (size_t)tile_splits(K, N, M) * M * N);
+    }
+    return most;
+}
+
 void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit)
 {
-    const int ksw = gemm_split_steps(K, N, M);
-    TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, ksw);
-    a.kwg = ksw;
-    *nsplit = (a.KS + ksw - 1) / ksw;
+    *nsplit = tile_splits(K, N, M);
+    TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, 0);
+    a.ksw = a.kwg = (a.KS + *nsplit - 1) / *nsplit;
     launch_tile<false>(s, a, *nsplit, TilePartial{part, N, M});
 }
 
@@ -523,47 +559,29 @@ void launch_tile_head(hipStream_t s, const Dims &D, const void *Wt, const void *
     else hipLaunchKernelGGL((tile_gemm_kernel<1, 4, 2, 2, 4, 3, false, TileHead>), dim3(a.per_xcd * 8), dim3(256), 0, s, a, e);
 }
 
-// 1/rms of the rows of x, with the sum of squares in the order of the skinny output projection's epilogue and its consumer: a row is cut into ranges
-// of tiles_per_range tiles of 32 features; inside a range the features fall into four bands (8 consecutive ones of every tile), each summed in order;
-// the bands are added pairwise, and the ranges (at most 32) in four groups of eight that are added pairwise too. One thread per (row, range, band);
-// RR rows per workgroup, as many as keep the threads busy. Bound: one read of x.
-__global__ __launch_bounds__(256) void row_rstd_kernel(const float *x, int M, int d, int tiles_per_range, int n_ranges, int RR, float eps, float inv_d, float *rstd)
+// 1/rms of the rows from their sums of squares, in place: sumsq[row][0] = 1/rms. The order is that of EpiSwiglu: four groups of eight, added pairwise. One
+// line of memory per row (8192 rows: 4.7 us; reading the rows themselves took 12). In the blocks of gate and up it would be done once per block, which cost
+// more than this launch (64 prompts 69.7 ms against 68.3).
+__global__ __launch_bounds__(64) void row_rstd_kernel(float *sumsq, int M, int n_ss, float eps, float inv_d)
 {
-    __shared__ float s_sum[256];        // [row][range] (RR * n_ranges <= 64), then [row][group]
-    const int n_tiles = (d + 31) / 32, tid = threadIdx.x, band = tid & 3, item = tid >> 2, rr = item / n_ranges, rg = item % n_ranges;
-    const int m = blockIdx.x * RR + rr;
-    float ss = 0.f;
-    if (rr < RR && m < M) {
-        const float *xr = x + (size_t)m * d;
-        const int t1 = min(n_tiles, (rg + 1) * tiles_per_range);
-#pragma unroll 4
-        for (int t = rg * tiles_per_range; t < t1; ++t) {
-            const int n0 = min(t * 32 + band * 8, d - 8);
-            const float4 p = *reinterpret_cast<const float4 *>(xr + n0), q = *reinterpret_cast<const float4 *>(xr + n0 + 4);
-            if (t * 32 + band * 8 < d) {
-                ss = fmaf(p.x, p.x, ss); ss = fmaf(p.y, p.y, ss); ss = fmaf(p.z, p.z, ss); ss = fmaf(p.w, p.w, ss);
-                ss = fmaf(q.x, q.x, ss); ss = fmaf(q.y, q.y, ss); ss = fmaf(q.z, q.z, ss); ss = fmaf(q.w, q.w, ss);
-            }
-        }
-    }
-    const float pair = ss + __shfl_xor(ss, 1, 64), all = pair + __shfl_xor(pair, 2, 64);   // (b0 + b1) + (b2 + b3): addition commutes
-    if (band == 0 && rr < RR) s_sum[rr * n_ranges + rg] = all;
-    __syncthreads();
-    if (tid < RR && blockIdx.x * RR + tid < M) {
-        float g[4];
+    const int m = blockIdx.x * 64 + threadIdx.x;
+    if (m >= M) return;
+    const float4 *sp = reinterpret_cast<const float4 *>(sumsq + (size_t)m * SS_STRIDE);
+    float p[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            g[i] = 0.f;
-            for (int e = 8 * i; e < min(n_ranges, 8 * i + 8); ++e) g[i] = e == 8 * i ? s_sum[tid * n_ranges + e] : g[i] + s_sum[tid * n_ranges + e];
-        }
-        rstd[blockIdx.x * RR + tid] = 1.0f / sqrtf(((g[0] + g[1]) + (g[2] + g[3])) * inv_d + eps);
+    for (int b = 0; b < 4; ++b) {
+        const float4 u = sp[2 * b], v = sp[2 * b + 1];
+        const float r[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+        p[b] = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[b] += 8 * b + i < n_ss ? r[i] : 0.f;
     }
+    sumsq[(size_t)m * SS_STRIDE] = 1.0f / sqrtf(((p[0] + p[1]) + (p[2] + p[3])) * inv_d + eps);
 }
 
-void launch_row_rstd(hipStream_t s, const float *x, int M, int d, int tiles_per_range, float eps, float *rstd)
+void launch_row_rstd(hipStream_t s, float *sumsq, int M, int d, int n_ss, float eps)
 {
-    const int n_ranges = ((d + 31) / 32 + tiles_per_range - 1) / tiles_per_range, RR = 64 / n_ranges;
-    hipLaunchKernelGGL(row_rstd_kernel, dim3((M + RR - 1) / RR), dim3(256), 0, s, x, M, d, tiles_per_range, n_ranges, RR, eps, 1.0f / (float)d, rstd);
+    hipLaunchKernelGGL(row_rstd_kernel, dim3((M + 63) / 64), dim3(64), 0, s, sumsq, M, n_ss, eps, 1.0f / (float)d);
 }
 
 }  // namespace tr

@@ -168,7 +168,9 @@ Layout make_layout(const tr_config *c)
         if (L.split) {
             const size_t n_qkv = qw + 2 * kvw, n_gu = 2 * tiles(F) * 32;
             part_floats = std::max({part_floats, gemm_partial_floats((int)d, (int)n_qkv, Ri), gemm_partial_floats((int)d, (int)n_gu, Ri)});
+            part_floats = std::max(part_floats, tile_partial_floats((int)d, (int)n_qkv, Ri));
         }
+        part_floats = std::max({part_floats, tile_partial_floats((int)qw, (int)d, Ri), tile_partial_floats((int)F, (int)d, Ri)});
         if (L.split_head)   // partial logits of a tail call: up to max_batch rows
             part_floats = std::max(part_floats, gemm_partial_floats((int)d, c->vocab, c->max_batch));
         const size_t part_bytes = part_floats * 4;
@@ -178,7 +180,7 @@ Layout make_layout(const tr_config *c)
     L.pack8 = take((size_t)((c->d_ffn + 31) / 32) * 1024);
     L.kvn = take(2 * 2 * kvw * 4);
     L.dev_len = take((size_t)c->max_batch * 4);
-    L.ss_stride = 32;
+    L.ss_stride = SS_STRIDE;
     L.sumsq = take((size_t)L.ss_stride * R * 4);
     L.total = off;
     return L;
@@ -355,21 +357,24 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
             launch_attention(s, ctx->c.kv_dtype, D, q_, ctx->kc_layer(l), ctx->vc_layer(l), rows_, max_ctx_, part_, part_floats_, cnt_, att_, pack_, ncb_, defer_);
         }
     };
-    // Many rows: block products (tile_kernels.hip) whose epilogues finish the layer, with the bits of the kernels below. Measured per layer, 0.5B-class
-    // at 1024 / 2048 / 8192 rows: 131 / 190 / 598 us against 119 / 201 / 697; 7B-class at 128 / 256 / 512 / 1152 rows: 230 / 420 / 640 / 1090 against
-    // 229 / 483 / 836 / 1690.
-    if (!live && ((L.mfma && R >= 1536) || (L.split && R >= 160))) {
-        float *rstd = ctx->at<float>(L.sumsq), *part = ctx->at<float>(L.part);
+    // Many rows: block products (tile_kernels.hip) whose epilogues finish the layer. The 0.5B-class layer takes them one by one: below these lines the
+    // skinny product of the layer is the faster one. Whole passes, all products skinny / FFN output and q|k|v as blocks / the output projection too /
+    // gate and up too / FFN output in one piece: 768 rows 2.73 / 2.80 / 2.87 ms, 896 rows 2.98 / 2.85 / 2.88 / 2.95, 1088 rows 3.43 / 3.18 / 3.17 / 3.30, 2000 rows
+    // 5.04 / 4.71 / 4.62 / 4.70 / 4.76, 2560 rows 6.25 / 5.95 / 5.81 / 5.79 / 5.85, 4000 rows 9.20 / 8.36 / 8.18 / 8.16 / 8.16, 8000 rows 17.50 / 15.93 / 15.34 /
+    // 15.42 / 15.22. 7B-class at 81 / 111 rows: skinny 6.28 / 6.90 ms, blocks 6.32 / 6.55.
+    if (!live && ((L.mfma && R >= 832) || (L.split && R >= 96))) {
+        float *sumsq = ctx->at<float>(L.sumsq), *part = ctx->at<float>(L.part);
         const bool defer = L.mfma && gemm_oproj_residual_supported(D);   // the output projection packs the FFN input itself
+        const bool tile_o = !defer || R >= 1024, tile_gu = L.split || R >= 2304;
         const int steps_d = D.d / 16, n_qkv = D.qw + 2 * D.kvw, n_gu = 2 * ((D.F + 31) / 32) * 32;
         const int k_qkv = L.mfma ? steps_d : gemm_split_steps(D.d, n_qkv, R), k_gu = L.mfma ? steps_d : gemm_split_steps(D.d, n_gu, R);
         const int k_o = defer ? D.qw / 16 : gemm_split_steps(D.qw, D.d, R), k_d = gemm_split_steps(D.F, D.d, R);
-        // a wide model's products with few blocks keep their K splits apart (7B-class at 512 / 768 / 1152 rows, down projection with the partials' share of the
+        // a wide model's products with few blocks keep parts of K apart (7B-class at 512 / 768 / 1152 rows, down projection with the partials' share of the
         // next launch 181 / 253 / 371 us, in one piece 188 / 277 / 317; q|k|v 44 blocks of 128 features: in one piece from 320 rows on)
-        const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = L.mfma || tile_fills_chip(D.d, R, 448);
+        const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = L.mfma ? R >= 3072 : tile_fills_chip(D.d, R, 448);
         PrepArgs p{};
         p.x = x; p.M = R; p.d = D.d; p.eps = D.eps; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = 4; p.part = part; p.part_M = R;
-        int pending = 0, ns = 0;
+        int pending = 0, ns = 0, n_ss = (D.d + 31) / 32;
         for (int l = 0; l < D.L; ++l) {
             const LayerW &w = ctx->layers[(size_t)l];
             p.gain = (const bf16_t *)w.ln1; p.nsplit = pending;
@@ -380,7 +385,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
                     launch_tile_qkv(s, ctx->c.kv_dtype, D, ctx->wt(l, L.wt_qkv), ctx->at<uint4>(L.pack_d), ctx->bias(l), rows, ctx->at<float2>(L.rope), q, ctx->kc_layer(l),
                                     ctx->vc_layer(l), k_qkv);
                 else {
-                    launch_gemm_partial(s, ctx->wt(l, L.wt_qkv), ctx->at<uint4>(L.pack_d), D.d, n_qkv, R, part, &ns);
+                    launch_tile_partial(s, ctx->wt(l, L.wt_qkv), ctx->at<uint4>(L.pack_d), D.d, n_qkv, R, part, &ns);
                     launch_qkv_finish(s, ctx->c.kv_dtype, D, part, ns, ctx->bias(l), rows, ctx->at<float2>(L.rope), q, ctx->kc_layer(l), ctx->vc_layer(l));
                 }
             }
@@ -388,10 +393,11 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
             p.nsplit = 0;
             {
                 Bracket br(ctx, s, TR_KERNEL_OPROJ);
-                if (defer || whole_d)
-                    launch_tile_residual(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, x, w.ln2, defer ? ctx->at<uint4>(L.pack_d) : nullptr, k_o);
+                if (!tile_o)
+                    n_ss = launch_gemm_oproj_residual(s, D, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), R, x, w.ln2, ctx->at<uint4>(L.pack_d), sumsq, L.ss_stride);
+                else if (defer || whole_d)
+                    launch_tile_residual(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, x, w.ln2, defer ? ctx->at<uint4>(L.pack_d) : nullptr, sumsq, k_o);
                 else launch_tile_partial(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, part, &p.nsplit);
-                if (defer) launch_row_rstd(s, x, R, D.d, oproj_tiles_per_range(D, R), D.eps, rstd);
             }
             if (!defer) {
                 p.gain = (const bf16_t *)w.ln2;
@@ -400,12 +406,14 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
             }
             {
                 Bracket br(ctx, s, TR_KERNEL_GATEUP);
-                launch_tile_swiglu(s, D, ctx->wt(l, L.wt_gu), ctx->at<uint4>(L.pack_d), R, ctx->at<uint4>(L.pack_h), defer ? rstd : nullptr, k_gu);
+                if (tile_gu && defer) launch_row_rstd(s, sumsq, R, D.d, n_ss, D.eps);
+                if (tile_gu) launch_tile_swiglu(s, D, ctx->wt(l, L.wt_gu), ctx->at<uint4>(L.pack_d), R, ctx->at<uint4>(L.pack_h), defer ? sumsq : nullptr, k_gu);
+                else launch_gemm_swiglu(s, D, ctx->wt(l, L.wt_gu), ctx->at<uint4>(L.pack_d), R, ctx->at<uint4>(L.pack_h), nullptr, defer ? sumsq : nullptr, n_ss, L.ss_stride);
             }
             {
                 Bracket br(ctx, s, TR_KERNEL_DOWN);
                 pending = 0;
-                if (whole_d) launch_tile_residual(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, x, nullptr, nullptr, k_d);
+                if (whole_d) launch_tile_residual(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, x, nullptr, nullptr, nullptr, k_d);
                 else launch_tile_partial(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, part, &pending);
             }
         }

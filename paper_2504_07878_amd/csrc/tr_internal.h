@@ -192,17 +192,17 @@ bool tile_fills_chip(int N, int M, int blocks);   // whether M rows x N features
 void launch_tile_qkv(hipStream_t s, int kdt, const Dims &D, const void *Wt, const void *pack, const float *bias, Rows rows, const float2 *rope, float *q,
                      void *kc, void *vc, int ksw);
 void launch_tile_swiglu(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, void *hpack, const float *rstd, int ksw);
-// x[M][N] += W . A; pack_out != NULL: also the next layer's packed input x * gain
-void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, int ksw);
-// split-K partials of the same sums (see launch_gemm_partial)
+void launch_row_rstd(hipStream_t s, float *sumsq, int M, int d, int n_ss, float eps);   // sumsq[row * SS_STRIDE] = 1/rms
+// x[M][N] += W . A; pack_out != NULL: also the next layer's packed input x * gain and the rows' sums of squares per 32 columns, sumsq[row][SS_STRIDE]
+constexpr int SS_STRIDE = 32;   // one cache line
+void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, float *sumsq, int ksw);
+// split-K partials of the same sums (see launch_gemm_partial), in parts of its own
 void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit);
+size_t tile_partial_floats(int K, int N, int max_rows);   // the most floats of partials it leaves for up to max_rows rows
 // LM head over more than 64 rows: softmax statistics per row and block of 256 features (tile_head_blocks of them), see TileHead
 int tile_head_blocks(int V, int router_tiles);
 void launch_tile_head(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, float *part, float *logits, float *r1, int router_tiles,
                       const int *live);
-// tile ranges of the skinny output projection over M rows (see launch_gemm_oproj_residual): tiles per range
-int oproj_tiles_per_range(const Dims &D, int M);
-void launch_row_rstd(hipStream_t s, const float *x, int M, int d, int tiles_per_range, float eps, float *rstd);
 // ---- decode steps of 3 to 8 rows (few_kernels.hip): fp32 rows in and out, no packing, no partials
 constexpr int FEW_MAX_ROWS = 8;
 bool few_supported(const Dims &D);

@@ -10,14 +10,20 @@ SEED = 7878
 
 # fused layers: 208 columns (13 k-steps), FFN 336 (a ragged last tile pair), 7 heads in one group; wide: 928 columns, K split in two and more
 FUSED = dict(n_layers=2, d_model=208, n_q_heads=7, n_kv_heads=1, head_dim=64, d_ffn=336, vocab=1000, router_hidden=40, dtype=synth.BF16, kv_dtype=synth.BF16)
+LONG_K = dict(FUSED, d_ffn=1296)     # an FFN output in uneven parts
 WIDE = dict(n_layers=2, d_model=928, n_q_heads=5, n_kv_heads=1, head_dim=128, d_ffn=1184, vocab=1000, router_hidden=40, dtype=synth.BF16, kv_dtype=synth.BF16)
 
 
 @pytest.mark.parametrize("name,shape,lens,kv_page", [
-    ("fused", FUSED, [97] * 15 + [81], 0),          # 1536 rows: the smallest pass of this kind
+    ("long_k", LONG_K, [97] * 8 + [56], 0),         # 832 rows: the smallest pass of this kind, output projection and gate/up by the skinny kernels
+    ("long_k", LONG_K, [128] * 7 + [127], 32),      # 1023 rows
+    ("long_k", LONG_K, [120] * 19 + [24], 0),       # 2304 rows: gate/up as blocks
+    ("long_k", LONG_K, [128] * 24, 0),              # 3072 rows: FFN output in one piece
+    ("fused", FUSED, [97] * 15 + [81], 0),
     ("fused", FUSED, [130] * 15 + [1, 64], 32),     # 2015 rows, paged
     ("fused_f32kv", dict(FUSED, kv_dtype=synth.F32), [111] * 14, 0),
-    ("wide", WIDE, [79, 81], 0),                    # 160 rows: K splits kept apart, projections by the skinny kernels
+    ("wide", WIDE, [33, 63], 0),                    # 96 rows: the smallest pass of a wide model, parts of K kept apart
+    ("wide", WIDE, [79, 81], 0),
     ("wide", WIDE, [100, 1, 120], 32),
     ("wide", WIDE, [127] * 20, 0),                  # whole projections
 ])
