@@ -638,16 +638,17 @@ __global__ __launch_bounds__(64 * ATT_ROW_WAVES) void attn_rows_kernel(Dims D, c
     if (pack) store_packed(pack + (size_t)(r >> 6) * (D.qw / 16) * ncb * 64, ncb, r & 63, col >> 3, o);
 }
 
-// Prompts and catch-up segments: one workgroup of 8 wavefronts per (block of up to 32/G consecutive query rows of one
+// Prompts and catch-up segments: one workgroup of NW wavefronts per (block of up to 32/G consecutive query rows of one
 // sequence, kv head). The rows share every key and value they read (a wavefront's 32 accumulator columns hold the heads of
 // all the rows, see AttnWave MULTI), so a prompt's cache is walked once per block of rows instead of once per row.
-// Wavefront w walks the key blocks w, w + 8, ... of the whole context; the eight results are combined through LDS in a fixed
-// order. qblock[b] = first row * 8 + number of rows of block b (consecutive positions of one slot).
-template <int DH, bool PAGED>
-__global__ __launch_bounds__(64 * ATT_ROW_WAVES) void attn_block_kernel(Dims D, const float *q, const bf16_t *kc, const bf16_t *vt, Rows rows,
+// Wavefront w walks the key blocks w, w + NW, ... of the whole context; the NW results are combined through LDS in a fixed
+// order. Bound: the fixed part of a workgroup (its rows' queries, converted by every wavefront, and the LDS exchange) and the vector arithmetic of the
+// softmax, so a launch that fills the chip anyway takes few wavefronts a workgroup, see launch_attention_blocks. qblock[b] = first row * 8 + number of rows of block b (consecutive positions of one slot).
+template <int DH, bool PAGED, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_block_kernel(Dims D, const float *q, const bf16_t *kc, const bf16_t *vt, Rows rows,
                                                                        const int *qblock, float *att, uint4 *pack, int ncb)
 {
-    constexpr int DB = DH / 32, NW = ATT_ROW_WAVES;
+    constexpr int DB = DH / 32;
     __shared__ float s_m[NW][32], s_l[NW][32];
     __shared__ __attribute__((aligned(16))) float s_o[NW][32][DH];
     const int code = qblock[blockIdx.x], r0 = code >> 3, nq = code & 7, g = blockIdx.y, wv = threadIdx.x >> 6;
@@ -670,43 +671,54 @@ __global__ __launch_bounds__(64 * ATT_ROW_WAVES) void attn_block_kernel(Dims D, 
     }
     __syncthreads();
     const int live = min(NW, (j1 + 31) / 32);        // wavefronts that had keys
-    const int task = threadIdx.x;                    // (column = row and head, 8 dims)
-    if (task >= nq * G * (DH / 8)) return;
-    const int c = task / (DH / 8), d0 = (task % (DH / 8)) * 8, r = r0 + c / G, h = c % G;
-    float M = -INFINITY, L = 0.f, o[8];
+    for (int task = threadIdx.x; task < nq * G * (DH / 8); task += 64 * NW) {   // (column = row and head, 8 dims)
+        const int c = task / (DH / 8), d0 = (task % (DH / 8)) * 8, r = r0 + c / G, h = c % G;
+        float M = -INFINITY, L = 0.f, o[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = 0.f;
-    for (int w2 = 0; w2 < live; ++w2) M = fmaxf(M, s_m[w2][c]);     // finite: key 0 is seen by every row
-    for (int w2 = 0; w2 < live; ++w2) {
-        const float f = __expf(s_m[w2][c] - M);                     // 0 for a wavefront whose keys all lie past this row
-        L = fmaf(s_l[w2][c], f, L);
-        const float4 a = *reinterpret_cast<const float4 *>(&s_o[w2][c][d0]), b = *reinterpret_cast<const float4 *>(&s_o[w2][c][d0 + 4]);
-        o[0] = fmaf(a.x, f, o[0]); o[1] = fmaf(a.y, f, o[1]); o[2] = fmaf(a.z, f, o[2]); o[3] = fmaf(a.w, f, o[3]);
-        o[4] = fmaf(b.x, f, o[4]); o[5] = fmaf(b.y, f, o[5]); o[6] = fmaf(b.z, f, o[6]); o[7] = fmaf(b.w, f, o[7]);
-    }
-    const float inv = 1.0f / L;
+        for (int e = 0; e < 8; ++e) o[e] = 0.f;
+        for (int w2 = 0; w2 < live; ++w2) M = fmaxf(M, s_m[w2][c]);     // finite: key 0 is seen by every row
+        for (int w2 = 0; w2 < live; ++w2) {
+            const float f = __expf(s_m[w2][c] - M);                     // 0 for a wavefront whose keys all lie past this row
+            L = fmaf(s_l[w2][c], f, L);
+            const float4 a = *reinterpret_cast<const float4 *>(&s_o[w2][c][d0]), b = *reinterpret_cast<const float4 *>(&s_o[w2][c][d0 + 4]);
+            o[0] = fmaf(a.x, f, o[0]); o[1] = fmaf(a.y, f, o[1]); o[2] = fmaf(a.z, f, o[2]); o[3] = fmaf(a.w, f, o[3]);
+            o[4] = fmaf(b.x, f, o[4]); o[5] = fmaf(b.y, f, o[5]); o[6] = fmaf(b.z, f, o[6]); o[7] = fmaf(b.w, f, o[7]);
+        }
+        const float inv = 1.0f / L;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] *= inv;
-    const int col = (g * G + h) * DH + d0;
-    if (att) {
-        *reinterpret_cast<float4 *>(att + (size_t)r * D.qw + col) = make_float4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<float4 *>(att + (size_t)r * D.qw + col + 4) = make_float4(o[4], o[5], o[6], o[7]);
+        for (int e = 0; e < 8; ++e) o[e] *= inv;
+        const int col = (g * G + h) * DH + d0;
+        if (att) {
+            *reinterpret_cast<float4 *>(att + (size_t)r * D.qw + col) = make_float4(o[0], o[1], o[2], o[3]);
+            *reinterpret_cast<float4 *>(att + (size_t)r * D.qw + col + 4) = make_float4(o[4], o[5], o[6], o[7]);
+        }
+        if (pack) store_packed(pack + (size_t)(r >> 6) * (D.qw / 16) * ncb * 64, ncb, r & 63, col >> 3, o);
     }
-    if (pack) store_packed(pack + (size_t)(r >> 6) * (D.qw / 16) * ncb * 64, ncb, r & 63, col >> 3, o);
 }
 
 int attention_block_rows(const Dims &D) { return std::min(4, 32 / D.G); }
 
-void launch_attention_blocks(hipStream_t s, const Dims &D, const float *q, const void *kc, const void *vt, Rows rows, const int *qblock, int nblocks,
+// Wavefronts per workgroup: two where the launch fills the chip with them, four where it takes those to fill it (or the context is short, or the exchange of
+// eight would take a compute unit's LDS: 128-wide heads), eight otherwise. Whole passes of the 0.5B-class model with 8 / 4 / 2: 36800 prompt rows 71.4 / 68.3 / 66.7 ms,
+// 2000 rows 4.94 / 4.79 / 4.73; 2048 catch-up rows at contexts to 1500 (1024 workgroups) 5.64 / 5.52 / 5.49; 800 rows (400 workgroups) 3.11 / 3.06 / 3.28; 280 rows
+// (160) 1.87 / 1.95 / 2.18; 256 rows of one prompt 1.54 / 1.51 / 1.55. 7B-class, 180 rows at contexts to 1500 (192): 8.38 / 8.29 / 8.77.
+void launch_attention_blocks(hipStream_t s, const Dims &D, const float *q, const void *kc, const void *vt, Rows rows, int max_ctx, const int *qblock, int nblocks,
                              float *att, void *pack, int ncb)
 {
     const dim3 grid(nblocks, D.Hkv);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(64 * ATT_ROW_WAVES), 0, s, D, q, (const bf16_t *)kc, (const bf16_t *)vt, rows, qblock, pack ? nullptr : att,
+    auto go = [&](auto kern, int nw) {
+        hipLaunchKernelGGL(kern, grid, dim3(64 * nw), 0, s, D, q, (const bf16_t *)kc, (const bf16_t *)vt, rows, qblock, pack ? nullptr : att,
                            (uint4 *)pack, ncb);
     };
-    if (D.dh == 64) { if (D.page) go(attn_block_kernel<64, true>); else go(attn_block_kernel<64, false>); }
-    else { if (D.page) go(attn_block_kernel<128, true>); else go(attn_block_kernel<128, false>); }
+    auto pick = [&](auto w) {
+        constexpr int W = decltype(w)::value;
+        if (D.dh == 64) { if (D.page) go(attn_block_kernel<64, true, W>, W); else go(attn_block_kernel<64, false, W>, W); }
+        else { if (D.page) go(attn_block_kernel<128, true, W>, W); else go(attn_block_kernel<128, false, W>, W); }
+    };
+    const int wgs = nblocks * D.Hkv;
+    if (wgs >= 900) pick(std::integral_constant<int, 2>{});
+    else if (wgs >= 400 || max_ctx <= 256 || D.dh == 128) pick(std::integral_constant<int, 4>{});
+    else pick(std::integral_constant<int, 8>{});
 }
 
 void launch_attention_mfma(hipStream_t s, const Dims &D, const float *q, const void *kc, const void *vt, Rows rows, int max_ctx, float *part,
