@@ -27,6 +27,7 @@ struct TileArgs {
     const uint4 *Wt;      // tiled weights [tile][KS][64]
     const uint4 *pack;    // packed activations [64-row group][KS][4][64]
     int KS, kwg, ksw;     // K / 16; k-steps per workgroup (gridDim.y of them along K); k-steps per split of the sum
+    int spw;              // splits per workgroup (TilePartial, TileResidualParts)
     int n_tiles, groups;  // 32-feature tiles, 64-row groups
     int M;
     int n_mblk, n_nblk;   // row blocks, feature blocks
@@ -60,16 +61,11 @@ struct TilePartial {   // split-K partial sums: part[split][m][n]
     float *part;
     int N, M;
     template <int WM> struct State { __device__ void init(const TilePartial &, const int (&)[WM], int) {} };
-    template <int WM> __device__ __forceinline__ void start(State<WM> &, int, int, int, float (&v)[8]) const
-    {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = 0.f;
-    }
-    template <int WM> __device__ __forceinline__ void store(State<WM> &, int, int m, int t, int i0, const float (&v)[8]) const
+    __device__ __forceinline__ void store(int split, int m, int t, int i0, const float (&v)[8]) const
     {
         const int n = t * 32 + i0;
         if (m < M && n < N) {
-            float *dst = part + ((size_t)blockIdx.y * M + m) * N + n;
+            float *dst = part + ((size_t)split * M + m) * N + n;
             *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
             *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
         }
@@ -186,6 +182,12 @@ struct TileResidual {
     }
 };
 
+// The same for a product whose K several workgroups share: those of the first part add their splits to x, the others leave theirs apart for the consumer
+// to add in order (x as the first part left it, then the partials), which gives the sums of TileResidual.
+struct TileResidualParts : TileResidual {
+    TilePartial rest;      // splits from the second part on
+};
+
 // LM head over more than 64 rows (0.14 PFLOP of bf16 work at 256 rows and 152 k features: 142 -> 129 us with the norm and the final kernel;
 // below that one 64-row group streams the weights at HBM speed). Softmax statistics of a block's features per row: part[feature block][m] = {max, lowest index that attains it, sum exp(z - max)}. The tiles from vt on are
 // the router's first layer: their sums go to r1 and stay out of the statistics (see EpiLmHead). logits: also written, or NULL.
@@ -246,18 +248,24 @@ struct TileHead {
     }
 };
 
+__device__ __forceinline__ const TilePartial &partial_of(const TilePartial &e) { return e; }
+__device__ __forceinline__ const TilePartial &partial_of(const TileResidualParts &e) { return e.rest; }
+
 // ------------------------------------------------------------------ the kernel
 
 // GM x GN wavefronts of WM x WN accumulators; ST: stages of one k-step in the ring; OCC: wavefronts per SIMD the registers must leave room for.
 // Sums are formed in the order of the skinny kernels: the k-steps of a split (ksw of them) fall into four runs of `per` = ksw / 4 rounded up, each
 // accumulated from zero by the matrix instructions (hi product, then lo product, k-step by k-step); the four runs of a split are added in order,
-// and the splits are added in order to the epilogue's starting value. A product in one piece then has the bits of its skinny kernel, and one in parts
-// (TilePartial) the same depth of sums.
+// and the splits are added in order to the epilogue's starting value. Where several workgroups share K (TilePartial, TileResidualParts) the splits are left
+// apart for the next kernel to add in the same order, however many of them one workgroup walks. A pass over many rows then leaves the same bits in the cache as one over few: a bf16 cache turns another order
+// of the same sums into other roundings, which 28 layers amplify to 1.3e-3 of the hidden rows (prompts of 39 to 71 tokens).
 // SPLITS: more than one split is walked (or the start is not zero), which takes a third set of sums.
 template <int GM, int GN, int WM, int WN, int ST, int OCC, bool SPLITS, class Epi>
 __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a, Epi epi)
 {
     constexpr bool PLAIN = std::is_same_v<Epi, TileHead>;   // nothing depends on the order of the sum: one run
+    constexpr bool APART = std::is_same_v<Epi, TilePartial>, CHAIN = std::is_same_v<Epi, TileResidualParts>;
+    const bool apart = APART || (CHAIN && blockIdx.y > 0);   // this workgroup leaves its splits apart (uniform)
     if constexpr (PLAIN)
         if (epi.live && *epi.live == 0) return;   // uniform over the launch
     constexpr int NWV = GM * GN, BT = GN * WN, RB = GM * WM, CH = BT + 2 * RB;   // wavefronts, weight tiles, 32-row blocks, 1 KiB operands per k-step
@@ -320,7 +328,7 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
         for (int e = 0; e < 8; ++e) v[e] = c[8 * h + e];
     };
     if constexpr (SPLITS)
-        each([&](int mi, int ni) {
+        if (!apart) each([&](int mi, int ni) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 float v[8];
@@ -362,7 +370,7 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
     wait_and_barrier<(P - 1) * L>();
     issue();                                                    // the ring is full
     fetch(even);
-    int left = nstep;
+    int left = nstep, split = (CHAIN ? blockIdx.y - 1 : blockIdx.y) * a.spw;
     if constexpr (PLAIN) {
         clear(acc);
 #pragma unroll 1
@@ -401,14 +409,26 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
             });
         }
         if constexpr (SPLITS)
-            each([&](int mi, int ni) {
+            if (!apart) each([&](int mi, int ni) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) tot[mi][ni][r] += sum[mi][ni][r];
             });
+        if constexpr (APART || CHAIN) if (apart) {   // (stores only make the waits of the next steps stricter: loads land in order)
+            each([&](int mi, int ni) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float v[8];
+                    run8(sum[mi][ni], h, v);
+                    partial_of(epi).store(split, m[mi], t0 + ni, 16 * h + 8 * hf, v);
+                }
+            });
+            ++split;
+        }
     }
     wait_and_barrier<0>();                                      // no load may be in flight into LDS when the workgroup ends
-    if constexpr (PLAIN) return;
+    if constexpr (PLAIN || APART) return;
     else {
+    if (apart) return;
     // one split: the starting value joins last (the same sum)
     auto value = [&](int mi, int ni, int h, float (&v)[8]) {
         if constexpr (SPLITS) run8(tot[mi][ni], h, v);
@@ -511,32 +531,29 @@ void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K
     else launch_tile<true>(s, a, 1, e);
 }
 
-// Parts of K for a product whose blocks leave compute units idle: as many as keep every block of 64 x 128 on a unit of its own, two blocks a unit where
-// the blocks of one part fill more than half of them. (What counts is the busiest unit: 111 rows of the 7B-class model with 2 x 28 x 4 blocks 6.5 ms, with
-// 2 x 28 x 7 6.9 ms; 300 rows with 5 x 28 blocks 12.4 ms, with 5 x 28 x 3 11.1 ms.) A part has at least 256 columns.
-static int tile_splits(int K, int N, int M)
+// Workgroups along K for a product of few blocks: as many as leave every block of 64 x 128 a compute unit of its own, at least two, each with whole splits of
+// the sum. Returns the number of splits.
+static int share_splits(TileArgs &a, int N, int M)
 {
-    const int whole = (M + 63) / 64 * ((N + 127) / 128), steps = K / 16;
-    const int want = std::max(1, (whole > 128 ? 512 : 256) / whole), S = std::min({want, 16, std::max(1, steps / 16)}), per = (steps + S - 1) / S;
-    return (steps + per - 1) / per;
-}
-
-size_t tile_partial_floats(int K, int N, int max_rows)
-{
-    size_t most = 0;
-    for (int groups = 1; groups <= (max_rows + 63) / 64; ++groups) {
-        const int M = std::min(max_rows, 64 * groups);
-        most = std::max(most, (size_t)tile_splits(K, N, M) * M * N);
-    }
-    return most;
+    const int S = (a.KS + a.ksw - 1) / a.ksw, blocks = (M + 63) / 64 * ((N + 127) / 128), P = std::min(S, std::max(2, 256 / blocks));
+    a.spw = (S + P - 1) / P;
+    a.kwg = a.spw * a.ksw;
+    return S;
 }
 
 void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit)
 {
-    *nsplit = tile_splits(K, N, M);
-    TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, 0);
-    a.ksw = a.kwg = (a.KS + *nsplit - 1) / *nsplit;
-    launch_tile<false>(s, a, *nsplit, TilePartial{part, N, M});
+    TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, gemm_split_steps(K, N, M));
+    *nsplit = share_splits(a, N, M);
+    launch_tile<false>(s, a, (*nsplit + a.spw - 1) / a.spw, TilePartial{part, N, M});
+}
+
+void launch_tile_residual_parts(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, float *part, int *nsplit)
+{
+    TileArgs a = tile_args(Wt, pack, K, (N + 31) / 32, M, gemm_split_steps(K, N, M));
+    const int S = share_splits(a, N, M);
+    *nsplit = S - a.spw;
+    launch_tile<true>(s, a, (S + a.spw - 1) / a.spw, TileResidualParts{{x, nullptr, nullptr, nullptr, M, N}, {part, N, M}});
 }
 
 int tile_head_blocks(int V, int router_tiles) { return ((V + 31) / 32 + router_tiles + 7) / 8; }

@@ -168,9 +168,7 @@ Layout make_layout(const tr_config *c)
         if (L.split) {
             const size_t n_qkv = qw + 2 * kvw, n_gu = 2 * tiles(F) * 32;
             part_floats = std::max({part_floats, gemm_partial_floats((int)d, (int)n_qkv, Ri), gemm_partial_floats((int)d, (int)n_gu, Ri)});
-            part_floats = std::max(part_floats, tile_partial_floats((int)d, (int)n_qkv, Ri));
         }
-        part_floats = std::max({part_floats, tile_partial_floats((int)qw, (int)d, Ri), tile_partial_floats((int)F, (int)d, Ri)});
         if (L.split_head)   // partial logits of a tail call: up to max_batch rows
             part_floats = std::max(part_floats, gemm_partial_floats((int)d, c->vocab, c->max_batch));
         const size_t part_bytes = part_floats * 4;
@@ -334,6 +332,16 @@ void profile_next_turn(tr_ctx *ctx)
     ctx->prof_seen = 0;
 }
 
+// Rows from which a wide model's layers are block products. Measured whole passes, skinny / blocks: 12 layers of 1024 columns (FFN 4096) 128 rows 0.740 / 0.825 ms,
+// 192 rows (24 blocks of the FFN output) 0.849 / 0.842, 256 rows 0.948 / 0.868; of 2048 columns (FFN 8192) 96 rows 1.254 / 1.192; of 4096 columns (FFN 14336)
+// 96 rows 2.551 / 2.539, 128 rows 2.75 / 2.63. Deeper FFN outputs leave more partials: the 7B-class model (22 splits) 112 rows 6.27 / 6.48 ms, 136 rows
+// 7.51 / 7.70, 160 rows 8.05 / 7.81.
+bool wide_takes_blocks(const Dims &D, int R)
+{
+    const int steps = D.F / 16, k_d = gemm_split_steps(D.F, D.d, R), splits = (steps + k_d - 1) / k_d;
+    return R >= (splits > 16 ? 144 : 96) && tile_fills_chip(D.d, R, 24);
+}
+
 // All layers over the rows currently described by the device row arrays. Returns the number of split-K partial
 // buffers of the last down projection that still have to be added to the residual stream (matrix-core path).
 // distinct_slots: every row belongs to a different slot (a decode step), so no row reads a key another row appends.
@@ -357,21 +365,23 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
             launch_attention(s, ctx->c.kv_dtype, D, q_, ctx->kc_layer(l), ctx->vc_layer(l), rows_, max_ctx_, part_, part_floats_, cnt_, att_, pack_, ncb_, defer_);
         }
     };
-    // Many rows: block products (tile_kernels.hip) whose epilogues finish the layer. The 0.5B-class layer takes them one by one: below these lines the
-    // skinny product of the layer is the faster one. Whole passes, all products skinny / FFN output and q|k|v as blocks / the output projection too /
-    // gate and up too / FFN output in one piece: 768 rows 2.73 / 2.80 / 2.87 ms, 896 rows 2.98 / 2.85 / 2.88 / 2.95, 1088 rows 3.43 / 3.18 / 3.17 / 3.30, 2000 rows
+    // Many rows: block products (tile_kernels.hip) whose epilogues finish the layer, with the sums of the skinny products below (only the 1/rms behind the
+    // output projection is added up in ranges of 32 columns whatever the rows). The 0.5B-class layer takes them one by one: below these lines the skinny
+    // product of the layer is the faster one. Whole passes, all products skinny / FFN output and q|k|v as blocks / the output projection too / gate and up
+    // too / FFN output in one piece: 768 rows 2.73 / 2.80 / 2.87 ms, 896 rows 2.98 / 2.85 / 2.88 / 2.95, 1088 rows 3.43 / 3.18 / 3.17 / 3.30, 2000 rows
     // 5.04 / 4.71 / 4.62 / 4.70 / 4.76, 2560 rows 6.25 / 5.95 / 5.81 / 5.79 / 5.85, 4000 rows 9.20 / 8.36 / 8.18 / 8.16 / 8.16, 8000 rows 17.50 / 15.93 / 15.34 /
-    // 15.42 / 15.22. 7B-class at 81 / 111 rows: skinny 6.28 / 6.90 ms, blocks 6.32 / 6.55.
-    if (!live && ((L.mfma && R >= 832) || (L.split && R >= 96))) {
+    // 15.42 / 15.22.
+    if (!live && ((L.mfma && R >= 832) || (L.split && wide_takes_blocks(D, R)))) {
         float *sumsq = ctx->at<float>(L.sumsq), *part = ctx->at<float>(L.part);
         const bool defer = L.mfma && gemm_oproj_residual_supported(D);   // the output projection packs the FFN input itself
         const bool tile_o = !defer || R >= 1024, tile_gu = L.split || R >= 2304;
         const int steps_d = D.d / 16, n_qkv = D.qw + 2 * D.kvw, n_gu = 2 * ((D.F + 31) / 32) * 32;
         const int k_qkv = L.mfma ? steps_d : gemm_split_steps(D.d, n_qkv, R), k_gu = L.mfma ? steps_d : gemm_split_steps(D.d, n_gu, R);
         const int k_o = defer ? D.qw / 16 : gemm_split_steps(D.qw, D.d, R), k_d = gemm_split_steps(D.F, D.d, R);
-        // a wide model's products with few blocks keep parts of K apart (7B-class at 512 / 768 / 1152 rows, down projection with the partials' share of the
-        // next launch 181 / 253 / 371 us, in one piece 188 / 277 / 317; q|k|v 44 blocks of 128 features: in one piece from 320 rows on)
-        const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = L.mfma ? R >= 3072 : tile_fills_chip(D.d, R, 448);
+        // Products of few blocks share K among workgroups (launch_tile_residual_parts), from 161 blocks on they are in one piece. Passes with the FFN output
+        // in parts / in one piece: 7B-class, 300 rows (140 blocks) 11.55 / 12.46 ms, 400 rows (196) 15.0 / 14.96, 512 rows (224) 15.92 / 15.59; 0.5B-class,
+        // 1197 rows (133) 3.28 / 3.43 ms, 1529 rows (168) 3.83 / 3.75, 2040 rows (224) 4.48 / 4.26. q|k|v of a wide model: in one piece from 320 rows on.
+        const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = tile_fills_chip(D.d, R, 161);
         PrepArgs p{};
         p.x = x; p.M = R; p.d = D.d; p.eps = D.eps; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = 4; p.part = part; p.part_M = R;
         int pending = 0, ns = 0, n_ss = (D.d + 31) / 32;
@@ -397,7 +407,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
                     n_ss = launch_gemm_oproj_residual(s, D, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), R, x, w.ln2, ctx->at<uint4>(L.pack_d), sumsq, L.ss_stride);
                 else if (defer || whole_d)
                     launch_tile_residual(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, x, w.ln2, defer ? ctx->at<uint4>(L.pack_d) : nullptr, sumsq, k_o);
-                else launch_tile_partial(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, part, &p.nsplit);
+                else launch_tile_residual_parts(s, ctx->wt(l, L.wt_o), ctx->at<uint4>(L.pack_a), D.qw, D.d, R, x, part, &p.nsplit);
             }
             if (!defer) {
                 p.gain = (const bf16_t *)w.ln2;
@@ -414,7 +424,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
                 Bracket br(ctx, s, TR_KERNEL_DOWN);
                 pending = 0;
                 if (whole_d) launch_tile_residual(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, x, nullptr, nullptr, nullptr, k_d);
-                else launch_tile_partial(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, part, &pending);
+                else launch_tile_residual_parts(s, ctx->wt(l, L.wt_d), ctx->at<uint4>(L.pack_h), D.F, D.d, R, x, part, &pending);
             }
         }
         return pending;

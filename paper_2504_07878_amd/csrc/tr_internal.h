@@ -196,9 +196,10 @@ void launch_row_rstd(hipStream_t s, float *sumsq, int M, int d, int n_ss, float 
 // x[M][N] += W . A; pack_out != NULL: also the next layer's packed input x * gain and the rows' sums of squares per 32 columns, sumsq[row][SS_STRIDE]
 constexpr int SS_STRIDE = 32;   // one cache line
 void launch_tile_residual(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, const void *gain, void *pack_out, float *sumsq, int ksw);
-// split-K partials of the same sums (see launch_gemm_partial), in parts of its own
+// split-K partials of the same sums (see launch_gemm_partial)
 void launch_tile_partial(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *part, int *nsplit);
-size_t tile_partial_floats(int K, int N, int max_rows);   // the most floats of partials it leaves for up to max_rows rows
+// x[M][N] += the first splits of W . A, the *nsplit others left as partials
+void launch_tile_residual_parts(hipStream_t s, const void *Wt, const void *pack, int K, int N, int M, float *x, float *part, int *nsplit);
 // LM head over more than 64 rows: softmax statistics per row and block of 256 features (tile_head_blocks of them), see TileHead
 int tile_head_blocks(int V, int router_tiles);
 void launch_tile_head(hipStream_t s, const Dims &D, const void *Wt, const void *pack, int M, float *part, float *logits, float *r1, int router_tiles,

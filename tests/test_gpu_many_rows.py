@@ -22,8 +22,8 @@ WIDE = dict(n_layers=2, d_model=928, n_q_heads=5, n_kv_heads=1, head_dim=128, d_
     ("fused", FUSED, [97] * 15 + [81], 0),
     ("fused", FUSED, [130] * 15 + [1, 64], 32),     # 2015 rows, paged
     ("fused_f32kv", dict(FUSED, kv_dtype=synth.F32), [111] * 14, 0),
-    ("wide", WIDE, [33, 63], 0),                    # 96 rows: the smallest pass of a wide model, parts of K kept apart
-    ("wide", WIDE, [79, 81], 0),
+    ("wide", WIDE, [33, 63], 0),
+    ("wide", WIDE, [79, 81], 0),                    # 160 rows: 24 blocks of the FFN output, the smallest pass of blocks, parts of K kept apart
     ("wide", WIDE, [100, 1, 120], 32),
     ("wide", WIDE, [127] * 20, 0),                  # whole projections
 ])
