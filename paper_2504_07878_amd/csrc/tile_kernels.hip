@@ -35,11 +35,11 @@ struct TileArgs {
     int items, per_xcd;   // n_mblk * n_nblk, and its eighth rounded up
 };
 
-// one wavefront: 64 x 16 bytes from base + lane's offset to LDS bytes lds .. lds + 1023. (A scalar write of M0 needs one wait state before an
-// LDS load uses it.)
+// one wavefront: 64 x 16 bytes from base + lane's offset to LDS bytes lds .. lds + 1023. The compiler writes M0, which must be one wait state before an LDS
+// load uses it.
 __device__ __forceinline__ void load_to_lds(uint32_t lds, uint32_t lane_off, const char *base)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(lane_off), "s"(base) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"{m0}"(lds), "v"(lane_off), "s"(base) : "memory");
 }
 // own loads but the youngest N have landed, own LDS reads are done, then the workgroup's barrier. (Built-ins rather than assembly for the wait: the
 // compiler then knows that no LDS read is outstanding and adds no waits of its own for the operands read a step earlier.)
