@@ -332,6 +332,11 @@ void profile_next_turn(tr_ctx *ctx)
     ctx->prof_seen = 0;
 }
 
+// Rows from which a fused model's layers are block products (run_layers has the 0.5B-class figures). The products of a narrow model are over before blocks gain
+// anything: the FFN output has to have 660 M multiplications. Measured whole passes of 12 layers, skinny / blocks: 256 columns (FFN 1024) 1536 rows 0.61 / 0.68 ms,
+// 2048 rows 0.66 / 0.69, 2560 rows 0.75 / 0.71; 256 columns (FFN 3072) 832 rows 0.600 / 0.621, 1536 rows 0.775 / 0.759; 512 columns (FFN 2048) 832 rows 0.706 / 0.680.
+bool fused_takes_blocks(const Dims &D, int R) { return R >= 832 && (long long)R * D.d * D.F >= 660000000ll; }
+
 // Rows from which a wide model's layers are block products. Measured whole passes, skinny / blocks: 12 layers of 1024 columns (FFN 4096) 128 rows 0.740 / 0.825 ms,
 // 192 rows (24 blocks of the FFN output) 0.849 / 0.842, 256 rows 0.948 / 0.868; of 2048 columns (FFN 8192) 96 rows 1.254 / 1.192; of 4096 columns (FFN 14336)
 // 96 rows 2.551 / 2.539, 128 rows 2.75 / 2.63. Deeper FFN outputs leave more partials: the 7B-class model (22 splits) 112 rows 6.27 / 6.48 ms, 136 rows
@@ -371,10 +376,12 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
     // too / FFN output in one piece: 768 rows 2.73 / 2.80 / 2.87 ms, 896 rows 2.98 / 2.85 / 2.88 / 2.95, 1088 rows 3.43 / 3.18 / 3.17 / 3.30, 2000 rows
     // 5.04 / 4.71 / 4.62 / 4.70 / 4.76, 2560 rows 6.25 / 5.95 / 5.81 / 5.79 / 5.85, 4000 rows 9.20 / 8.36 / 8.18 / 8.16 / 8.16, 8000 rows 17.50 / 15.93 / 15.34 /
     // 15.42 / 15.22.
-    if (!live && ((L.mfma && R >= 832) || (L.split && wide_takes_blocks(D, R)))) {
+    if (!live && ((L.mfma && fused_takes_blocks(D, R)) || (L.split && wide_takes_blocks(D, R)))) {
         float *sumsq = ctx->at<float>(L.sumsq), *part = ctx->at<float>(L.part);
         const bool defer = L.mfma && gemm_oproj_residual_supported(D);   // the output projection packs the FFN input itself
-        const bool tile_o = !defer || R >= 1024, tile_gu = L.split || R >= 2304;
+        // (output projection: 1024 rows of the 0.5B-class model are 112 blocks; 12 layers of 384 columns at 1024 rows, skinny / blocks 0.660 / 0.695 ms, of 256
+        // columns with an FFN of 3072 0.643 / 0.681, of 512 columns at 1280 rows 0.861 / 0.885)
+        const bool tile_o = !defer || tile_fills_chip(D.d, R, 112), tile_gu = L.split || R >= 2304;
         const int steps_d = D.d / 16, n_qkv = D.qw + 2 * D.kvw, n_gu = 2 * ((D.F + 31) / 32) * 32;
         const int k_qkv = L.mfma ? steps_d : gemm_split_steps(D.d, n_qkv, R), k_gu = L.mfma ? steps_d : gemm_split_steps(D.d, n_gu, R);
         const int k_o = defer ? D.qw / 16 : gemm_split_steps(D.qw, D.d, R), k_d = gemm_split_steps(D.F, D.d, R);

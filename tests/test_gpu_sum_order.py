@@ -12,7 +12,7 @@ SEED = 7878
 WIDE = dict(n_layers=2, d_model=928, n_q_heads=5, n_kv_heads=1, head_dim=128, d_ffn=1184, vocab=1000, router_hidden=0, tie_lm_head=0, dtype=synth.BF16, kv_dtype=synth.BF16)
 WIDE_7B = dict(WIDE, n_layers=1, d_model=3584, n_q_heads=28, n_kv_heads=4, d_ffn=18944)
 WIDE_2048 = dict(WIDE, d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=8192)
-LONG_K = dict(n_layers=2, d_model=208, n_q_heads=7, n_kv_heads=1, head_dim=64, d_ffn=1296, vocab=1000, router_hidden=0, dtype=synth.BF16, kv_dtype=synth.BF16)
+LONG_K = dict(n_layers=2, d_model=256, n_q_heads=7, n_kv_heads=1, head_dim=64, d_ffn=3104, vocab=1000, router_hidden=0, dtype=synth.BF16, kv_dtype=synth.BF16)
 
 
 def _weights(s, gen):
