@@ -390,7 +390,7 @@ def measured_traffic(family):
     if not t:
         return None
     h = hashlib.sha256()
-    for name in ("mfma_kernels.hip", "tr_internal.h"):
+    for name in ("mfma_kernels.hip", "mfma_common.h", "tr_internal.h"):
         path = os.path.join(ROOT, "paper_2504_07878_amd", "csrc", name)
         if not os.path.exists(path):
             return None
@@ -401,13 +401,13 @@ def measured_traffic(family):
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on `bench.py --workload counters`, scaled by the 1 GiB copy kernel of the same
 # run (see profiles/); bytes per launch, per kernel family, with the hash of the kernel sources they were taken on.
 TRAFFIC = {
-    "attention": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 20754989, "write_bytes": 1660144},
-    "gateup": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 19572731, "write_bytes": 1245184},
-    "down": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 19317768, "write_bytes": 1376256},
-    "qkv": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 6232760, "write_bytes": 507904},
-    "oproj": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 5444322, "write_bytes": 516096},
-    "prep": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 946608, "write_bytes": 809562},
-    "lmhead": {"source_sha256": "3c3c251f49f4dae610eb9c84ca2080ead685e0ede0a9a81077ff54542a8f159d", "fetch_bytes": 274908243, "write_bytes": 322567},
+    "attention": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 20803047, "write_bytes": 1660144},
+    "gateup": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 19569671, "write_bytes": 1245184},
+    "down": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 19309588, "write_bytes": 1376256},
+    "qkv": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 6239932, "write_bytes": 507904},
+    "oproj": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 5437157, "write_bytes": 516096},
+    "prep": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 953821, "write_bytes": 809562},
+    "lmhead": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 274896646, "write_bytes": 322560},
 }
 
 

@@ -366,7 +366,8 @@ struct AttnWave {
         // NB blocks of 32 keys are in flight (64-wide heads: 64 keys; three or four measured no faster: a compute unit's requests in flight are limited
         // well below what one wavefront can ask for). Rows on their own (one or two wavefronts per SIMD): a block's registers take the block NB further on
         // as soon as the products have read them (64 rows of 760 keys, 64-wide: 11.9 -> 11.0 us; 63 rows of up to 937 keys, 128-wide: 20.1 -> 16.8 us).
-        // Blocks of rows leave that to the other wavefronts of the SIMD: the registers it takes cost one of three (4600 prompt rows: 90 -> 104 us).
+        // Blocks of rows do without: with eight wavefronts a block (three per SIMD) the registers it takes cost one of them, 4600 prompt rows 90 -> 104 us.
+        // The blocks of two and four that most launches take have two wavefronts per SIMD (128-wide heads: one) as it is; not measured on those.
         constexpr int NB = NBLK;
         constexpr bool AHEAD = !MULTI;
         uint4 ka[NB][KSQ], va[NB][2][DB];
@@ -701,7 +702,9 @@ int attention_block_rows(const Dims &D) { return std::min(4, 32 / D.G); }
 // Wavefronts per workgroup: two where the launch fills the chip with them, four where it takes those to fill it (or the context is short, or the exchange of
 // eight would take a compute unit's LDS: 128-wide heads), eight otherwise. Whole passes of the 0.5B-class model with 8 / 4 / 2: 36800 prompt rows 71.4 / 68.3 / 66.7 ms,
 // 2000 rows 4.94 / 4.79 / 4.73; 2048 catch-up rows at contexts to 1500 (1024 workgroups) 5.64 / 5.52 / 5.49; 800 rows (400 workgroups) 3.11 / 3.06 / 3.28; 280 rows
-// (160) 1.87 / 1.95 / 2.18; 256 rows of one prompt 1.54 / 1.51 / 1.55. 7B-class, 180 rows at contexts to 1500 (192): 8.38 / 8.29 / 8.77.
+// (160) 1.87 / 1.95 / 2.18; 256 rows of one prompt 1.54 / 1.51 / 1.55. 7B-class, 180 rows at contexts to 1500 (192): 8.38 / 8.29 / 8.77. These compare the kernels
+// as the compiler makes them: 154 registers with eight wavefronts (three per SIMD; 128-wide heads 202, two), 201 vector and accumulation registers with two or
+// four (two per SIMD; 128-wide heads 281, one), since nothing but the workgroup's size bounds them there.
 void launch_attention_blocks(hipStream_t s, const Dims &D, const float *q, const void *kc, const void *vt, Rows rows, int max_ctx, const int *qblock, int nblocks,
                              float *att, void *pack, int ncb)
 {

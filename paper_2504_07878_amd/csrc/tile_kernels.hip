@@ -14,9 +14,9 @@
 //     8 consecutive features of one row (tile_feature), which is what the epilogues consume.
 //   * Blocks are dealt to the XCDs in contiguous pieces of an order that walks groups of gm row blocks x features, so that the workgroups
 //     of an XCD share operands in its L2.
-// What bounds it: the chip's power at this mix of matrix instructions and operand traffic. 1152 x 37888 x 3584 (hi and lo products, 0.63 PFLOP of bf16
-// work) takes 545 us = 1.15 PFLOP/s at 1.8 GHz with the matrix pipes 57 % busy; a bf16 library product of the same work 549 us; the bare matrix
-// instructions on random data, without loads and LDS reads, 345 us (1.8 PFLOP/s).
+// What bounds it: the chip's power at this mix of matrix instructions and operand traffic. 1151 x 37888 x 3584 (hi and lo products, 0.63 TFLOP of bf16
+// work) takes 515 to 525 us = 1.2 PFLOP/s at 1.6 GHz with the matrix pipes 72 % busy; a bf16 library product of the same work 569 us. Launches of few
+// rounds of blocks leave the pipes idle at their ends: 8192 x 896 x 896 42 us, 24 % busy.
 #include "mfma_common.h"
 #include <algorithm>
 #include <type_traits>
@@ -188,7 +188,7 @@ struct TileResidualParts : TileResidual {
     TilePartial rest;      // splits from the second part on
 };
 
-// LM head over more than 64 rows (0.14 PFLOP of bf16 work at 256 rows and 152 k features: 142 -> 129 us with the norm and the final kernel;
+// LM head over more than 64 rows (139.6 GFLOP of bf16 work at 256 rows and 152 k features: 142 -> 129 us with the norm and the final kernel;
 // below that one 64-row group streams the weights at HBM speed). Softmax statistics of a block's features per row: part[feature block][m] = {max, lowest index that attains it, sum exp(z - max)}. The tiles from vt on are
 // the router's first layer: their sums go to r1 and stay out of the statistics (see EpiLmHead). logits: also written, or NULL.
 struct TileHead {

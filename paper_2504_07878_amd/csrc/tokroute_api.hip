@@ -387,7 +387,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
         const int k_o = defer ? D.qw / 16 : gemm_split_steps(D.qw, D.d, R), k_d = gemm_split_steps(D.F, D.d, R);
         // Products of few blocks share K among workgroups (launch_tile_residual_parts), from 161 blocks on they are in one piece. Passes with the FFN output
         // in parts / in one piece: 7B-class, 300 rows (140 blocks) 11.55 / 12.46 ms, 400 rows (196) 15.0 / 14.96, 512 rows (224) 15.92 / 15.59; 0.5B-class,
-        // 1197 rows (133) 3.28 / 3.43 ms, 1529 rows (168) 3.83 / 3.75, 2040 rows (224) 4.48 / 4.26. q|k|v of a wide model: in one piece from 320 rows on.
+        // 1197 rows (133) 3.28 / 3.43 ms, 1529 rows (168) 3.83 / 3.75, 2040 rows (224) 4.48 / 4.26. q|k|v of a wide model: in one piece from 180 blocks on (7B-class: 257 rows).
         const bool whole_qkv = L.mfma || tile_fills_chip(n_qkv, R, 180), whole_d = tile_fills_chip(D.d, R, 161);
         PrepArgs p{};
         p.x = x; p.M = R; p.d = D.d; p.eps = D.eps; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = 4; p.part = part; p.part_M = R;
