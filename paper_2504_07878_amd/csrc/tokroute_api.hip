@@ -58,8 +58,8 @@ struct Layout {
 };
 
 // Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists. Measured decode step of the
-// 0.5B-class model (context 256): 0.63 ms at 1 row and 0.83 at 2 on the streaming kernels, which then climb to 1.15 (3 rows),
-// 1.26 (4) and 1.40 (8), while the matrix-core path takes 1.05 ms from 3 to 16 rows.
+// 0.5B-class model (context 256): 0.64 ms at 1 row and 0.69 at 2 on the streaming kernels, which then climb to 1.15 (3 rows),
+// 1.26 (4) and 1.40 (8); 0.81 to 0.83 from 3 to 8 rows on the kernels for these, 0.93 from 9 to 32 on the others.
 constexpr int GEMV_MAX_ROWS = 2;
 
 // The matrix-core kernels keep 896 columns of K per workgroup resident, and the layers with a non-linear
