@@ -413,9 +413,8 @@ TRAFFIC = {
 
 # kernel families of a decode step of the 0.5B-class model at 64 rows: launches per step, and the kernels behind them
 B64_FAMILIES = {"setup": 1, "prep": 25, "qkv": 24, "attention": 24, "oproj": 24, "gateup": 24, "down": 24, "lmhead": 1, "tail_merge": 1}
-B1_FAMILIES = {"setup": 1, "qkv_attention": 24, "oproj": 24, "gateup": 24, "down": 24, "prep": 1, "lmhead": 1, "tail_merge": 1}
-B1_KERNELS = {"setup": "setup_embed_kernel", "qkv_attention": "qkv_attn_kernel", "oproj": "residual_gemv_kernel<1,StageAttn>", "gateup": "gateup_kernel<1>",
-              "down": "residual_splitk_kernel<3,1>", "prep": "prep_kernel (final norm)", "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
+B1_FAMILIES = {"setup": 1, "layers": 1, "prep": 1, "lmhead": 1, "tail_merge": 1}
+B1_KERNELS = {"setup": "flow_setup_kernel", "layers": "flow_kernel<1,64>", "prep": "prep_kernel (final norm)", "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
 B64_KERNELS = {"setup": "setup_embed_kernel", "prep": "prep_kernel", "qkv": "gemm_kernel<2,14,EpiQkv>", "attention": "attn_rows_kernel<64>",
                "oproj": "gemm_kernel<2,14,EpiResidualNorm>", "gateup": "gemm22_kernel<28,EpiSwiglu>", "down": "gemm22_kernel<28,EpiPartial>",
                "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
@@ -428,7 +427,7 @@ def family_bytes(s, rows, attention_bytes):
     return {"setup": 0, "prep": 0, "tail_merge": 0,
             "qkv": 2 * (qw + 2 * kvw) * d + rows * 2 * kvw * 2, "attention": attention_bytes, "oproj": 2 * d * qw,
             "gateup": 2 * 2 * F * d, "down": 2 * d * F, "lmhead": 2 * (s.vocab + s.router_hidden) * d,
-            "qkv_attention": 2 * (qw + 2 * kvw) * d + rows * 2 * kvw * 2 + attention_bytes}
+            "layers": s.n_layers * (2 * (qw + 2 * kvw) * d + 2 * d * qw + 2 * 3 * F * d + rows * 2 * kvw * 2 + attention_bytes)}
 
 
 def kernel_table(s, fam, kernels, rows, attention_bytes):

@@ -254,6 +254,7 @@ enum { TR_KERNEL_SETUP = 0,      /* row set-up + embedding lookup */
        TR_KERNEL_LMHEAD,         /* LM head with the running softmax statistics */
        TR_KERNEL_TAIL_MERGE,     /* merge of the slices, router, flag, counters */
        TR_KERNEL_QKV_ATTENTION,  /* 1-2 row steps: projection and attention in one launch */
+       TR_KERNEL_LAYERS,         /* decode steps of few rows: all layers in one launch */
        TR_KERNEL_FAMILIES };
 int tr_profile_select(tr_ctx *ctx, int32_t family);
 int tr_profile_enable(tr_ctx *ctx, int32_t on);

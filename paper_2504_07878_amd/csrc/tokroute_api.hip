@@ -55,6 +55,8 @@ struct Layout {
     bool split_head;   // wide model whose LM head runs through split-K partial logits (vocabulary a multiple of 8)
     size_t wt_layers, wt_layer_stride, wt_qkv, wt_o, wt_gu, wt_d, wt_head, bias, bias_stride;
     size_t pack_d, pack_a, pack_h, part;
+    bool flow;         // decode steps of few rows as one launch over all layers
+    size_t flow_buf, flow_ticket;
 };
 
 // Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists. Measured decode step of the
@@ -102,6 +104,17 @@ int check_config(const tr_config *c)
         if (pool * c->kv_page >= (1ll << 31)) return TR_ERR_CAPACITY;
     }
     return TR_OK;
+}
+
+// the model's sizes (the cache's places come with the workspace)
+Dims make_dims(const tr_config *c)
+{
+    Dims D{};
+    D.L = c->n_layers; D.d = c->d_model; D.Hq = c->n_q_heads; D.Hkv = c->n_kv_heads; D.dh = c->head_dim; D.F = c->d_ffn;
+    D.V = c->vocab; D.qw = D.Hq * D.dh; D.kvw = D.Hkv * D.dh; D.G = D.Hq / D.Hkv; D.rh = c->router_hidden;
+    D.max_batch = c->max_batch; D.max_seq = c->max_seq; D.eps = c->rms_eps;
+    D.vts = c->kv_dtype == TR_BF16 ? (c->max_seq + 31) / 32 * 32 : 0;
+    return D;
 }
 
 Layout make_layout(const tr_config *c)
@@ -180,6 +193,12 @@ Layout make_layout(const tr_config *c)
     L.dev_len = take((size_t)c->max_batch * 4);
     L.ss_stride = SS_STRIDE;
     L.sumsq = take((size_t)L.ss_stride * R * 4);
+    const Dims D = make_dims(c);
+    L.flow = L.mfma && flow_supported(D, c->dtype, c->kv_dtype);
+    if (L.flow) {
+        L.flow_buf = take(flow_floats(D, c->max_batch) * 4);
+        L.flow_ticket = take(FLOW_TICKET_INTS * 4);
+    }
     L.total = off;
     return L;
 }
@@ -538,9 +557,22 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
     return pending;
 }
 
-// The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials (rows indexed
-// like x, part_M rows per split) are added first.
-void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pending, int part_M)
+// A decode step of few rows (flow_takes): row set-up, embedding and all layers. Returns the rows of the residual stream; FLOW_KQ partial sums are still to be added.
+float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, float **partials)
+{
+    const Layout &L = ctx->lay;
+    float *buf = ctx->at<float>(L.flow_buf);
+    int *ticket = ctx->at<int>(L.flow_ticket), *d_slot = ctx->at<int>(L.slot), *d_pos = ctx->at<int>(L.pos);
+    { Bracket br(ctx, s, TR_KERNEL_SETUP); launch_flow_setup(s, ctx->D, ctx->tok_emb, R, max_ctx, slots, toks, poss, dev_toks, d_slot, ctx->at<int>(L.tok), d_pos, buf, ticket); }
+    const FlowModel m{ctx->wt(0, 0), L.wt_layer_stride, L.wt_qkv, L.wt_o, L.wt_gu, L.wt_d, ctx->bias(0), L.bias_stride / 4, ctx->layers.data(),
+                      ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
+    Bracket br(ctx, s, TR_KERNEL_LAYERS);
+    return launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, partials);
+}
+
+// The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials part[pending][part_M][d] (rows indexed
+// like x) are added first.
+void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pending, int part_M, const float *part)
 {
     const Dims &D = ctx->D;
     const Layout &L = ctx->lay;
@@ -548,7 +580,7 @@ void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pe
         // wide model, more rows than one pass of the streaming head takes: final norm + pack, the head as split-K partial
         // logits on the matrix cores, softmax statistics per vocabulary slice from the partials
         PrepArgs p{};
-        p.x = x; p.row0 = row0; p.gather = t.gather; p.part = ctx->at<float>(L.part); p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
+        p.x = x; p.row0 = row0; p.gather = t.gather; p.part = part; p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
         p.eps = D.eps;
         p.gain = (const bf16_t *)ctx->final_norm; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = mfma_ncb(t.n);
         p.hn = t.hn; p.hidden = t.hidden; p.hidden_tap = t.hidden_tap;
@@ -565,7 +597,7 @@ void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pe
     if (!ctx->lay.mfma) {
         if (pending > 0) {   // wide model: add the last down projection's partials to the rows the tail reads
             PrepArgs p{};
-            p.x = x; p.row0 = row0; p.gather = t.gather; p.part = ctx->at<float>(L.part); p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
+            p.x = x; p.row0 = row0; p.gather = t.gather; p.part = part; p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
             p.eps = D.eps;
             Bracket br(ctx, s, TR_KERNEL_PREP);
             launch_prep(s, p);
@@ -578,7 +610,7 @@ void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pe
         return;
     }
     PrepArgs p{};
-    p.x = x; p.row0 = row0; p.gather = t.gather; p.part = ctx->at<float>(L.part); p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
+    p.x = x; p.row0 = row0; p.gather = t.gather; p.part = part; p.nsplit = pending; p.part_M = part_M; p.M = t.n; p.d = D.d;
     p.eps = D.eps;
     p.gain = (const bf16_t *)ctx->final_norm; p.pack = ctx->at<uint4>(L.pack_d); p.ncb = mfma_ncb(t.n);
     p.hn = t.hn; p.hidden = t.hidden; p.hidden_tap = t.hidden_tap;
@@ -664,6 +696,16 @@ static int ingest(tr_ctx *ctx, hipStream_t s, int n, const int32_t *slots, const
             ps.out_slot.push_back(slots[j]);
             if (base + T > max_ctx) max_ctx = base + T;
         }
+        if (one_token_each && L.flow && flow_takes(ctx->D, rows, max_ctx)) {   // a decode step of few rows
+            float *part = nullptr, *x = run_flow(ctx, s, rows, max_ctx, ps.slot.data(), tokens_flat + offsets[i], ps.pos.data(), nullptr, &part);
+            TailArgs t = tail_args(ctx, out, i, rows);
+            t.slot = ctx->at<int>(L.slot);
+            t.counter_mode = counter_mode;
+            run_tail(ctx, s, t, x, 0, FLOW_KQ, rows, part);
+            profile_next_turn(ctx);
+            i = j;
+            continue;
+        }
         // pageable sources: each copy has left the host array when the call returns
         hipError_t e = hipMemcpyAsync(ctx->at<int>(L.tok), tokens_flat + offsets[i], (size_t)rows * 4, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) e = hipMemcpyAsync(ctx->at<int>(L.slot), ps.slot.data(), (size_t)rows * 4, hipMemcpyHostToDevice, s);
@@ -684,7 +726,7 @@ static int ingest(tr_ctx *ctx, hipStream_t s, int n, const int32_t *slots, const
         t.gather = ctx->at<int>(L.gather);
         t.slot = ctx->at<int>(L.out_slot);
         t.counter_mode = counter_mode;
-        run_tail(ctx, s, t, ctx->at<float>(L.x), 0, pending, rows);
+        run_tail(ctx, s, t, ctx->at<float>(L.x), 0, pending, rows, ctx->at<float>(L.part));
         profile_next_turn(ctx);
         i = j;
     }
@@ -744,11 +786,7 @@ int tr_create(const tr_config *cfg, const tr_weights *w, void *workspace, size_t
     ctx->c = *cfg;
     ctx->lay = lay;
     ctx->ws = static_cast<char *>(workspace);
-    Dims &D = ctx->D;
-    D.L = cfg->n_layers; D.d = cfg->d_model; D.Hq = cfg->n_q_heads; D.Hkv = cfg->n_kv_heads; D.dh = cfg->head_dim; D.F = cfg->d_ffn;
-    D.V = cfg->vocab; D.qw = D.Hq * D.dh; D.kvw = D.Hkv * D.dh; D.G = D.Hq / D.Hkv; D.rh = cfg->router_hidden;
-    D.max_batch = cfg->max_batch; D.max_seq = cfg->max_seq; D.eps = cfg->rms_eps;
-    D.vts = cfg->kv_dtype == TR_BF16 ? (cfg->max_seq + 31) / 32 * 32 : 0;
+    Dims &D = ctx->D = make_dims(cfg);
     D.page = cfg->kv_page; D.maxp = lay.maxp; D.units = cfg->kv_page ? lay.pool : cfg->max_batch;
     D.ptab = reinterpret_cast<const int *>(ctx->ws + lay.ptab);
     if (cfg->kv_page) ctx->pages.init(cfg->max_batch, cfg->kv_page, lay.maxp, lay.pool);
@@ -967,17 +1005,24 @@ static int decode_step_impl(tr_ctx *ctx, void *hip_stream, int32_t n, const int3
         const int prc = reserve_pages(ctx, s, n, slots, pos.data(), to.data(), "tr_decode_step: page table");
         if (prc != TR_OK) return prc;
     }
-    {
-        Bracket br(ctx, s, TR_KERNEL_SETUP);
-        launch_setup_rows_embed(s, n, slots, in_tokens, pos.data(), ctx->at<int>(L.slot), ctx->at<int>(L.tok), ctx->at<int>(L.pos), ctx->c.dtype,
-                                ctx->tok_emb, ctx->D.d, ctx->at<float>(L.x), dev_tokens, ctx->c.vocab);
+    float *x = ctx->at<float>(L.x), *part = ctx->at<float>(L.part);
+    int pending = 0;
+    if (L.flow && flow_takes(ctx->D, n, max_ctx)) {
+        x = run_flow(ctx, s, n, max_ctx, slots, in_tokens, pos.data(), dev_tokens, &part);
+        pending = FLOW_KQ;
+    } else {
+        {
+            Bracket br(ctx, s, TR_KERNEL_SETUP);
+            launch_setup_rows_embed(s, n, slots, in_tokens, pos.data(), ctx->at<int>(L.slot), ctx->at<int>(L.tok), ctx->at<int>(L.pos), ctx->c.dtype,
+                                    ctx->tok_emb, ctx->D.d, x, dev_tokens, ctx->c.vocab);
+        }
+        pending = run_layers(ctx, s, n, max_ctx, false, true);
     }
-    const int pending = run_layers(ctx, s, n, max_ctx, false, true);
     TailArgs t = tail_args(ctx, out, 0, n);
     t.gather = nullptr;
     t.slot = ctx->at<int>(L.slot);
     t.counter_mode = 1;
-    run_tail(ctx, s, t, ctx->at<float>(L.x), 0, pending, n);
+    run_tail(ctx, s, t, x, 0, pending, n, part);
     profile_next_turn(ctx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(ctx, e, "tr_decode_step: launch");
@@ -1026,7 +1071,7 @@ int tr_decode_step_active(tr_ctx *ctx, void *hip_stream, int32_t n, const int32_
     t.gather = nullptr;
     t.slot = ctx->at<int>(L.slot);
     t.counter_mode = 1;
-    run_tail(ctx, s, t, ctx->at<float>(L.x), 0, pending, n_max);
+    run_tail(ctx, s, t, ctx->at<float>(L.x), 0, pending, n_max, ctx->at<float>(L.part));
     profile_next_turn(ctx);
     ctx->live = ctx->cand = nullptr; ctx->scatter = nullptr;
     hipError_t e = hipGetLastError();
@@ -1049,7 +1094,7 @@ int tr_tail(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, const tr_o
     t.slot = nullptr;
     t.counters = nullptr;
     t.counter_mode = 0;
-    run_tail(ctx, s, t, const_cast<float *>(x), 0, 0, n);   // no partials pending: x is only read
+    run_tail(ctx, s, t, const_cast<float *>(x), 0, 0, n, nullptr);   // no partials pending: x is only read
     profile_next_turn(ctx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(ctx, e, "tr_tail: launch");

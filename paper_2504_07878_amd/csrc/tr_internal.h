@@ -213,6 +213,26 @@ void launch_few_oproj(hipStream_t s, const Dims &D, const void *Wt, const float 
 void launch_few_swiglu(hipStream_t s, const Dims &D, const void *Wt, const float *x, const void *gain, int R, void *hpack, const int *live);
 void launch_few_down(hipStream_t s, const Dims &D, const void *Wt, const void *hpack, int R, float *x, const int *live);
 
+// ---- all layers of a decode step of few rows in one launch (flow_kernels.hip)
+constexpr int FLOW_MAX_ROWS = 8, FLOW_MAX_LAYERS = 64, FLOW_MAX_PARTS = 16;
+constexpr int FLOW_KQ = 4;   // parts of the FFN's columns in the FFN output
+constexpr int FLOW_TICKET_INTS = 32;
+struct FlowModel {
+    const char *wt; size_t wt_stride, wt_qkv, wt_o, wt_gu, wt_d;   // tiled weights (bytes)
+    const float *bias; size_t bias_stride;
+    const LayerW *layers;
+    char *kc, *vc; size_t k_layer, v_layer;
+    const float2 *rope;
+};
+bool flow_supported(const Dims &D, int wdt, int kdt);
+size_t flow_floats(const Dims &D, int max_rows);   // most floats that the hand-over buffers take
+bool flow_takes(const Dims &D, int R, int max_ctx);
+// Rows of different slots (a decode step). Setup: row tables, embedding, the hand-over buffers as the layers expect them.
+void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks,
+                       int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
+// All layers; returns the rows of the residual stream (in buf), *partials: FLOW_KQ sums to add to them first ([FLOW_KQ][R][d])
+float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, float **partials);
+
 // Wide models (K beyond what one workgroup keeps resident): every linear layer goes through split-K partials, and the
 // layers with a non-linear epilogue are finished by a small kernel of their own.
 // number of partial buffers launch_gemm_partial will produce for a K x N layer

@@ -21,7 +21,7 @@ JOINT, SMALL_ONLY = 0, 1
 ROUTE_IF_BELOW, ROUTE_IF_ABOVE = 0, 1
 POLICY_MLP, POLICY_CONFIDENCE, POLICY_LINEAR = 0, 1, 2
 POST_FINAL_NORM, PRE_FINAL_NORM = 0, 1
-KERNEL_FAMILIES = ("setup", "prep", "qkv", "attention", "oproj", "gateup", "down", "lmhead", "tail_merge", "qkv_attention")   # TR_KERNEL_*
+KERNEL_FAMILIES = ("setup", "prep", "qkv", "attention", "oproj", "gateup", "down", "lmhead", "tail_merge", "qkv_attention", "layers")   # TR_KERNEL_*
 
 EXPORTS = ["tr_workspace_bytes", "tr_create", "tr_destroy", "tr_prefill", "tr_decode_step", "tr_decode_step_dev", "tr_decode_step_active", "tr_extend", "tr_tail", "tr_tail_noalloc", "tr_set_threshold",
            "tr_set_mode", "tr_seq_len", "tr_seq_truncate", "tr_seq_fork", "tr_seq_load_kv", "tr_counters_ptr", "tr_profile_enable", "tr_profile_select",
