@@ -773,7 +773,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_kernel(FlowArgs args)
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
         else if ((i -= a.nQ) < a.nA) f.attention(l, i);
-        else if ((i -= a.nA) < a.nM) f.merge(l, i);
+        else if ((i -= a.nA) < a.nM) { f.merge(l, i); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
         else if ((i -= a.nM) < a.nO) f.oproj(l, i);
         else if ((i -= a.nO) < a.nG) f.gateup(l, i);
         else f.down(l, i - a.nG);
@@ -807,11 +807,14 @@ __global__ __launch_bounds__(256) void flow_setup_kernel(FlowSetup a, int R, int
     }
 }
 
-// blocks of 32 keys per wavefront, and parts that gives the longest row
-static void flow_split(const Dims &D, int R, int max_ctx, int *U, int *P)
+// Blocks of 32 cached keys per wavefront (U), and parts that gives the longest row. One part as long as the registers hold its blocks: a block more costs 11 us
+// a step of the 0.5B-class model, parts and their merge 24 (one row) to 38 (8 rows). Past that as few blocks as make 6 parts (1 / 2 / 3 blocks: one row after 1000
+// keys 351 / 362 / 371 us, after 2000 keys 365 / 364 / 374; 8 rows 476 / 483 / 492 and 498 / 495 / 503).
+static void flow_split(const Dims &D, int max_ctx, int *U, int *P)
 {
-    const int umax = D.dh == 64 ? (R > 4 ? 2 : 3) : 1, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
-    *U = std::min(umax, (blocks + FLOW_WAVES - 1) / FLOW_WAVES);
+    const int umax = D.dh == 64 ? 3 : 1, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
+    auto per = [&](int parts) { return (blocks + FLOW_WAVES * parts - 1) / (FLOW_WAVES * parts); };
+    *U = per(1) <= umax ? per(1) : std::min(umax, per(6));
     *P = (blocks + FLOW_WAVES * *U - 1) / (FLOW_WAVES * *U);
 }
 
@@ -853,7 +856,7 @@ bool flow_supported(const Dims &D, int wdt, int kdt)
 bool flow_takes(const Dims &D, int R, int max_ctx)
 {
     int U, P;
-    flow_split(D, R, max_ctx, &U, &P);
+    flow_split(D, max_ctx, &U, &P);
     return R <= FLOW_MAX_ROWS && P <= FLOW_MAX_PARTS;
 }
 
@@ -861,7 +864,7 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
                        int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket)
 {
     FlowArgs a{};
-    flow_split(D, R, max_ctx, &a.U, &a.P);
+    flow_split(D, max_ctx, &a.U, &a.P);
     const size_t n = flow_layout(D, R, a.P, a);
     FlowSetup su{};
     for (int i = 0; i < R; ++i) { su.slot[i] = slots[i]; su.tok[i] = toks ? toks[i] : 0; su.pos[i] = poss[i]; }
@@ -873,7 +876,7 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
 float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, float **partials)
 {
     FlowArgs a{};
-    flow_split(D, R, max_ctx, &a.U, &a.P);
+    flow_split(D, max_ctx, &a.U, &a.P);
     const size_t n = flow_layout(D, R, a.P, a);
     a.wt = m.wt; a.wt_stride = m.wt_stride; a.wt_qkv = (uint32_t)m.wt_qkv; a.wt_o = (uint32_t)m.wt_o; a.wt_gu = (uint32_t)m.wt_gu; a.wt_d = (uint32_t)m.wt_d;
     a.bias = m.bias; a.bias_stride = m.bias_stride;
