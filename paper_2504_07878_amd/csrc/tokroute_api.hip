@@ -56,6 +56,7 @@ struct Layout {
     size_t wt_layers, wt_layer_stride, wt_qkv, wt_o, wt_gu, wt_d, wt_head, bias, bias_stride;
     size_t pack_d, pack_a, pack_h, part;
     bool flow;         // decode steps of few rows as one launch over all layers
+    bool flow32;       // the same of an fp32 model, with the LM head
     size_t flow_buf, flow_ticket;
 };
 
@@ -153,9 +154,11 @@ Layout make_layout(const tr_config *c)
     L.split = split_supported(c);
     // fused matrix-core tail with the MLP router on the normalised hidden state: the router's first layer rides along in the LM-head launch
     L.router_tiles = (L.mfma && c->route_policy == TR_POLICY_MLP && c->router_hidden > 0 && c->hidden_tap == TR_POST_FINAL_NORM) ? (c->router_hidden + 31) / 32 : 0;
-    L.r1 = take((size_t)c->max_batch * (L.router_tiles ? L.router_tiles : 1) * 32 * 4);
+    L.r1 = take(std::max((size_t)c->max_batch * (L.router_tiles ? L.router_tiles : 1) * 32, (size_t)FLOW32_MAX_ROWS * c->router_hidden) * 4);
     const int head_wgs = L.mfma ? lmhead_mfma_wgs(c->vocab, L.router_tiles) : 0;
-    L.tail_part = take((size_t)(L.nslices > head_wgs ? L.nslices : head_wgs) * c->max_batch * sizeof(float4));
+    const Dims D = make_dims(c);
+    L.flow32 = flow32_supported(D, c->dtype, c->kv_dtype);
+    L.tail_part = take((size_t)std::max({L.nslices, head_wgs, L.flow32 ? flow32_slices(D) : 0}) * c->max_batch * sizeof(float4));
     if (L.mfma || L.split) {
         const size_t d = (size_t)c->d_model, F = (size_t)c->d_ffn;
         auto tiles = [](size_t n) { return (n + 31) / 32; };
@@ -193,10 +196,9 @@ Layout make_layout(const tr_config *c)
     L.dev_len = take((size_t)c->max_batch * 4);
     L.ss_stride = SS_STRIDE;
     L.sumsq = take((size_t)L.ss_stride * R * 4);
-    const Dims D = make_dims(c);
     L.flow = L.mfma && flow_supported(D, c->dtype, c->kv_dtype);
-    if (L.flow) {
-        L.flow_buf = take(flow_floats(D, c->max_batch) * 4);
+    if (L.flow || L.flow32) {
+        L.flow_buf = take((L.flow ? flow_floats(D, c->max_batch) : flow32_floats(D, c->max_batch)) * 4);
         L.flow_ticket = take(FLOW_TICKET_INTS * 4);
     }
     L.total = off;
@@ -629,6 +631,33 @@ void run_tail(tr_ctx *ctx, hipStream_t s, TailArgs t, float *x, int row0, int pe
     launch_tail_final(s, ctx->c.dtype, D, t);
 }
 
+// A decode step of few rows, each of a slot of its own, in one launch over all layers and, for an fp32 model, the LM head. Returns false, having done nothing, when
+// the step is not such a one.
+bool run_step_of_few(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, TailArgs t)
+{
+    const Dims &D = ctx->D;
+    const Layout &L = ctx->lay;
+    if (L.flow && flow_takes(D, R, max_ctx)) {
+        float *part = nullptr, *x = run_flow(ctx, s, R, max_ctx, slots, toks, poss, dev_toks, &part);
+        run_tail(ctx, s, t, x, 0, FLOW_KQ, R, part);
+        return true;
+    }
+    if (L.flow32 && flow32_takes(D, R, max_ctx)) {
+        const Flow32Model m{ctx->layers.data(), ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
+        float *buf = ctx->at<float>(L.flow_buf);
+        int *ticket = ctx->at<int>(L.flow_ticket), *d_slot = ctx->at<int>(L.slot), *d_pos = ctx->at<int>(L.pos);
+        { Bracket br(ctx, s, TR_KERNEL_SETUP); launch_flow32_setup(s, D, ctx->tok_emb, R, slots, toks, poss, dev_toks, d_slot, ctx->at<int>(L.tok), d_pos, buf, ticket); }
+        {
+            Bracket br(ctx, s, TR_KERNEL_LAYERS);
+            launch_flow32(s, D, m, R, d_slot, d_pos, buf, ticket, t, t.policy == TR_POLICY_MLP && D.rh > 0 ? ctx->at<float>(L.r1) : nullptr);
+        }
+        Bracket br(ctx, s, TR_KERNEL_TAIL_MERGE);
+        launch_tail_final(s, ctx->c.dtype, D, t);
+        return true;
+    }
+    return false;
+}
+
 TailArgs tail_args(tr_ctx *ctx, const tr_out *out, int out_offset, int n)
 {
     const Layout &L = ctx->lay;
@@ -696,15 +725,15 @@ static int ingest(tr_ctx *ctx, hipStream_t s, int n, const int32_t *slots, const
             ps.out_slot.push_back(slots[j]);
             if (base + T > max_ctx) max_ctx = base + T;
         }
-        if (one_token_each && L.flow && flow_takes(ctx->D, rows, max_ctx)) {   // a decode step of few rows
-            float *part = nullptr, *x = run_flow(ctx, s, rows, max_ctx, ps.slot.data(), tokens_flat + offsets[i], ps.pos.data(), nullptr, &part);
+        if (one_token_each) {   // a decode step of few rows
             TailArgs t = tail_args(ctx, out, i, rows);
             t.slot = ctx->at<int>(L.slot);
             t.counter_mode = counter_mode;
-            run_tail(ctx, s, t, x, 0, FLOW_KQ, rows, part);
-            profile_next_turn(ctx);
-            i = j;
-            continue;
+            if (run_step_of_few(ctx, s, rows, max_ctx, ps.slot.data(), tokens_flat + offsets[i], ps.pos.data(), nullptr, t)) {
+                profile_next_turn(ctx);
+                i = j;
+                continue;
+            }
         }
         // pageable sources: each copy has left the host array when the call returns
         hipError_t e = hipMemcpyAsync(ctx->at<int>(L.tok), tokens_flat + offsets[i], (size_t)rows * 4, hipMemcpyHostToDevice, s);
@@ -1005,24 +1034,20 @@ static int decode_step_impl(tr_ctx *ctx, void *hip_stream, int32_t n, const int3
         const int prc = reserve_pages(ctx, s, n, slots, pos.data(), to.data(), "tr_decode_step: page table");
         if (prc != TR_OK) return prc;
     }
-    float *x = ctx->at<float>(L.x), *part = ctx->at<float>(L.part);
-    int pending = 0;
-    if (L.flow && flow_takes(ctx->D, n, max_ctx)) {
-        x = run_flow(ctx, s, n, max_ctx, slots, in_tokens, pos.data(), dev_tokens, &part);
-        pending = FLOW_KQ;
-    } else {
+    TailArgs t = tail_args(ctx, out, 0, n);
+    t.gather = nullptr;
+    t.slot = ctx->at<int>(L.slot);
+    t.counter_mode = 1;
+    if (!run_step_of_few(ctx, s, n, max_ctx, slots, in_tokens, pos.data(), dev_tokens, t)) {
+        float *x = ctx->at<float>(L.x);
         {
             Bracket br(ctx, s, TR_KERNEL_SETUP);
             launch_setup_rows_embed(s, n, slots, in_tokens, pos.data(), ctx->at<int>(L.slot), ctx->at<int>(L.tok), ctx->at<int>(L.pos), ctx->c.dtype,
                                     ctx->tok_emb, ctx->D.d, x, dev_tokens, ctx->c.vocab);
         }
-        pending = run_layers(ctx, s, n, max_ctx, false, true);
+        const int pending = run_layers(ctx, s, n, max_ctx, false, true);
+        run_tail(ctx, s, t, x, 0, pending, n, ctx->at<float>(L.part));
     }
-    TailArgs t = tail_args(ctx, out, 0, n);
-    t.gather = nullptr;
-    t.slot = ctx->at<int>(L.slot);
-    t.counter_mode = 1;
-    run_tail(ctx, s, t, x, 0, pending, n, part);
     profile_next_turn(ctx);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail_hip(ctx, e, "tr_decode_step: launch");

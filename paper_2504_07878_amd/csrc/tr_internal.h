@@ -232,6 +232,21 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
                        int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
 // All layers; returns the rows of the residual stream (in buf), *partials: FLOW_KQ sums to add to them first ([FLOW_KQ][R][d])
 float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, float **partials);
+// the same for fp32 models of up to 4 rows, with the LM head's slices and the router's first layer (flow_f32_kernels.hip)
+constexpr int FLOW32_MAX_ROWS = 4, FLOW32_MAX_LAYERS = 24;
+struct Flow32Model {
+    const LayerW *layers;
+    char *kc, *vc; size_t k_layer, v_layer;   // bytes from layer to layer
+    const float2 *rope;
+};
+bool flow32_supported(const Dims &D, int wdt, int kdt);
+bool flow32_takes(const Dims &D, int R, int max_ctx);
+size_t flow32_floats(const Dims &D, int max_rows);   // hand-over buffers
+int flow32_slices(const Dims &D);   // vocabulary slices it leaves for launch_tail_final
+void launch_flow32_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R, const int *slots, const int *toks, const int *poss, const int *dev_toks,
+                         int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
+// Everything up to launch_tail_final, for which it completes t. r1: [R][rh] sums of the router's first layer, or NULL (not wanted)
+void launch_flow32(hipStream_t s, const Dims &D, const Flow32Model &m, int R, const int *d_slot, const int *d_pos, float *buf, int *ticket, TailArgs &t, float *r1);
 
 // Wide models (K beyond what one workgroup keeps resident): every linear layer goes through split-K partials, and the
 // layers with a non-linear epilogue are finished by a small kernel of their own.

@@ -1,4 +1,4 @@
-"""Decode steps of 1 to 8 rows of a bf16 model in one launch over all layers, against the oracle: contexts around the blocks of 32 keys, the wavefronts of a
+"""Decode steps of 1 to 8 rows of a bf16 model and 1 to 4 rows of an fp32 model in one launch over all layers, against the oracle: contexts around the blocks of 32 keys, the wavefronts of a
 workgroup and the parts of a context, both head widths, FFN widths of unequal shares and of several rounds; NaNs that must end the step, not stall it; two models'
 steps at the same time on two streams."""
 import numpy as np
@@ -104,3 +104,63 @@ def test_steps_of_two_models_at_the_same_time():
     torch.cuda.synchronize()
     for o, h in zip(outs, want):
         assert torch.equal(o.hidden, h)
+
+
+F32 = dict(n_layers=2, n_q_heads=4, n_kv_heads=2, head_dim=64, vocab=1000, router_hidden=40, dtype=synth.F32, kv_dtype=synth.F32, d_model=256, d_ffn=1024)
+
+
+@pytest.mark.parametrize("name,shape,rows,lens,options", [
+    # both widths of a row, 1 to 8 wavefronts that share the FFN's columns, columns and vocabularies that fill no task; cached keys around a step of all wavefronts (32
+    # keys, 16 of wide heads), a round (256, 128) and the longest (2047, 1023 and the new one)
+    ("narrow", {}, 2, [0, 1, 31, 32, 33, 255, 256, 257], {}),
+    ("one", dict(d_model=200, d_ffn=24, vocab=33, router_hidden=0), 1, [3, 600, 64], {}),
+    ("short", dict(d_model=40, d_ffn=2048, n_q_heads=1, n_kv_heads=1, vocab=31), 3, [0, 63, 511, 2047, 2048], {}),
+    ("wide", dict(d_model=1024, d_ffn=8192, n_q_heads=8, n_kv_heads=8, head_dim=128, vocab=4100), 4, [0, 127, 128, 129, 1023, 1024], {}),
+    ("tapped", dict(d_model=264, d_ffn=4104, head_dim=128, vocab=65), 2, [15, 17, 1022], dict(hidden_tap=1)),
+])
+def test_steps_of_fp32_models(name, shape, rows, lens, options):
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name=name, **{**F32, **shape})
+    w = synth.make_weights(s, SEED + 9, std=0.05, bias_std=0.05, gain_std=0.1)
+    n, max_seq = len(lens), (max(lens) + 4 + 63) // 64 * 64
+    g = tr.Model(s.asdict(), w, n, max_seq, **options)
+    o = tro.Model(s.asdict(), w, n, max_seq, hidden_tap=options.get("hidden_tap", 0))
+    rng = synth.rng(SEED, name)
+    first = synth.prompt_tokens(SEED, "flow.first", n, s.vocab)
+    for m in (g, o):
+        m.prefill(list(range(n)), [first[i:i + 1] for i in range(n)])
+    for i, m in enumerate(lens):
+        if m == 0:
+            g.seq_truncate(i, 0); o.seq_truncate(i, 0)
+            continue
+        k, v = (rng.standard_normal((s.n_layers, s.n_kv_heads, m, s.head_dim), dtype=np.float32) for _ in range(2))
+        g.load_kv(i, tr.to_device(k, s.kv_dtype), tr.to_device(v, s.kv_dtype)); o.load_kv(i, k, v)
+    toks = synth.prompt_tokens(SEED, "flow.tok", n, s.vocab).copy()
+    exempt = 0
+    for at in range(n):
+        slots = [(at + i) % n for i in range(rows)]
+        go = g.decode_step(slots, toks[slots], want_logits=True).cpu()
+        oo = o.decode_step(slots, toks[slots], want_logits=True)
+        exempt += compare_outputs(go, oo, s.dtype, s.threshold, f"{name} rows {slots}")
+        np.put(toks, slots, oo.token)
+        for b in slots:
+            g.seq_truncate(b, lens[b]); o.seq_truncate(b, lens[b])
+    assert exempt <= 2
+
+
+def test_nans_end_the_step_of_an_fp32_model():
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="nan32", **F32)
+    for key in ("tok_emb", "l0.wk", "l0.wo", "l1.wg", "l1.wd", "l0.ln1"):
+        w = {k: v.copy() for k, v in synth.make_weights(s, SEED + 9, std=0.05).items()}
+        w[key].view(np.uint32).reshape(-1)[:] = 0xffffffff
+        m = tr.Model(s.asdict(), w, 8, 64)
+        rng = synth.rng(SEED, "nan")
+        for b in range(2):
+            k, v = (rng.standard_normal((s.n_layers, s.n_kv_heads, 33, s.head_dim), dtype=np.float32) for _ in range(2))
+            m.load_kv(b, tr.to_device(k, s.kv_dtype), tr.to_device(v, s.kv_dtype))
+        out = m.decode_step([0, 1], np.arange(2, dtype=np.int32))
+        torch.cuda.synchronize()
+        assert torch.isnan(out.hidden).all(), key
