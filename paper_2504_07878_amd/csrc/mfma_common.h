@@ -11,30 +11,32 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 
 // value = hi + lo with hi = bf16(value), lo = bf16(value - hi), both rounded to nearest even by the hardware's packed
 // conversion (two values per instruction)
+__device__ __forceinline__ void split_hi_lo(float v0, float v1, uint32_t &h, uint32_t &l)
+{
+    const f32x2 x = {v0, v1};
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
+    const f32x2 rest = {v0 - __uint_as_float(h << 16), v1 - __uint_as_float(h & 0xffff0000u)};
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
+}
 __device__ __forceinline__ void split_hi_lo(const float (&v)[8], uint4 &hi, uint4 &lo)
 {
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const f32x2 x = {v[2 * p], v[2 * p + 1]};
-        h[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
-        const f32x2 rest = {v[2 * p] - __uint_as_float(h[p] << 16), v[2 * p + 1] - __uint_as_float(h[p] & 0xffff0000u)};
-        l[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, bf16x2));
-    }
-    hi = make_uint4(h[0], h[1], h[2], h[3]);
-    lo = make_uint4(l[0], l[1], l[2], l[3]);
+    split_hi_lo(v[0], v[1], hi.x, lo.x); split_hi_lo(v[2], v[3], hi.y, lo.y);
+    split_hi_lo(v[4], v[5], hi.z, lo.z); split_hi_lo(v[6], v[7], hi.w, lo.w);
 }
 
 // Packed activations of one group of up to 64 rows: [k-step][column block][lane] of 16 bytes, column blocks =
 // {hi rows 0-31, (hi rows 32-63), lo rows 0-31, (lo rows 32-63)}; lane = row%32 + 32*(k%16 / 8).
-__device__ __forceinline__ void store_packed(uint4 *pack, int ncb, int row_in_group, int k8 /* index of the 8-column chunk */,
-                                             const float (&v)[8])
+__device__ __forceinline__ void store_packed(uint4 *pack, int ncb, int row_in_group, int k8 /* index of the 8-column chunk */, uint4 hi, uint4 lo)
 {
-    uint4 hi, lo;
-    split_hi_lo(v, hi, lo);
     const int ks = k8 >> 1, lane = (row_in_group & 31) + 32 * (k8 & 1), cb = row_in_group >> 5;
     pack[((size_t)ks * ncb + cb) * 64 + lane] = hi;
     pack[((size_t)ks * ncb + (ncb >> 1) + cb) * 64 + lane] = lo;
+}
+__device__ __forceinline__ void store_packed(uint4 *pack, int ncb, int row_in_group, int k8, const float (&v)[8])
+{
+    uint4 hi, lo;
+    split_hi_lo(v, hi, lo);
+    store_packed(pack, ncb, row_in_group, k8, hi, lo);
 }
 
 // MFMA row rho of a tile (the accumulator holds rows 8*qd + 4*hf + e in register 4*qd + e of the lanes with lane/32 = hf)

@@ -798,25 +798,41 @@ struct GemmArgs {
     int half;           // 1: every 64-row group is served by two workgroups of 32 rows each (more workgroups for short tile ranges)
     const int *live;    // device-side row count or NULL: with zero live rows the whole launch returns at once
 };
+struct GroupGrid { int nx, ny, groups, all; float rgroups, rnx; };   // a grid of several 64-row groups: all of its workgroups, 1 / groups and 1 / nx
+
+// f(0), f(1), ... f(N - 1), each index a compile-time constant
+template <int N, int I = 0, class F> __device__ __forceinline__ void each_index(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        each_index<N, I + 1>(f);
+    }
+}
+// the value is computed here, not where it is used
+template <class T> __device__ __forceinline__ void here(T &v) { asm volatile("" : "+v"(v)); }
 
 // Epilogues receive, per thread, 8 consecutive output features (rows i0..i0+7 of tile t) of one batch row. PAR is the
 // parity of the tile's index inside its workgroup's range, known at compile time. An epilogue does its arithmetic
 // unconditionally and keeps conditions to its stores at the very end: the arithmetic then shares a basic block with the
-// MFMAs of the next tile, which the matrix pipe executes while the vector ALUs do the epilogue.
+// MFMAs of the next tile, which the matrix pipe executes while the vector ALUs do the epilogue. Epilogues of gemm_groups_kernel also offer their arithmetic in
+// pieces (piece<PAR, 0 ..>, then stored() in place of tile()).
 
 struct EpiPartial {   // split-K partial sums: part[split][m][n]
     static constexpr bool half_only = false, one_group = false;
     float *part;
-    int N, M;
-    __device__ void block(int, int) {}
+    int N, M, split;
+    __device__ void block(int, int y) { split = y; }
     __device__ void begin() {}
     __device__ void row(int, int) {}
     __device__ void row_ready(float *, int, int) {}
+    template <int PAR> static constexpr int pieces = 0;
+    template <int PAR, int I> __device__ void piece(const float (&)[8]) {}
+    template <int PAR> __device__ void stored(int t, int m, int i0, const float (&v)[8]) { tile<PAR>(t, m, i0, v); }
     template <int PAR> __device__ void tile(int t, int m, int i0, const float (&v)[8])
     {
         const int n = t * 32 + i0;
         if (m < M && n < N) {
-            float *dst = part + ((size_t)blockIdx.y * M + m) * N + n;
+            float *dst = part + ((size_t)split * M + m) * N + n;
             *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
             *reinterpret_cast<float4 *>(dst + 4) = make_float4(v[4], v[5], v[6], v[7]);
         }
@@ -863,6 +879,7 @@ struct EpiSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written 
     uint4 *hpack;     // [group][F/16][NCB][64]
     int M, F, ncb;
     float hold[8];
+    uint32_t hi[4], lo[4];
     const float *sumsq;
     int n_ss, ss_stride;
     float eps, inv_d;
@@ -893,6 +910,30 @@ struct EpiSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written 
         }
     }
     // a workgroup's tile range starts at a gate tile (even index), so PAR = 0 is a gate tile, PAR = 1 its up tile
+    template <int PAR> static constexpr int pieces = PAR ? 12 : 1;
+    template <int PAR, int I> __device__ void piece(const float (&v)[8])
+    {
+        if constexpr (PAR == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { hold[e] = DEFER ? v[e] * rstd : v[e]; here(hold[e]); }
+        } else if constexpr (I < 8) {
+            hold[I] = silu(hold[I]);
+            here(hold[I]);
+        } else {   // (product and split together: what is left of a product is taken from it before it is rounded)
+            constexpr int e = 2 * (I - 8);
+            split_hi_lo(hold[e] * (DEFER ? v[e] * rstd : v[e]), hold[e + 1] * (DEFER ? v[e + 1] * rstd : v[e + 1]), hi[I - 8], lo[I - 8]);
+            here(hi[I - 8]); here(lo[I - 8]);
+        }
+    }
+    __device__ static float silu(float g) { return g * __frcp_rn(1.0f + __expf(-g)); }   // hardware exp2 and reciprocal (1 ulp each)
+    template <int PAR> __device__ void stored(int t, int m, int i0, const float (&)[8])
+    {
+        if (PAR == 0) return;
+        const int f0 = (t >> 1) * 32 + i0;
+        // rows past M are written too: they lie inside the padded 64-row group and are never read back as valid rows
+        if (!RAGGED || f0 < F)
+            store_packed(hpack + (size_t)(m >> 6) * (F / 16) * ncb * 64, ncb, m & 63, f0 >> 3, make_uint4(hi[0], hi[1], hi[2], hi[3]), make_uint4(lo[0], lo[1], lo[2], lo[3]));
+    }
     template <int PAR> __device__ void tile(int t, int m, int i0, const float (&v)[8])
     {
         if (PAR == 0) {
@@ -902,9 +943,8 @@ struct EpiSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written 
         }
         float h[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) h[e] = hold[e] * __frcp_rn(1.0f + __expf(-hold[e])) * (DEFER ? v[e] * rstd : v[e]);   // hardware exp2 and reciprocal (1 ulp each)
+        for (int e = 0; e < 8; ++e) h[e] = silu(hold[e]) * (DEFER ? v[e] * rstd : v[e]);
         const int f0 = (t >> 1) * 32 + i0;
-        // rows past M are written too: they lie inside the padded 64-row group and are never read back as valid rows
         if (!RAGGED || f0 < F) store_packed(hpack + (size_t)(m >> 6) * (F / 16) * ncb * 64, ncb, m & 63, f0 >> 3, h);
     }
     __device__ void end(float *, int, int) {}
@@ -1041,10 +1081,10 @@ struct EpiLmHead {    // running softmax statistics per batch row (one 64-row gr
 // interleaved so that consecutive MFMAs never share an accumulator.)
 constexpr int RED_FLOATS = NWAVES * 64 * 36;   // [wavefront][batch column][feature row padded to 36]
 
-template <int NCB, int KW, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a, Epi epi_in)
+template <int KW, class Epi>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a, Epi epi_in)   // 32 rows
 {
-    constexpr int NCO = NCB / 2;
+    constexpr int NCB = 2, NCO = NCB / 2;
     __shared__ __attribute__((aligned(16))) float red[2 * RED_FLOATS];
     if (a.live && *a.live == 0) return;   // uniform over the launch
     Epi epi = epi_in;   // per-thread epilogue state lives in registers
@@ -1054,7 +1094,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wk0 = ks0 + wave * per;
     const int nk = max(0, min(ks1, wk0 + per) - wk0);
     const int bx = blockIdx.x, group = blockIdx.z;
-    epi.block(bx, group);
+    epi.block(bx, blockIdx.y);
     // half mode: the packed activations hold 4 column blocks per 64-row group; this workgroup takes {h, 2 + h}
     const int pgroup = a.half ? group >> 1 : group, hsel = a.half ? group & 1 : 0, pncb = a.half ? 4 : NCB;
     const int row0 = pgroup * 64 + hsel * 32;
@@ -1179,10 +1219,164 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     epi.end(red, threadIdx.x & 63, threadIdx.x >> 6);
 }
 
-template <int NCB, int KW, class Epi>
-static void launch_gemm_one(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
+// Several 64-row groups: the same with two column blocks each of hi and lo. A tile's 56 matrix instructions take 1792 clocks, its cross-wavefront sum and its
+// epilogue 1400 more when they follow them, so they are spread among those of the next tile; and every group reads all weights, which came from beyond the L2 each
+// time until a tile range's groups were dealt to one XCD. 896 columns, FFN 4864, before / spread / and dealt: gate and up of 256 rows 18.5 / 17.3 / 14.8 us, of 896
+// rows 35.9 / 34.0 / 33.1; FFN output of 256 rows 13.9 / 13.7 / 10.7. What is left is the way of the weights into the compute unit (57 KB a tile at 31 bytes a
+// nanosecond) and the first 229 KB of activations.
+template <int KW, class Epi>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_groups_kernel(GemmArgs a, GroupGrid g, Epi epi_in)
 {
-    hipLaunchKernelGGL((gemm_kernel<NCB, KW, Epi>), grid, dim3(256), 0, s, a, epi);
+    constexpr int NCB = 4, NCO = NCB / 2;
+    __shared__ __attribute__((aligned(16))) float red[2 * RED_FLOATS];
+    if (a.live && *a.live == 0) return;   // uniform over the launch
+    Epi epi = epi_in;   // per-thread epilogue state lives in registers
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // Workgroups are dealt to the 8 XCDs round-robin, 64-row groups share their weights: the work is numbered group by group within a tile range and split in
+    // contiguous pieces, so that a range's groups find its weights in the L2 of one XCD.
+    const int id = blockIdx.x + g.nx * (blockIdx.y + g.ny * blockIdx.z), xcd = id & 7, lin = xcd * (g.all >> 3) + min(xcd, g.all & 7) + (id >> 3);
+    const int range = __builtin_amdgcn_readfirstlane((int)(((float)lin + 0.5f) * g.rgroups));
+    const int group = lin - range * g.groups, split = __builtin_amdgcn_readfirstlane((int)(((float)range + 0.5f) * g.rnx)), bx = range - split * g.nx;
+    const int ks0 = split * a.ksw, ks1 = min(a.KS, ks0 + a.ksw);
+    const int per = (ks1 - ks0 + NWAVES - 1) / NWAVES;   // <= KW
+    const int wk0 = ks0 + wave * per;
+    const int nk = max(0, min(ks1, wk0 + per) - wk0);
+    epi.block(bx, split);
+    const int row0 = group * 64;
+    // what the epilogue needs per batch row is requested first: it is then the oldest request in flight and can be waited for
+    // without waiting for anything younger
+    epi.row(row0 + (threadIdx.x & 63), threadIdx.x >> 6);
+
+    // resident activations of this wavefront's k-steps (zero beyond its share, so the extra products vanish)
+    bf16x8 b[KW][NCB];
+    int koff[KW];   // k-step of each resident slot, clamped into the matrix
+#pragma unroll
+    for (int kk = 0; kk < KW; ++kk) {
+        koff[kk] = min(wk0 + kk, a.KS - 1);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb) {
+            uint4 u = make_uint4(0, 0, 0, 0);
+            if (kk < nk) u = a.pack[(((size_t)group * a.KS + wk0 + kk) * NCB + cb) * 64 + lane];
+            b[kk][cb] = __builtin_bit_cast(bf16x8, u);
+        }
+    }
+
+    const int t0 = min(bx * a.tiles_per_wg, a.n_tiles), t1 = min(a.n_tiles, t0 + a.tiles_per_wg);
+    const size_t tile_stride = (size_t)a.KS * 64;
+    uint4 w[2][KW];
+    f32x16 acc[2][NCO];   // sums of the tile under way and of the one before, by the parity of their index in the range
+    const int j = threadIdx.x & 63, i0 = (threadIdx.x >> 6) * 8, rho0 = (i0 >> 4) * 16 + ((i0 >> 3) & 1) * 4;
+
+    auto load_tile = [&](int t, uint4 (&ws)[KW]) __attribute__((always_inline)) {   // unconditional: t must be a valid tile
+        const uint4 *wp = a.Wt + (size_t)t * tile_stride + lane;
+#pragma unroll
+        for (int kk = 0; kk < KW; ++kk) ws[kk] = wp[(size_t)koff[kk] * 64];
+    };
+    // matrix instruction i of the 2 NCO KW of the tile in ws; with REFILL a k-step's register is overwritten by tile tn (which must exist) behind its last one
+    auto multiply = [&](auto ic, auto refill, f32x16 (&c)[NCO], uint4 (&ws)[KW], int tn) __attribute__((always_inline)) {
+        constexpr int i = decltype(ic)::value, kk = i / (2 * NCO), hl = i / NCO % 2, co = i % NCO;
+        if constexpr (kk == 0 && hl == 0)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) c[co][r] = 0.f;
+        c[co] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ws[kk]), b[kk][hl * NCO + co], c[co], 0, 0, 0);
+        if constexpr (decltype(refill)::value && hl == 1 && co == NCO - 1) ws[kk] = (a.Wt + (size_t)tn * tile_stride + lane)[(size_t)koff[kk] * 64];
+    };
+    // quarter q % 4 of a column block's sums, to LDS: registers 4qd..4qd+3 are the 4 consecutive MFMA rows 8qd + 4(lane/32) .. of one batch column
+    auto put = [&](auto qc, const f32x16 (&c)[NCO], float *rb) __attribute__((always_inline)) {
+        constexpr int co = decltype(qc)::value / 4, qd = decltype(qc)::value % 4;
+        *reinterpret_cast<float4 *>(&rb[(wave * 64 + co * 32 + (lane & 31)) * 36 + qd * 8 + (lane >> 5) * 4]) =
+            make_float4(c[co][4 * qd], c[co][4 * qd + 1], c[co][4 * qd + 2], c[co][4 * qd + 3]);
+    };
+    // The cross-wavefront sum of tile t goes through one of two LDS buffers in the shadow of the matrix instructions of tile t + 1: the first BAR k-steps of
+    // these hide its writes, one barrier, the others hide its reads, the sums and the epilogue's arithmetic (its pieces), a piece behind a matrix instruction
+    // each. The fences keep that order: left alone the compiler puts all of it behind the last matrix instruction. A buffer is rewritten two barriers after it
+    // was read, and every wavefront reads before it reaches the next barrier.
+    constexpr int BAR = KW >= 8 ? 3 : 1, SLOTS = (KW - BAR) * 2 * NCO;
+    using No = std::integral_constant<bool, false>;
+    using Yes = std::integral_constant<bool, true>;
+    float *const red0 = red, *const red1 = red + RED_FLOATS;
+    // tile t (acc[P]) is finished while tile t + 1 (w[1 - P]) is multiplied and tile tn takes its registers
+    auto step = [&](auto par, auto next, auto refill, int t, int tn) __attribute__((always_inline)) {
+        constexpr int P = decltype(par)::value, PIECES = NWAVES + Epi::template pieces<P>, LEAD = SLOTS > 8 ? 4 : 1;
+        constexpr bool NEXT = decltype(next)::value;
+        float *const rb = P ? red1 : red0;
+        if constexpr (NEXT)
+            each_index<BAR * 2 * NCO>([&](auto i) __attribute__((always_inline)) {
+                multiply(i, refill, acc[1 - P], w[1 - P], tn);
+                each_index<4 * NCO>([&](auto q) __attribute__((always_inline)) {   // the writes follow the second and later instructions
+                    if constexpr (q.value * (BAR * 2 * NCO - 1) / (4 * NCO) + 1 == i.value) put(q, acc[P], rb);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        else each_index<4 * NCO>([&](auto q) __attribute__((always_inline)) { put(q, acc[P], rb); });
+        __syncthreads();
+        float4 lo4[NWAVES], hi4[NWAVES];
+        float v[8];
+        auto read = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int ww = 0; ww < NWAVES; ++ww) {   // features i0..i0+3 and i0+4..i0+7 sit in MFMA rows rho0.. and rho0+8.. (see tile_feature)
+                lo4[ww] = *reinterpret_cast<const float4 *>(&rb[(ww * 64 + j) * 36 + rho0]);
+                hi4[ww] = *reinterpret_cast<const float4 *>(&rb[(ww * 64 + j) * 36 + rho0 + 8]);
+            }
+        };
+        auto piece = [&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            if constexpr (i < NWAVES) {
+                const float e[8] = {lo4[i].x, lo4[i].y, lo4[i].z, lo4[i].w, hi4[i].x, hi4[i].y, hi4[i].z, hi4[i].w};
+#pragma unroll
+                for (int r = 0; r < 8; ++r) v[r] = i == 0 ? 0.f + e[r] : v[r] + e[r];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) here(v[r]);
+            } else epi.template piece<P, i - NWAVES>(v);
+        };
+        if constexpr (NEXT)
+            each_index<SLOTS>([&](auto i) __attribute__((always_inline)) {
+                constexpr int n = decltype(i)::value;
+                multiply(std::integral_constant<int, BAR * 2 * NCO + n>{}, refill, acc[1 - P], w[1 - P], tn);
+                if constexpr (n == 0) read();
+                each_index<PIECES>([&](auto q) __attribute__((always_inline)) {
+                    if constexpr (LEAD + q.value * (SLOTS - LEAD) / PIECES == n) piece(q);
+                });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        else {
+            read();
+            each_index<PIECES>(piece);
+        }
+        epi.template stored<P>(t, row0 + j, i0, v);
+    };
+    using Par0 = std::integral_constant<int, 0>;
+    using Par1 = std::integral_constant<int, 1>;
+    epi.begin();
+    int t = t0;
+    if (t0 < t1) {
+        load_tile(t0, w[0]);
+        if (t0 + 1 < t1) load_tile(t0 + 1, w[1]);
+        // per-row inputs: they were requested before everything else, and nothing younger is waited for here.
+        // The second LDS buffer is first written after the tile loop's first barrier.
+        epi.row_ready(red1, threadIdx.x & 63, threadIdx.x >> 6);
+        if (t0 + 2 < t1) each_index<2 * NCO * KW>([&](auto i) __attribute__((always_inline)) { multiply(i, Yes{}, acc[0], w[0], t0 + 2); });
+        else each_index<2 * NCO * KW>([&](auto i) __attribute__((always_inline)) { multiply(i, No{}, acc[0], w[0], t0); });
+        // from here on: acc[0] = sums of tile t, w[1] = tile t + 1, w[0] = tile t + 2 (where they exist).
+        // Long tile ranges: nothing conditional inside, so the compiler can wait for exactly the registers it needs
+        // and leave the younger loads in flight.
+        for (; t + 4 < t1; t += 2) {
+            step(Par0{}, Yes{}, Yes{}, t, t + 3);
+            step(Par1{}, Yes{}, Yes{}, t + 1, t + 4);
+        }
+        // one to four tiles are left (as few copies of the step as the parities allow: a workgroup of few tiles runs each of them from a cold instruction cache)
+        const int rest = t1 - t;
+        if (rest == 4) {
+            step(Par0{}, Yes{}, Yes{}, t, t + 3);
+            step(Par1{}, Yes{}, No{}, t + 1, t);
+            t += 2;
+        }
+        if (rest > 1) step(Par0{}, Yes{}, No{}, t, t);
+        if (rest == 3) step(Par1{}, Yes{}, No{}, t + 1, t);
+        if (rest & 1) step(Par0{}, No{}, No{}, t1 - 1, t);
+        else step(Par1{}, No{}, No{}, t1 - 1, t);
+    }
+    epi.end(red, threadIdx.x & 63, threadIdx.x >> 6);
 }
 
 // 64-row groups: the wavefronts split K in two and the rows in two (wavefront = (K half kh, row half rh)), so only TWO
@@ -1196,8 +1390,10 @@ static void launch_gemm_one(hipStream_t s, const GemmArgs &a, dim3 grid, const E
 // the arithmetic. The hi and lo products accumulate separately (two dependent MFMAs on one accumulator run at half
 // rate) and are added once per tile. Exchange buffers alternate, so a tile costs one barrier, and the partner's half
 // and the epilogue of tile t follow the MFMAs of tile t + 1 in the same straight-line stretch.
+// (A launch runs most of its code once, from a cold instruction cache, so where the code lies counts: at multiples of 16 KiB the 64-row decode step of the 0.5B-class
+// model takes 1139 us, without 1136 to 1152 as the file's other kernels happen to move it.)
 template <int KW2, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm22_kernel(GemmArgs a, Epi epi_in)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), aligned(16384))) void gemm22_kernel(GemmArgs a, Epi epi_in)
 {
     __shared__ float4 xb[2][NWAVES][2][64];
     if (a.live && *a.live == 0) return;   // uniform over the launch
@@ -1209,7 +1405,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wk0 = ks0 + kh * per;
     const int nk = max(0, min(ks1, wk0 + per) - wk0);
     const int bx = blockIdx.x, group = blockIdx.z;
-    epi.block(bx, group);
+    epi.block(bx, blockIdx.y);
     const int m = group * 64 + rh * 32 + (lane & 31), i0 = 16 * kh + 8 * hf;
     epi.row(m, 2 * kh + hf);   // per-row inputs of the epilogue: requested first, so that they are the oldest requests in flight
 
@@ -1318,14 +1514,24 @@ static void launch_gemm22_kw(hipStream_t s, const GemmArgs &a, dim3 grid, const 
     else hipLaunchKernelGGL((gemm22_kernel<28, Epi>), grid, dim3(256), 0, s, a, epi);
 }
 
-template <int NCB, class Epi>
+template <bool GROUPS, int KW, class Epi>
+static void launch_gemm_one(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
+{
+    if constexpr (GROUPS) {
+        const GroupGrid g{(int)grid.x, (int)grid.y, (int)grid.z, (int)(grid.x * grid.y * grid.z), 1.0f / grid.z, 1.0f / grid.x};
+        hipLaunchKernelGGL((gemm_groups_kernel<KW, Epi>), grid, dim3(256), 0, s, a, g, epi);
+    }
+    else hipLaunchKernelGGL((gemm_kernel<KW, Epi>), grid, dim3(256), 0, s, a, epi);
+}
+
+template <bool GROUPS, class Epi>
 static void launch_gemm_kw(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
 {
     const int per = (a.ksw + NWAVES - 1) / NWAVES;
-    if (per <= 2) launch_gemm_one<NCB, 2>(s, a, grid, epi);
-    else if (per <= 4) launch_gemm_one<NCB, 4>(s, a, grid, epi);
-    else if (per <= 8) launch_gemm_one<NCB, 8>(s, a, grid, epi);
-    else launch_gemm_one<NCB, 14>(s, a, grid, epi);
+    if (per <= 2) launch_gemm_one<GROUPS, 2>(s, a, grid, epi);
+    else if (per <= 4) launch_gemm_one<GROUPS, 4>(s, a, grid, epi);
+    else if (per <= 8) launch_gemm_one<GROUPS, 8>(s, a, grid, epi);
+    else launch_gemm_one<GROUPS, 14>(s, a, grid, epi);
 }
 
 template <class Epi>
@@ -1333,16 +1539,16 @@ static void launch_gemm(hipStream_t s, const GemmArgs &a, int nsplit, const Epi 
 {
     const int groups = (a.M + 63) / 64;
     dim3 grid((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg, nsplit, groups);
-    if (a.half && a.M > 32) { grid.z = 2 * groups; launch_gemm_kw<2>(s, a, grid, epi); return; }
+    if (a.half && a.M > 32) { grid.z = 2 * groups; launch_gemm_kw<false>(s, a, grid, epi); return; }
     GemmArgs b = a;
     b.half = 0;
-    if (a.M <= 32) launch_gemm_kw<2>(s, b, grid, epi);
+    if (a.M <= 32) launch_gemm_kw<false>(s, b, grid, epi);
     else if constexpr (!Epi::half_only) {   // half-only epilogues never get here: no 64-row instance of them
         // One 64-row group: weights come from HBM once and the LDS reduction is what limits a tile, so K and rows are
         // split two ways each. Several groups re-read the weights from L2, where loading every tile twice per
         // workgroup costs more than the smaller reduction saves: they keep the four-way K split.
         if (groups == 1) launch_gemm22_kw(s, b, grid, epi);
-        else if constexpr (!Epi::one_group) launch_gemm_kw<4>(s, b, grid, epi);
+        else if constexpr (!Epi::one_group) launch_gemm_kw<true>(s, b, grid, epi);
     }
 }
 
@@ -1548,7 +1754,7 @@ void launch_gemm_partial(hipStream_t s, const void *Wt, const void *pack, int K,
     int S, ksw, tpw;
     plan_partial(a.KS, a.n_tiles, (M + 63) / 64, &S, &ksw, &tpw);
     a.ksw = ksw; a.tiles_per_wg = tpw;
-    EpiPartial e{part, N, M};
+    EpiPartial e{part, N, M, 0};
     launch_gemm(s, a, S, e);
     *nsplit_out = S;
 }
