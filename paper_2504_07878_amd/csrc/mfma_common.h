@@ -90,15 +90,8 @@ struct QkvOut {
 // Bias, rotation and store of 8 outputs of one row: features i0 .. i0+7 of tile t, which are the pairs (j, j + dh/2), j = 16*sub +
 // i0/2 .. +3, as (first, partner) x 4 (see repack_kernel). pos: the row's position; its key and value go to position upos of storage unit `unit`.
 // BIASED: v includes the bias.
-// (cos, sin) of the four pairs; a value tile has no use for them
-struct QkvTurn { float4 c0, c1; };
-template <typename KT> __device__ __forceinline__ QkvTurn qkv_turn(const QkvOut<KT> &o, int t, int i0, int pos)
-{
-    const float4 *rp = reinterpret_cast<const float4 *>(o.rope + (size_t)pos * (o.dh >> 1) + (t % (o.dh >> 5)) * 16 + (i0 >> 1));   // 32 bytes, aligned
-    return QkvTurn{rp[0], rp[1]};
-}
 template <bool BIASED, typename KT>
-__device__ __forceinline__ void qkv_emit(const QkvOut<KT> &o, const QkvTurn &turn, int t, int m, int i0, const float (&v)[8], int unit, int upos)
+__device__ __forceinline__ void qkv_emit(const QkvOut<KT> &o, int t, int m, int i0, const float (&v)[8], int pos, int unit, int upos)
 {
     const int tph = o.dh >> 5, half = o.dh >> 1, hh = t / tph, j0 = (t % tph) * 16 + (i0 >> 1);
     float4 ba = make_float4(0.f, 0.f, 0.f, 0.f), bb = ba;
@@ -106,7 +99,9 @@ __device__ __forceinline__ void qkv_emit(const QkvOut<KT> &o, const QkvTurn &tur
     const float a[4] = {v[0] + ba.x, v[2] + ba.y, v[4] + ba.z, v[6] + ba.w}, b[4] = {v[1] + bb.x, v[3] + bb.y, v[5] + bb.z, v[7] + bb.w};
     float lo[4], hi[4];
     if (hh < o.Hq + o.Hkv) {
-        const float cx[4] = {turn.c0.x, turn.c0.z, turn.c1.x, turn.c1.z}, sy[4] = {turn.c0.y, turn.c0.w, turn.c1.y, turn.c1.w};
+        const float4 *rp = reinterpret_cast<const float4 *>(o.rope + (size_t)pos * half + j0);   // 4 (cos, sin) pairs, 32 bytes, aligned
+        const float4 c0 = rp[0], c1 = rp[1];
+        const float cx[4] = {c0.x, c0.z, c1.x, c1.z}, sy[4] = {c0.y, c0.w, c1.y, c1.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             lo[e] = a[e] * cx[e] - b[e] * sy[e];
@@ -132,12 +127,6 @@ __device__ __forceinline__ void qkv_emit(const QkvOut<KT> &o, const QkvTurn &tur
             for (int e = 0; e < 4; ++e) { kv_store1(dst + e * 32, lo[e]); kv_store1(dst + (half + e) * 32, hi[e]); }
         }
     }
-}
-
-template <bool BIASED, typename KT>
-__device__ __forceinline__ void qkv_emit(const QkvOut<KT> &o, int t, int m, int i0, const float (&v)[8], int pos, int unit, int upos)
-{
-    qkv_emit<BIASED>(o, t / (o.dh >> 5) < o.Hq + o.Hkv ? qkv_turn(o, t, i0, pos) : QkvTurn{}, t, m, i0, v, unit, upos);
 }
 
 }  // namespace tr

@@ -54,8 +54,7 @@ template <int N> __device__ __forceinline__ void wait_and_barrier()
 // ------------------------------------------------------------------ epilogues
 // init(): once per workgroup, m[mi] = this lane's row of accumulator row mi. start(): the value the split sums are added to, 8 consecutive features
 // from n0 on of row mi. store(): the finished value of the same 8 features (tile t, features i0 .. i0 + 7 of it). pair(): in place of store for
-// gate/up tiles. extra(): what store() needs from memory besides; the extras (and starting values) of all of a lane's runs are requested before the first store,
-// behind which the compiler could not move a load.
+// gate/up tiles. fini(): after the last block (lds: the kernel's whole LDS buffer, free by then).
 
 struct TilePartial {   // split-K partial sums: part[split][m][n]
     static constexpr bool pairs = false;
@@ -97,11 +96,9 @@ struct TileQkv {       // bias, rotary embedding, q out, cache append
         const float4 ba = *reinterpret_cast<const float4 *>(out.bias + hh * out.dh + j0), bb = *reinterpret_cast<const float4 *>(out.bias + hh * out.dh + half + j0);
         v[0] = ba.x; v[1] = bb.x; v[2] = ba.y; v[3] = bb.y; v[4] = ba.z; v[5] = bb.z; v[6] = ba.w; v[7] = bb.w;
     }
-    typedef QkvTurn Extra;
-    template <int WM> __device__ __forceinline__ Extra extra(const State<WM> &st, int mi, int, int t, int i0) const { return qkv_turn(out, t, i0, st.p[mi]); }
-    template <int WM> __device__ __forceinline__ void store(State<WM> &st, int mi, int m, int t, int i0, const float (&v)[8], const Extra &e) const
+    template <int WM> __device__ __forceinline__ void store(State<WM> &st, int mi, int m, int t, int i0, const float (&v)[8]) const
     {
-        if (m < M && t < n_tiles) qkv_emit<true>(out, e, t, m, i0, v, st.unit[mi], st.up[mi]);
+        if (m < M && t < n_tiles) qkv_emit<true>(out, t, m, i0, v, st.p[mi], st.unit[mi], st.up[mi]);
     }
 };
 
@@ -156,12 +153,7 @@ struct TileResidual {
         const float4 p = *reinterpret_cast<const float4 *>(xr), q = *reinterpret_cast<const float4 *>(xr + 4);
         v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w; v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
     }
-    typedef uint4 Extra;   // gains
-    template <int WM> __device__ __forceinline__ Extra extra(const State<WM> &, int, int, int t, int i0) const
-    {
-        return pack ? *reinterpret_cast<const uint4 *>(gain + min(t * 32 + i0, d - 8)) : make_uint4(0, 0, 0, 0);
-    }
-    template <int WM> __device__ __forceinline__ void store(State<WM> &st, int, int m, int t, int i0, const float (&xn)[8], const Extra &gbits) const
+    template <int WM> __device__ __forceinline__ void store(State<WM> &st, int, int m, int t, int i0, const float (&xn)[8]) const
     {
         const int n0 = t * 32 + i0;
         if (pack) {   // the lanes l and l + 32 hold the same row
@@ -180,6 +172,7 @@ struct TileResidual {
         *reinterpret_cast<float4 *>(xr) = make_float4(xn[0], xn[1], xn[2], xn[3]);
         *reinterpret_cast<float4 *>(xr + 4) = make_float4(xn[4], xn[5], xn[6], xn[7]);
         if (pack) {
+            const uint4 gbits = *reinterpret_cast<const uint4 *>(gain + n0);
             const uint32_t gw[4] = {gbits.x, gbits.y, gbits.z, gbits.w};
             float gx[8];
 #pragma unroll
@@ -302,15 +295,15 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
             src[i] = reinterpret_cast<const char *>(a.pack + (((size_t)g * a.KS + ks0) * 4 + (j & 1) * 2 + (r32 & 1)) * 64); inc[i] = 4096;
         }
     }
-    int ahead = nstep - 1;   // steps after the next one to be loaded
+    int more = nstep - 1;   // steps after the next one to be loaded
     uint32_t lbuf = lds0 + wave * 1024;
     auto issue = [&]() {
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             load_to_lds(lbuf + i * (NWV * 1024), lane_off, src[i]);
-            src[i] += ahead > 0 ? inc[i] : 0;
+            src[i] += more > 0 ? inc[i] : 0;
         }
-        --ahead;
+        --more;
         lbuf = lbuf + STG * 16 < lds0 + ST * STG * 16 ? lbuf + STG * 16 : lds0 + wave * 1024;
     };
 #pragma unroll
@@ -437,18 +430,14 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
     else {
     if (apart) return;
     // one split: the starting value joins last (the same sum)
-    float first[SPLITS ? 1 : WM][SPLITS ? 1 : WN][2][8];
-    if constexpr (!SPLITS)
-        each([&](int mi, int ni) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) epi.start(st, mi, m[mi], (t0 + ni) * 32 + 16 * h + 8 * hf, first[mi][ni][h]);
-        });
     auto value = [&](int mi, int ni, int h, float (&v)[8]) {
         if constexpr (SPLITS) run8(tot[mi][ni], h, v);
         else {
+            float b[8];
+            epi.start(st, mi, m[mi], (t0 + ni) * 32 + 16 * h + 8 * hf, b);
             run8(sum[mi][ni], h, v);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = first[mi][ni][h][e] + v[e];
+            for (int e = 0; e < 8; ++e) v[e] = b[e] + v[e];
         }
     };
     if constexpr (Epi::pairs) {
@@ -464,17 +453,12 @@ __global__ __launch_bounds__(64 * GM *GN, OCC) void tile_gemm_kernel(TileArgs a,
                     epi.pair(st, mi, m[mi], t0 + ni, 16 * h + 8 * hf, g, u);
                 }
     } else {
-        typename Epi::Extra more[WM][WN][2];
-        each([&](int mi, int ni) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) more[mi][ni][h] = epi.extra(st, mi, m[mi], t0 + ni, 16 * h + 8 * hf);
-        });
         each([&](int mi, int ni) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 float v[8];
                 value(mi, ni, h, v);
-                epi.store(st, mi, m[mi], t0 + ni, 16 * h + 8 * hf, v, more[mi][ni][h]);
+                epi.store(st, mi, m[mi], t0 + ni, 16 * h + 8 * hf, v);
             }
         });
     }
