@@ -1,4 +1,5 @@
-// Linear layers of a decode step of 3 to 8 rows on the gfx950 matrix cores.
+// Linear layers of a decode step of 3 to 8 rows on the gfx950 matrix cores: wide models, and rows that are selected on the device (other steps of narrow models are
+// one launch, flow_kernels.hip).
 //
 // The skinny kernels of mfma_kernels.hip fill a 32-column operand with rows (8 rows use a quarter of it, hi and lo twice), split the work of a layer
 // over K and leave partial sums, and need packed, normalised activations: a launch per layer for the residual and the norm, and for wide models two

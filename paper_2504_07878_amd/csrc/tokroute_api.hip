@@ -60,9 +60,9 @@ struct Layout {
     size_t flow_buf, flow_ticket;
 };
 
-// Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists. Measured decode step of the
-// 0.5B-class model (context 256): 0.64 ms at 1 row and 0.69 at 2 on the streaming kernels, which then climb to 1.15 (3 rows),
-// 1.26 (4) and 1.40 (8); 0.81 to 0.83 from 3 to 8 rows on the kernels for these, 0.93 from 9 to 32 on the others.
+// Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists (and the step is not one launch, run_step_of_few, which takes
+// 0.32 to 0.51 ms from 1 to 8 rows). Measured decode step of the 0.5B-class model (context 256): 0.64 ms at 1 row and 0.69 at 2 on the streaming kernels, which then
+// climb to 1.15 (3 rows), 1.26 (4) and 1.40 (8); 0.81 to 0.83 from 3 to 8 rows on the kernels for these, 0.93 from 9 to 32 on the others.
 constexpr int GEMV_MAX_ROWS = 2;
 
 // The matrix-core kernels keep 896 columns of K per workgroup resident, and the layers with a non-linear
@@ -459,7 +459,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
     }
     // Wide model, 2 to 4 rows whose count the host knows: the streaming kernels that keep the rows in registers (the last branch below)
     const bool rows_kernels = !live && ffn_rows_supported(ctx->c.dtype, D, R);
-    // A decode step of 3 to 8 rows (one or two: the streaming kernels, four launches a layer): every product on kernels that take and leave fp32 rows.
+    // A decode step of 3 to 8 rows that is not one launch (wide models; rows selected on the device): every product on kernels that take and leave fp32 rows.
     // 7B-class at 3 / 4 / 8 rows 3.64 / 3.62 / 3.77 ms, the streaming kernels 3.54 / 3.50 ms up to 4 rows, the split-K path below 3.97 ms at 8.
     if ((L.mfma || L.split) && (live || distinct_slots) && R >= 3 && R <= FEW_MAX_ROWS && !rows_kernels && few_supported(D)) {
         for (int l = 0; l < D.L; ++l) {
