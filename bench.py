@@ -401,13 +401,13 @@ def measured_traffic(family):
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on `bench.py --workload counters`, scaled by the 1 GiB copy kernel of the same
 # run (see profiles/); bytes per launch, per kernel family, with the hash of the kernel sources they were taken on.
 TRAFFIC = {
-    "attention": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 20803047, "write_bytes": 1660144},
-    "gateup": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 19569671, "write_bytes": 1245184},
-    "down": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 19309588, "write_bytes": 1376256},
-    "qkv": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 6239932, "write_bytes": 507904},
-    "oproj": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 5437157, "write_bytes": 516096},
-    "prep": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 953821, "write_bytes": 809562},
-    "lmhead": {"source_sha256": "0999df4960eac27037cbd8811fb121b9a2e4beafb41e513145b38326c524dc67", "fetch_bytes": 274896646, "write_bytes": 322560},
+    "attention": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 20792545, "write_bytes": 1660144},
+    "gateup": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 19564816, "write_bytes": 1245184},
+    "down": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 19300635, "write_bytes": 1376256},
+    "qkv": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 6244112, "write_bytes": 507904},
+    "oproj": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 5437231, "write_bytes": 516096},
+    "prep": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 953887, "write_bytes": 809562},
+    "lmhead": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 274895631, "write_bytes": 322560},
 }
 
 
