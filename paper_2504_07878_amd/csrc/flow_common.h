@@ -144,7 +144,7 @@ template <int N> __device__ __forceinline__ float flow_sum(float v)
     if constexpr (N >= 64) v = flow_sum2(v);
     return v;
 }
-// reciprocal and reciprocal square root: the hardware's and one Newton step (below 1 ulp)
+// reciprocal and reciprocal square root of finite values: the hardware's and one Newton step (below 1 ulp; of infinity a NaN)
 __device__ __forceinline__ float flow_rcp(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x), e = fmaf(-x, r, 1.0f);

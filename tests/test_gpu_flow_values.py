@@ -1,0 +1,50 @@
+"""What a decode step of few rows of a bf16 model (one launch over all layers) makes of values at the ends of their range, against the definition in 64 bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2504_07878_amd import synth
+
+pytestmark = pytest.mark.gpu
+# One layer. Its attention adds nothing (wo = 0), so the FFN sees the embedding: 16 in column 0, zeros elsewhere, whose root mean square over 256 columns is 1 (rms_eps
+# = 0). Gate f is 16 wg[f][0], up 16 wu[f][0] = 1, and column 1 + f of the residual row takes h[f]: every SwiGLU value comes out of the call by itself.
+GATED = synth.TINY.with_(name="gated", n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=256, vocab=64, router_hidden=0, rms_eps=0.0,
+                         dtype=synth.BF16, kv_dtype=synth.BF16)
+
+
+def gated_step(gates, rows, x0=16.0):
+    """rows of hidden (before the final norm) of a decode step whose 255 gates are given (bf16 values)"""
+    from paper_2504_07878_amd import tokroute as tr
+    s, bf = GATED, lambda *shape: torch.zeros(shape, dtype=torch.bfloat16)   # noqa: E731
+    w = {"tok_emb": bf(s.vocab, s.d_model), "final_norm": bf(s.d_model) + 1, "l0.ln1": bf(s.d_model) + 1, "l0.ln2": bf(s.d_model) + 1, "l0.wq": bf(128, s.d_model),
+         "l0.wk": bf(64, s.d_model), "l0.wv": bf(64, s.d_model), "l0.wo": bf(s.d_model, 128), "l0.wg": bf(s.d_ffn, s.d_model), "l0.wu": bf(s.d_ffn, s.d_model),
+         "l0.wd": bf(s.d_model, s.d_ffn)}
+    w["tok_emb"][:, 0] = x0
+    w["l0.wg"][:255, 0] = torch.tensor(gates, dtype=torch.float64).bfloat16() / 16
+    w["l0.wu"][:, 0] = 1 / 16
+    w["l0.wd"][1 + torch.arange(255), torch.arange(255)] = 1
+    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, 8, 64, hidden_tap=tr.PRE_FINAL_NORM)
+    g.prefill(list(range(rows)), [[3, 4]] * rows)
+    out = g.decode_step(list(range(rows)), np.arange(rows, dtype=np.int32)).cpu()
+    return out.hidden.astype(np.float64)
+
+
+def bf16_values(lo, hi, n):
+    return np.unique(torch.linspace(lo, hi, n, dtype=torch.float64).bfloat16().double().numpy())
+
+
+def silu(t):
+    return t / (1 + np.exp(-t))
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4, 8])
+def test_saturated_gates(rows):
+    """exp(-t) of a gate t below -88.7 is infinite in fp32: SwiGLU is -0 there, as in passes of more rows."""
+    t = np.resize(np.concatenate([bf16_values(-120, -80, 60), bf16_values(-20, 20, 60), bf16_values(80, 300, 20), [-300, -1e4, -2.0 ** 100, 1e4, 88.5, 0.0]]), 255)
+    t = torch.tensor(t).bfloat16().double().numpy()
+    with np.errstate(over="ignore"):
+        want = silu(t)
+    got = gated_step(t, rows)[:, 1:]
+    assert np.isfinite(got).all()
+    # the hardware's exponential is off by 2^-24 |t| of itself (1.2e-6 at 20), activations of 8 rows are carried to 2^-17; below 1e-30 parts of them may vanish
+    assert (np.abs(got - want) <= 1e-5 * np.abs(want) + 1e-30).all(), np.abs(got - want).max()
