@@ -559,7 +559,7 @@ struct Flow {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float t = v[e] * rs, up = flow_dpp<0x4e>(v[e]) * rs;   // gate rows: fo 0 and 1, up rows: 2 lanes on
-            h[e] = t / (1.0f + __expf(-t)) * up;   // (-0 where the exponential is infinite: flow_rcp is for finite values)
+            h[e] = t / (1.0f + expf(-t)) * up;   // (-0 where the exponential is infinite: flow_rcp is for finite values; the hardware's exponential is off by 2^-24 |t|)
         }
         // each of the lanes that share a sum stores a part
         uint32_t w0[NP], w1[NP];
