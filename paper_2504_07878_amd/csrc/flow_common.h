@@ -144,16 +144,11 @@ template <int N> __device__ __forceinline__ float flow_sum(float v)
     if constexpr (N >= 64) v = flow_sum2(v);
     return v;
 }
-// reciprocal and reciprocal square root of finite values: the hardware's and one Newton step (below 1 ulp; of infinity a NaN)
+// reciprocal of a finite value: the hardware's and one Newton step (below 1 ulp; of infinity a NaN)
 __device__ __forceinline__ float flow_rcp(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x), e = fmaf(-x, r, 1.0f);
     return fmaf(e, r, r);
-}
-__device__ __forceinline__ float flow_rsqrt(float x)
-{
-    const float r = __builtin_amdgcn_rsqf(x), e = fmaf(-x * r, r, 1.0f);
-    return fmaf(0.5f * e, r, r);
 }
 // an argument that is wanted behind a wait: read before it, not when it is used
 template <class T> __device__ __forceinline__ T flow_now(T v) { asm volatile("" : "+s"(v)); return v; }

@@ -195,7 +195,7 @@ struct Flow {
     __device__ __forceinline__ float rstd(float inv_d, float eps) const   // of row fm (after the barrier in product)
     {
         const f32x4 t = *reinterpret_cast<const f32x4 *>(&lds.g.ss[fm][0]) + *reinterpret_cast<const f32x4 *>(&lds.g.ss[fm][4]);
-        return flow_rsqrt(fmaf((t.x + t.y) + (t.z + t.w), inv_d, eps));
+        return 1.0f / sqrtf(fmaf((t.x + t.y) + (t.z + t.w), inv_d, eps));   // (0 where the sum overflows, as in the other kernels)
     }
     template <int N> __device__ __forceinline__ void accumulate(f32x4 (&c)[FLOW_UNITS], const uint4 (&w)[FLOW_UNITS][N]) const
     {

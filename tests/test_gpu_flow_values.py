@@ -58,3 +58,12 @@ def test_gates_to_24_bits(rows):
     off = np.abs(got - want)[:, want != 0] / np.abs(want[want != 0])
     print(f"{rows} rows: mean {off.mean():.1e} largest {off.max():.1e}")
     assert off.max() < 3.6e-7
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4, 8])
+def test_rows_whose_sum_of_squares_overflows(rows):
+    """1/rms is 0 then, as in passes of more rows: the row goes through unchanged."""
+    got = gated_step(np.linspace(-4, 4, 255), rows, x0=2.0 ** 70)
+    want = np.zeros_like(got)
+    want[:, 0] = 2.0 ** 70
+    assert np.array_equal(got, want), got
