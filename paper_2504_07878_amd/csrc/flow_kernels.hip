@@ -364,6 +364,11 @@ struct Flow {
             if (t + 32 > pos) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) sc[i][e] = t + 8 * o + e < pos ? sc[i][e] : -INFINITY;
+                // a probability of 0 does not make up for what an earlier sequence left there: infinities and NaNs go
+                const int left = pos - t - 8 * o;   // of this lane's 8 values of a dim
+                auto keep = [&](int w) { return left > 2 * w + 1 ? ~0u : left > 2 * w ? 0xffffu : 0u; };
+#pragma unroll
+                for (int d = 0; d < DT; ++d) { vr[i][d].x &= keep(0); vr[i][d].y &= keep(1); vr[i][d].z &= keep(2); vr[i][d].w &= keep(3); }
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) mx = fmaxf(mx, sc[i][e]);

@@ -6,6 +6,7 @@ import torch
 from paper_2504_07878_amd import synth
 
 pytestmark = pytest.mark.gpu
+SEED = 7878
 # One layer. Its attention adds nothing (wo = 0), so the FFN sees the embedding: 16 in column 0, zeros elsewhere, whose root mean square over 256 columns is 1 (rms_eps
 # = 0). Gate f is 16 wg[f][0], up 16 wu[f][0] = 1, and column 1 + f of the residual row takes h[f]: every SwiGLU value comes out of the call by itself.
 GATED = synth.TINY.with_(name="gated", n_layers=1, d_model=256, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ffn=256, vocab=64, router_hidden=0, rms_eps=0.0,
@@ -67,3 +68,24 @@ def test_rows_whose_sum_of_squares_overflows(rows):
     want = np.zeros_like(got)
     want[:, 0] = 2.0 ** 70
     assert np.array_equal(got, want), got
+
+
+@pytest.mark.parametrize("rows", [1, 2, 4, 8])
+def test_values_past_the_context_count_for_nothing(rows):
+    """A cache block's places past the row's context hold what an earlier sequence left there, a NaN too."""
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name="past", n_layers=2, n_q_heads=7, n_kv_heads=1, vocab=1000, router_hidden=40, dtype=synth.BF16, kv_dtype=synth.BF16, d_ffn=704)
+    w = synth.make_weights(s, SEED + 9, std=0.05)
+    gen = torch.Generator().manual_seed(SEED)
+    k, v = (torch.empty((s.n_layers, s.n_kv_heads, 64, s.head_dim)).normal_(generator=gen).bfloat16() for _ in range(2))
+    outs = []
+    for left in (0.0, float("nan")):
+        g = tr.Model(s.asdict(), w, 8, 64)
+        for b in range(rows):
+            n = 33 + 3 * b
+            vb = v.clone()
+            vb[:, :, n:] = left
+            g.load_kv(b, k.cuda(), vb.cuda())
+            g.seq_truncate(b, n)
+        outs.append(g.decode_step(list(range(rows)), np.arange(rows, dtype=np.int32)).cpu().hidden)
+    assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
