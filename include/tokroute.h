@@ -20,6 +20,12 @@
  *    has been enqueued: the sequence lengths are not advanced, but cache contents, page tables and
  *    counters of the slots named in the call are undefined afterwards; reset those slots (tr_prefill)
  *    or destroy the context.
+ *  - Decode steps of few rows run as one launch whose workgroups hand their results on to each other. Every wait inside it
+ *    is bounded (seconds); should one end without its input (which means a fault of the machine), the step is given up: it
+ *    ends, the call has long returned TR_OK, and the context is lost. That step and every later step and prompt of the
+ *    context then report token -1, conf 0, score 0, flag 0 for all rows and count nothing (hidden and logits are undefined),
+ *    the word behind the counters is set (tr_counters_ptr), and calls that read lengths back from the device return
+ *    TR_ERR_HIP. Destroy the context.
  *  - "device" pointers are HIP device memory of the current device; "host" pointers are
  *    ordinary host memory. The library allocates no device memory and creates no stream: the
  *    caller hands in a workspace and a hipStream_t (as void*; NULL = the default stream).
@@ -231,7 +237,8 @@ int tr_seq_load_kv(tr_ctx *ctx, void *hip_stream, int32_t slot, int32_t len, con
 
 /* Device address of the per-slot counters, int64 [max_batch][2] = {n_generated, n_routed}
  * (the routing history of Figure 5 as counts). They live in the workspace and are updated by the tail
- * kernel; read them with a device-to-host copy after synchronising. */
+ * kernel; read them with a device-to-host copy after synchronising. One more row follows, {given_up, 0}: given_up is
+ * non-zero once a step of this context was given up (see the general conventions). */
 int tr_counters_ptr(const tr_ctx *ctx, const int64_t **dev_counters);
 
 /* Kernel timing for benchmarks (infrastructure). The launches of a step belong to kernel families (TR_KERNEL_*);

@@ -20,7 +20,7 @@ constexpr uint32_t FLOW_SPINS = 1u << 22;   // polls until a wait is given up (s
 struct FlowWait {
     int *gave_up;
     uint32_t spins = 0;
-    __device__ __forceinline__ bool over()
+    __device__ __forceinline__ bool over()   // a wait that ends so leaves its mark, which the last kernel of the step and every later one report
     {
         asm volatile("" ::: "memory");
         ++spins;
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(256) void flow_setup_kernel(FlowSetup a, int R, int
     if (b < R) {
         const int tok = dev_tok ? min(max(dev_tok[b], 0), vocab - 1) : a.tok[b];
         if (threadIdx.x == 0) { d_slot[b] = a.slot[b]; d_tok[b] = tok; d_pos[b] = a.pos[b]; }
-        if (b == 0 && threadIdx.x < 32) ticket[threadIdx.x] = 0;
+        if (b == 0 && threadIdx.x == 0) *ticket = 0;
         const WT *e = E + (size_t)tok * d;
         for (int j = threadIdx.x; j < d; j += 256) {
             if constexpr (std::is_same_v<WT, float>) x0[(size_t)b * d + j] = __uint_as_float(flow_word(e[j]));   // (the first layer takes it as arrived)

@@ -32,7 +32,7 @@ struct Flow32Args {
     float *hn, *hidden, *logits, *r1; // tail: normalised rows, the exposed ones, logits (or NULL), sums of the router's first layer [R][rh]
     float4 *part;                     // [nV][R]: maximum, its lowest index, sum of exponentials
     int tap;
-    int *ticket;
+    int *ticket, *given_up;
 };
 
 // RC: rows the registers are laid out for (1, 2, 4); KC: 256-column pieces per row (1, 4); DH: head width (64, 128)
@@ -56,7 +56,7 @@ struct Flow32 {
         buf = buffer_of(a.buf, a.buf_bytes);
         wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); lane = threadIdx.x & 63;
     }
-    __device__ __forceinline__ FlowWait wait() const { return FlowWait{a.ticket + 16}; }
+    __device__ __forceinline__ FlowWait wait() const { return FlowWait{a.given_up}; }
     // A task far ahead of the chain: one wavefront waits for a word of the link before its own input. Tasks take different ones of n runs of 32 words.
     __device__ __forceinline__ void gate(uint32_t words, int n, int task) const
     {
@@ -448,13 +448,13 @@ void launch_flow32_setup(hipStream_t s, const Dims &D, const void *tok_emb, int 
     flow_setup(s, flow_tables(R, slots, toks, poss), R, d_slot, d_tok, d_pos, (const float *)tok_emb, D, dev_toks, buf, n, a.s_x, 0, 0, ticket);
 }
 
-void launch_flow32(hipStream_t s, const Dims &D, const Flow32Model &m, int R, const int *d_slot, const int *d_pos, float *buf, int *ticket, TailArgs &t, float *r1)
+void launch_flow32(hipStream_t s, const Dims &D, const Flow32Model &m, int R, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, TailArgs &t, float *r1)
 {
     Flow32Args a{};
     const size_t n = flow32_layout(D, R, a);
     for (int l = 0; l < D.L; ++l) a.layers[l] = m.layers[l];
     a.kc = (float *)m.kc; a.vc = (float *)m.vc; a.k_layer = m.k_layer / 4; a.v_layer = m.v_layer / 4;
-    a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket;
+    a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket; a.given_up = given_up;
     const bool wide = std::max(D.d, D.qw) > 256 || D.F > 2048;
     const int share = wide ? 1024 : 256;   // columns of a wavefront
     a.wk = 1;

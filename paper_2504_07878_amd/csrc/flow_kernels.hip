@@ -47,7 +47,7 @@ struct FlowArgs {
     uint32_t o_x1, o_xp, o_q, o_kvn, o_ap, o_at, o_h, s_x1, s_xp, s_q, s_kvn, s_ap, s_at, s_h;
     int nQ, nA, nM, nO, nG, nD;       // tasks of a layer
     int uQ, uO, uG;                   // groups of 16 rows of a layer
-    int *ticket;                      // [0] next task, [16] set when a wait was given up
+    int *ticket, *given_up;           // next task; set when a wait was given up
 };
 
 // two values as bf16, and what is left of them
@@ -108,7 +108,7 @@ struct Flow {
         fo = lane & 3; fu = (lane >> 2) & 3; fm = min(row, a.R - 1); fg = RPW == 2 ? lane >> 5 : lane >> 4;
         fin = wave < NF && row < a.R;
     }
-    __device__ __forceinline__ FlowWait wait() const { return FlowWait{a.ticket + 16}; }
+    __device__ __forceinline__ FlowWait wait() const { return FlowWait{a.given_up}; }
     // what the lanes of a wavefront wrote to the LDS is read by others of them: its LDS operations are carried out in order, the compiler is to leave them so
     __device__ __forceinline__ static void wave_fence() { asm volatile("" ::: "memory"); __builtin_amdgcn_wave_barrier(); }
     __device__ __forceinline__ const char *layer(int l) const { return a.wt + (size_t)l * a.wt_stride; }
@@ -708,7 +708,7 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
     flow_setup(s, flow_tables(R, slots, toks, poss), R, d_slot, d_tok, d_pos, (const bf16_t *)tok_emb, D, dev_toks, buf, n, a.s_x1, a.o_xp, a.o_xp + a.s_xp, ticket);
 }
 
-float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, float **partials)
+float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, float **partials)
 {
     FlowArgs a{};
     flow_split(D, max_ctx, &a.U, &a.P);
@@ -717,7 +717,7 @@ float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int 
     a.bias = m.bias; a.bias_stride = m.bias_stride;
     for (int l = 0; l < D.L; ++l) { a.ln1[l] = (const bf16_t *)m.layers[l].ln1; a.ln2[l] = (const bf16_t *)m.layers[l].ln2; }
     a.kc = m.kc; a.vc = m.vc; a.k_layer = m.k_layer; a.v_layer = m.v_layer;
-    a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket;
+    a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket; a.given_up = given_up;
     a.uQ = (D.qw + 2 * D.kvw) / 16; a.uO = D.d / 16; a.uG = D.F / 8;
     auto tasks = [](int units) { return (units + FLOW_UNITS - 1) / FLOW_UNITS; };
     a.nQ = tasks(a.uQ); a.nA = R * D.Hkv * a.P; a.nM = a.P > 1 ? R * D.Hkv : 0; a.nO = tasks(a.uO); a.nG = tasks(a.uG); a.nD = a.nO * FLOW_KQ;

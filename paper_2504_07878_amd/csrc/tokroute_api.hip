@@ -57,7 +57,7 @@ struct Layout {
     size_t pack_d, pack_a, pack_h, part;
     bool flow;         // decode steps of few rows as one launch over all layers
     bool flow32;       // the same of an fp32 model, with the LM head
-    size_t flow_buf, flow_ticket;
+    size_t flow_buf, flow_ticket, given_up;
 };
 
 // Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists (and the step is not one launch, run_step_of_few, which takes
@@ -142,7 +142,8 @@ Layout make_layout(const tr_config *c)
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     L.kc = take(L.k_layer_bytes * c->n_layers); L.vc = take(L.v_layer_bytes * c->n_layers);
     L.rope = take((size_t)c->max_seq * (c->head_dim / 2) * sizeof(float2));
-    L.counters = take((size_t)c->max_batch * 2 * sizeof(long long));
+    L.counters = take((size_t)(c->max_batch + 1) * 2 * sizeof(long long));
+    L.given_up = L.counters + (size_t)c->max_batch * 2 * sizeof(long long);   // (the low half of the first word of the last row)
     L.slot = take(R * 4); L.tok = take(R * 4); L.pos = take(R * 4); L.gather = take((size_t)c->max_batch * 4); L.out_slot = take((size_t)c->max_batch * 4);
     L.x = take(R * c->d_model * 4); L.q = take(R * qw * 4); L.att = take(R * qw * 4); L.h = take(R * c->d_ffn * 4);
     L.hn = take((size_t)c->max_batch * c->d_model * 4);
@@ -569,7 +570,7 @@ float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots
     const FlowModel m{ctx->wt(0, 0), L.wt_layer_stride, L.wt_qkv, L.wt_o, L.wt_gu, L.wt_d, ctx->bias(0), L.bias_stride / 4, ctx->layers.data(),
                       ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
     Bracket br(ctx, s, TR_KERNEL_LAYERS);
-    return launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, partials);
+    return launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, ctx->at<int>(L.given_up), partials);
 }
 
 // The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials part[pending][part_M][d] (rows indexed
@@ -649,7 +650,7 @@ bool run_step_of_few(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *
         { Bracket br(ctx, s, TR_KERNEL_SETUP); launch_flow32_setup(s, D, ctx->tok_emb, R, slots, toks, poss, dev_toks, d_slot, ctx->at<int>(L.tok), d_pos, buf, ticket); }
         {
             Bracket br(ctx, s, TR_KERNEL_LAYERS);
-            launch_flow32(s, D, m, R, d_slot, d_pos, buf, ticket, t, t.policy == TR_POLICY_MLP && D.rh > 0 ? ctx->at<float>(L.r1) : nullptr);
+            launch_flow32(s, D, m, R, d_slot, d_pos, buf, ticket, ctx->at<int>(L.given_up), t, t.policy == TR_POLICY_MLP && D.rh > 0 ? ctx->at<float>(L.r1) : nullptr);
         }
         Bracket br(ctx, s, TR_KERNEL_TAIL_MERGE);
         launch_tail_final(s, ctx->c.dtype, D, t);
@@ -675,6 +676,7 @@ TailArgs tail_args(tr_ctx *ctx, const tr_out *out, int out_offset, int n)
     t.threshold = ctx->threshold; t.route_dir = ctx->c.route_dir; t.mode = ctx->mode; t.hidden_tap = ctx->c.hidden_tap;
     t.policy = ctx->c.route_policy;
     t.rpart = ctx->at<float>(L.tail_rpart); t.rcnt = ctx->at<int>(L.tail_rcnt);
+    t.given_up = L.flow || L.flow32 ? ctx->at<int>(L.given_up) : nullptr;
     t.live = ctx->live; t.cand = ctx->cand; t.scatter = ctx->scatter;
     return t;
 }
@@ -687,9 +689,12 @@ static int sync_lengths(tr_ctx *ctx)
 {
     if (!ctx->unsynced) return TR_OK;
     std::vector<int> dev((size_t)ctx->c.max_batch);
+    int given_up = 0;
     hipError_t e = hipMemcpyAsync(dev.data(), ctx->ws + ctx->lay.dev_len, dev.size() * 4, hipMemcpyDeviceToHost, ctx->active_stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(&given_up, ctx->ws + ctx->lay.given_up, 4, hipMemcpyDeviceToHost, ctx->active_stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->active_stream);
     if (e != hipSuccess) return fail_hip(ctx, e, "reading back the device-side sequence lengths");
+    if (given_up) return fail(ctx, TR_ERR_HIP, "a step of this context was given up: its caches are undefined");
     for (size_t b = 0; b < dev.size(); ++b)
         if (ctx->ahead[b] > 0) { ctx->len[b] = dev[b]; ctx->ahead[b] = 0; }
     ctx->unsynced = false;
@@ -850,7 +855,7 @@ int tr_create(const tr_config *cfg, const tr_weights *w, void *workspace, size_t
         }
     }
     hipError_t e = hipMemcpy(ctx->ws + lay.rope, rope.data(), rope.size() * sizeof(float2), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(ctx->ws + lay.counters, 0, (size_t)cfg->max_batch * 2 * sizeof(long long));
+    if (e == hipSuccess) e = hipMemset(ctx->ws + lay.counters, 0, (size_t)(cfg->max_batch + 1) * 2 * sizeof(long long));
     // the attention kernels read whole 32-key blocks and mask afterwards: cache positions never written must hold finite values
     if (e == hipSuccess) e = hipMemset(ctx->ws + lay.kc, 0, lay.rope - lay.kc);
     if (e == hipSuccess) e = hipMemset(ctx->ws + lay.attn_cnt, 0, (size_t)lay.max_rows * cfg->n_kv_heads * 4);
@@ -1119,6 +1124,7 @@ int tr_tail(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, const tr_o
     t.slot = nullptr;
     t.counters = nullptr;
     t.counter_mode = 0;
+    t.given_up = nullptr;   // (reads no cache)
     run_tail(ctx, s, t, const_cast<float *>(x), 0, 0, n, nullptr);   // no partials pending: x is only read
     profile_next_turn(ctx);
     hipError_t e = hipGetLastError();
@@ -1144,6 +1150,7 @@ int tr_tail_noalloc(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, co
     t.slot = nullptr;
     t.counters = nullptr;
     t.counter_mode = 0;
+    t.given_up = nullptr;   // (reads no cache)
     t.x = x;
     t.hn = sc + NOALLOC_HN;
     t.part = sc + NOALLOC_PART;

@@ -111,6 +111,7 @@ struct TailArgs {
     const float *r1;         // [n][r1_stride]: sums W1 . hidden of the router's first layer, computed by the LM-head launch (NULL: computed here)
     int r1_stride;
     const int *live;         // device-side row count (see Rows::live); rows from *live on report token -1, score 0, flag 0 and count nothing
+    const int *given_up;     // set: a step of this context was given up, its caches are not to be trusted; every row reports like one from *live on (NULL: cannot happen)
     const int *cand;         // with scatter: index of output i in the caller's candidate list
     int32_t *scatter;        // scatter[cand[i]] = token of live row i (the other model's next-input buffer), or NULL
 };
@@ -216,7 +217,7 @@ void launch_few_down(hipStream_t s, const Dims &D, const void *Wt, const void *h
 // ---- all layers of a decode step of few rows in one launch (flow_kernels.hip)
 constexpr int FLOW_MAX_ROWS = 8, FLOW_MAX_LAYERS = 64, FLOW_MAX_PARTS = 16;
 constexpr int FLOW_KQ = 4;   // parts of the FFN's columns in the FFN output
-constexpr int FLOW_TICKET_INTS = 32;
+constexpr int FLOW_TICKET_INTS = 32;   // (a cache line)
 struct FlowModel {
     const char *wt; size_t wt_stride, wt_qkv, wt_o, wt_gu, wt_d;   // tiled weights (bytes)
     const float *bias; size_t bias_stride;
@@ -230,8 +231,8 @@ bool flow_takes(const Dims &D, int R, int max_ctx);
 // Rows of different slots (a decode step). Setup: row tables, embedding, the hand-over buffers as the layers expect them.
 void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks,
                        int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
-// All layers; returns the rows of the residual stream (in buf), *partials: FLOW_KQ sums to add to them first ([FLOW_KQ][R][d])
-float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, float **partials);
+// All layers; returns the rows of the residual stream (in buf), *partials: FLOW_KQ sums to add to them first ([FLOW_KQ][R][d]). *given_up: set if a wait inside was given up
+float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, float **partials);
 // the same for fp32 models of up to 4 rows, with the LM head's slices and the router's first layer (flow_f32_kernels.hip)
 constexpr int FLOW32_MAX_ROWS = 4, FLOW32_MAX_LAYERS = 24;
 struct Flow32Model {
@@ -246,7 +247,7 @@ int flow32_slices(const Dims &D);   // vocabulary slices it leaves for launch_ta
 void launch_flow32_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R, const int *slots, const int *toks, const int *poss, const int *dev_toks,
                          int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
 // Everything up to launch_tail_final, for which it completes t. r1: [R][rh] sums of the router's first layer, or NULL (not wanted)
-void launch_flow32(hipStream_t s, const Dims &D, const Flow32Model &m, int R, const int *d_slot, const int *d_pos, float *buf, int *ticket, TailArgs &t, float *r1);
+void launch_flow32(hipStream_t s, const Dims &D, const Flow32Model &m, int R, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, TailArgs &t, float *r1);
 
 // Wide models (K beyond what one workgroup keeps resident): every linear layer goes through split-K partials, and the
 // layers with a non-linear epilogue are finished by a small kernel of their own.

@@ -283,13 +283,16 @@ class Model:
         self._check(self.lib.tr_seq_load_kv(self._h, self._stream(), int(slot), k.shape[2], k.data_ptr(), v.data_ptr()), "tr_seq_load_kv")
 
     def counters(self):
-        """Synchronise and return the [max_batch][2] int64 counters (n_generated, n_routed)."""
+        """Synchronise and return the [max_batch][2] int64 counters (n_generated, n_routed); an error if a step was given up."""
         p = C.c_void_p()
         self._check(self.lib.tr_counters_ptr(self._h, C.byref(p)), "tr_counters_ptr")
         off = p.value - self.workspace.data_ptr()
-        n = self.cfg.max_batch * 2 * 8
+        n = (self.cfg.max_batch + 1) * 2 * 8
         torch.cuda.synchronize()
-        return self.workspace[off:off + n].cpu().numpy().view(np.int64).reshape(self.cfg.max_batch, 2).copy()
+        rows = self.workspace[off:off + n].cpu().numpy().view(np.int64).reshape(self.cfg.max_batch + 1, 2)
+        if rows[-1, 0]:
+            raise TokrouteError(ERR_HIP, "tr_decode_step", "a step of this context was given up: its caches are undefined")
+        return rows[:-1].copy()
 
     def profile_enable(self, on=True):
         self._check(self.lib.tr_profile_enable(self._h, int(bool(on))), "tr_profile_enable")

@@ -75,6 +75,7 @@ def test_nans_end_the_step(rows):
         out = m.decode_step(list(range(rows)), np.arange(rows, dtype=np.int32))
         torch.cuda.synchronize()
         assert torch.isnan(out.hidden).all(), key
+        m.counters()   # (an error if a wait was given up: the words of a step that was are NaNs too)
 
 
 def test_steps_of_two_models_at_the_same_time():
@@ -164,3 +165,46 @@ def test_nans_end_the_step_of_an_fp32_model():
         out = m.decode_step([0, 1], np.arange(2, dtype=np.int32))
         torch.cuda.synchronize()
         assert torch.isnan(out.hidden).all(), key
+        m.counters()   # (an error if a wait was given up: the words of a step that was are NaNs too)
+
+
+def given_up_word(m):
+    """The word behind the counters, as the header describes it."""
+    import ctypes
+    p = ctypes.c_void_p()
+    m._check(m.lib.tr_counters_ptr(m._h, ctypes.byref(p)), "tr_counters_ptr")
+    off = p.value - m.workspace.data_ptr() + m.cfg.max_batch * 16
+    return m.workspace[off:off + 4]
+
+
+@pytest.mark.parametrize("shape", [BASE, F32], ids=["bf16", "fp32"])
+def test_a_step_that_was_given_up_is_reported(shape):
+    """The word is set from the host, as a wait that ends without its input would: the steps and prompts from then on say so, whatever kernels they take."""
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="given-up", **shape)
+    m = tr.Model(s.asdict(), synth.make_weights(s, SEED + 9, std=0.05), 16, 64)
+    prompts = [[1, 2, 3]] * 12
+    m.prefill(list(range(12)), prompts)
+    out = m.decode_step([0, 1], [4, 5]).cpu()
+    assert (out.token >= 0).all() and (out.conf > 0).all() and m.counters()[0, 0] == 2
+    assert int(given_up_word(m).view(torch.int32)) == 0
+    given_up_word(m).view(torch.int32).fill_(1)
+    for out in (m.decode_step([0, 1], [4, 5]), m.decode_step(list(range(9)), [4] * 9), m.decode_step_dev([3], torch.full((1,), 4, dtype=torch.int32, device="cuda")),
+                m.extend([0, 1], [[1], [2]]), m.extend([0, 1], [[1], [2, 3]]), m.prefill([0], prompts[:1])):
+        o = out.cpu()
+        assert (o.token == -1).all() and not o.conf.any() and not o.score.any() and not o.flag.any()
+    x = torch.randn((2, s.d_model), device="cuda")
+    assert (m.tail(x).cpu().token >= 0).all()   # touches no cache
+    with pytest.raises(tr.TokrouteError) as e:
+        m.counters()
+    assert e.value.code == tr.ERR_HIP
+    if s.dtype == synth.BF16:   # lengths that only the device knows
+        n, one = 3, torch.ones(3, dtype=torch.int32, device="cuda")
+        o = m.decode_step_active([4, 5, 6], one, one, n, torch.zeros(2 + n, dtype=torch.int32, device="cuda")).cpu()
+        assert (o.token == -1).all()
+        with pytest.raises(tr.TokrouteError) as e:
+            m.seq_len(4)
+        assert e.value.code == tr.ERR_HIP
+    given_up_word(m).view(torch.int32).fill_(0)   # (nothing was counted meanwhile)
+    assert m.counters()[1, 0] == 2 and m.counters()[3, 0] == 1
