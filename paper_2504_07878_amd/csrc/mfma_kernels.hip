@@ -819,6 +819,7 @@ template <class T> __device__ __forceinline__ void here(T &v) { asm volatile("" 
 
 struct EpiPartial {   // split-K partial sums: part[split][m][n]
     static constexpr bool half_only = false, one_group = false;
+    static constexpr int min_tiles = 1;   // of a workgroup's range
     float *part;
     int N, M, split;
     __device__ void block(int, int y) { split = y; }
@@ -876,6 +877,7 @@ struct EpiQkv {       // bias, rotary embedding, q out, cache append; tiles hold
 template <bool RAGGED, bool DEFER>
 struct EpiSwiglu {    // tiles alternate gate, up; h = silu(gate) * up, written as packed activations of the down projection
     static constexpr bool half_only = false, one_group = false;
+    static constexpr int min_tiles = 2;
     uint4 *hpack;     // [group][F/16][NCB][64]
     int M, F, ncb;
     float hold[8];
@@ -1081,10 +1083,11 @@ struct EpiLmHead {    // running softmax statistics per batch row (one 64-row gr
 // interleaved so that consecutive MFMAs never share an accumulator.)
 constexpr int RED_FLOATS = NWAVES * 64 * 36;   // [wavefront][batch column][feature row padded to 36]
 
-template <int KW, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a, Epi epi_in)   // 32 rows
+// NCB = 2: 32 rows; 4: 64 of several groups of them, where gemm_groups_kernel has nothing to spread
+template <int NCB, int KW, class Epi>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_kernel(GemmArgs a, Epi epi_in)
 {
-    constexpr int NCB = 2, NCO = NCB / 2;
+    constexpr int NCO = NCB / 2;
     __shared__ __attribute__((aligned(16))) float red[2 * RED_FLOATS];
     if (a.live && *a.live == 0) return;   // uniform over the launch
     Epi epi = epi_in;   // per-thread epilogue state lives in registers
@@ -1224,8 +1227,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // time until a tile range's groups were dealt to one XCD. 896 columns, FFN 4864, before / spread / and dealt: gate and up of 256 rows 18.5 / 17.3 / 14.8 us, of 896
 // rows 35.9 / 34.0 / 33.1; FFN output of 256 rows 13.9 / 13.7 / 10.7. What is left is the way of the weights into the compute unit (57 KB a tile at 31 bytes a
 // nanosecond) and the first 229 KB of activations.
+// (Its code lies at multiples of 16 KiB for gemm22_kernel's reason: prompts of narrow models take 197 to 253 us with that, 207 to 258 as it happened to lie without.)
 template <int KW, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_groups_kernel(GemmArgs a, GroupGrid g, Epi epi_in)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), aligned(16384))) void gemm_groups_kernel(GemmArgs a, GroupGrid g, Epi epi_in)
 {
     constexpr int NCB = 4, NCO = NCB / 2;
     __shared__ __attribute__((aligned(16))) float red[2 * RED_FLOATS];
@@ -1514,24 +1518,28 @@ static void launch_gemm22_kw(hipStream_t s, const GemmArgs &a, dim3 grid, const 
     else hipLaunchKernelGGL((gemm22_kernel<28, Epi>), grid, dim3(256), 0, s, a, epi);
 }
 
-template <bool GROUPS, int KW, class Epi>
+// Several 64-row groups go to gemm_groups_kernel, but for ranges of one weight tile, which have no next tile to hide anything behind, and wavefronts of at most two
+// k-steps, whose 8 matrix instructions hide nothing: its start and its order cost these 0.2 to 0.5 us. gemm_groups_kernel / gemm_kernel: FFN output of 256 columns (FFN
+// 704) over 65 / 256 / 500 rows 3.9 / 4.3 / 4.9 us, 3.5 / 4.0 / 4.5; 32 columns (FFN 48) over 831 rows, gate and up 4.8 / 4.2, FFN output 3.5 / 3.2.
+template <int NCB, int KW, class Epi>
 static void launch_gemm_one(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
 {
-    if constexpr (GROUPS) {
-        const GroupGrid g{(int)grid.x, (int)grid.y, (int)grid.z, (int)(grid.x * grid.y * grid.z), 1.0f / grid.z, 1.0f / grid.x};
-        hipLaunchKernelGGL((gemm_groups_kernel<KW, Epi>), grid, dim3(256), 0, s, a, g, epi);
-    }
-    else hipLaunchKernelGGL((gemm_kernel<KW, Epi>), grid, dim3(256), 0, s, a, epi);
+    if constexpr (NCB == 4 && KW > 2) {
+        if (Epi::min_tiles > 1 || a.tiles_per_wg > 1) {
+            const GroupGrid g{(int)grid.x, (int)grid.y, (int)grid.z, (int)(grid.x * grid.y * grid.z), 1.0f / grid.z, 1.0f / grid.x};
+            hipLaunchKernelGGL((gemm_groups_kernel<KW, Epi>), grid, dim3(256), 0, s, a, g, epi);
+        } else if constexpr (Epi::min_tiles == 1) hipLaunchKernelGGL((gemm_kernel<NCB, KW, Epi>), grid, dim3(256), 0, s, a, epi);
+    } else hipLaunchKernelGGL((gemm_kernel<NCB, KW, Epi>), grid, dim3(256), 0, s, a, epi);
 }
 
-template <bool GROUPS, class Epi>
+template <int NCB, class Epi>
 static void launch_gemm_kw(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
 {
     const int per = (a.ksw + NWAVES - 1) / NWAVES;
-    if (per <= 2) launch_gemm_one<GROUPS, 2>(s, a, grid, epi);
-    else if (per <= 4) launch_gemm_one<GROUPS, 4>(s, a, grid, epi);
-    else if (per <= 8) launch_gemm_one<GROUPS, 8>(s, a, grid, epi);
-    else launch_gemm_one<GROUPS, 14>(s, a, grid, epi);
+    if (per <= 2) launch_gemm_one<NCB, 2>(s, a, grid, epi);
+    else if (per <= 4) launch_gemm_one<NCB, 4>(s, a, grid, epi);
+    else if (per <= 8) launch_gemm_one<NCB, 8>(s, a, grid, epi);
+    else launch_gemm_one<NCB, 14>(s, a, grid, epi);
 }
 
 template <class Epi>
@@ -1539,16 +1547,16 @@ static void launch_gemm(hipStream_t s, const GemmArgs &a, int nsplit, const Epi 
 {
     const int groups = (a.M + 63) / 64;
     dim3 grid((a.n_tiles + a.tiles_per_wg - 1) / a.tiles_per_wg, nsplit, groups);
-    if (a.half && a.M > 32) { grid.z = 2 * groups; launch_gemm_kw<false>(s, a, grid, epi); return; }
+    if (a.half && a.M > 32) { grid.z = 2 * groups; launch_gemm_kw<2>(s, a, grid, epi); return; }
     GemmArgs b = a;
     b.half = 0;
-    if (a.M <= 32) launch_gemm_kw<false>(s, b, grid, epi);
+    if (a.M <= 32) launch_gemm_kw<2>(s, b, grid, epi);
     else if constexpr (!Epi::half_only) {   // half-only epilogues never get here: no 64-row instance of them
         // One 64-row group: weights come from HBM once and the LDS reduction is what limits a tile, so K and rows are
         // split two ways each. Several groups re-read the weights from L2, where loading every tile twice per
         // workgroup costs more than the smaller reduction saves: they keep the four-way K split.
         if (groups == 1) launch_gemm22_kw(s, b, grid, epi);
-        else if constexpr (!Epi::one_group) launch_gemm_kw<true>(s, b, grid, epi);
+        else if constexpr (!Epi::one_group) launch_gemm_kw<4>(s, b, grid, epi);
     }
 }
 

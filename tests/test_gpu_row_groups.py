@@ -13,6 +13,8 @@ SEED = 7878
     (32, 48, [65]),                 # one k-step of two wavefronts; one and a half tile pairs
     (144, 1040, [63, 66]),          # 9 k-steps for four wavefronts; 33 pairs
     (256, 704, [100, 1, 92]),       # 4 of a wavefront
+    (256, 704, [448]),              # FFN output: one tile a range, 6 k-steps of a wavefront in two splits
+    (256, 704, [200, 440]),         # the same in one split, 11
     (512, 2048, [129, 128]),        # 8; 5 groups
     (896, 4864, [70, 300]),         # 14; 6 groups
     (896, 4880, [831]),             # the most rows that come this way; 13 groups
