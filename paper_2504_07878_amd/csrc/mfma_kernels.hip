@@ -1227,9 +1227,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // time until a tile range's groups were dealt to one XCD. 896 columns, FFN 4864, before / spread / and dealt: gate and up of 256 rows 18.5 / 17.3 / 14.8 us, of 896
 // rows 35.9 / 34.0 / 33.1; FFN output of 256 rows 13.9 / 13.7 / 10.7. What is left is the way of the weights into the compute unit (57 KB a tile at 31 bytes a
 // nanosecond) and the first 229 KB of activations.
-// (Its code lies at multiples of 16 KiB for gemm22_kernel's reason: prompts of narrow models take 197 to 253 us with that, 207 to 258 as it happened to lie without.)
 template <int KW, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), aligned(16384))) void gemm_groups_kernel(GemmArgs a, GroupGrid g, Epi epi_in)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_groups_kernel(GemmArgs a, GroupGrid g, Epi epi_in)
 {
     constexpr int NCB = 4, NCO = NCB / 2;
     __shared__ __attribute__((aligned(16))) float red[2 * RED_FLOATS];
@@ -1394,10 +1393,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), alig
 // the arithmetic. The hi and lo products accumulate separately (two dependent MFMAs on one accumulator run at half
 // rate) and are added once per tile. Exchange buffers alternate, so a tile costs one barrier, and the partner's half
 // and the epilogue of tile t follow the MFMAs of tile t + 1 in the same straight-line stretch.
-// (A launch runs most of its code once, from a cold instruction cache, so where the code lies counts: at multiples of 16 KiB the 64-row decode step of the 0.5B-class
-// model takes 1139 us, without 1136 to 1152 as the file's other kernels happen to move it.)
 template <int KW2, class Epi>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), aligned(16384))) void gemm22_kernel(GemmArgs a, Epi epi_in)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm22_kernel(GemmArgs a, Epi epi_in)
 {
     __shared__ float4 xb[2][NWAVES][2][64];
     if (a.live && *a.live == 0) return;   // uniform over the launch
@@ -1507,6 +1504,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1), alig
     }
     epi.end(reinterpret_cast<float *>(&xb[0][0][0][0]), rh * 32 + (lane & 31), 2 * kh + hf);
 }
+
+// The products of a layer of the 0.5B-class model lie one behind the other in the code object, in the order of their launches. A launch runs most of its code once, and
+// the code of a layer's launches is about as large as an instruction cache (62 KB at 9 to 32 rows): what is still there from the layer before depends on where each
+// kernel lies. As the compiler happened to place them / at multiples of 16 KiB / so: prompts of 64 rows 914 / 923 / 914 us, steps of 64 rows 937 / 945 / 940, of 32 rows
+// 882 / 887 / 881, prompts of 65 rows 1041 / 1035 / 1035 (and 1 % more or less with every change to this file, as long as the places were the compiler's).
+template __global__ void gemm_kernel<2, 14, EpiQkv<bf16_t>>(GemmArgs, EpiQkv<bf16_t>);
+template __global__ void gemm_kernel<2, 14, EpiResidualNorm>(GemmArgs, EpiResidualNorm);
+template __global__ void gemm_kernel<2, 14, EpiSwiglu<false, true>>(GemmArgs, EpiSwiglu<false, true>);
+template __global__ void gemm_kernel<2, 14, EpiPartial>(GemmArgs, EpiPartial);
+template __global__ void gemm22_kernel<28, EpiSwiglu<false, true>>(GemmArgs, EpiSwiglu<false, true>);
+template __global__ void gemm22_kernel<28, EpiPartial>(GemmArgs, EpiPartial);
+template __global__ void gemm_groups_kernel<14, EpiSwiglu<false, true>>(GemmArgs, GroupGrid, EpiSwiglu<false, true>);
+template __global__ void gemm_groups_kernel<14, EpiPartial>(GemmArgs, GroupGrid, EpiPartial);
 
 template <class Epi>
 static void launch_gemm22_kw(hipStream_t s, const GemmArgs &a, dim3 grid, const Epi &epi)
