@@ -1,8 +1,8 @@
 """A model's forward pass in 64 bits, from its definition alone (plain torch on the CPU), for tests whose bound is the precision that the kernels keep rather
 than the parity tolerance: bf16 weights times activations carried as a high and a low bf16 part (16 bits), sums in fp32.
 
-`coarse` names a product (or attention's queries q, weights p) whose activations are rounded to bf16 first, as if their low parts were lost: the distance a
-test has to be able to see.
+`coarse` names a product (or attention's queries q, weights p) whose activations are cut to their first `parts` bf16 parts (one: rounded to bf16), as if the others
+were lost: the distance a test has to be able to see.
 """
 import numpy as np
 import torch
@@ -16,6 +16,9 @@ REL, WORST = 1.5e-5, 9e-5
 # Keys and values that the pass itself rounds to a bf16 cache: where an fp32 value lies within its error (4e-6 of itself) of the middle between two bf16 values it
 # may go the other way: up to 2^-17 / 2^-9 = 4e-3 of the values by 2^-8, 2.5e-4 rms where a row sees one key, less with every key more.
 REL_BF16_CACHE, WORST_BF16_CACHE = 1.5e-4, 1.5e-3
+# Three bf16 parts hold an activation's 24 bits: what is left is fp32 arithmetic, about ten roundings of 2^-24 / sqrt(3) = 3.4e-8 rms between a row and its hidden
+# row, an exponential and a root, 1.0e-7 to 1.5e-7 as measured. Without its third part a product is off by 2^-17 at most, 7e-7 of the hidden row and more.
+REL_24 = 3e-7
 
 
 def weights(s, seed):
@@ -34,7 +37,7 @@ def weights(s, seed):
     return w
 
 
-def forward(s, w, segments, caches=None, coarse=None):
+def forward(s, w, segments, caches=None, coarse=None, parts=1):
     """hidden rows (after the final norm) and logits of the last token of each segment, float64 arrays. caches[i] = (k, v) of segment i, float64
     [layer][kv head][position][head_dim], or None."""
     d, Hq, Hkv, dh = s.d_model, s.n_q_heads, s.n_kv_heads, s.head_dim
@@ -48,7 +51,13 @@ def forward(s, w, segments, caches=None, coarse=None):
         return x / torch.sqrt((x * x).mean(-1, keepdim=True) + s.rms_eps) * gain.double()
 
     def low_lost(name, x):
-        return x.bfloat16().double() if coarse == name else x
+        if coarse != name:
+            return x
+        kept, rest = 0, x
+        for _ in range(parts):
+            p = rest.bfloat16().double()
+            kept, rest = kept + p, rest - p
+        return kept
 
     def product(name, x, m):
         return low_lost(name, x) @ m.double().T

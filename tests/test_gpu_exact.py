@@ -16,6 +16,9 @@ HEADS = dict(FUSED, d_model=128, n_q_heads=16, n_kv_heads=8, d_ffn=96, vocab=500
 # contexts given, rows of the pass: 208 blocks of rows and kv heads over contexts to 360 (eight wavefronts a block; 128-wide heads four), contexts to 160 (four),
 # 928 blocks (two)
 SEGMENTS = [(64, [300, 150], [60, 41]), (64, [100, 31], [60, 41]), (64, [200, 33], [290, 171]), (128, [300, 150], [60, 41]), (128, [200, 33], [290, 171])]
+# decode steps in one launch: the smallest and the widest rows, both head widths, contexts that leave the keys of a step their weight
+ONE_LAUNCH = [("one", HEADS), ("one_896", dict(HEADS, d_model=896, n_q_heads=14, n_kv_heads=2, d_ffn=4864)), ("one_128", dict(HEADS, head_dim=128, n_q_heads=8, n_kv_heads=1))]
+ONE_LAUNCH_LENS = [5, 9, 2, 12, 3, 7]
 SEGMENTS_REL = 4e-5   # between REL and REL_BF16_CACHE: most keys are given, those of the pass are rounded
 
 
@@ -25,6 +28,10 @@ def shape(name, kw):
 
 def tokens(s, lens, name):
     return [synth.prompt_tokens(SEED, f"exact.{name}.{i}", n, s.vocab) for i, n in enumerate(lens)]
+
+
+def step_tokens(s, name, n):
+    return [[t] for t in synth.prompt_tokens(SEED, f"exact.step.{name}", n, s.vocab)]
 
 
 def check(out, ref, what, rel=exact.REL, worst=exact.WORST):
@@ -69,6 +76,18 @@ def test_the_bound_sees_attention_without_its_low_parts(head_dim, lens, segs):
         h, _ = exact.forward(s, w, toks, caches, coarse=p)
         print(p, exact.distance(h, hidden))
         assert exact.distance(h, hidden)[0] > SEGMENTS_REL, (p, exact.distance(h, hidden))
+
+
+@pytest.mark.parametrize("name,kw", ONE_LAUNCH)
+def test_the_bound_sees_a_product_without_its_third_part(name, kw):
+    s = shape(name, kw)
+    w, toks, caches = exact.weights(s, SEED), step_tokens(s, name, 4), [(k.double(), v.double()) for k, v in caches_of(s, ONE_LAUNCH_LENS[:4])]
+    hidden, _ = exact.forward(s, w, toks, caches)
+    for p in ("qkv", "q", "p", "o", "gate_up", "down"):
+        h, _ = exact.forward(s, w, toks, caches, coarse=p, parts=2)
+        print(p, exact.distance(h, hidden))
+        assert exact.distance(h, hidden)[0] > 2 * exact.REL_24, (p, exact.distance(h, hidden))
+        assert exact.distance(exact.forward(s, w, toks, caches, coarse=p, parts=3)[0], hidden)[0] < exact.REL_24 / 50
 
 
 @pytest.mark.gpu
@@ -116,6 +135,46 @@ def test_steps_over_given_caches(name, kw, lens):
     g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, max(8, len(lens)), 1100)
     ref = exact.forward(s, w, [[t] for t in toks], given_caches(g, s, lens))
     check(g.decode_step(list(range(len(lens))), toks, want_logits=True).cpu(), ref, f"{name} {len(lens)} rows")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [1, 2, 3, 4, 6])
+@pytest.mark.parametrize("name,kw", ONE_LAUNCH)
+def test_one_launch_steps(name, kw, rows):
+    """All 24 bits of up to 4 rows' activations, 16 of more. (Slots and tokens for which no key or value of the step comes so near the middle between two bf16 values
+    that fp32 decides how the cache rounds it: one that goes the other way is 5e-6 and more.)"""
+    from paper_2504_07878_amd import tokroute as tr
+    s = shape(name, kw)
+    w, lens, toks = exact.weights(s, SEED), ONE_LAUNCH_LENS[:rows], step_tokens(s, name, rows)
+    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, 8, 64)
+    ref = exact.forward(s, w, toks, given_caches(g, s, lens))
+    out = g.decode_step(list(range(rows)), np.concatenate(toks), want_logits=True).cpu()
+    check(out, ref, f"{name} {rows} rows")
+    if rows <= 4:
+        assert exact.distance(out.hidden, ref[0])[0] < exact.REL_24
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("head_dim,kv_page,lens,in_one", [
+    # 64-wide heads: up to 12288 cached keys go through one launch (16 parts of a context, three blocks a wavefront; from 4609 on more than 6), 128-wide up to 4096;
+    # past that 1 and 2 rows of 64-wide heads take the projection with the attention in it, others the chunked attention
+    (64, 0, [12288], True), (64, 0, [12289], False), (64, 64, [12288, 40], True), (64, 64, [4609, 12289], False), (64, 0, [9000, 4609, 12288, 6145], True),
+    (64, 64, [9000, 4609, 12289], False), (64, 0, [4609, 12288, 1, 31, 7000, 12000, 8000, 513], True),
+    (128, 0, [4096], True), (128, 0, [4097, 1537], False), (128, 64, [1537, 4096], True), (128, 0, [2049, 1537, 33, 4096], True), (128, 0, [2049, 4097, 33], False),
+    (128, 64, [1537, 4096, 1, 31, 2500, 4000, 3000, 300], True),
+])
+def test_steps_over_the_longest_contexts(head_dim, kv_page, lens, in_one):
+    from paper_2504_07878_amd import tokroute as tr
+    s = shape("longest", dict(HEADS, head_dim=head_dim, n_q_heads=7, n_kv_heads=1))
+    w = exact.weights(s, SEED)
+    w["l0.wq"] = (w["l0.wq"].float() * 3).bfloat16()   # (few keys have most of the weight, wherever they are)
+    toks = step_tokens(s, "longest", len(lens))
+    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, len(lens), 12352 if head_dim == 64 else 4160, kv_page=kv_page)
+    ref = exact.forward(s, w, toks, given_caches(g, s, lens))
+    out = g.decode_step(list(range(len(lens))), np.concatenate(toks), want_logits=True).cpu()
+    check(out, ref, f"{head_dim} {lens}")
+    if in_one and len(lens) <= 4:
+        assert exact.distance(out.hidden, ref[0])[0] < 2 * exact.REL_24   # (scores three times as large)
 
 
 @pytest.mark.gpu
