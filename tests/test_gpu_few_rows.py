@@ -1,4 +1,5 @@
-"""Decode steps of 3 to 8 rows: the kernels that take and leave fp32 rows, against the oracle, at widths that leave wavefronts with unequal
+"""Decode steps of 3 to 8 rows: the kernels that take and leave fp32 rows (fp32 caches, wide models) and, where model and cache allow it, the launch over all
+layers, against the oracle, at widths that leave wavefronts with unequal
 shares of the reduction dimension or none, for both kinds of model and both cache forms."""
 import numpy as np
 import pytest
@@ -14,6 +15,8 @@ BASE = dict(n_layers=2, n_q_heads=7, n_kv_heads=1, head_dim=64, vocab=1000, rout
 @pytest.mark.parametrize("name,shape,kv_page", [
     ("fused", dict(d_model=224, d_ffn=352), 0),                             # 7 steps of 32 columns: one wavefront without any
     ("fused_paged", dict(d_model=896, n_q_heads=14, n_kv_heads=2, d_ffn=5152), 32),   # FFN columns past one round of steps in flight
+    ("fused_224_f32kv", dict(d_model=224, d_ffn=352, kv_dtype=synth.F32), 0),
+    ("fused_896_f32kv", dict(d_model=896, n_q_heads=14, n_kv_heads=2, d_ffn=5152, kv_dtype=synth.F32), 0),
     ("fused_f32kv", dict(d_model=480, d_ffn=96, kv_dtype=synth.F32), 0),    # fewer FFN pairs than wavefronts
     ("wide", dict(d_model=1120, n_q_heads=6, head_dim=128, d_ffn=1184), 0),     # 5 steps a wavefront
     ("wide_paged", dict(d_model=2208, n_q_heads=5, head_dim=128, d_ffn=9248), 32),   # 9 steps a wavefront; two units of FFN rows for some workgroups

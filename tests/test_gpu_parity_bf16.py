@@ -270,9 +270,8 @@ def test_flags_with_the_threshold_at_the_seven_percent_quantile(tr, tro, weights
     say(f"[threshold at the 7 % quantile: {routed_g} of {srt.size} routed on the GPU, {routed_o} on the oracle, {exempt} exempt]")
 
 
-def test_two_sequences_decode_on_the_fused_projection_and_attention_kernel(tr, tro, weights, dev_weights):
-    """Two rows at d = 896: the q|k|v projection and the attention in one launch, the LDS-free short rows, the split-K
-    residual kernel for two rows and the per-row workgroups of the merging output projection, on the benchmark's model."""
+def test_two_sequences_decode(tr, tro, weights, dev_weights):
+    """Two rows at d = 896, a short and a longer context: all layers in one launch, on the benchmark's model."""
     prompts = [synth.prompt_tokens(SEED, "two.b0", 45, S.vocab), synth.prompt_tokens(SEED, "two.b1", 301, S.vocab)]
     exempt = 0
     for go, oo in _follow(tr, tro, weights, dev_weights, S, prompts, 8, "two rows"):

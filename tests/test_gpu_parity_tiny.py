@@ -213,8 +213,8 @@ def test_small_bf16_model_on_the_matrix_core_path(tr, tro, B):
 
 @pytest.mark.parametrize("B,ctx", [(3, 1200), (1, 4500), (12, 2300), (40, 900)])
 def test_small_bf16_model_long_contexts(tr, tro, B, ctx):
-    """Long loaded caches with a bf16 KV cache: many attention chunks per row (merged by a separate kernel for a few rows,
-    by the consumer or the batched merge otherwise), chunks longer than 64 keys past 4096 positions, contexts of very
+    """Long loaded caches with a bf16 KV cache: several parts of a row's context (1 and 3 rows: tasks of one launch; 12 and 40 rows: merged by
+    a separate kernel or the batched merge), three blocks of keys a wavefront past 4096 positions, contexts of very
     different lengths in one call, and decoding right up to the last position of the cache (max_seq not a multiple of 32)."""
     s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
     w = synth.make_weights(s, SEED + 4, std=0.05, bias_std=0.05, gain_std=0.1)
@@ -241,8 +241,8 @@ def test_small_bf16_model_long_contexts(tr, tro, B, ctx):
 @pytest.mark.parametrize("dtype", [synth.F32, synth.BF16])
 def test_catch_up_step_over_an_existing_cache(tr, tro, dtype):
     """tr_extend against the oracle's definition (cached decode steps, only the last one visible): segments of 1, 5, 14
-    (the paper's ~7 % routing means about 14 small-model tokens between two routed ones), 40 and 130 tokens — one or two rows
-    run the GEMV kernels, more run the matrix-core ones (bf16) — over caches of very different lengths, several slots per call,
+    (the paper's ~7 % routing means about 14 small-model tokens between two routed ones), 40 and 130 tokens — passes of one
+    token a slot run as decode steps (few rows: one launch), others the streaming kernels (fp32) or the matrix-core ones (bf16) — over caches of very different lengths, several slots per call,
     alternating with ordinary decode steps; counters, lengths and error paths included."""
     s = synth.TINY.with_(dtype=dtype, kv_dtype=dtype)
     w = synth.make_weights(s, SEED + 5, std=0.05, bias_std=0.05, gain_std=0.1)
@@ -524,11 +524,11 @@ def test_decode_steps_fed_from_device_memory(tr, tro, tiny_weights, dtype):
     assert np.array_equal(ya.logits, yb.logits)
 
 
-@pytest.mark.parametrize("B", [2, 8])
+@pytest.mark.parametrize("B", [2, 8, 12])
 def test_decode_step_replayed_from_a_captured_graph(tr, B):
     """A device-fed decode step enqueues kernels only (no allocation, no host copy, no memset), so it can be captured into a
     HIP graph. Every replay, with eager work of the same model and synchronisations in between, must give the bits of the
-    eager step it was captured from (2 rows: the streaming kernels; 8 rows: the matrix-core path with its exchange counters)."""
+    eager step it was captured from (2 and 8 rows: all layers in one launch; 12 rows: a launch per product, with exchange counters)."""
     s = synth.TINY.with_(name="graph", dtype=synth.BF16, kv_dtype=synth.BF16, vocab=5003)
     w = synth.make_weights(s, SEED + 41, std=0.05, bias_std=0.05, gain_std=0.1)
     g = tr.Model(s.asdict(), w, B, 1200)
@@ -563,14 +563,16 @@ def test_decode_step_replayed_from_a_captured_graph(tr, B):
             g.seq_truncate(sl, n + 1)
 
 
+@pytest.mark.parametrize("d_model", [256, 248])
 @pytest.mark.parametrize("kv_page", [0, 32])
-def test_one_and_two_row_decode_steps_at_chunk_boundaries(tr, tro, kv_page):
-    """Decode steps of one or two sequences with bf16 weights and cache run the projection and the attention over the cached
-    keys as one kernel, whose partials (chunks of 128 cached keys) the output projection merges with the row's own new key.
+def test_one_and_two_row_decode_steps_at_chunk_boundaries(tr, tro, kv_page, d_model):
+    """Decode steps of one or two sequences with bf16 weights and cache run all layers in one launch or, where a width is no multiple
+    of 32, the projection and the attention over the cached keys as one kernel, whose partials (chunks of 128 cached keys) the output
+    projection merges with the row's own new key.
     Cases: a sequence rolled back to nothing and decoded from position 0 (no cached key at all), one whose cache crosses
     positions 127, 128 and 129 (first chunk filling up, second chunk starting), both in one call (very different contexts)
     and each alone; the same on the paged cache (pages of 32)."""
-    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
+    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16, d_model=d_model)
     w = synth.make_weights(s, SEED + 41, std=0.05, bias_std=0.05, gain_std=0.1)
     g = tr.Model(s.asdict(), w, 2, 300, kv_page=kv_page); o = tro.Model(s.asdict(), w, 2, 300)
     p0 = synth.prompt_tokens(SEED, "qa.p0", 3, s.vocab)

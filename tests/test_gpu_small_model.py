@@ -1,5 +1,5 @@
-"""Small fp32 and bf16 models on the streaming kernels: the head that normalises its own rows and the attention that finishes a row in one
-workgroup, against the oracle at widths, vocabularies and contexts around their limits."""
+"""Small fp32 and bf16 models: the streaming kernels (a head that normalises its own rows, attention that finishes a row in one workgroup) and, up to 4 rows of
+fp32 models of up to 32768 words, the launch over all layers, against the oracle at widths, vocabularies and contexts around their limits."""
 import numpy as np
 import pytest
 
@@ -15,6 +15,7 @@ SEED = 7878
     (520, 4097, 6, 2, synth.F32),      # a second half of columns of one lane; a slice of one row; three heads a group
     (1024, 20000, 5, 1, synth.F32),    # the widest row; slices of 80 rows; five heads a group
     (1032, 4100, 8, 1, synth.F32),     # one column block too wide: a norm of its own
+    (72, 32769, 3, 3, synth.F32),      # one word too many for the launch over all layers: 1 to 4 rows on the streaming kernels
     (256, 28700, 4, 2, synth.BF16),    # slices of the full 128 rows: a norm of its own
     (248, 4099, 4, 2, synth.BF16),
 ])
