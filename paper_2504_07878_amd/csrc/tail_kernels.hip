@@ -309,9 +309,9 @@ __global__ __launch_bounds__(TF_THREADS) void tail_final_kernel(int d, int rh, T
     const int per = (rh + nparts - 1) / nparts, j_lo = part_id * per, j_hi = min(rh, j_lo + per);   // this part's hidden units
 
     // requests first: this thread's slice triple, the router's input row, the first batch of router weights
-    const bool lost = t.given_up && *t.given_up;
     const bool has = part_id == 0 && tid < t.nslices;
     const float4 p0 = part[(size_t)min(tid, t.nslices - 1) * n + i];
+    const int given_up = __hip_atomic_load(t.given_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (a scalar load is waited for at once: 7.1 us a launch without it / 7.2 / 7.5)
     const float *u = t.hidden_tap == 0 ? t.hn + (size_t)i * d : t.x + (size_t)(t.gather ? t.gather[i] : i) * d;
     TRaw8<WT> rw[RQ][2];
     // weight rows j0 + q*TF_WAVES (clamped to the last row), columns k0 + h*512 + lane*8 (clamped to the last 8)
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(TF_THREADS) void tail_final_kernel(int d, int rh, T
     __syncthreads();
     if (tid != 0) return;
     // padding row of a launch sized before the row count was known, or a context that gave a step up: fixed outputs, nothing counted or scattered
-    const bool dead = lost || (t.live && i >= *t.live);
+    const bool dead = (given_up && t.cached) || (t.live && i >= *t.live);
     float conf = 0.f;
     if (part_id == 0) {
         float Ssum = 0.f;

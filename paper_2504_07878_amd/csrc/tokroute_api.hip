@@ -676,7 +676,8 @@ TailArgs tail_args(tr_ctx *ctx, const tr_out *out, int out_offset, int n)
     t.threshold = ctx->threshold; t.route_dir = ctx->c.route_dir; t.mode = ctx->mode; t.hidden_tap = ctx->c.hidden_tap;
     t.policy = ctx->c.route_policy;
     t.rpart = ctx->at<float>(L.tail_rpart); t.rcnt = ctx->at<int>(L.tail_rcnt);
-    t.given_up = L.flow || L.flow32 ? ctx->at<int>(L.given_up) : nullptr;
+    t.given_up = ctx->at<int>(L.given_up);
+    t.cached = 1;
     t.live = ctx->live; t.cand = ctx->cand; t.scatter = ctx->scatter;
     return t;
 }
@@ -1124,7 +1125,7 @@ int tr_tail(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, const tr_o
     t.slot = nullptr;
     t.counters = nullptr;
     t.counter_mode = 0;
-    t.given_up = nullptr;   // (reads no cache)
+    t.cached = 0;
     run_tail(ctx, s, t, const_cast<float *>(x), 0, 0, n, nullptr);   // no partials pending: x is only read
     profile_next_turn(ctx);
     hipError_t e = hipGetLastError();
@@ -1150,7 +1151,7 @@ int tr_tail_noalloc(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, co
     t.slot = nullptr;
     t.counters = nullptr;
     t.counter_mode = 0;
-    t.given_up = nullptr;   // (reads no cache)
+    t.cached = 0;
     t.x = x;
     t.hn = sc + NOALLOC_HN;
     t.part = sc + NOALLOC_PART;

@@ -111,7 +111,8 @@ struct TailArgs {
     const float *r1;         // [n][r1_stride]: sums W1 . hidden of the router's first layer, computed by the LM-head launch (NULL: computed here)
     int r1_stride;
     const int *live;         // device-side row count (see Rows::live); rows from *live on report token -1, score 0, flag 0 and count nothing
-    const int *given_up;     // set: a step of this context was given up, its caches are not to be trusted; every row reports like one from *live on (NULL: cannot happen)
+    const int *given_up;     // set: a step of this context was given up, its caches are not to be trusted; with `cached` every row reports like one from *live on
+    int cached;              // the rows come from the caches
     const int *cand;         // with scatter: index of output i in the caller's candidate list
     int32_t *scatter;        // scatter[cand[i]] = token of live row i (the other model's next-input buffer), or NULL
 };
