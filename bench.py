@@ -401,22 +401,22 @@ def measured_traffic(family):
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on `bench.py --workload counters`, scaled by the 1 GiB copy kernel of the same
 # run (see profiles/); bytes per launch, per kernel family, with the hash of the kernel sources they were taken on.
 TRAFFIC = {
-    "attention": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 20792545, "write_bytes": 1660144},
-    "gateup": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 19564816, "write_bytes": 1245184},
-    "down": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 19300635, "write_bytes": 1376256},
-    "qkv": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 6244112, "write_bytes": 507904},
-    "oproj": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 5437231, "write_bytes": 516096},
-    "prep": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 953887, "write_bytes": 809562},
-    "lmhead": {"source_sha256": "c8b7721c2ce47b21d81984e01c28efb43e42f6dd820d0dbec27b484d61a065d0", "fetch_bytes": 274895631, "write_bytes": 322560},
+    "attention": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 20805876, "write_bytes": 1660144},
+    "gateup": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 19540244, "write_bytes": 1245184},
+    "down": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 19300637, "write_bytes": 1376256},
+    "qkv": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 6226706, "write_bytes": 507904},
+    "oproj": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 5448496, "write_bytes": 516096},
+    "prep": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 953895, "write_bytes": 809562},
+    "lmhead": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 274895650, "write_bytes": 322560},
 }
 
 
 # kernel families of a decode step of the 0.5B-class model at 64 rows: launches per step, and the kernels behind them
 B64_FAMILIES = {"setup": 1, "prep": 25, "qkv": 24, "attention": 24, "oproj": 24, "gateup": 24, "down": 24, "lmhead": 1, "tail_merge": 1}
 B1_FAMILIES = {"setup": 1, "layers": 1, "prep": 1, "lmhead": 1, "tail_merge": 1}
-B1_KERNELS = {"setup": "flow_setup_kernel", "layers": "flow_kernel<1,64>", "prep": "prep_kernel (final norm)", "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
-B64_KERNELS = {"setup": "setup_embed_kernel", "prep": "prep_kernel", "qkv": "gemm_kernel<14,EpiQkv>", "attention": "attn_rows_kernel<64>",
-               "oproj": "gemm_kernel<14,EpiResidualNorm>", "gateup": "gemm22_kernel<28,EpiSwiglu>", "down": "gemm22_kernel<28,EpiPartial>",
+B1_KERNELS = {"setup": "flow_setup_kernel", "layers": "flow_kernel<1,64>", "prep": "prep_kernel (final norm)", "lmhead": "gemm_kernel<2,14,EpiLmHead>", "tail_merge": "tail_final_kernel"}
+B64_KERNELS = {"setup": "setup_embed_kernel", "prep": "prep_kernel", "qkv": "gemm_kernel<2,14,EpiQkv>", "attention": "attn_rows_kernel<64>",
+               "oproj": "gemm_kernel<2,14,EpiResidualNorm>", "gateup": "gemm22_kernel<28,EpiSwiglu>", "down": "gemm22_kernel<28,EpiPartial>",
                "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
 
 

@@ -14,9 +14,9 @@
 // Products: v_mfma_f32_16x16x32_bf16, weights as the tiles of repack_kernel, one wavefront per 16 weight rows. The 16 columns are parts of the fp32
 // activations: 3 bf16 parts (all 24 bits) of up to 4 rows, or hi and lo parts of up to 8 (as in few_kernels.hip). Attention: 3 parts of the query and of the
 // probabilities (hi and middle in columns 0-7 and 8-15, lo in a second product).
-// What bounds it: the hand-overs of a layer, 11 us against 4.3 us for its bytes. 0.5B-class model, a launch per link / here: 1 row after 256 keys 636 / 324 us a step,
-// 7 rows in pages after 100 to 1900 keys 944 / 484, 1 to 8 rows after 16 to 2000 keys 625-926 / 318-507. Error of the hidden rows against 64 bits 6.6e-7 / 6.3e-7 (1 row),
-// 1.6e-5 / 1.4e-5 (8 rows).
+// What bounds it: the hand-overs of a layer, 11 us against 4.3 us for its bytes. 0.5B-class model, a launch per link / here: 1 row after 256 keys 636 / 325 us a step,
+// 7 rows in pages after 100 to 1900 keys 944 / 486, 1 to 8 rows after 16 to 2000 keys 625-926 / 319-510. Error of the hidden rows against 64 bits after 256 keys 1.4e-6 /
+// 1.3e-6 (1 row), 2.5e-5 / 1.3e-6 (4 rows), 2.6e-5 / 2.4e-5 (8 rows).
 #include "flow_common.h"
 #include <algorithm>
 #include <type_traits>
@@ -692,6 +692,9 @@ bool flow_supported(const Dims &D, int wdt, int kdt)
            flow_floats(D, FLOW_MAX_ROWS) < (size_t)1 << 29;
 }
 
+// FLOW_MAX_PARTS is what the buffers are sized for, 12288 cached keys (4096 of 128-wide heads): the launch is still the faster one there. 6 layers of 896 columns, 1 / 2 /
+// 4 / 8 rows after 12200 keys: a launch per link 175 / 221 / 267 / 293 us, here 110 / 122 / 142 / 182; 128-wide heads (768 columns) after 4000 keys 184 / 208 / 242 / 269 and
+// 106 / 114 / 132 / 161; the closest, 3 layers of 256 columns with 16 kv heads, 8 rows after 12200 keys, 298 and 272.
 bool flow_takes(const Dims &D, int R, int max_ctx)
 {
     int U, P;
