@@ -142,8 +142,11 @@ Layout make_layout(const tr_config *c)
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     L.kc = take(L.k_layer_bytes * c->n_layers); L.vc = take(L.v_layer_bytes * c->n_layers);
     L.rope = take((size_t)c->max_seq * (c->head_dim / 2) * sizeof(float2));
-    L.counters = take((size_t)(c->max_batch + 1) * 2 * sizeof(long long));
-    L.given_up = L.counters + (size_t)c->max_batch * 2 * sizeof(long long);   // (the low half of the first word of the last row)
+    // the counters, one more row, and the device-side lengths right behind it: both are read back in one copy
+    const size_t row = 2 * sizeof(long long);
+    L.counters = take((size_t)(c->max_batch + 1) * row + (size_t)c->max_batch * 4);
+    L.given_up = L.counters + (size_t)c->max_batch * row;   // (the low half of the first word of the last row)
+    L.dev_len = L.given_up + row;
     L.slot = take(R * 4); L.tok = take(R * 4); L.pos = take(R * 4); L.gather = take((size_t)c->max_batch * 4); L.out_slot = take((size_t)c->max_batch * 4);
     L.x = take(R * c->d_model * 4); L.q = take(R * qw * 4); L.att = take(R * qw * 4); L.h = take(R * c->d_ffn * 4);
     L.hn = take((size_t)c->max_batch * c->d_model * 4);
@@ -194,7 +197,6 @@ Layout make_layout(const tr_config *c)
     L.qblock = take(R * 4);
     L.pack8 = take((size_t)((c->d_ffn + 31) / 32) * 1024);
     L.kvn = take(2 * 2 * kvw * 4);
-    L.dev_len = take((size_t)c->max_batch * 4);
     L.ss_stride = SS_STRIDE;
     L.sumsq = take((size_t)L.ss_stride * R * 4);
     L.flow = L.mfma && flow_supported(D, c->dtype, c->kv_dtype);
@@ -689,14 +691,15 @@ TailArgs tail_args(tr_ctx *ctx, const tr_out *out, int out_offset, int n)
 static int sync_lengths(tr_ctx *ctx)
 {
     if (!ctx->unsynced) return TR_OK;
-    std::vector<int> dev((size_t)ctx->c.max_batch);
-    int given_up = 0;
-    hipError_t e = hipMemcpyAsync(dev.data(), ctx->ws + ctx->lay.dev_len, dev.size() * 4, hipMemcpyDeviceToHost, ctx->active_stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(&given_up, ctx->ws + ctx->lay.given_up, 4, hipMemcpyDeviceToHost, ctx->active_stream);
+    const Layout &L = ctx->lay;
+    const size_t first = (L.dev_len - L.given_up) / 4, n = (size_t)ctx->c.max_batch;
+    std::vector<int> back(first + n);   // the word of a given-up step, then the lengths
+    hipError_t e = hipMemcpyAsync(back.data(), ctx->ws + L.given_up, back.size() * 4, hipMemcpyDeviceToHost, ctx->active_stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->active_stream);
     if (e != hipSuccess) return fail_hip(ctx, e, "reading back the device-side sequence lengths");
-    if (given_up) return fail(ctx, TR_ERR_HIP, "a step of this context was given up: its caches are undefined");
-    for (size_t b = 0; b < dev.size(); ++b)
+    if (back[0]) return fail(ctx, TR_ERR_HIP, "a step of this context was given up: its caches are undefined");
+    const int *dev = back.data() + first;
+    for (size_t b = 0; b < n; ++b)
         if (ctx->ahead[b] > 0) { ctx->len[b] = dev[b]; ctx->ahead[b] = 0; }
     ctx->unsynced = false;
     return TR_OK;
