@@ -150,6 +150,36 @@ __device__ __forceinline__ float flow_rcp(float x)
     const float r = __builtin_amdgcn_rcpf(x), e = fmaf(-x, r, 1.0f);
     return fmaf(e, r, r);
 }
+// 1 / sqrt(x): the hardware's and one Newton step (below 1 ulp); zeros, subnormals, infinities and NaNs, which the step would spoil, by the definition
+__device__ __forceinline__ float flow_rsqrt(float x)
+{
+    if (!__builtin_amdgcn_classf(x, 0x100)) return 1.0f / sqrtf(x);   // (0x100: positive and normal)
+    const float r = __builtin_amdgcn_rsqf(x), e = fmaf(-x * r, r, 1.0f);
+    return fmaf(0.5f * e, r, r);
+}
+// t / (1 + exp(-t)) of N values. exp(-t) = 2^n 2^f, n the whole number nearest to -t log2 e; the quotient is corrected by its remainder. Gates beyond 80, where a sum or
+// a quotient leaves the normal range, by the definition, so that a saturated gate gives -0.
+// Steps of the 0.5B-class model with expf, divisions and 1 / sqrtf throughout / with these two: 1 row 326.9 / 321.7 us, 7 rows 488.7 / 483.5; SwiGLU's error, gates of
+// -20 to 0, mean 3.1e-8 / 3.2e-8, largest 1.0e-7 / 1.0e-7.
+template <int N> __device__ __forceinline__ void flow_silu(const float (&t)[N], float (&s)[N])
+{
+    float most = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) most = fmaxf(most, fabsf(t[i]));
+    if (!(most < 80.f)) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) s[i] = t[i] / (1.0f + expf(-t[i]));
+        return;
+    }
+    constexpr double LOG2E = 1.4426950408889634074;
+    constexpr float L = (float)LOG2E, L_REST = (float)(LOG2E - (double)L);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const float n = rintf(-t[i] * L), f = fmaf(-t[i], L_REST, fmaf(-t[i], L, -n)), den = 1.0f + ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
+        const float r = __builtin_amdgcn_rcpf(den), q = t[i] * r;
+        s[i] = fmaf(fmaf(-q, den, t[i]), r, q);
+    }
+}
 // an argument that is wanted behind a wait: read before it, not when it is used
 template <class T> __device__ __forceinline__ T flow_now(T v) { asm volatile("" : "+s"(v)); return v; }
 

@@ -14,8 +14,8 @@
 // Products: v_mfma_f32_16x16x32_bf16, weights as the tiles of repack_kernel, one wavefront per 16 weight rows. The 16 columns are parts of the fp32
 // activations: 3 bf16 parts (all 24 bits) of up to 4 rows, or hi and lo parts of up to 8 (as in few_kernels.hip). Attention: 3 parts of the query and of the
 // probabilities (hi and middle in columns 0-7 and 8-15, lo in a second product).
-// What bounds it: the hand-overs of a layer, 11 us against 4.3 us for its bytes. 0.5B-class model, a launch per link / here: 1 row after 256 keys 636 / 325 us a step,
-// 7 rows in pages after 100 to 1900 keys 944 / 486, 1 to 8 rows after 16 to 2000 keys 625-926 / 319-510. Error of the hidden rows against 64 bits after 256 keys 1.4e-6 /
+// What bounds it: the hand-overs of a layer, 11 us against 4.3 us for its bytes. 0.5B-class model, a launch per link / here: 1 row after 256 keys 636 / 322 us a step,
+// 7 rows in pages after 100 to 1900 keys 944 / 483, 1 to 8 rows after 16 to 2000 keys 625-926 / 319-510. Error of the hidden rows against 64 bits after 256 keys 1.4e-6 /
 // 1.3e-6 (1 row), 2.5e-5 / 1.3e-6 (4 rows), 2.6e-5 / 2.4e-5 (8 rows).
 #include "flow_common.h"
 #include <algorithm>
@@ -195,7 +195,7 @@ struct Flow {
     __device__ __forceinline__ float rstd(float inv_d, float eps) const   // of row fm (after the barrier in product)
     {
         const f32x4 t = *reinterpret_cast<const f32x4 *>(&lds.g.ss[fm][0]) + *reinterpret_cast<const f32x4 *>(&lds.g.ss[fm][4]);
-        return 1.0f / sqrtf(fmaf((t.x + t.y) + (t.z + t.w), inv_d, eps));   // (0 where the sum overflows, as in the other kernels)
+        return flow_rsqrt(fmaf((t.x + t.y) + (t.z + t.w), inv_d, eps));   // (0 where the sum overflows, as in the other kernels)
     }
     template <int N> __device__ __forceinline__ void accumulate(f32x4 (&c)[FLOW_UNITS], const uint4 (&w)[FLOW_UNITS][N]) const
     {
@@ -560,12 +560,12 @@ struct Flow {
         const f32x4 v = finish(c);
         if (wave >= NF) return;
         const float rs = rstd(inv_d, eps);
-        float h[4];
+        float t[4], h[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float t = v[e] * rs, up = flow_dpp<0x4e>(v[e]) * rs;   // gate rows: fo 0 and 1, up rows: 2 lanes on
-            h[e] = t / (1.0f + expf(-t)) * up;   // (-0 where the exponential is infinite: flow_rcp is for finite values; the hardware's exponential is off by 2^-24 |t|)
-        }
+        for (int e = 0; e < 4; ++e) t[e] = v[e] * rs;
+        flow_silu(t, h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) h[e] *= flow_dpp<0x4e>(v[e]) * rs;   // gate rows: fo 0 and 1, up rows: 2 lanes on
         // each of the lanes that share a sum stores a part
         uint32_t w0[NP], w1[NP];
 #pragma unroll

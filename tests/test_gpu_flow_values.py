@@ -51,13 +51,14 @@ def test_saturated_gates(rows):
     assert (np.abs(got - want) <= 1e-5 * np.abs(want) + 1e-30).all(), np.abs(got - want).max()
 
 
+@pytest.mark.parametrize("lo,hi", [(-20, 0), (-60, -20), (0, 79.75), (79, 90)])   # (from 80 on another form)
 @pytest.mark.parametrize("rows", [1, 2, 4])
-def test_gates_to_24_bits(rows):
+def test_gates_to_24_bits(rows, lo, hi):
     """Exponential 1 ulp, the sum below the fraction, the division, the product with up and the sum of the parts half a one each: 3 ulp of 1.2e-7."""
-    t = np.resize(bf16_values(-20, 0, 400)[:255], 255)
+    t = np.resize(bf16_values(lo, hi, 400)[:255], 255)
     got, want = gated_step(t, rows)[:, 1:], silu(t)
     off = np.abs(got - want)[:, want != 0] / np.abs(want[want != 0])
-    print(f"{rows} rows: mean {off.mean():.1e} largest {off.max():.1e}")
+    print(f"{rows} rows, gates {lo} to {hi}: mean {off.mean():.1e} largest {off.max():.1e}")
     assert off.max() < 3.6e-7
 
 
