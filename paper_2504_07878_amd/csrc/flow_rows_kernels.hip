@@ -1,0 +1,529 @@
+// All layers of a decode step of 9 to 64 rows in ONE launch (bf16 models of up to 1024 columns, bf16 cache).
+//
+// The tasks, the way outputs are handed on and the order that lets the launch end are those of flow_kernels.hip. What differs is the work of a task: with this many rows a
+// compute unit is bound by the activations it has to fetch (229 KB for 64 rows of 896 columns as hi and lo parts), so a task takes 16 rows (gate and up: 16 or 32) and few
+// weight rows, and the operands need no conversion and no LDS on their way:
+//   * Rows come in groups of 16, the columns of one v_mfma_f32_16x16x32_bf16. A producer leaves its outputs as the hi and lo operand of the next product: 16 bytes a lane,
+//     1 KB a step of 32 columns and part, which a wavefront of the consumer loads straight into the registers the product reads.
+//   * The norms are deferred: what is handed on is x * gain, with the sums of squares of each 16 columns of a row beside it; the consumer scales its sums by 1/rms.
+//   * Nothing is split over workgroups but by rows and features, so no sum is put together by a task of its own: q|k|v 32 features x 16 rows, output projection and FFN output
+//     16 x 16, gate/up 24 or 40 features x 16 or 32 rows. The 8 wavefronts share K and add up through the LDS.
+#include "flow_attention.h"
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+namespace tr {
+
+constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 1024 columns
+constexpr int FR_NSD = 21;     // of the FFN output, per round: 5376 columns
+constexpr int FR_BATCH = 7;    // of these, activations in flight
+constexpr int FR_QU = 2;       // groups of 16 weight rows of a q|k|v task
+
+struct FlowRowsArgs {
+    const char *wt;                   // tiled weights of layer 0
+    size_t wt_stride;                 // bytes from layer to layer
+    uint32_t wt_qkv, wt_o, wt_gu, wt_d;
+    const float *bias; size_t bias_stride;
+    const bf16_t *ln1[FLOW_MAX_LAYERS], *ln2[FLOW_MAX_LAYERS];
+    char *kc, *vc; size_t k_layer, v_layer;   // bytes from layer to layer
+    const int *slot, *pos;
+    const float2 *rope;
+    Dims D;
+    float inv_d;                      // 1 / d
+    int R, U, P;                      // rows; blocks of 32 keys per wavefront; most parts of a row's context
+    int nG16, nPair;                  // groups of 16 rows; of 16 * PAIR rows
+    float *buf;                       // the hand-over buffers, offsets and strides in words of 4 bytes
+    uint32_t buf_bytes;
+    // xa, pa, sa: a layer's input: residual rows, times the norm's gain as operands, sums of squares; x1, p1, s1: the same behind the output projection; q, kvn: query, new
+    // key and value; ap: attention of parts of a context; at: attention; h: FFN activations as operands; out: the last layer's rows
+    uint32_t o_xa, o_pa, o_sa, o_x1, o_p1, o_s1, o_q, o_kvn, o_ap, o_at, o_h, o_out, s_in, s_q, s_kvn, s_ap, s_at, s_h;
+    int nQ, nA, nM, nO, nG, nD;       // tasks of a layer
+    int uG;                           // groups of 8 gate and 8 up rows of a layer
+    int *ticket, *given_up;           // next task; set when a wait was given up
+};
+
+// PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows
+template <int DH, int PAIR, int GU>
+struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
+    static constexpr int MOST = PAIR * GU;
+    union Lds {
+        f32x4 red[FLOW_WAVES][MOST][64];
+        FlowAttentionLds<DH> att;
+    };
+    static_assert(MOST >= FR_QU, "");
+    typedef FlowPiece<u32x4, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
+    const FlowRowsArgs &a;
+    Lds &lds;
+    __amdgpu_buffer_rsrc_t buf;
+    int wave, lane, col, o;
+
+    __device__ __forceinline__ FlowRows(const FlowRowsArgs &args, Lds &l) : a(args), lds(l)
+    {
+        buf = buffer_of(a.buf, a.buf_bytes);
+        wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); lane = threadIdx.x & 63;
+        col = lane & 15; o = lane >> 4;
+    }
+    __device__ __forceinline__ FlowWait wait() const { return FlowWait{a.given_up}; }
+    __device__ __forceinline__ const char *layer(int l) const { return a.wt + (size_t)l * a.wt_stride; }
+
+    struct Share { int s0, ns; };   // a wavefront's steps s0 .. s0 + ns - 1
+    __device__ __forceinline__ Share share(int n32) const
+    {
+        const int s0 = wave * n32 / FLOW_WAVES;
+        return Share{s0, (wave + 1) * n32 / FLOW_WAVES - s0};
+    }
+    // this lane's 16 bytes of a step: row col of a group
+    __device__ __forceinline__ uint32_t row_off(uint32_t tile, uint32_t row, int n32) const { return tile * (uint32_t)n32 * 2048 + (o >> 1) * 1024 + (o & 1) * 512 + row * 16; }
+    __device__ __forceinline__ uint32_t group_off(int unit, int n32) const { return row_off(unit >> 1, 16 * (unit & 1) + col, n32); }
+    template <int N> __device__ __forceinline__ static void weights(uint4 (&w)[N], const char *base, uint32_t off, Share sh)   // past the share: its last step again
+    {
+#pragma unroll
+        for (int s = 0; s < N; ++s) {
+            const char *p = base + (size_t)(sh.s0 + min(s, max(sh.ns, 1) - 1)) * 2048;
+            asm("" : "+s"(p));
+            w[s] = *reinterpret_cast<const uint4 *>(p + off);
+        }
+    }
+    // operands of rows 16 rg .. as a producer left them at `base` (bytes, of this group): steps of the share; rows that do not exist: zeros
+    template <int N> __device__ __forceinline__ void operand_places(FlowPiece<u32x4, N> &x, uint32_t base, int rg, int s0, int ns) const
+    {
+        const bool in = 16 * rg + col < a.R;
+        const uint32_t at = base + s0 * 2048 + lane * 16;
+#pragma unroll
+        for (int i = 0; i < N; ++i) x.off[i] = in && i / 2 < ns ? at + i * 1024 : BUFFER_NOWHERE;
+    }
+    template <int N> __device__ __forceinline__ static void multiply(f32x4 &c, const uint4 *w, const FlowPiece<u32x4, N> &x, int ns)
+    {
+#pragma unroll
+        for (int s = 0; s < N / 2; ++s) {
+            if (s < ns) {   // (uniform)
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[0][2 * s]), c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[0][2 * s + 1]), c, 0, 0, 0);
+            }
+        }
+    }
+    // sums of squares of the rows of a group, left per 16 columns: [tile][row]
+    struct Norm { FlowPiece<uint32_t, FR_NS * 4> ss; };   // (up to 64 tiles, four lanes a row)
+    __device__ __forceinline__ void norm_places(Norm &n, uint32_t base, int rg, bool wanted) const
+    {
+        const int tiles = a.D.d / 16;
+        const bool in = wanted && 16 * rg + col < a.R;
+#pragma unroll
+        for (int i = 0; i < FR_NS * 4; ++i) n.ss.off[i] = in && 4 * i + o < tiles ? base + ((4 * i + o) * 16 + col) * 4 : BUFFER_NOWHERE;
+    }
+    __device__ __forceinline__ static float rstd(const Norm &n, float inv_d, float eps)   // of row col, in all four of its lanes
+    {
+        float s = 0.f;
+#pragma unroll
+        for (int i = 0; i < FR_NS * 4; ++i) s += __uint_as_float(n.ss.v[0][i]);
+        return flow_rsqrt(fmaf(flow_sum4(s), inv_d, eps));
+    }
+    // combination c of a task's sums (16 weight rows x 16 rows), over the wavefronts
+    __device__ __forceinline__ f32x4 sum(int c) const
+    {
+        f32x4 v = lds.red[0][c][lane];
+#pragma unroll
+        for (int w = 1; w < FLOW_WAVES; ++w) v += lds.red[w][c][lane];
+        return v;
+    }
+    // first of the 4 consecutive features that a lane's results of a group of 16 are (tile_feature)
+    __device__ __forceinline__ int feature4(int unit) const { return 16 * unit + 8 * (o & 1) + 4 * (o >> 1); }
+    // bytes of group rg: residual rows and operands (both 64 bytes a column); sums of squares
+    __device__ __forceinline__ uint32_t at_group(uint32_t words, int rg, int K) const { return words * 4 + rg * K * 64; }
+    __device__ __forceinline__ uint32_t at_squares(uint32_t words, int rg) const { return words * 4 + rg * a.D.d * 4; }
+    __device__ __forceinline__ uint32_t at_tile(uint32_t words, int rg, int unit) const { return at_group(words, rg, a.D.d) + unit * 1024 + lane * 16; }   // residual rows: as the products leave them
+    // a layer's rows handed on: residual, operand of the next product, sums of squares
+    __device__ __forceinline__ void leave(uint32_t x, uint32_t p, uint32_t s, int rg, int unit, f32x4 v, uint2 gain) const
+    {
+        float sq = v.x * v.x;
+        sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
+        sq = flow_sum4(sq);
+        if (16 * rg + col >= a.R) return;
+        uint32_t h0, h1, l0, l1;
+        split_hi_lo(v.x * __uint_as_float(gain.x << 16), v.y * __uint_as_float(gain.x & 0xffff0000u), h0, l0);
+        split_hi_lo(v.z * __uint_as_float(gain.y << 16), v.w * __uint_as_float(gain.y & 0xffff0000u), h1, l1);
+        const uint32_t at = at_group(p, rg, a.D.d) + (unit >> 1) * 2048 + ((2 * (unit & 1) + (o & 1)) * 16 + col) * 16 + (o >> 1) * 8;
+        flow_store_pair(buf, at, h0, h1);
+        flow_store_pair(buf, at + 1024, l0, l1);
+        if (o == 0) flow_store(buf, at_squares(s, rg) + (unit * 16 + col) * 4, sq);
+        flow_store(buf, at_tile(x, rg, unit), v);
+    }
+
+    // ---- tasks
+    __device__ __forceinline__ void qkv(int l, int task) const
+    {
+        const int rg = task % a.nG16, u0 = task / a.nG16 * FR_QU, n32 = a.D.d / 32, unit = u0 + min(wave, FR_QU - 1), m = min(16 * rg + col, a.R - 1);
+        const Share sh = share(n32);
+        uint4 w[FR_QU][FR_NS];
+#pragma unroll
+        for (int u = 0; u < FR_QU; ++u) weights(w[u], layer(l) + a.wt_qkv, group_off(u0 + u, n32), sh);
+        const bool fin = wave < FR_QU;
+        const int half = DH / 2, Hq = flow_now(a.D.Hq), Hkv = flow_now(a.D.Hkv);
+        const int f = feature4(unit), tph = DH >> 5, hh = (f >> 5) / tph, j = ((f >> 5) % tph) * 16 + ((f & 31) >> 1);   // rotary pairs j, j + 1 of head hh
+        const int pos = a.pos[m], slot = a.slot[m];
+        const float *bias = a.bias + l * a.bias_stride + hh * DH + j;
+        const float2 ba = *reinterpret_cast<const float2 *>(bias), bb = *reinterpret_cast<const float2 *>(bias + half);
+        const float4 cs = *reinterpret_cast<const float4 *>(a.rope + (size_t)pos * half + j);
+        const KvPlace at = kv_place(a.D, slot, pos);
+        const bool key = hh < Hq + Hkv;
+        const int head = key ? hh - Hq : hh - Hq - Hkv;
+        bf16_t *cache = key ? reinterpret_cast<bf16_t *>(a.kc + (size_t)l * a.k_layer) + k_offset(a.D, at.unit, max(head, 0), at.pos, j)
+                            : reinterpret_cast<bf16_t *>(a.vc + (size_t)l * a.v_layer) + v_offset(a.D, at.unit, max(head, 0), at.pos, j);
+        const uint32_t at_q = (a.o_q + l * a.s_q) * 4 + ((rg * Hq + hh) * 3 * (DH / 8) + (j >> 3)) * 256 + col * 16 + (j & 7) * 2;
+        const uint32_t at_n = (a.o_kvn + l * a.s_kvn) * 4 + ((rg * Hkv + head) * 2 * (DH / 8) + (key ? 0 : DH / 8) + (j >> 3)) * 256 + col * 16 + (j & 7) * 2;
+        const float inv_d = flow_now(a.inv_d), eps = flow_now(a.D.eps);
+        Operands x;
+        Norm n;
+        const uint32_t base = at_group(a.o_pa + l * a.s_in, rg, a.D.d);
+        operand_places(x, base, rg, sh.s0, sh.ns);
+        norm_places(n, at_squares(a.o_sa + l * a.s_in, rg), rg, fin);
+        flow_gate(buf, l > 0 ? at_group(a.o_h + (l - 1) * a.s_h, rg, a.D.F) + task % (a.D.F / 32) * 2048 : base, wait());
+        wait_operands(base, sh.s0, sh.ns, 2);
+        flow_fetch(buf, wait(), x, n.ss);
+#pragma unroll
+        for (int u = 0; u < FR_QU; ++u) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+            multiply(c, w[u], x, sh.ns);
+            lds.red[wave][u][lane] = c;
+        }
+        __syncthreads();
+        if (!fin) return;
+        const float rs = rstd(n, inv_d, eps);
+        const f32x4 v = sum(wave);
+        if (16 * rg + col >= a.R) return;
+        const float a0 = fmaf(v.x, rs, ba.x), b0 = fmaf(v.y, rs, bb.x), a1 = fmaf(v.z, rs, ba.y), b1 = fmaf(v.w, rs, bb.y);
+        float lo0 = a0, hi0 = b0, lo1 = a1, hi1 = b1;
+        if (key) {   // (queries too)
+            lo0 = a0 * cs.x - b0 * cs.y; hi0 = b0 * cs.x + a0 * cs.y;
+            lo1 = a1 * cs.z - b1 * cs.w; hi1 = b1 * cs.z + a1 * cs.w;
+        }
+        if (hh < Hq) {   // three parts of the scaled query
+            const float scale = 1.0f / sqrtf((float)DH);
+            lo0 *= scale; lo1 *= scale; hi0 *= scale; hi1 *= scale;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const uint32_t wl = flow_part(lo0, lo1), wh = flow_part(hi0, hi1);
+                flow_store_pair(buf, at_q + p * DH * 32, wl);
+                flow_store_pair(buf, at_q + p * DH * 32 + half * 32, wh);
+            }
+            return;
+        }
+        const uint32_t plo = flow_part(lo0, lo1), phi = flow_part(hi0, hi1);
+        flow_store_pair(buf, at_n, plo);   // the values that the cache will hold, for this step's attention
+        flow_store_pair(buf, at_n + half * 32, phi);
+        if (key) {
+            *reinterpret_cast<uint32_t *>(cache) = plo;
+            *reinterpret_cast<uint32_t *>(cache + half) = phi;
+        } else {
+            cache[0] = (bf16_t)plo; cache[32] = (bf16_t)(plo >> 16);
+            cache[half * 32] = (bf16_t)phi; cache[half * 32 + 32] = (bf16_t)(phi >> 16);
+        }
+    }
+    // One word of the last part of what each of `per` producers (2: 16 columns each, 4: 8 columns) left of each step; up to 16 steps, 32 with two producers
+    __device__ __forceinline__ void wait_operands(uint32_t base, int s0, int ns, int per) const
+    {
+        FlowPiece<uint32_t, 1> sample;
+        const int s = lane / per, q = lane % per;
+        sample.off[0] = s < ns ? base + (s0 + s) * 2048 + 1024 + q * (1024 / per) : BUFFER_NOWHERE;
+        flow_poll(buf, wait(), sample);
+    }
+
+    // ---- attention: where its input and output lie (bytes): queries, keys and values of 16 rows side by side, 8 dims each; its output row by row
+    __device__ __forceinline__ uint32_t q_at(int l, int r, int head) const { return (a.o_q + l * a.s_q) * 4 + ((r >> 4) * a.D.Hq + head) * 3 * DH * 32 + (r & 15) * 16; }
+    __device__ __forceinline__ uint32_t kvn_at(int l, int r, int g) const { return (a.o_kvn + l * a.s_kvn) * 4 + ((r >> 4) * a.D.Hkv + g) * 2 * DH * 32 + (r & 15) * 16; }
+    __device__ __forceinline__ uint32_t vn_behind() const { return DH * 32; }
+    __device__ __forceinline__ uint32_t plane() const { return a.R * a.D.qw * 2; }
+    __device__ __forceinline__ uint32_t out_of(int l, int r, int g) const { return (a.o_at + l * a.s_at) * 4 + (r * a.D.qw + g * a.D.G * DH) * 2; }
+    __device__ __forceinline__ uint32_t attention_gate(int l, int r) const { return at_group(a.o_pa + l * a.s_in, r >> 4, a.D.d) + r % (a.D.d / 32) * 2048; }
+    __device__ __forceinline__ uint32_t merge_gate(int l, int r) const { return kvn_at(l, r, 0); }
+
+    // x1 = x + Wo . attention
+    __device__ __forceinline__ void oproj(int l, int task) const
+    {
+        const int rg = task % a.nG16, unit = task / a.nG16, n32 = a.D.qw / 32, m = 16 * rg + col;
+        const Share sh = share(n32);
+        uint4 w[FR_NS];
+        weights(w, layer(l) + a.wt_o, group_off(unit, n32), sh);
+        const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln2[l] + feature4(unit));
+        FlowPiece<u32x4, 1> old;
+        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit) : BUFFER_NOWHERE;
+        const uint32_t base = (a.o_at + l * a.s_at) * 4, plane = a.R * a.D.qw * 2;
+        Operands x;
+#pragma unroll
+        for (int i = 0; i < 2 * FR_NS; ++i) x.off[i] = m < a.R && i / 2 < sh.ns ? base + (i & 1) * plane + (m * a.D.qw + 32 * (sh.s0 + i / 2) + 8 * o) * 2 : BUFFER_NOWHERE;
+        // one word of the last part of each row and head of the share (at most four heads)
+        FlowPiece<uint32_t, 1> sample;
+        const int first = 32 * sh.s0, last = 32 * (sh.s0 + max(sh.ns, 1)) - 1, k = max(first, min((first / DH + o) * DH, last)) & ~1;
+        sample.off[0] = m < a.R ? base + plane + (m * a.D.qw + k) * 2 : BUFFER_NOWHERE;
+        const uint32_t out_x = a.o_x1 + l * a.s_in, out_p = a.o_p1 + l * a.s_in, out_s = a.o_s1 + l * a.s_in;
+        flow_gate(buf, (a.o_q + l * a.s_q) * 4 + (rg * a.D.Hq + unit % a.D.Hq) * 3 * DH * 32, wait());
+        flow_poll(buf, wait(), sample);
+        flow_fetch(buf, wait(), x, old);
+        f32x4 c = {0.f, 0.f, 0.f, 0.f};
+        multiply(c, w, x, sh.ns);
+        lds.red[wave][0][lane] = c;
+        __syncthreads();
+        if (wave > 0) return;
+        leave(out_x, out_p, out_s, rg, unit, sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
+    }
+
+    // 8 gate rows and the 8 up rows of the same features in one operand
+    __device__ __forceinline__ void gateup(int l, int task) const
+    {
+        const int rg0 = task % a.nPair * PAIR, u0 = task / a.nPair * GU, n32 = a.D.d / 32;
+        const Share sh = share(n32);
+        uint4 w[GU][FR_NS];
+#pragma unroll
+        for (int u = 0; u < GU; ++u) {   // features 8 t .. + 7 of gate and of up
+            const int t = min(u0 + u, a.uG - 1);
+            weights(w[u], layer(l) + a.wt_gu, row_off(2 * (t >> 2) + (col >> 3), 16 * ((t & 3) >> 1) + 4 * (t & 1) + 8 * ((col >> 2) & 1) + (col & 3), n32), sh);
+        }
+        const float inv_d = flow_now(a.inv_d), eps = flow_now(a.D.eps);
+        const uint32_t base = at_group(a.o_p1 + l * a.s_in, rg0, a.D.d);
+        Operands x[PAIR];
+        Norm n;   // of the rows of group rg0 + wave % PAIR
+#pragma unroll
+        for (int p = 0; p < PAIR; ++p) operand_places(x[p], base + p * a.D.d * 64, rg0 + p, sh.s0, sh.ns);
+        const int mine = rg0 + wave % PAIR;
+        norm_places(n, at_squares(a.o_s1 + l * a.s_in, mine), mine, true);
+        flow_gate(buf, (a.o_at + l * a.s_at) * 4 + (min(16 * rg0 + task % (16 * PAIR), a.R - 1) * a.D.qw) * 2, wait());
+        wait_operands(base, sh.s0, sh.ns, 2);
+        if (PAIR > 1 && rg0 + 1 < a.nG16) wait_operands(base + a.D.d * 64, sh.s0, sh.ns, 2);
+        if constexpr (PAIR > 1) flow_fetch(buf, wait(), x[0], x[1], n.ss);
+        else flow_fetch(buf, wait(), x[0], n.ss);
+#pragma unroll
+        for (int u = 0; u < GU; ++u)
+#pragma unroll
+            for (int p = 0; p < PAIR; ++p) {
+                f32x4 c = {0.f, 0.f, 0.f, 0.f};
+                multiply(c, w[u], x[p], sh.ns);
+                lds.red[wave][u * PAIR + p][lane] = c;
+            }
+        const float rs = rstd(n, inv_d, eps);
+        const uint32_t out = at_group(a.o_h + l * a.s_h, mine, a.D.F) + (o >> 1) * 1024 + col * 16 + (o & 1) * 8;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < (MOST + FLOW_WAVES - 1) / FLOW_WAVES; ++i) {
+            const int c = wave + i * FLOW_WAVES, unit = u0 + c / PAIR;
+            if (c >= MOST || unit >= a.uG) break;   // (uniform)
+            const f32x4 v = sum(c);
+            float t[4], h[4];
+            f32x4 up;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { const FlowTwo two = flow_halves(v[e]); t[e] = two.a * rs; up[e] = two.b * rs; }   // gate rows: lanes 0 to 31, up rows: 32 to 63
+            flow_silu(t, h);
+            uint32_t h0, h1, l0, l1;
+            split_hi_lo(h[0] * up[0], h[1] * up[1], h0, l0);
+            split_hi_lo(h[2] * up[2], h[3] * up[3], h1, l1);
+            if (16 * mine + col < a.R) flow_store_pair(buf, out + (unit >> 2) * 2048 + (unit & 3) * 256, o < 2 ? h0 : l0, o < 2 ? h1 : l1);
+        }
+    }
+
+    // x of the next layer = x1 + Wd . h
+    __device__ __forceinline__ void down(int l, int task) const
+    {
+        const int rg = task % a.nG16, unit = task / a.nG16, n32 = a.D.F / 32, m = 16 * rg + col;
+        const Share sh = share(n32);
+        const char *wbase = layer(l) + a.wt_d;
+        const uint32_t woff = group_off(unit, n32);
+        uint4 w[FR_NSD];
+        weights(w, wbase, woff, sh);
+        const bool last = l == a.D.L - 1;
+        const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln1[last ? l : l + 1] + feature4(unit));
+        const uint32_t base = at_group(a.o_h + l * a.s_h, rg, a.D.F), out = (a.o_out + m * a.D.d + feature4(unit)) * 4;
+        const uint32_t out_x = a.o_xa + (l + 1) * a.s_in, out_p = a.o_pa + (l + 1) * a.s_in, out_s = a.o_sa + (l + 1) * a.s_in;
+        FlowPiece<u32x4, 1> old;
+        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_x1 + l * a.s_in, rg, unit) : BUFFER_NOWHERE;
+        flow_gate(buf, at_group(a.o_p1 + l * a.s_in, rg, a.D.d) + task % (a.D.d / 32) * 2048, wait());
+        f32x4 c = {0.f, 0.f, 0.f, 0.f};
+        for (int done = 0; done < sh.ns; done += FR_NSD) {   // (one round up to 5376 FFN columns)
+            if (done > 0) weights(w, wbase, woff, Share{sh.s0 + done, sh.ns - done});
+            const int ns = min(sh.ns - done, FR_NSD);
+            wait_operands(base, sh.s0 + done, min(ns, 16), 4);
+            if (ns > 16) wait_operands(base, sh.s0 + done + 16, ns - 16, 4);
+#pragma unroll
+            for (int b = 0; b < FR_NSD; b += FR_BATCH) {
+                if (b < ns) {   // (uniform)
+                    FlowPiece<u32x4, 2 * FR_BATCH> x;
+                    operand_places(x, base, rg, sh.s0 + done + b, ns - b);
+                    flow_fetch(buf, wait(), x);
+                    multiply(c, w + b, x, ns - b);
+                }
+            }
+        }
+        lds.red[wave][0][lane] = c;
+        if (wave == 0) flow_fetch(buf, wait(), old);
+        __syncthreads();
+        if (wave > 0) return;
+        const f32x4 v = sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]);
+        if (!last) leave(out_x, out_p, out_s, rg, unit, v, gain);
+        else if (m < a.R) flow_store(buf, out, v);
+    }
+};
+
+template <int DH, int PAIR, int GU>
+__global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_rows_kernel(FlowRowsArgs args)
+{
+    __shared__ typename FlowRows<DH, PAIR, GU>::Lds lds;
+    __shared__ int s_task[2];
+    if (threadIdx.x == 0) s_task[0] = atomicAdd(args.ticket, 1);
+    __syncthreads();
+    for (int it = 0;; it ^= 1) {
+        const int t = __builtin_amdgcn_readfirstlane(s_task[it]);
+        // (the arguments are read again for every task: kept in registers over the loop they would not fit)
+        auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(kernarg));
+        const FlowRowsArgs &a = *(const FlowRowsArgs *)kernarg;
+        const int per_layer = a.nQ + a.nA + a.nM + a.nO + a.nG + a.nD;
+        if (t >= per_layer * a.D.L) break;   // uniform over the workgroup
+        FlowRows<DH, PAIR, GU> f(a, lds);
+        const int l = t / per_layer;
+        int i = t - l * per_layer;
+        if (i < a.nQ) f.qkv(l, i);
+        else if ((i -= a.nQ) < a.nA) f.attention(l, i);
+        else if ((i -= a.nA) < a.nM) { f.merge(l, i); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
+        else if ((i -= a.nM) < a.nO) f.oproj(l, i);
+        else if ((i -= a.nO) < a.nG) f.gateup(l, i);
+        else f.down(l, i - a.nG);
+        // (see flow_kernel)
+        if (threadIdx.x == 64 * (FLOW_WAVES - 1)) s_task[it ^ 1] = atomicAdd(a.ticket, 1);
+        __syncthreads();   // also: the LDS is free for the next task
+    }
+}
+
+// ------------------------------------------------------------------ set-up
+
+struct FlowRowsSetup { int slot[FLOW_ROWS_MAX], tok[FLOW_ROWS_MAX], pos[FLOW_ROWS_MAX]; };
+
+// Row tables and the first layer's input (blocks 0 .. R - 1: a row each), the other hand-over buffers to SENT (the others), task counter to zero
+__global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, int R, int *d_slot, int *d_tok, int *d_pos, const bf16_t *E, const bf16_t *gain, int d, int vocab,
+                                                              const int *dev_tok, char *x, char *pack, char *squares, uint4 *fill, uint32_t n_fill, uint32_t skip, int *ticket)
+{
+    const int b = blockIdx.x;
+    if (b < R) {
+        const int tok = dev_tok ? min(max(dev_tok[b], 0), vocab - 1) : a.tok[b], rg = b >> 4, col = b & 15;
+        if (threadIdx.x == 0) { d_slot[b] = a.slot[b]; d_tok[b] = tok; d_pos[b] = a.pos[b]; }
+        if (b == 0 && threadIdx.x == 0) *ticket = 0;
+        for (int t = threadIdx.x; t < d / 16; t += 256) {   // 16 columns
+            const uint4 *e = reinterpret_cast<const uint4 *>(E + (size_t)tok * d + 16 * t), *gp = reinterpret_cast<const uint4 *>(gain + 16 * t);
+            float sq = 0.f;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 u = e[h], g = gp[h];
+                float v[8], n[8];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t ui = i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w, gi = i == 0 ? g.x : i == 1 ? g.y : i == 2 ? g.z : g.w;
+                    v[2 * i] = __uint_as_float(ui << 16); v[2 * i + 1] = __uint_as_float(ui & 0xffff0000u);
+                    n[2 * i] = v[2 * i] * __uint_as_float(gi << 16); n[2 * i + 1] = v[2 * i + 1] * __uint_as_float(gi & 0xffff0000u);
+                    sq = fmaf(v[2 * i], v[2 * i], sq); sq = fmaf(v[2 * i + 1], v[2 * i + 1], sq);
+                }
+                uint4 hi, lo;
+                split_hi_lo(n, hi, lo);
+                hi = make_uint4(flow_pair(hi.x), flow_pair(hi.y), flow_pair(hi.z), flow_pair(hi.w));
+                lo = make_uint4(flow_pair(lo.x), flow_pair(lo.y), flow_pair(lo.z), flow_pair(lo.w));
+                char *at = pack + (size_t)rg * d * 64 + (t >> 1) * 2048 + ((2 * (t & 1) + h) * 16 + col) * 16;
+                *reinterpret_cast<uint4 *>(at) = hi;
+                *reinterpret_cast<uint4 *>(at + 1024) = lo;
+                char *ax = x + (size_t)rg * d * 64 + t * 1024 + (h * 16 + col) * 16;   // columns 8 h + 4 q: lanes of quarter h + 2 q
+                *reinterpret_cast<float4 *>(ax) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4 *>(ax + 512) = make_float4(v[4], v[5], v[6], v[7]);
+            }
+            reinterpret_cast<uint32_t *>(squares + (size_t)rg * d * 4)[t * 16 + col] = flow_word(sq);
+        }
+        return;
+    }
+    for (uint32_t i = skip + (b - R) * 256 + threadIdx.x; i < n_fill; i += (gridDim.x - R) * 256) fill[i] = make_uint4(SENT, SENT, SENT, SENT);
+}
+
+// ------------------------------------------------------------------ launches
+
+static void flow_rows_split(const Dims &D, int max_ctx, int *U, int *P)
+{
+    const int umax = D.dh == 64 ? 3 : 1, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
+    *P = (blocks + FLOW_WAVES * umax - 1) / (FLOW_WAVES * umax);
+    *U = (blocks + FLOW_WAVES * *P - 1) / (FLOW_WAVES * *P);
+}
+
+// words that the buffers take; *first: the first layer's input, at the front; *filled: what is to be SENT or that
+static size_t flow_rows_layout(const Dims &D, int R, int P, FlowRowsArgs &a, size_t *first, size_t *filled)
+{
+    const size_t rows = (size_t)(R + 15) / 16 * 16;
+    size_t at = 0;
+    auto take = [&](size_t per, int layers, uint32_t &off, uint32_t &stride) {
+        stride = (uint32_t)((per + 31) / 32 * 32); off = (uint32_t)at; at += (size_t)stride * layers;
+    };
+    const size_t x = rows * D.d, in = 2 * x + x / 16;   // residual rows, operands, sums of squares
+    take(in, D.L, a.o_xa, a.s_in); take(in, D.L, a.o_x1, a.s_in);
+    a.o_pa = a.o_xa + (uint32_t)x; a.o_sa = a.o_pa + (uint32_t)x; a.o_p1 = a.o_x1 + (uint32_t)x; a.o_s1 = a.o_p1 + (uint32_t)x;
+    *first = a.s_in;
+    take(rows * D.qw * 3 / 2, D.L, a.o_q, a.s_q);   // three bf16 parts
+    take(rows * D.kvw, D.L, a.o_kvn, a.s_kvn);
+    take((size_t)R * D.qw, D.L, a.o_at, a.s_at);    // hi and lo
+    take(rows * D.F, D.L, a.o_h, a.s_h);
+    take((size_t)R * D.Hq * P * (D.dh + 4), P > 1 ? D.L : 0, a.o_ap, a.s_ap);
+    *filled = at;
+    uint32_t none;
+    take((size_t)R * D.d, 1, a.o_out, none);
+    return at;
+}
+
+size_t flow_rows_floats(const Dims &D, int max_rows)
+{
+    if (max_rows <= FLOW_MAX_ROWS) return 0;
+    size_t first, filled;
+    FlowRowsArgs a;
+    return flow_rows_layout(D, std::min(max_rows, FLOW_ROWS_MAX), FLOW_ROWS_PARTS, a, &first, &filled);
+}
+
+bool flow_rows_takes(const Dims &D, int R, int max_ctx)
+{
+    int U, P;
+    flow_rows_split(D, max_ctx, &U, &P);
+    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && P <= FLOW_ROWS_PARTS && flow_rows_floats(D, R) < (size_t)1 << 29;
+}
+
+void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, int max_ctx, const int *slots, const int *toks, const int *poss,
+                            const int *dev_toks, int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket)
+{
+    FlowRowsArgs a{};
+    size_t first, filled;
+    flow_rows_split(D, max_ctx, &a.U, &a.P);
+    flow_rows_layout(D, R, a.P, a, &first, &filled);
+    FlowRowsSetup su{};
+    for (int i = 0; i < R; ++i) { su.slot[i] = slots[i]; su.tok[i] = toks ? toks[i] : 0; su.pos[i] = poss[i]; }
+    const uint32_t skip = (uint32_t)(first / 4), n_fill = (uint32_t)(filled / 4);   // 16-byte words
+    hipLaunchKernelGGL(flow_rows_setup_kernel, dim3(R + std::min<uint32_t>(2048, (n_fill - skip + 255) / 256)), dim3(256), 0, s, su, R, d_slot, d_tok, d_pos,
+                       (const bf16_t *)tok_emb, (const bf16_t *)gain, D.d, D.V, dev_toks, (char *)(buf + a.o_xa), (char *)(buf + a.o_pa), (char *)(buf + a.o_sa),
+                       reinterpret_cast<uint4 *>(buf), n_fill, skip, ticket);
+}
+
+float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
+{
+    FlowRowsArgs a{};
+    size_t first, filled;
+    flow_rows_split(D, max_ctx, &a.U, &a.P);
+    const size_t n = flow_rows_layout(D, R, a.P, a, &first, &filled);
+    a.wt = m.wt; a.wt_stride = m.wt_stride; a.wt_qkv = (uint32_t)m.wt_qkv; a.wt_o = (uint32_t)m.wt_o; a.wt_gu = (uint32_t)m.wt_gu; a.wt_d = (uint32_t)m.wt_d;
+    a.bias = m.bias; a.bias_stride = m.bias_stride;
+    for (int l = 0; l < D.L; ++l) { a.ln1[l] = (const bf16_t *)m.layers[l].ln1; a.ln2[l] = (const bf16_t *)m.layers[l].ln2; }
+    a.kc = m.kc; a.vc = m.vc; a.k_layer = m.k_layer; a.v_layer = m.v_layer;
+    a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket; a.given_up = given_up;
+    auto go = [&](auto kern, int pair, int gu) {
+        a.nG16 = (R + 15) / 16; a.nPair = (a.nG16 + pair - 1) / pair; a.uG = D.F / 8;
+        a.nQ = (D.qw + 2 * D.kvw) / 16 / FR_QU * a.nG16; a.nA = R * D.Hkv * a.P; a.nM = a.P > 1 ? R * D.Hkv : 0; a.nO = a.nD = D.d / 16 * a.nG16;
+        a.nG = (a.uG + gu - 1) / gu * a.nPair;
+        hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FLOW_WAVES), 0, s, a);
+    };
+    auto rows = [&](auto dh) {
+        constexpr int DH = decltype(dh)::value;
+        if (R <= 16) go(flow_rows_kernel<DH, 1, 3>, 1, 3);
+        else if (R <= 32) go(flow_rows_kernel<DH, 2, 3>, 2, 3);
+        else go(flow_rows_kernel<DH, 2, 5>, 2, 5);
+    };
+    if (D.dh == 64) rows(std::integral_constant<int, 64>{}); else rows(std::integral_constant<int, 128>{});
+    return buf + a.o_out;
+}
+
+}  // namespace tr

@@ -201,7 +201,7 @@ Layout make_layout(const tr_config *c)
     L.sumsq = take((size_t)L.ss_stride * R * 4);
     L.flow = L.mfma && flow_supported(D, c->dtype, c->kv_dtype);
     if (L.flow || L.flow32) {
-        L.flow_buf = take((L.flow ? flow_floats(D, c->max_batch) : flow32_floats(D, c->max_batch)) * 4);
+        L.flow_buf = take((L.flow ? std::max(flow_floats(D, c->max_batch), flow_rows_floats(D, c->max_batch)) : flow32_floats(D, c->max_batch)) * 4);
         L.flow_ticket = take(FLOW_TICKET_INTS * 4);
     }
     L.total = off;
@@ -562,17 +562,24 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
     return pending;
 }
 
-// A decode step of few rows (flow_takes): row set-up, embedding and all layers. Returns the rows of the residual stream; FLOW_KQ partial sums are still to be added.
-float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, float **partials)
+// A decode step of few rows (flow_takes, flow_rows_takes): row set-up, embedding and all layers. Returns the rows of the residual stream; *pending partial sums are
+// still to be added.
+float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, float **partials, int *pending)
 {
     const Layout &L = ctx->lay;
     float *buf = ctx->at<float>(L.flow_buf);
-    int *ticket = ctx->at<int>(L.flow_ticket), *d_slot = ctx->at<int>(L.slot), *d_pos = ctx->at<int>(L.pos);
-    { Bracket br(ctx, s, TR_KERNEL_SETUP); launch_flow_setup(s, ctx->D, ctx->tok_emb, R, max_ctx, slots, toks, poss, dev_toks, d_slot, ctx->at<int>(L.tok), d_pos, buf, ticket); }
+    int *ticket = ctx->at<int>(L.flow_ticket), *given_up = ctx->at<int>(L.given_up), *d_slot = ctx->at<int>(L.slot), *d_tok = ctx->at<int>(L.tok), *d_pos = ctx->at<int>(L.pos);
+    const bool few = R <= FLOW_MAX_ROWS;
+    {
+        Bracket br(ctx, s, TR_KERNEL_SETUP);
+        if (few) launch_flow_setup(s, ctx->D, ctx->tok_emb, R, max_ctx, slots, toks, poss, dev_toks, d_slot, d_tok, d_pos, buf, ticket);
+        else launch_flow_rows_setup(s, ctx->D, ctx->tok_emb, ctx->layers[0].ln1, R, max_ctx, slots, toks, poss, dev_toks, d_slot, d_tok, d_pos, buf, ticket);
+    }
     const FlowModel m{ctx->wt(0, 0), L.wt_layer_stride, L.wt_qkv, L.wt_o, L.wt_gu, L.wt_d, ctx->bias(0), L.bias_stride / 4, ctx->layers.data(),
                       ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
     Bracket br(ctx, s, TR_KERNEL_LAYERS);
-    return launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, ctx->at<int>(L.given_up), partials);
+    *pending = few ? FLOW_KQ : 0;
+    return few ? launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up, partials) : launch_flow_rows(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up);
 }
 
 // The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials part[pending][part_M][d] (rows indexed
@@ -640,9 +647,11 @@ bool run_step_of_few(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *
 {
     const Dims &D = ctx->D;
     const Layout &L = ctx->lay;
-    if (L.flow && flow_takes(D, R, max_ctx)) {
-        float *part = nullptr, *x = run_flow(ctx, s, R, max_ctx, slots, toks, poss, dev_toks, &part);
-        run_tail(ctx, s, t, x, 0, FLOW_KQ, R, part);
+    if (L.flow && (flow_takes(D, R, max_ctx) || flow_rows_takes(D, R, max_ctx))) {
+        float *part = nullptr;
+        int pending;
+        float *x = run_flow(ctx, s, R, max_ctx, slots, toks, poss, dev_toks, &part, &pending);
+        run_tail(ctx, s, t, x, 0, pending, R, part);
         return true;
     }
     if (L.flow32 && flow32_takes(D, R, max_ctx)) {

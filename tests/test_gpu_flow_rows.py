@@ -1,0 +1,103 @@
+"""Decode steps of 9 to 64 rows of a bf16 model in one launch over all layers, against the oracle: groups of 16 rows that are full, short and missing, contexts around the
+blocks of 32 keys and the parts of a context, both head widths, widths that fill no task, FFN columns of several rounds, a paged cache; NaNs must end the step; two steps at once."""
+import numpy as np
+import pytest
+
+from paper_2504_07878_amd import synth
+from parity import compare_outputs
+
+pytestmark = pytest.mark.gpu
+SEED = 7878
+BASE = dict(n_layers=2, n_q_heads=7, n_kv_heads=1, head_dim=64, vocab=1000, router_hidden=40, dtype=synth.BF16, kv_dtype=synth.BF16, d_model=256, d_ffn=704)
+
+
+def bf16(rng, shape):
+    bits = synth.f32_to_bf16_bits(rng.standard_normal(shape, dtype=np.float32))
+    return synth.bf16_bits_to_f32(bits), bits
+
+
+@pytest.mark.parametrize("name,shape,rows,lens,page", [
+    ("nine", {}, 9, [0, 1, 31, 32, 33, 255, 256, 257, 767, 768, 769], 0),
+    ("sixteen", dict(d_model=896, d_ffn=4864, n_q_heads=14, n_kv_heads=2), 16, [255, 256, 257, 511, 40] * 4, 0),
+    ("seventeen", dict(d_ffn=32, n_q_heads=8, n_kv_heads=8), 17, [0, 31, 256, 64, 3] * 4, 32),            # one FFN step; heads of their own keys
+    ("narrow", dict(d_model=32, n_q_heads=2, d_ffn=5408), 32, [0, 31, 32, 255] * 8, 0),                    # FFN columns past one round; one step of columns
+    ("odd_groups", dict(d_model=896, d_ffn=4864, n_q_heads=14, n_kv_heads=2), 37, [64, 100, 1, 513] * 10, 64),
+    ("wide_heads", dict(head_dim=128, n_q_heads=4, n_kv_heads=2, d_ffn=96), 41, [0, 1, 32, 255, 256, 257, 600, 1000] * 6, 0),
+    ("all", dict(d_model=480, d_ffn=1120), 64, [1537, 2300] + [5 * i for i in range(62)], 0),
+])
+def test_steps(name, shape, rows, lens, page):
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name=name, **{**BASE, **shape})
+    w = synth.make_weights(s, SEED + 9, std=0.05, bias_std=0.05, gain_std=0.1)
+    n, max_seq = len(lens), max(lens) + 4
+    g = tr.Model(s.asdict(), w, n, max_seq, kv_page=page)
+    o = tro.Model(s.asdict(), w, n, max_seq)
+    rng = synth.rng(SEED, name)
+    first = synth.prompt_tokens(SEED, "rows.first", n, s.vocab)
+    g.prefill(list(range(n)), [first[i:i + 1] for i in range(n)])
+    o.prefill(list(range(n)), [first[i:i + 1] for i in range(n)])
+    for i, m in enumerate(lens):
+        if m == 0:
+            g.seq_truncate(i, 0); o.seq_truncate(i, 0)
+            continue
+        (kf, kb), (vf, vb) = (bf16(rng, (s.n_layers, s.n_kv_heads, m, s.head_dim)) for _ in range(2))
+        g.load_kv(i, tr.to_device(kb, s.kv_dtype), tr.to_device(vb, s.kv_dtype)); o.load_kv(i, kf, vf)
+    toks = synth.prompt_tokens(SEED, "rows.tok", n, s.vocab).copy()
+    exempt = 0
+    for at in (0, 1):
+        slots = [(7 * at + i) % n for i in range(rows)]
+        go = g.decode_step(slots, toks[slots], want_logits=True).cpu()
+        oo = o.decode_step(slots, toks[slots], want_logits=True)
+        exempt += compare_outputs(go, oo, s.dtype, s.threshold, f"{name} rows {slots}")
+        np.put(toks, slots, oo.token)   # (the second step attends to what the first has appended)
+    assert exempt <= 2
+
+
+@pytest.mark.parametrize("rows", [9, 64])
+def test_nans_end_the_step(rows):
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="nan", **BASE)
+    for key in ("tok_emb", "l0.wk", "l0.wo", "l1.wg", "l1.wd", "l0.ln1"):
+        w = {k: v.copy() for k, v in synth.make_weights(s, SEED + 9, std=0.05).items()}
+        w[key].reshape(-1)[:] = 0xffff   # a negative NaN with every bit set
+        m = tr.Model(s.asdict(), w, 64, 64)
+        rng = synth.rng(SEED, "nan")
+        for b in range(rows):
+            (_, kb), (_, vb) = (bf16(rng, (s.n_layers, s.n_kv_heads, 33, s.head_dim)) for _ in range(2))
+            m.load_kv(b, tr.to_device(kb, s.kv_dtype), tr.to_device(vb, s.kv_dtype))
+        out = m.decode_step(list(range(rows)), np.arange(rows, dtype=np.int32))
+        torch.cuda.synchronize()
+        assert torch.isnan(out.hidden).all(), key
+        m.counters()   # (an error if a wait was given up)
+
+
+def test_steps_of_two_models_at_the_same_time():
+    """Each launch wants every compute unit; neither may depend on having them all."""
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="pair", **{**BASE, **dict(d_model=896, d_ffn=4864, n_q_heads=14, n_kv_heads=2)})
+    rng = synth.rng(SEED, "pair")
+    (_, kb), (_, vb) = (bf16(rng, (s.n_layers, s.n_kv_heads, 900, s.head_dim)) for _ in range(2))
+    models = [tr.Model(s.asdict(), synth.make_weights(s, SEED + i, std=0.05), 64, 1000) for i in range(2)]
+    for m in models:
+        for b in range(64):
+            m.load_kv(b, tr.to_device(kb, s.kv_dtype), tr.to_device(vb, s.kv_dtype))
+            m.seq_truncate(b, 900 - 13 * b)
+    toks = [np.arange(64, dtype=np.int32), np.arange(20, dtype=np.int32)]
+    want, outs = [], [m.outputs(len(t)) for m, t in zip(models, toks)]
+    for m, t, o in zip(models, toks, outs):
+        m.decode_step(list(range(len(t))), t, o)
+        torch.cuda.synchronize()
+        want.append(o.hidden.clone())
+    streams = [torch.cuda.Stream() for _ in models]
+    for _ in range(20):
+        for m, t, o, st in zip(models, toks, outs, streams):
+            for b in range(len(t)):
+                m.seq_truncate(b, 900 - 13 * b)
+            with torch.cuda.stream(st):
+                m.decode_step(list(range(len(t))), t, o)
+    torch.cuda.synchronize()
+    for o, h in zip(outs, want):
+        assert torch.equal(o.hidden, h)
