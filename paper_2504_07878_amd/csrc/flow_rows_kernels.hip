@@ -15,10 +15,13 @@
 
 namespace tr {
 
-constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 1024 columns
-constexpr int FR_NSD = 21;     // of the FFN output, per round: 5376 columns
-constexpr int FR_BATCH = 7;    // of these, activations in flight
+constexpr int FR_W = 8;        // wavefronts of a workgroup
+constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 896 columns
+constexpr int FR_NSO = 4;      // of the output projection: up to 1024
+constexpr int FR_NSD = 20;     // of the FFN output, per round: 5120 columns
+constexpr int FR_BATCH = 10;    // of these, activations in flight
 constexpr int FR_QU = 2;       // groups of 16 weight rows of a q|k|v task
+template <int DH> constexpr int FR_U = DH == 64 ? 3 : 1;   // blocks of 32 keys per wavefront
 
 struct FlowRowsArgs {
     const char *wt;                   // tiled weights of layer 0
@@ -43,16 +46,16 @@ struct FlowRowsArgs {
     int *ticket, *given_up;           // next task; set when a wait was given up
 };
 
-// PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows
-template <int DH, int PAIR, int GU>
-struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
+// PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
+template <int DH, int PAIR, int GU, int DR>
+struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
     static constexpr int MOST = PAIR * GU;
     union Lds {
-        f32x4 red[FLOW_WAVES][MOST][64];
-        FlowAttentionLds<DH> att;
+        struct { f32x4 red[FR_W][MOST][64]; float ss[PAIR][FR_W][16]; } g;
+        FlowAttentionLds<DH, FR_W> att;
     };
     static_assert(MOST >= FR_QU, "");
-    typedef FlowPiece<u32x4, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
+    typedef FlowPiece<u32x4, 1, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
     const FlowRowsArgs &a;
     Lds &lds;
     __amdgpu_buffer_rsrc_t buf;
@@ -70,8 +73,8 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
     struct Share { int s0, ns; };   // a wavefront's steps s0 .. s0 + ns - 1
     __device__ __forceinline__ Share share(int n32) const
     {
-        const int s0 = wave * n32 / FLOW_WAVES;
-        return Share{s0, (wave + 1) * n32 / FLOW_WAVES - s0};
+        const int s0 = wave * n32 / FR_W;
+        return Share{s0, (wave + 1) * n32 / FR_W - s0};
     }
     // this lane's 16 bytes of a step: row col of a group
     __device__ __forceinline__ uint32_t row_off(uint32_t tile, uint32_t row, int n32) const { return tile * (uint32_t)n32 * 2048 + (o >> 1) * 1024 + (o & 1) * 512 + row * 16; }
@@ -85,46 +88,52 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
             w[s] = *reinterpret_cast<const uint4 *>(p + off);
         }
     }
-    // operands of rows 16 rg .. as a producer left them at `base` (bytes, of this group): steps of the share; rows that do not exist: zeros
-    template <int N> __device__ __forceinline__ void operand_places(FlowPiece<u32x4, N> &x, uint32_t base, int rg, int s0, int ns) const
+    // operands of rows 16 rg .. as a producer left them at `base` (bytes, of this group): steps of the share, hi and lo of each (past the share: its last step again); rows
+    // that do not exist: zeros
+    template <int N> __device__ __forceinline__ void operand_places(FlowPiece<u32x4, 1, N> &x, uint32_t base, int rg, int s0, int ns) const
     {
-        const bool in = 16 * rg + col < a.R;
-        const uint32_t at = base + s0 * 2048 + lane * 16;
+        x.off[0] = 16 * rg + col < a.R ? base + s0 * 2048 + lane * 16 : BUFFER_NOWHERE;
 #pragma unroll
-        for (int i = 0; i < N; ++i) x.off[i] = in && i / 2 < ns ? at + i * 1024 : BUFFER_NOWHERE;
+        for (int i = 0; i < N; ++i) x.set[i] = min(i / 2, max(ns, 1) - 1) * 2048 + (i & 1) * 1024;
     }
-    template <int N> __device__ __forceinline__ static void multiply(f32x4 &c, const uint4 *w, const FlowPiece<u32x4, N> &x, int ns)
+    template <int N> __device__ __forceinline__ static void multiply(f32x4 &c, const uint4 *w, const FlowPiece<u32x4, 1, N> &x, int ns)
     {
 #pragma unroll
         for (int s = 0; s < N / 2; ++s) {
             if (s < ns) {   // (uniform)
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[0][2 * s]), c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[0][2 * s + 1]), c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[2 * s][0]), c, 0, 0, 0);
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[s]), __builtin_bit_cast(bf16x8, x.v[2 * s + 1][0]), c, 0, 0, 0);
             }
         }
     }
-    // sums of squares of the rows of a group, left per 16 columns: [tile][row]
-    struct Norm { FlowPiece<uint32_t, FR_NS * 4> ss; };   // (up to 64 tiles, four lanes a row)
-    __device__ __forceinline__ void norm_places(Norm &n, uint32_t base, int rg, bool wanted) const
+    // Sums of squares of the rows of a group, left per 16 columns: [tile][row]. A wavefront brings those of its share, four lanes a row.
+    typedef FlowPiece<uint32_t, FR_NS / 2> Norm;
+    __device__ __forceinline__ void norm_places(Norm &n, uint32_t base, int rg, Share sh) const
     {
-        const int tiles = a.D.d / 16;
-        const bool in = wanted && 16 * rg + col < a.R;
 #pragma unroll
-        for (int i = 0; i < FR_NS * 4; ++i) n.ss.off[i] = in && 4 * i + o < tiles ? base + ((4 * i + o) * 16 + col) * 4 : BUFFER_NOWHERE;
+        for (int i = 0; i < FR_NS / 2; ++i) n.off[i] = 16 * rg + col < a.R && 4 * i + o < 2 * sh.ns ? base + ((2 * sh.s0 + 4 * i + o) * 16 + col) * 4 : BUFFER_NOWHERE;
     }
-    __device__ __forceinline__ static float rstd(const Norm &n, float inv_d, float eps)   // of row col, in all four of its lanes
+    __device__ __forceinline__ void add_squares(const Norm &n, int p) const
     {
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < FR_NS * 4; ++i) s += __uint_as_float(n.ss.v[0][i]);
-        return flow_rsqrt(fmaf(flow_sum4(s), inv_d, eps));
+        for (int i = 0; i < FR_NS / 2; ++i) s += __uint_as_float(n.v[0][i]);
+        s = flow_sum4(s);
+        if (o == 0) lds.g.ss[p][wave][col] = s;
+    }
+    __device__ __forceinline__ float rstd(int p, float inv_d, float eps) const   // of row col (after the barrier)
+    {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < FR_W; ++w) s += lds.g.ss[p][w][col];
+        return flow_rsqrt(fmaf(s, inv_d, eps));
     }
     // combination c of a task's sums (16 weight rows x 16 rows), over the wavefronts
     __device__ __forceinline__ f32x4 sum(int c) const
     {
-        f32x4 v = lds.red[0][c][lane];
+        f32x4 v = lds.g.red[0][c][lane];
 #pragma unroll
-        for (int w = 1; w < FLOW_WAVES; ++w) v += lds.red[w][c][lane];
+        for (int w = 1; w < FR_W; ++w) v += lds.g.red[w][c][lane];
         return v;
     }
     // first of the 4 consecutive features that a lane's results of a group of 16 are (tile_feature)
@@ -132,22 +141,22 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
     // bytes of group rg: residual rows and operands (both 64 bytes a column); sums of squares
     __device__ __forceinline__ uint32_t at_group(uint32_t words, int rg, int K) const { return words * 4 + rg * K * 64; }
     __device__ __forceinline__ uint32_t at_squares(uint32_t words, int rg) const { return words * 4 + rg * a.D.d * 4; }
-    __device__ __forceinline__ uint32_t at_tile(uint32_t words, int rg, int unit) const { return at_group(words, rg, a.D.d) + unit * 1024 + lane * 16; }   // residual rows: as the products leave them
-    // a layer's rows handed on: residual, operand of the next product, sums of squares
-    __device__ __forceinline__ void leave(uint32_t x, uint32_t p, uint32_t s, int rg, int unit, f32x4 v, uint2 gain) const
+    __device__ __forceinline__ uint32_t at_tile(uint32_t words, int rg, int unit, int row) const { return at_group(words, rg, a.D.d) + unit * 1024 + (o * 16 + row) * 16; }   // residual rows: as the products leave them
+    // a layer's rows handed on: residual, operand of the next product, sums of squares; row `row` of group rg, if `on`
+    __device__ __forceinline__ void leave(uint32_t x, uint32_t p, uint32_t s, int rg, int row, bool on, int unit, f32x4 v, uint2 gain) const
     {
         float sq = v.x * v.x;
         sq = fmaf(v.y, v.y, sq); sq = fmaf(v.z, v.z, sq); sq = fmaf(v.w, v.w, sq);
         sq = flow_sum4(sq);
-        if (16 * rg + col >= a.R) return;
+        if (!on) return;
         uint32_t h0, h1, l0, l1;
         split_hi_lo(v.x * __uint_as_float(gain.x << 16), v.y * __uint_as_float(gain.x & 0xffff0000u), h0, l0);
         split_hi_lo(v.z * __uint_as_float(gain.y << 16), v.w * __uint_as_float(gain.y & 0xffff0000u), h1, l1);
-        const uint32_t at = at_group(p, rg, a.D.d) + (unit >> 1) * 2048 + ((2 * (unit & 1) + (o & 1)) * 16 + col) * 16 + (o >> 1) * 8;
+        const uint32_t at = at_group(p, rg, a.D.d) + (unit >> 1) * 2048 + ((2 * (unit & 1) + (o & 1)) * 16 + row) * 16 + (o >> 1) * 8;
         flow_store_pair(buf, at, h0, h1);
         flow_store_pair(buf, at + 1024, l0, l1);
-        if (o == 0) flow_store(buf, at_squares(s, rg) + (unit * 16 + col) * 4, sq);
-        flow_store(buf, at_tile(x, rg, unit), v);
+        if (o == 0) flow_store(buf, at_squares(s, rg) + (unit * 16 + row) * 4, sq);
+        flow_store(buf, at_tile(x, rg, unit, row), v);
     }
 
     // ---- tasks
@@ -177,19 +186,20 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
         Norm n;
         const uint32_t base = at_group(a.o_pa + l * a.s_in, rg, a.D.d);
         operand_places(x, base, rg, sh.s0, sh.ns);
-        norm_places(n, at_squares(a.o_sa + l * a.s_in, rg), rg, fin);
+        norm_places(n, at_squares(a.o_sa + l * a.s_in, rg), rg, sh);
         flow_gate(buf, l > 0 ? at_group(a.o_h + (l - 1) * a.s_h, rg, a.D.F) + task % (a.D.F / 32) * 2048 : base, wait());
         wait_operands(base, sh.s0, sh.ns, 2);
-        flow_fetch(buf, wait(), x, n.ss);
+        flow_fetch(buf, wait(), x, n);
+        add_squares(n, 0);
 #pragma unroll
         for (int u = 0; u < FR_QU; ++u) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             multiply(c, w[u], x, sh.ns);
-            lds.red[wave][u][lane] = c;
+            lds.g.red[wave][u][lane] = c;
         }
         __syncthreads();
         if (!fin) return;
-        const float rs = rstd(n, inv_d, eps);
+        const float rs = rstd(0, inv_d, eps);
         const f32x4 v = sum(wave);
         if (16 * rg + col >= a.R) return;
         const float a0 = fmaf(v.x, rs, ba.x), b0 = fmaf(v.y, rs, bb.x), a1 = fmaf(v.z, rs, ba.y), b1 = fmaf(v.w, rs, bb.y);
@@ -243,29 +253,34 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
     {
         const int rg = task % a.nG16, unit = task / a.nG16, n32 = a.D.qw / 32, m = 16 * rg + col;
         const Share sh = share(n32);
-        uint4 w[FR_NS];
+        uint4 w[FR_NSO];
         weights(w, layer(l) + a.wt_o, group_off(unit, n32), sh);
         const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln2[l] + feature4(unit));
         FlowPiece<u32x4, 1> old;
-        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit) : BUFFER_NOWHERE;
+        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit, col) : BUFFER_NOWHERE;
         const uint32_t base = (a.o_at + l * a.s_at) * 4, plane = a.R * a.D.qw * 2;
-        Operands x;
+        FlowPiece<u32x4, 1, 2 * FR_NSO> x;
+        x.off[0] = m < a.R ? base + (m * a.D.qw + 32 * sh.s0 + 8 * o) * 2 : BUFFER_NOWHERE;
 #pragma unroll
-        for (int i = 0; i < 2 * FR_NS; ++i) x.off[i] = m < a.R && i / 2 < sh.ns ? base + (i & 1) * plane + (m * a.D.qw + 32 * (sh.s0 + i / 2) + 8 * o) * 2 : BUFFER_NOWHERE;
-        // one word of the last part of each row and head of the share (at most four heads)
-        FlowPiece<uint32_t, 1> sample;
-        const int first = 32 * sh.s0, last = 32 * (sh.s0 + max(sh.ns, 1)) - 1, k = max(first, min((first / DH + o) * DH, last)) & ~1;
-        sample.off[0] = m < a.R ? base + plane + (m * a.D.qw + k) * 2 : BUFFER_NOWHERE;
+        for (int i = 0; i < 2 * FR_NSO; ++i) x.set[i] = (i & 1) * plane + min(i / 2, max(sh.ns, 1) - 1) * 64;
+        // one word of the last part of each row and head of the share (at most five heads)
+        FlowPiece<uint32_t, 2> sample;
+        const int first = 32 * sh.s0, last = 32 * (sh.s0 + max(sh.ns, 1)) - 1;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = max(first, min((first / DH + o + 4 * i) * DH, last)) & ~1;
+            sample.off[i] = m < a.R ? base + plane + (m * a.D.qw + k) * 2 : BUFFER_NOWHERE;
+        }
         const uint32_t out_x = a.o_x1 + l * a.s_in, out_p = a.o_p1 + l * a.s_in, out_s = a.o_s1 + l * a.s_in;
         flow_gate(buf, (a.o_q + l * a.s_q) * 4 + (rg * a.D.Hq + unit % a.D.Hq) * 3 * DH * 32, wait());
         flow_poll(buf, wait(), sample);
         flow_fetch(buf, wait(), x, old);
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
         multiply(c, w, x, sh.ns);
-        lds.red[wave][0][lane] = c;
+        lds.g.red[wave][0][lane] = c;
         __syncthreads();
         if (wave > 0) return;
-        leave(out_x, out_p, out_s, rg, unit, sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
+        leave(out_x, out_p, out_s, rg, col, m < a.R, unit, sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
     }
 
     // 8 gate rows and the 8 up rows of the same features in one operand
@@ -282,30 +297,34 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
         const float inv_d = flow_now(a.inv_d), eps = flow_now(a.D.eps);
         const uint32_t base = at_group(a.o_p1 + l * a.s_in, rg0, a.D.d);
         Operands x[PAIR];
-        Norm n;   // of the rows of group rg0 + wave % PAIR
+        Norm n[PAIR];
 #pragma unroll
-        for (int p = 0; p < PAIR; ++p) operand_places(x[p], base + p * a.D.d * 64, rg0 + p, sh.s0, sh.ns);
-        const int mine = rg0 + wave % PAIR;
-        norm_places(n, at_squares(a.o_s1 + l * a.s_in, mine), mine, true);
+        for (int p = 0; p < PAIR; ++p) {
+            operand_places(x[p], base + p * a.D.d * 64, rg0 + p, sh.s0, sh.ns);
+            norm_places(n[p], at_squares(a.o_s1 + l * a.s_in, rg0 + p), rg0 + p, sh);
+        }
+        const int mine = rg0 + wave % PAIR;   // the rows that the wavefront finishes
         flow_gate(buf, (a.o_at + l * a.s_at) * 4 + (min(16 * rg0 + task % (16 * PAIR), a.R - 1) * a.D.qw) * 2, wait());
         wait_operands(base, sh.s0, sh.ns, 2);
         if (PAIR > 1 && rg0 + 1 < a.nG16) wait_operands(base + a.D.d * 64, sh.s0, sh.ns, 2);
-        if constexpr (PAIR > 1) flow_fetch(buf, wait(), x[0], x[1], n.ss);
-        else flow_fetch(buf, wait(), x[0], n.ss);
+        if constexpr (PAIR > 1) flow_fetch(buf, wait(), x[0], x[1], n[0], n[1]);
+        else flow_fetch(buf, wait(), x[0], n[0]);
+#pragma unroll
+        for (int p = 0; p < PAIR; ++p) add_squares(n[p], p);
 #pragma unroll
         for (int u = 0; u < GU; ++u)
 #pragma unroll
             for (int p = 0; p < PAIR; ++p) {
                 f32x4 c = {0.f, 0.f, 0.f, 0.f};
                 multiply(c, w[u], x[p], sh.ns);
-                lds.red[wave][u * PAIR + p][lane] = c;
+                lds.g.red[wave][u * PAIR + p][lane] = c;
             }
-        const float rs = rstd(n, inv_d, eps);
         const uint32_t out = at_group(a.o_h + l * a.s_h, mine, a.D.F) + (o >> 1) * 1024 + col * 16 + (o & 1) * 8;
         __syncthreads();
+        const float rs = rstd(wave % PAIR, inv_d, eps);
 #pragma unroll
-        for (int i = 0; i < (MOST + FLOW_WAVES - 1) / FLOW_WAVES; ++i) {
-            const int c = wave + i * FLOW_WAVES, unit = u0 + c / PAIR;
+        for (int i = 0; i < (MOST + FR_W - 1) / FR_W; ++i) {
+            const int c = wave + i * FR_W, unit = u0 + c / PAIR;
             if (c >= MOST || unit >= a.uG) break;   // (uniform)
             const f32x4 v = sum(c);
             float t[4], h[4];
@@ -320,10 +339,13 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
         }
     }
 
-    // x of the next layer = x1 + Wd . h
-    __device__ __forceinline__ void down(int l, int task) const
+    // x of the next layer = x1 + Wd . h, of 16 rows, or of 8: their hi and lo parts side by side in the 16 columns of one product
+    template <int ROWS> __device__ __forceinline__ void down(int l, int task) const
     {
-        const int rg = task % a.nG16, unit = task / a.nG16, n32 = a.D.F / 32, m = 16 * rg + col;
+        constexpr int PARTS = ROWS / 8, GROUPS = 16 / ROWS, BATCH = ROWS == 16 ? FR_BATCH : FR_NSD;
+        const int n8 = (a.R + ROWS - 1) / ROWS, r0 = task % n8 * ROWS, rg = r0 >> 4, unit = task / n8, n32 = a.D.F / 32;
+        const int row = (r0 & 15) + col % ROWS, m = 16 * rg + row;
+        const bool in = m < a.R;
         const Share sh = share(n32);
         const char *wbase = layer(l) + a.wt_d;
         const uint32_t woff = group_off(unit, n32);
@@ -331,41 +353,50 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU>, DH, 256, 2> {
         weights(w, wbase, woff, sh);
         const bool last = l == a.D.L - 1;
         const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln1[last ? l : l + 1] + feature4(unit));
-        const uint32_t base = at_group(a.o_h + l * a.s_h, rg, a.D.F), out = (a.o_out + m * a.D.d + feature4(unit)) * 4;
+        const uint32_t base = at_group(a.o_h + l * a.s_h, rg, a.D.F) + (r0 & 15) * 16, out = (a.o_out + m * a.D.d + feature4(unit)) * 4;
         const uint32_t out_x = a.o_xa + (l + 1) * a.s_in, out_p = a.o_pa + (l + 1) * a.s_in, out_s = a.o_sa + (l + 1) * a.s_in;
         FlowPiece<u32x4, 1> old;
-        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_x1 + l * a.s_in, rg, unit) : BUFFER_NOWHERE;
+        old.off[0] = in ? at_tile(a.o_x1 + l * a.s_in, rg, unit, row) : BUFFER_NOWHERE;
         flow_gate(buf, at_group(a.o_p1 + l * a.s_in, rg, a.D.d) + task % (a.D.d / 32) * 2048, wait());
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
-        for (int done = 0; done < sh.ns; done += FR_NSD) {   // (one round up to 5376 FFN columns)
+        for (int done = 0; done < sh.ns; done += FR_NSD) {   // (one round up to 5120 FFN columns)
             if (done > 0) weights(w, wbase, woff, Share{sh.s0 + done, sh.ns - done});
             const int ns = min(sh.ns - done, FR_NSD);
-            wait_operands(base, sh.s0 + done, min(ns, 16), 4);
-            if (ns > 16) wait_operands(base, sh.s0 + done + 16, ns - 16, 4);
+            for (int b = 0; b < ns; b += 16) wait_operands(base, sh.s0 + done + b, min(ns - b, 16), 4);
 #pragma unroll
-            for (int b = 0; b < FR_NSD; b += FR_BATCH) {
+            for (int b = 0; b < FR_NSD; b += BATCH) {
                 if (b < ns) {   // (uniform)
-                    FlowPiece<u32x4, 2 * FR_BATCH> x;
-                    operand_places(x, base, rg, sh.s0 + done + b, ns - b);
+                    FlowPiece<u32x4, 1, PARTS * BATCH> x;
+                    const uint32_t at = base + (sh.s0 + done + b) * 2048 + o * 256 + col % ROWS * 16;
+                    x.off[0] = in ? ROWS == 16 ? at : at + (col >> 3) * 1024 : BUFFER_NOWHERE;
+#pragma unroll
+                    for (int i = 0; i < PARTS * BATCH; ++i) x.set[i] = min(i / PARTS, ns - b - 1) * 2048 + i % PARTS * 1024;
                     flow_fetch(buf, wait(), x);
-                    multiply(c, w + b, x, ns - b);
+#pragma unroll
+                    for (int i = 0; i < PARTS * BATCH; ++i)
+                        if (i / PARTS < ns - b) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[b + i / PARTS]), __builtin_bit_cast(bf16x8, x.v[i][0]), c, 0, 0, 0);
                 }
             }
         }
-        lds.red[wave][0][lane] = c;
+        lds.g.red[wave][0][lane] = c;
         if (wave == 0) flow_fetch(buf, wait(), old);
         __syncthreads();
         if (wave > 0) return;
-        const f32x4 v = sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]);
-        if (!last) leave(out_x, out_p, out_s, rg, unit, v, gain);
-        else if (m < a.R) flow_store(buf, out, v);
+        f32x4 v = sum(0);
+        if (GROUPS > 1)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += flow_next<8>(v[e]);
+        v += __builtin_bit_cast(f32x4, old.v[0][0]);
+        const bool on = in && col < ROWS;
+        if (!last) leave(out_x, out_p, out_s, rg, row, on, unit, v, gain);
+        else if (on) flow_store(buf, out, v);
     }
 };
 
-template <int DH, int PAIR, int GU>
-__global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_rows_kernel(FlowRowsArgs args)
+template <int DH, int PAIR, int GU, int DR>
+__global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs args)
 {
-    __shared__ typename FlowRows<DH, PAIR, GU>::Lds lds;
+    __shared__ typename FlowRows<DH, PAIR, GU, DR>::Lds lds;
     __shared__ int s_task[2];
     if (threadIdx.x == 0) s_task[0] = atomicAdd(args.ticket, 1);
     __syncthreads();
@@ -377,7 +408,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_rows_kernel(FlowRowsA
         const FlowRowsArgs &a = *(const FlowRowsArgs *)kernarg;
         const int per_layer = a.nQ + a.nA + a.nM + a.nO + a.nG + a.nD;
         if (t >= per_layer * a.D.L) break;   // uniform over the workgroup
-        FlowRows<DH, PAIR, GU> f(a, lds);
+        FlowRows<DH, PAIR, GU, DR> f(a, lds);
         const int l = t / per_layer;
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
@@ -385,9 +416,9 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_rows_kernel(FlowRowsA
         else if ((i -= a.nA) < a.nM) { f.merge(l, i); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
         else if ((i -= a.nM) < a.nO) f.oproj(l, i);
         else if ((i -= a.nO) < a.nG) f.gateup(l, i);
-        else f.down(l, i - a.nG);
+        else f.template down<DR>(l, i - a.nG);
         // (see flow_kernel)
-        if (threadIdx.x == 64 * (FLOW_WAVES - 1)) s_task[it ^ 1] = atomicAdd(a.ticket, 1);
+        if (threadIdx.x == 64 * (FR_W - 1)) s_task[it ^ 1] = atomicAdd(a.ticket, 1);
         __syncthreads();   // also: the LDS is free for the next task
     }
 }
@@ -441,9 +472,9 @@ __global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, i
 
 static void flow_rows_split(const Dims &D, int max_ctx, int *U, int *P)
 {
-    const int umax = D.dh == 64 ? 3 : 1, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
-    *P = (blocks + FLOW_WAVES * umax - 1) / (FLOW_WAVES * umax);
-    *U = (blocks + FLOW_WAVES * *P - 1) / (FLOW_WAVES * *P);
+    int umax = D.dh == 64 ? FR_U<64> : FR_U<128>; if (getenv("FRU")) umax = atoi(getenv("FRU")); const int blocks = std::max(1, (max_ctx - 1 + 31) / 32);
+    *P = (blocks + FR_W * umax - 1) / (FR_W * umax);
+    *U = (blocks + FR_W * *P - 1) / (FR_W * *P);
 }
 
 // words that the buffers take; *first: the first layer's input, at the front; *filled: what is to be SENT or that
@@ -510,17 +541,17 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
     for (int l = 0; l < D.L; ++l) { a.ln1[l] = (const bf16_t *)m.layers[l].ln1; a.ln2[l] = (const bf16_t *)m.layers[l].ln2; }
     a.kc = m.kc; a.vc = m.vc; a.k_layer = m.k_layer; a.v_layer = m.v_layer;
     a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket; a.given_up = given_up;
-    auto go = [&](auto kern, int pair, int gu) {
+    auto go = [&](auto kern, int pair, int gu, int dr) {
         a.nG16 = (R + 15) / 16; a.nPair = (a.nG16 + pair - 1) / pair; a.uG = D.F / 8;
-        a.nQ = (D.qw + 2 * D.kvw) / 16 / FR_QU * a.nG16; a.nA = R * D.Hkv * a.P; a.nM = a.P > 1 ? R * D.Hkv : 0; a.nO = a.nD = D.d / 16 * a.nG16;
+        a.nQ = (D.qw + 2 * D.kvw) / 16 / FR_QU * a.nG16; a.nA = R * D.Hkv * a.P; a.nM = a.P > 1 ? R * D.Hkv : 0; a.nO = D.d / 16 * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
         a.nG = (a.uG + gu - 1) / gu * a.nPair;
-        hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FLOW_WAVES), 0, s, a);
+        hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FR_W), 0, s, a);
     };
     auto rows = [&](auto dh) {
         constexpr int DH = decltype(dh)::value;
-        if (R <= 16) go(flow_rows_kernel<DH, 1, 3>, 1, 3);
-        else if (R <= 32) go(flow_rows_kernel<DH, 2, 3>, 2, 3);
-        else go(flow_rows_kernel<DH, 2, 5>, 2, 5);
+        if (R <= 16) go(flow_rows_kernel<DH, 1, 4, 8>, 1, 4, 8);
+        else if (R <= 32) go(flow_rows_kernel<DH, 2, 3, 8>, 2, 3, 8);
+        else go(flow_rows_kernel<DH, 2, 5, 16>, 2, 5, 16);
     };
     if (D.dh == 64) rows(std::integral_constant<int, 64>{}); else rows(std::integral_constant<int, 128>{});
     return buf + a.o_out;

@@ -235,7 +235,7 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
 // All layers; returns the rows of the residual stream (in buf), *partials: FLOW_KQ sums to add to them first ([FLOW_KQ][R][d]). *given_up: set if a wait inside was given up
 float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, float **partials);
 // the same for 9 to 64 rows (flow_rows_kernels.hip); gain: of the first layer's first norm; the rows come complete
-constexpr int FLOW_ROWS_MAX = 64, FLOW_ROWS_PARTS = 4;
+constexpr int FLOW_ROWS_MAX = 64, FLOW_ROWS_PARTS = 8;
 size_t flow_rows_floats(const Dims &D, int max_rows);
 bool flow_rows_takes(const Dims &D, int R, int max_ctx);
 void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, int max_ctx, const int *slots, const int *toks, const int *poss,
