@@ -35,14 +35,14 @@ struct FlowAttention {
     // Parts of a row's context: blocks of 32 keys cached before this step, W U to a part
     __device__ __forceinline__ int parts_of(int pos) const { const int n = W * self().a.U; return max(1, ((pos + 31) / 32 + n - 1) / n); }
     // Part c of the keys of one row and kv head: wavefront w takes the blocks W U c + w + W i. The row's own key and value join in the last part, as a block of one.
-    __device__ __forceinline__ void attention(int l, int task) const
+    __device__ __forceinline__ void attention(int l, int r, int g, int c) const
     {
         const F &f = self();
         const auto &a = f.a;
         auto &lds = f.lds;
         const auto buf = f.buf;
         const int wave = f.wave, lane = f.lane, col = f.col, o = f.o;
-        const int r = task / (a.D.Hkv * a.P), g = (task / a.P) % a.D.Hkv, c = task % a.P, G = flow_now(a.D.G);
+        const int G = flow_now(a.D.G);
         const int pos = a.pos[r], slot = a.slot[r], nblk = (pos + 31) / 32, parts = parts_of(pos), b0 = c * W * a.U + wave;
         if (c >= parts) return;   // uniform over the workgroup
         const int ulen = kv_unit_len(a.D), uvts = kv_unit_vts(a.D);
@@ -193,12 +193,12 @@ struct FlowAttention {
         for (int p = 0; p < NP; ++p) { const uint32_t w = flow_part(O0, O1); flow_store_pair(f.buf, at + p * plane, w); }
     }
     // the parts of a row and kv head put together
-    __device__ __forceinline__ void merge(int l, int task) const
+    __device__ __forceinline__ void merge(int l, int r, int g) const
     {
         const F &f = self();
         const auto &a = f.a;
         const auto buf = f.buf;
-        const int r = task / a.D.Hkv, g = task % a.D.Hkv, G = a.D.G, parts = parts_of(a.pos[r]);
+        const int G = a.D.G, parts = parts_of(a.pos[r]);
         if (parts == 1) return;
 #pragma unroll
         for (int i = 0; i < ROUNDS; ++i) {

@@ -87,6 +87,14 @@ __device__ __forceinline__ void flow_gate(__amdgpu_buffer_rsrc_t b, uint32_t off
     }
 }
 
+// until every word has arrived; while they have not, one word of the link before is looked at
+template <class... P> __device__ __forceinline__ void flow_await(__amdgpu_buffer_rsrc_t b, uint32_t gate, FlowWait w, P &...p)
+{
+    if (flow_there<FLOW_SC1>(b, p...)) return;
+    flow_gate(b, gate, w);
+    flow_poll(b, w, p...);
+}
+
 // what is handed on: never SENT
 __device__ __forceinline__ uint32_t flow_word(float v)
 {

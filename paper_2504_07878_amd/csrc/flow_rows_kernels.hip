@@ -6,12 +6,13 @@
 //   * Rows come in groups of 16, the columns of one v_mfma_f32_16x16x32_bf16. A producer leaves its outputs as the hi and lo operand of the next product: 16 bytes a lane,
 //     1 KB a step of 32 columns and part, which a wavefront of the consumer loads straight into the registers the product reads.
 //   * The norms are deferred: what is handed on is x * gain, with the sums of squares of each 16 columns of a row beside it; the consumer scales its sums by 1/rms.
-//   * Nothing is split over workgroups but by rows and features, so no sum is put together by a task of its own: q|k|v 32 features x 16 rows, output projection and FFN output
-//     16 x 16, gate/up 24 or 40 features x 16 or 32 rows. The 8 wavefronts share K and add up through the LDS.
+//   * Nothing is split over workgroups but by rows and features, so no sum is put together by a task of its own: q|k|v 32 features x 16 rows,  The 8 wavefronts share K and add up through the LDS.
 #include "flow_attention.h"
 #include <algorithm>
+#include <numeric>
 #include <type_traits>
 #include <utility>
+#include <vector>
 
 namespace tr {
 
@@ -20,7 +21,7 @@ constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 896 c
 constexpr int FR_NSO = 4;      // of the output projection: up to 1024
 constexpr int FR_NSD = 20;     // of the FFN output, per round: 5120 columns
 constexpr int FR_BATCH = 10;    // of these, activations in flight
-constexpr int FR_QU = 2;       // groups of 16 weight rows of a q|k|v task
+constexpr int FR_OU = 2;       // groups of 16 weight rows of an output projection task
 template <int DH> constexpr int FR_U = DH == 64 ? 3 : 1;   // blocks of 32 keys per wavefront
 
 struct FlowRowsArgs {
@@ -44,17 +45,21 @@ struct FlowRowsArgs {
     int nQ, nA, nM, nO, nG, nD;       // tasks of a layer
     int uG;                           // groups of 8 gate and 8 up rows of a layer
     int *ticket, *given_up;           // next task; set when a wait was given up
+    // the parts of all rows' contexts, row + 256 * part: first parts of the rows, those of several parts first, then the other parts
+    uint32_t part[FLOW_ROWS_MAX * FLOW_ROWS_PARTS];
 };
+static_assert(sizeof(FlowRowsArgs) <= 4096, "kernel arguments");
 
-// PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
-template <int DH, int PAIR, int GU, int DR>
-struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
+// QU: groups of 16 weight rows of a q|k|v task; PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
+template <int DH, int QU, int PAIR, int GU, int DR>
+struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
     static constexpr int MOST = PAIR * GU;
     union Lds {
         struct { f32x4 red[FR_W][MOST][64]; float ss[PAIR][FR_W][16]; } g;
         FlowAttentionLds<DH, FR_W> att;
     };
-    static_assert(MOST >= FR_QU, "");
+    static_assert(FR_W % PAIR == 0, "");
+    static_assert(MOST >= QU && MOST >= FR_OU, "");
     typedef FlowPiece<u32x4, 1, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
     const FlowRowsArgs &a;
     Lds &lds;
@@ -162,12 +167,12 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
     // ---- tasks
     __device__ __forceinline__ void qkv(int l, int task) const
     {
-        const int rg = task % a.nG16, u0 = task / a.nG16 * FR_QU, n32 = a.D.d / 32, unit = u0 + min(wave, FR_QU - 1), m = min(16 * rg + col, a.R - 1);
+        const int rg = task % a.nG16, u0 = task / a.nG16 * QU, n32 = a.D.d / 32, unit = u0 + min(wave, QU - 1), m = min(16 * rg + col, a.R - 1);
         const Share sh = share(n32);
-        uint4 w[FR_QU][FR_NS];
+        uint4 w[QU][FR_NS];
 #pragma unroll
-        for (int u = 0; u < FR_QU; ++u) weights(w[u], layer(l) + a.wt_qkv, group_off(u0 + u, n32), sh);
-        const bool fin = wave < FR_QU;
+        for (int u = 0; u < QU; ++u) weights(w[u], layer(l) + a.wt_qkv, group_off(u0 + u, n32), sh);
+        const bool fin = wave < QU;
         const int half = DH / 2, Hq = flow_now(a.D.Hq), Hkv = flow_now(a.D.Hkv);
         const int f = feature4(unit), tph = DH >> 5, hh = (f >> 5) / tph, j = ((f >> 5) % tph) * 16 + ((f & 31) >> 1);   // rotary pairs j, j + 1 of head hh
         const int pos = a.pos[m], slot = a.slot[m];
@@ -187,12 +192,13 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
         const uint32_t base = at_group(a.o_pa + l * a.s_in, rg, a.D.d);
         operand_places(x, base, rg, sh.s0, sh.ns);
         norm_places(n, at_squares(a.o_sa + l * a.s_in, rg), rg, sh);
-        flow_gate(buf, l > 0 ? at_group(a.o_h + (l - 1) * a.s_h, rg, a.D.F) + task % (a.D.F / 32) * 2048 : base, wait());
-        wait_operands(base, sh.s0, sh.ns, 2);
+        Sample sample;
+        sample_rows(sample, base, sh, 1, 0);
+        flow_await(buf, l > 0 ? at_group(a.o_h + (l - 1) * a.s_h, rg, a.D.F) + task % (a.D.F / 32) * 2048 : base, wait(), sample);
         flow_fetch(buf, wait(), x, n);
         add_squares(n, 0);
 #pragma unroll
-        for (int u = 0; u < FR_QU; ++u) {
+        for (int u = 0; u < QU; ++u) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             multiply(c, w[u], x, sh.ns);
             lds.g.red[wave][u][lane] = c;
@@ -230,13 +236,23 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
             cache[half * 32] = (bf16_t)phi; cache[half * 32 + 32] = (bf16_t)(phi >> 16);
         }
     }
-    // One word of the last part of what each of `per` producers (2: 16 columns each, 4: 8 columns) left of each step; up to 16 steps, 32 with two producers
-    __device__ __forceinline__ void wait_operands(uint32_t base, int s0, int ns, int per) const
+    // One word of the last part of what each producer left of a share: 16 columns each (the rows' operands; `groups` of 16 rows, `stride` bytes apart) ..
+    typedef FlowPiece<uint32_t, 1> Sample;
+    __device__ __forceinline__ void sample_rows(Sample &x, uint32_t base, Share sh, int groups, uint32_t stride) const
     {
-        FlowPiece<uint32_t, 1> sample;
-        const int s = lane / per, q = lane % per;
-        sample.off[0] = s < ns ? base + (s0 + s) * 2048 + 1024 + q * (1024 / per) : BUFFER_NOWHERE;
-        flow_poll(buf, wait(), sample);
+        static_assert(2 * FR_NS * PAIR <= 64, "");
+        const int p = lane / (2 * FR_NS), s = lane / 2 % FR_NS;
+        x.off[0] = p < groups && s < sh.ns ? base + p * stride + (sh.s0 + s) * 2048 + 1024 + (lane & 1) * 512 : BUFFER_NOWHERE;
+    }
+    // .. or 8 columns each (FFN activations)
+    static constexpr int HS = (4 * FR_NSD + 63) / 64;
+    __device__ __forceinline__ void sample_ffn(FlowPiece<uint32_t, HS> &x, uint32_t base, Share sh) const
+    {
+#pragma unroll
+        for (int i = 0; i < HS; ++i) {
+            const int s = lane / 4 + 16 * i;
+            x.off[i] = s < min(sh.ns, FR_NSD) ? base + (sh.s0 + s) * 2048 + 1024 + (lane & 3) * 256 : BUFFER_NOWHERE;
+        }
     }
 
     // ---- attention: where its input and output lie (bytes): queries, keys and values of 16 rows side by side, 8 dims each; its output row by row
@@ -251,13 +267,14 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
     // x1 = x + Wo . attention
     __device__ __forceinline__ void oproj(int l, int task) const
     {
-        const int rg = task % a.nG16, unit = task / a.nG16, n32 = a.D.qw / 32, m = 16 * rg + col;
+        const int rg = task % a.nG16, u0 = task / a.nG16 * FR_OU, unit = u0 + min(wave, FR_OU - 1), n32 = a.D.qw / 32, m = 16 * rg + col;
         const Share sh = share(n32);
-        uint4 w[FR_NSO];
-        weights(w, layer(l) + a.wt_o, group_off(unit, n32), sh);
+        uint4 w[FR_OU][FR_NSO];
+#pragma unroll
+        for (int u = 0; u < FR_OU; ++u) weights(w[u], layer(l) + a.wt_o, group_off(u0 + u, n32), sh);
         const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln2[l] + feature4(unit));
         FlowPiece<u32x4, 1> old;
-        old.off[0] = wave == 0 && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit, col) : BUFFER_NOWHERE;
+        old.off[0] = wave < FR_OU && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit, col) : BUFFER_NOWHERE;
         const uint32_t base = (a.o_at + l * a.s_at) * 4, plane = a.R * a.D.qw * 2;
         FlowPiece<u32x4, 1, 2 * FR_NSO> x;
         x.off[0] = m < a.R ? base + (m * a.D.qw + 32 * sh.s0 + 8 * o) * 2 : BUFFER_NOWHERE;
@@ -272,15 +289,17 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
             sample.off[i] = m < a.R ? base + plane + (m * a.D.qw + k) * 2 : BUFFER_NOWHERE;
         }
         const uint32_t out_x = a.o_x1 + l * a.s_in, out_p = a.o_p1 + l * a.s_in, out_s = a.o_s1 + l * a.s_in;
-        flow_gate(buf, (a.o_q + l * a.s_q) * 4 + (rg * a.D.Hq + unit % a.D.Hq) * 3 * DH * 32, wait());
-        flow_poll(buf, wait(), sample);
+        flow_await(buf, (a.o_q + l * a.s_q) * 4 + (rg * a.D.Hq + unit % a.D.Hq) * 3 * DH * 32, wait(), sample);
         flow_fetch(buf, wait(), x, old);
-        f32x4 c = {0.f, 0.f, 0.f, 0.f};
-        multiply(c, w, x, sh.ns);
-        lds.g.red[wave][0][lane] = c;
+#pragma unroll
+        for (int u = 0; u < FR_OU; ++u) {
+            f32x4 c = {0.f, 0.f, 0.f, 0.f};
+            multiply(c, w[u], x, sh.ns);
+            lds.g.red[wave][u][lane] = c;
+        }
         __syncthreads();
-        if (wave > 0) return;
-        leave(out_x, out_p, out_s, rg, col, m < a.R, unit, sum(0) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
+        if (wave >= FR_OU) return;
+        leave(out_x, out_p, out_s, rg, col, m < a.R, unit, sum(wave) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
     }
 
     // 8 gate rows and the 8 up rows of the same features in one operand
@@ -304,9 +323,9 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
             norm_places(n[p], at_squares(a.o_s1 + l * a.s_in, rg0 + p), rg0 + p, sh);
         }
         const int mine = rg0 + wave % PAIR;   // the rows that the wavefront finishes
-        flow_gate(buf, (a.o_at + l * a.s_at) * 4 + (min(16 * rg0 + task % (16 * PAIR), a.R - 1) * a.D.qw) * 2, wait());
-        wait_operands(base, sh.s0, sh.ns, 2);
-        if (PAIR > 1 && rg0 + 1 < a.nG16) wait_operands(base + a.D.d * 64, sh.s0, sh.ns, 2);
+        Sample sample;
+        sample_rows(sample, base, sh, min(PAIR, a.nG16 - rg0), a.D.d * 64);
+        flow_await(buf, (a.o_at + l * a.s_at) * 4 + (min(16 * rg0 + task % (16 * PAIR), a.R - 1) * a.D.qw) * 2, wait(), sample);
         if constexpr (PAIR > 1) flow_fetch(buf, wait(), x[0], x[1], n[0], n[1]);
         else flow_fetch(buf, wait(), x[0], n[0]);
 #pragma unroll
@@ -356,13 +375,15 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
         const uint32_t base = at_group(a.o_h + l * a.s_h, rg, a.D.F) + (r0 & 15) * 16, out = (a.o_out + m * a.D.d + feature4(unit)) * 4;
         const uint32_t out_x = a.o_xa + (l + 1) * a.s_in, out_p = a.o_pa + (l + 1) * a.s_in, out_s = a.o_sa + (l + 1) * a.s_in;
         FlowPiece<u32x4, 1> old;
-        old.off[0] = in ? at_tile(a.o_x1 + l * a.s_in, rg, unit, row) : BUFFER_NOWHERE;
-        flow_gate(buf, at_group(a.o_p1 + l * a.s_in, rg, a.D.d) + task % (a.D.d / 32) * 2048, wait());
+        old.off[0] = wave == 0 && in ? at_tile(a.o_x1 + l * a.s_in, rg, unit, row) : BUFFER_NOWHERE;
+        const uint32_t gate = at_group(a.o_p1 + l * a.s_in, rg, a.D.d) + task % (a.D.d / 32) * 2048;
         f32x4 c = {0.f, 0.f, 0.f, 0.f};
-        for (int done = 0; done < sh.ns; done += FR_NSD) {   // (one round up to 5120 FFN columns)
+        for (int done = 0; done == 0 || done < sh.ns; done += FR_NSD) {   // (one round up to 5120 FFN columns)
             if (done > 0) weights(w, wbase, woff, Share{sh.s0 + done, sh.ns - done});
             const int ns = min(sh.ns - done, FR_NSD);
-            for (int b = 0; b < ns; b += 16) wait_operands(base, sh.s0 + done + b, min(ns - b, 16), 4);
+            FlowPiece<uint32_t, HS> sample;
+            sample_ffn(sample, base, Share{sh.s0 + done, ns});
+            flow_await(buf, gate, wait(), sample, old);
 #pragma unroll
             for (int b = 0; b < FR_NSD; b += BATCH) {
                 if (b < ns) {   // (uniform)
@@ -379,7 +400,6 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
             }
         }
         lds.g.red[wave][0][lane] = c;
-        if (wave == 0) flow_fetch(buf, wait(), old);
         __syncthreads();
         if (wave > 0) return;
         f32x4 v = sum(0);
@@ -393,10 +413,10 @@ struct FlowRows : FlowAttention<FlowRows<DH, PAIR, GU, DR>, DH, 256, 2, FR_W, FR
     }
 };
 
-template <int DH, int PAIR, int GU, int DR>
+template <int DH, int QU, int PAIR, int GU, int DR>
 __global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs args)
 {
-    __shared__ typename FlowRows<DH, PAIR, GU, DR>::Lds lds;
+    __shared__ typename FlowRows<DH, QU, PAIR, GU, DR>::Lds lds;
     __shared__ int s_task[2];
     if (threadIdx.x == 0) s_task[0] = atomicAdd(args.ticket, 1);
     __syncthreads();
@@ -408,12 +428,12 @@ __global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs ar
         const FlowRowsArgs &a = *(const FlowRowsArgs *)kernarg;
         const int per_layer = a.nQ + a.nA + a.nM + a.nO + a.nG + a.nD;
         if (t >= per_layer * a.D.L) break;   // uniform over the workgroup
-        FlowRows<DH, PAIR, GU, DR> f(a, lds);
+        FlowRows<DH, QU, PAIR, GU, DR> f(a, lds);
         const int l = t / per_layer;
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
-        else if ((i -= a.nQ) < a.nA) f.attention(l, i);
-        else if ((i -= a.nA) < a.nM) { f.merge(l, i); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
+        else if ((i -= a.nQ) < a.nA) { const uint32_t p = a.part[i / a.D.Hkv]; f.attention(l, p & 0xff, i % a.D.Hkv, p >> 8); }
+        else if ((i -= a.nA) < a.nM) { f.merge(l, a.part[i / a.D.Hkv] & 0xff, i % a.D.Hkv); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
         else if ((i -= a.nM) < a.nO) f.oproj(l, i);
         else if ((i -= a.nO) < a.nG) f.gateup(l, i);
         else f.template down<DR>(l, i - a.nG);
@@ -530,7 +550,7 @@ void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, c
                        reinterpret_cast<uint4 *>(buf), n_fill, skip, ticket);
 }
 
-float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
+float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
 {
     FlowRowsArgs a{};
     size_t first, filled;
@@ -541,17 +561,28 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
     for (int l = 0; l < D.L; ++l) { a.ln1[l] = (const bf16_t *)m.layers[l].ln1; a.ln2[l] = (const bf16_t *)m.layers[l].ln2; }
     a.kc = m.kc; a.vc = m.vc; a.k_layer = m.k_layer; a.v_layer = m.v_layer;
     a.slot = d_slot; a.pos = d_pos; a.rope = m.rope; a.D = D; a.inv_d = 1.0f / (float)D.d; a.R = R; a.buf = buf; a.buf_bytes = (uint32_t)(n * 4); a.ticket = ticket; a.given_up = given_up;
-    auto go = [&](auto kern, int pair, int gu, int dr) {
+    int n_parts = 0, n_split = 0;
+    {
+        std::vector<int> rows(R);
+        std::iota(rows.begin(), rows.end(), 0);
+        std::stable_sort(rows.begin(), rows.end(), [&](int i, int j) { return poss[i] > poss[j]; });
+        const int per = 32 * FR_W * a.U;   // keys of a part
+        for (int c = 0; c < a.P; ++c)
+            for (int r : rows)
+                if (c == 0 || poss[r] > c * per) a.part[n_parts++] = r + 256 * c;
+        for (int r : rows) n_split += poss[r] > per;
+    }
+    auto go = [&](auto kern, int qu, int pair, int gu, int dr) {
         a.nG16 = (R + 15) / 16; a.nPair = (a.nG16 + pair - 1) / pair; a.uG = D.F / 8;
-        a.nQ = (D.qw + 2 * D.kvw) / 16 / FR_QU * a.nG16; a.nA = R * D.Hkv * a.P; a.nM = a.P > 1 ? R * D.Hkv : 0; a.nO = D.d / 16 * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
+        a.nQ = (D.qw + 2 * D.kvw) / 16 / qu * a.nG16; a.nA = n_parts * D.Hkv; a.nM = n_split * D.Hkv; a.nO = D.d / 16 / FR_OU * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
         a.nG = (a.uG + gu - 1) / gu * a.nPair;
         hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FR_W), 0, s, a);
     };
     auto rows = [&](auto dh) {
         constexpr int DH = decltype(dh)::value;
-        if (R <= 16) go(flow_rows_kernel<DH, 1, 4, 8>, 1, 4, 8);
-        else if (R <= 32) go(flow_rows_kernel<DH, 2, 3, 8>, 2, 3, 8);
-        else go(flow_rows_kernel<DH, 2, 5, 16>, 2, 5, 16);
+        if (R <= 16) go(flow_rows_kernel<DH, 2, 1, 5, 8>, 2, 1, 5, 8);
+        else if (R <= 32) go(flow_rows_kernel<DH, 2, 2, 6, 16>, 2, 2, 6, 16);
+        else go(flow_rows_kernel<DH, 4, 4, 4, 16>, 4, 4, 4, 16);
     };
     if (D.dh == 64) rows(std::integral_constant<int, 64>{}); else rows(std::integral_constant<int, 128>{});
     return buf + a.o_out;

@@ -579,7 +579,7 @@ float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots
                       ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
     Bracket br(ctx, s, TR_KERNEL_LAYERS);
     *pending = few ? FLOW_KQ : 0;
-    return few ? launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up, partials) : launch_flow_rows(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up);
+    return few ? launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up, partials) : launch_flow_rows(s, ctx->D, m, R, max_ctx, poss, d_slot, d_pos, buf, ticket, given_up);
 }
 
 // The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials part[pending][part_M][d] (rows indexed
