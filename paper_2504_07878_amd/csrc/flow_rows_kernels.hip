@@ -58,7 +58,7 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W
         struct { f32x4 red[FR_W][MOST][64]; float ss[PAIR][FR_W][16]; } g;
         FlowAttentionLds<DH, FR_W> att;
     };
-    static_assert(FR_W % PAIR == 0, "");
+    static_assert(PAIR == 1 || PAIR == 2, "");
     static_assert(MOST >= QU && MOST >= FR_OU, "");
     typedef FlowPiece<u32x4, 1, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
     const FlowRowsArgs &a;
@@ -326,7 +326,7 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W
         Sample sample;
         sample_rows(sample, base, sh, min(PAIR, a.nG16 - rg0), a.D.d * 64);
         flow_await(buf, (a.o_at + l * a.s_at) * 4 + (min(16 * rg0 + task % (16 * PAIR), a.R - 1) * a.D.qw) * 2, wait(), sample);
-        if constexpr (PAIR > 1) flow_fetch(buf, wait(), x[0], x[1], n[0], n[1]);
+        if constexpr (PAIR == 2) flow_fetch(buf, wait(), x[0], x[1], n[0], n[1]);
         else flow_fetch(buf, wait(), x[0], n[0]);
 #pragma unroll
         for (int p = 0; p < PAIR; ++p) add_squares(n[p], p);
@@ -492,7 +492,7 @@ __global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, i
 
 static void flow_rows_split(const Dims &D, int max_ctx, int *U, int *P)
 {
-    int umax = D.dh == 64 ? FR_U<64> : FR_U<128>; if (getenv("FRU")) umax = atoi(getenv("FRU")); const int blocks = std::max(1, (max_ctx - 1 + 31) / 32);
+    const int umax = D.dh == 64 ? FR_U<64> : FR_U<128>, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
     *P = (blocks + FR_W * umax - 1) / (FR_W * umax);
     *U = (blocks + FR_W * *P - 1) / (FR_W * *P);
 }
@@ -580,9 +580,9 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
     };
     auto rows = [&](auto dh) {
         constexpr int DH = decltype(dh)::value;
-        if (R <= 16) go(flow_rows_kernel<DH, 2, 1, 5, 8>, 2, 1, 5, 8);
+        if (R <= 16) go(flow_rows_kernel<DH, 1, 1, 5, 8>, 1, 1, 5, 8);
         else if (R <= 32) go(flow_rows_kernel<DH, 2, 2, 6, 16>, 2, 2, 6, 16);
-        else go(flow_rows_kernel<DH, 4, 4, 4, 16>, 4, 4, 4, 16);
+        else go(flow_rows_kernel<DH, 4, 2, 5, 16>, 4, 2, 5, 16);
     };
     if (D.dh == 64) rows(std::integral_constant<int, 64>{}); else rows(std::integral_constant<int, 128>{});
     return buf + a.o_out;
