@@ -21,7 +21,6 @@ constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 896 c
 constexpr int FR_NSO = 4;      // of the output projection: up to 1024
 constexpr int FR_NSD = 20;     // of the FFN output, per round: 5120 columns
 constexpr int FR_BATCH = 10;    // of these, activations in flight
-constexpr int FR_OU = 2;       // groups of 16 weight rows of an output projection task
 template <int DH> constexpr int FR_U = DH == 64 ? 3 : 1;   // blocks of 32 keys per wavefront
 
 struct FlowRowsArgs {
@@ -46,20 +45,20 @@ struct FlowRowsArgs {
     int uG;                           // groups of 8 gate and 8 up rows of a layer
     int *ticket, *given_up;           // next task; set when a wait was given up
     // the parts of all rows' contexts, row + 256 * part: first parts of the rows, those of several parts first, then the other parts
-    uint32_t part[FLOW_ROWS_MAX * FLOW_ROWS_PARTS];
+    uint32_t part[FLOW_ROWS_PARTS];
 };
 static_assert(sizeof(FlowRowsArgs) <= 4096, "kernel arguments");
 
-// QU: groups of 16 weight rows of a q|k|v task; PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
-template <int DH, int QU, int PAIR, int GU, int DR>
-struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
+// QU, OU: groups of 16 weight rows of a q|k|v and of an output projection task; PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
+template <int DH, int QU, int OU, int PAIR, int GU, int DR>
+struct FlowRows : FlowAttention<FlowRows<DH, QU, OU, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
     static constexpr int MOST = PAIR * GU;
     union Lds {
         struct { f32x4 red[FR_W][MOST][64]; float ss[PAIR][FR_W][16]; } g;
         FlowAttentionLds<DH, FR_W> att;
     };
     static_assert(PAIR == 1 || PAIR == 2, "");
-    static_assert(MOST >= QU && MOST >= FR_OU, "");
+    static_assert(MOST >= QU && MOST >= OU, "");
     typedef FlowPiece<u32x4, 1, 2 * FR_NS> Operands;          // a wavefront's steps of one group of rows, hi and lo
     const FlowRowsArgs &a;
     Lds &lds;
@@ -267,14 +266,14 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W
     // x1 = x + Wo . attention
     __device__ __forceinline__ void oproj(int l, int task) const
     {
-        const int rg = task % a.nG16, u0 = task / a.nG16 * FR_OU, unit = u0 + min(wave, FR_OU - 1), n32 = a.D.qw / 32, m = 16 * rg + col;
+        const int rg = task % a.nG16, u0 = task / a.nG16 * OU, nU = a.D.d / 16, unit = min(u0 + min(wave, OU - 1), nU - 1), n32 = a.D.qw / 32, m = 16 * rg + col;
         const Share sh = share(n32);
-        uint4 w[FR_OU][FR_NSO];
+        uint4 w[OU][FR_NSO];
 #pragma unroll
-        for (int u = 0; u < FR_OU; ++u) weights(w[u], layer(l) + a.wt_o, group_off(u0 + u, n32), sh);
+        for (int u = 0; u < OU; ++u) weights(w[u], layer(l) + a.wt_o, group_off(min(u0 + u, nU - 1), n32), sh);
         const uint2 gain = *reinterpret_cast<const uint2 *>(a.ln2[l] + feature4(unit));
         FlowPiece<u32x4, 1> old;
-        old.off[0] = wave < FR_OU && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit, col) : BUFFER_NOWHERE;
+        old.off[0] = wave < OU && m < a.R ? at_tile(a.o_xa + l * a.s_in, rg, unit, col) : BUFFER_NOWHERE;
         const uint32_t base = (a.o_at + l * a.s_at) * 4, plane = a.R * a.D.qw * 2;
         FlowPiece<u32x4, 1, 2 * FR_NSO> x;
         x.off[0] = m < a.R ? base + (m * a.D.qw + 32 * sh.s0 + 8 * o) * 2 : BUFFER_NOWHERE;
@@ -292,13 +291,13 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W
         flow_await(buf, (a.o_q + l * a.s_q) * 4 + (rg * a.D.Hq + unit % a.D.Hq) * 3 * DH * 32, wait(), sample);
         flow_fetch(buf, wait(), x, old);
 #pragma unroll
-        for (int u = 0; u < FR_OU; ++u) {
+        for (int u = 0; u < OU; ++u) {
             f32x4 c = {0.f, 0.f, 0.f, 0.f};
             multiply(c, w[u], x, sh.ns);
             lds.g.red[wave][u][lane] = c;
         }
         __syncthreads();
-        if (wave >= FR_OU) return;
+        if (wave >= OU || u0 + wave >= nU) return;
         leave(out_x, out_p, out_s, rg, col, m < a.R, unit, sum(wave) + __builtin_bit_cast(f32x4, old.v[0][0]), gain);
     }
 
@@ -413,10 +412,10 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, PAIR, GU, DR>, DH, 256, 2, FR_W
     }
 };
 
-template <int DH, int QU, int PAIR, int GU, int DR>
+template <int DH, int QU, int OU, int PAIR, int GU, int DR>
 __global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs args)
 {
-    __shared__ typename FlowRows<DH, QU, PAIR, GU, DR>::Lds lds;
+    __shared__ typename FlowRows<DH, QU, OU, PAIR, GU, DR>::Lds lds;
     __shared__ int s_task[2];
     if (threadIdx.x == 0) s_task[0] = atomicAdd(args.ticket, 1);
     __syncthreads();
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs ar
         const FlowRowsArgs &a = *(const FlowRowsArgs *)kernarg;
         const int per_layer = a.nQ + a.nA + a.nM + a.nO + a.nG + a.nD;
         if (t >= per_layer * a.D.L) break;   // uniform over the workgroup
-        FlowRows<DH, QU, PAIR, GU, DR> f(a, lds);
+        FlowRows<DH, QU, OU, PAIR, GU, DR> f(a, lds);
         const int l = t / per_layer;
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
@@ -490,11 +489,22 @@ __global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, i
 
 // ------------------------------------------------------------------ launches
 
-static void flow_rows_split(const Dims &D, int max_ctx, int *U, int *P)
+// parts of a context of `pos` cached keys, U blocks of 32 keys to a wavefront
+static int flow_rows_parts(int pos, int U) { return std::max(1, (pos + 32 * FR_W * U - 1) / (32 * FR_W * U)); }
+static int flow_rows_most(int R) { return FLOW_ROWS_PARTS / R; }
+
+// The smallest parts that make no more tasks than can be under way while their queries are computed; false: more parts than there is room for. Blocks per wavefront 1 / 2 / 3:
+// 16 rows after 100 to 1900 keys 542 / 512 / 540 us a step, 32 rows after 128 to 1024 616 / 590 / 594, 64 rows 834 / 765 / 771.
+static bool flow_rows_split(const Dims &D, int R, const int *poss, int *U, int *P)
 {
-    const int umax = D.dh == 64 ? FR_U<64> : FR_U<128>, blocks = std::max(1, (max_ctx - 1 + 31) / 32);
-    *P = (blocks + FR_W * umax - 1) / (FR_W * umax);
-    *U = (blocks + FR_W * *P - 1) / (FR_W * *P);
+    const int umax = D.dh == 64 ? FR_U<64> : FR_U<128>, longest = *std::max_element(poss, poss + R);
+    for (*U = 1;; ++*U) {
+        *P = flow_rows_parts(longest, *U);
+        int tasks = 0;
+        for (int r = 0; r < R; ++r) tasks += flow_rows_parts(poss[r], *U) * D.Hkv;
+        if (*P <= flow_rows_most(R) && (tasks <= (R <= 32 ? 128 : 256) || *U == umax || *P == 1)) return true;
+        if (*U == umax) return false;
+    }
 }
 
 // words that the buffers take; *first: the first layer's input, at the front; *filled: what is to be SENT or that
@@ -525,22 +535,23 @@ size_t flow_rows_floats(const Dims &D, int max_rows)
     if (max_rows <= FLOW_MAX_ROWS) return 0;
     size_t first, filled;
     FlowRowsArgs a;
-    return flow_rows_layout(D, std::min(max_rows, FLOW_ROWS_MAX), FLOW_ROWS_PARTS, a, &first, &filled);
+    size_t most = 0;
+    for (int R = FLOW_MAX_ROWS + 1; R <= std::min(max_rows, FLOW_ROWS_MAX); ++R) most = std::max(most, flow_rows_layout(D, R, flow_rows_most(R), a, &first, &filled));
+    return most;
 }
 
-bool flow_rows_takes(const Dims &D, int R, int max_ctx)
+bool flow_rows_takes(const Dims &D, int R, const int *poss)
 {
     int U, P;
-    flow_rows_split(D, max_ctx, &U, &P);
-    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && P <= FLOW_ROWS_PARTS && flow_rows_floats(D, R) < (size_t)1 << 29;
+    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && flow_rows_split(D, R, poss, &U, &P) && flow_rows_floats(D, R) < (size_t)1 << 29;
 }
 
-void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, int max_ctx, const int *slots, const int *toks, const int *poss,
+void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,
                             const int *dev_toks, int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket)
 {
     FlowRowsArgs a{};
     size_t first, filled;
-    flow_rows_split(D, max_ctx, &a.U, &a.P);
+    flow_rows_split(D, R, poss, &a.U, &a.P);
     flow_rows_layout(D, R, a.P, a, &first, &filled);
     FlowRowsSetup su{};
     for (int i = 0; i < R; ++i) { su.slot[i] = slots[i]; su.tok[i] = toks ? toks[i] : 0; su.pos[i] = poss[i]; }
@@ -550,11 +561,11 @@ void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, c
                        reinterpret_cast<uint4 *>(buf), n_fill, skip, ticket);
 }
 
-float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
+float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
 {
     FlowRowsArgs a{};
     size_t first, filled;
-    flow_rows_split(D, max_ctx, &a.U, &a.P);
+    flow_rows_split(D, R, poss, &a.U, &a.P);
     const size_t n = flow_rows_layout(D, R, a.P, a, &first, &filled);
     a.wt = m.wt; a.wt_stride = m.wt_stride; a.wt_qkv = (uint32_t)m.wt_qkv; a.wt_o = (uint32_t)m.wt_o; a.wt_gu = (uint32_t)m.wt_gu; a.wt_d = (uint32_t)m.wt_d;
     a.bias = m.bias; a.bias_stride = m.bias_stride;
@@ -566,23 +577,22 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
         std::vector<int> rows(R);
         std::iota(rows.begin(), rows.end(), 0);
         std::stable_sort(rows.begin(), rows.end(), [&](int i, int j) { return poss[i] > poss[j]; });
-        const int per = 32 * FR_W * a.U;   // keys of a part
         for (int c = 0; c < a.P; ++c)
             for (int r : rows)
-                if (c == 0 || poss[r] > c * per) a.part[n_parts++] = r + 256 * c;
-        for (int r : rows) n_split += poss[r] > per;
+                if (c < flow_rows_parts(poss[r], a.U)) a.part[n_parts++] = r + 256 * c;
+        for (int r : rows) n_split += flow_rows_parts(poss[r], a.U) > 1;
     }
-    auto go = [&](auto kern, int qu, int pair, int gu, int dr) {
+    auto go = [&](auto kern, int qu, int ou, int pair, int gu, int dr) {
         a.nG16 = (R + 15) / 16; a.nPair = (a.nG16 + pair - 1) / pair; a.uG = D.F / 8;
-        a.nQ = (D.qw + 2 * D.kvw) / 16 / qu * a.nG16; a.nA = n_parts * D.Hkv; a.nM = n_split * D.Hkv; a.nO = D.d / 16 / FR_OU * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
+        a.nQ = (D.qw + 2 * D.kvw) / 16 / qu * a.nG16; a.nA = n_parts * D.Hkv; a.nM = n_split * D.Hkv; a.nO = (D.d / 16 + ou - 1) / ou * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
         a.nG = (a.uG + gu - 1) / gu * a.nPair;
         hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FR_W), 0, s, a);
     };
     auto rows = [&](auto dh) {
         constexpr int DH = decltype(dh)::value;
-        if (R <= 16) go(flow_rows_kernel<DH, 1, 1, 5, 8>, 1, 1, 5, 8);
-        else if (R <= 32) go(flow_rows_kernel<DH, 2, 2, 6, 16>, 2, 2, 6, 16);
-        else go(flow_rows_kernel<DH, 4, 2, 5, 16>, 4, 2, 5, 16);
+        if (R <= 16) go(flow_rows_kernel<DH, 1, 2, 1, 5, 8>, 1, 2, 1, 5, 8);
+        else if (R <= 32) go(flow_rows_kernel<DH, 2, 2, 2, 5, 16>, 2, 2, 2, 5, 16);
+        else go(flow_rows_kernel<DH, 4, 4, 2, 6, 16>, 4, 4, 2, 6, 16);
     };
     if (D.dh == 64) rows(std::integral_constant<int, 64>{}); else rows(std::integral_constant<int, 128>{});
     return buf + a.o_out;
