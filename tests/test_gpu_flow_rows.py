@@ -3,6 +3,7 @@ blocks of 32 keys and the parts of a context, both head widths, widths that fill
 import numpy as np
 import pytest
 
+import exact
 from paper_2504_07878_amd import synth
 from parity import compare_outputs
 
@@ -101,3 +102,53 @@ def test_steps_of_two_models_at_the_same_time():
     torch.cuda.synchronize()
     for o, h in zip(outs, want):
         assert torch.equal(o.hidden, h)
+
+
+@pytest.mark.parametrize("rows", [9, 16, 31, 48, 64])
+@pytest.mark.parametrize("shape", [dict(d_model=896, n_q_heads=14, n_kv_heads=2, d_ffn=4864), dict(d_model=128, n_q_heads=8, n_kv_heads=8, d_ffn=96, head_dim=128)])
+def test_steps_against_64_bits(shape, rows):
+    """One layer over given keys. hi + lo activations (exact.REL, exact.WORST); a new key or value that the cache's type rounds the other way weighs at most 1/60 of a row."""
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="exact", **{**BASE, **dict(n_layers=1, vocab=500, router_hidden=0), **shape})
+    w = exact.weights(s, SEED)
+    lens = [60 + 41 * i % 700 for i in range(rows)]
+    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, 64, 800)
+    gen = torch.Generator().manual_seed(SEED)
+    caches = [tuple(torch.empty((1, s.n_kv_heads, n, s.head_dim)).normal_(generator=gen).bfloat16() for _ in range(2)) for n in lens]
+    for b, (k, v) in enumerate(caches):
+        g.load_kv(b, k.cuda(), v.cuda())
+    toks = synth.prompt_tokens(SEED, "rows.exact", rows, s.vocab)
+    ref = exact.forward(s, w, [[t] for t in toks], [(k.double(), v.double()) for k, v in caches])
+    out = g.decode_step(list(range(rows)), toks, want_logits=True).cpu()
+    d, worst = exact.distance(out.hidden, ref[0])
+    print(f"{shape['d_model']} columns {rows} rows: {d:.2e} of the norm, largest {worst:.2e} of the rms")
+    assert d < exact.REL and worst < exact.WORST
+
+
+def test_catch_up_rows_over_contexts_in_parts():
+    """Segments of two tokens keep the launch of attention by rows whose contexts are split over workgroups: every repetition has the same bits."""
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    import torch
+    s = synth.TINY.with_(name="parts", **BASE)
+    w = synth.make_weights(s, SEED + 9, std=0.05)
+    lens = [1990, 800, 1500, 33] + [769 + i for i in range(20)]
+    n = len(lens)
+    g, o = tr.Model(s.asdict(), w, 64, 2000), tro.Model(s.asdict(), w, n, 2000)
+    rng = synth.rng(SEED, "parts")
+    (kf, kb), (vf, vb) = (bf16(rng, (s.n_layers, s.n_kv_heads, 1990, s.head_dim)) for _ in range(2))
+    for b, m in enumerate(lens):
+        g.load_kv(b, *(tr.to_device(np.ascontiguousarray(c[:, :, :m]), s.kv_dtype) for c in (kb, vb)))
+        o.load_kv(b, *(np.ascontiguousarray(c[:, :, :m]) for c in (kf, vf)))
+    segs = [synth.prompt_tokens(SEED, f"parts.{b}", 2, s.vocab) for b in range(n)]
+    want, first = o.extend(list(range(n)), segs, want_logits=True), None
+    for _ in range(100):
+        out = g.extend(list(range(n)), segs, want_logits=True)
+        got = out.logits.clone()
+        for b, m in enumerate(lens):
+            g.seq_truncate(b, m)
+        if first is None:
+            assert compare_outputs(out.cpu(), want, s.dtype, s.threshold, "parts") <= 1
+            first = got
+        assert torch.equal(got, first)
