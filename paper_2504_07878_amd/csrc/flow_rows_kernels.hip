@@ -6,7 +6,10 @@
 //   * Rows come in groups of 16, the columns of one v_mfma_f32_16x16x32_bf16. A producer leaves its outputs as the hi and lo operand of the next product: 16 bytes a lane,
 //     1 KB a step of 32 columns and part, which a wavefront of the consumer loads straight into the registers the product reads.
 //   * The norms are deferred: what is handed on is x * gain, with the sums of squares of each 16 columns of a row beside it; the consumer scales its sums by 1/rms.
-//   * Nothing is split over workgroups but by rows and features, so no sum is put together by a task of its own: q|k|v 32 features x 16 rows,  The 8 wavefronts share K and add up through the LDS.
+//   * Work is split over workgroups by rows and features alone, so no sum is put together by a task of its own: the 8 wavefronts of a task share K and add up through the LDS.
+//     Only long contexts are split (flow_rows_split), merged by tasks of their own.
+// What bounds it: five or six hand-overs a layer and the rows that each task brings from the L2; 64 rows take 28 us a layer where their bytes take 10 at the copy rate.
+// 0.5B-class model, a launch per link / here: 64 rows after 128 to 1024 keys 1132 / 763 us a step.
 #include "flow_attention.h"
 #include <algorithm>
 #include <numeric>
@@ -17,7 +20,7 @@
 namespace tr {
 
 constexpr int FR_W = 8;        // wavefronts of a workgroup
-constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 896 columns
+constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 1024 columns
 constexpr int FR_NSO = 4;      // of the output projection: up to 1024
 constexpr int FR_NSD = 20;     // of the FFN output, per round: 5120 columns
 constexpr int FR_BATCH = 10;    // of these, activations in flight
@@ -493,16 +496,21 @@ __global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, i
 static int flow_rows_parts(int pos, int U) { return std::max(1, (pos + 32 * FR_W * U - 1) / (32 * FR_W * U)); }
 static int flow_rows_most(int R) { return FLOW_ROWS_PARTS / R; }
 
-// The smallest parts that make no more tasks than can be under way while their queries are computed; false: more parts than there is room for. Blocks per wavefront 1 / 2 / 3:
-// 16 rows after 100 to 1900 keys 542 / 512 / 540 us a step, 32 rows after 128 to 1024 616 / 590 / 594, 64 rows 834 / 765 / 771.
+// One part of every context where the registers hold the longest (768 keys; 256 of 128-wide heads): a part and its merge cost more than the blocks that they save. Against the
+// rule below, which splits from 257 keys on: 16 rows after 200 to 600 keys 476 us a step and 490, 32 after 128 to 700 559 and 577, 64 after 128 to 512 709 and 744.
+// Else the smallest parts that make no more tasks than can be under way while their queries are computed; false: more parts than there is room for. Blocks per wavefront
+// 1 / 2 / 3: 16 rows after 100 to 1900 keys 542 / 512 / 540 us, 32 rows after 128 to 1024 616 / 590 / 594, 64 rows 834 / 765 / 771.
 static bool flow_rows_split(const Dims &D, int R, const int *poss, int *U, int *P)
 {
     const int umax = D.dh == 64 ? FR_U<64> : FR_U<128>, longest = *std::max_element(poss, poss + R);
+    *P = 1;
+    for (*U = 1; *U <= umax; ++*U)
+        if (flow_rows_parts(longest, *U) == 1) return true;
     for (*U = 1;; ++*U) {
         *P = flow_rows_parts(longest, *U);
         int tasks = 0;
         for (int r = 0; r < R; ++r) tasks += flow_rows_parts(poss[r], *U) * D.Hkv;
-        if (*P <= flow_rows_most(R) && (tasks <= (R <= 32 ? 128 : 256) || *U == umax || *P == 1)) return true;
+        if (*P <= flow_rows_most(R) && (tasks <= (R <= 32 ? 128 : 256) || *U == umax)) return true;
         if (*U == umax) return false;
     }
 }
