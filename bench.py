@@ -390,7 +390,7 @@ def measured_traffic(family):
     if not t:
         return None
     h = hashlib.sha256()
-    for name in ("mfma_kernels.hip", "mfma_common.h", "tr_internal.h"):
+    for name in ("mfma_kernels.hip", "mfma_common.h", "flow_rows_kernels.hip", "flow_attention.h", "flow_common.h", "tr_internal.h"):
         path = os.path.join(ROOT, "paper_2504_07878_amd", "csrc", name)
         if not os.path.exists(path):
             return None
@@ -401,32 +401,25 @@ def measured_traffic(family):
 # rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE on `bench.py --workload counters`, scaled by the 1 GiB copy kernel of the same
 # run (see profiles/); bytes per launch, per kernel family, with the hash of the kernel sources they were taken on.
 TRAFFIC = {
-    "attention": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 20805876, "write_bytes": 1660144},
-    "gateup": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 19540244, "write_bytes": 1245184},
-    "down": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 19300637, "write_bytes": 1376256},
-    "qkv": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 6226706, "write_bytes": 507904},
-    "oproj": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 5448496, "write_bytes": 516096},
-    "prep": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 953895, "write_bytes": 809562},
-    "lmhead": {"source_sha256": "fd17a91fc30be46cc728dd6259f293b2aebf7f65961d7ea6ad40eef068769359", "fetch_bytes": 274895650, "write_bytes": 322560},
+    # all 24 layers: 12 times the launch of the 2-layer model
+    "layers": {"source_sha256": "66116eeb3d8d15e79902f0a68a20d49b198f95fa93dd7d3e027afc10588cde3c", "fetch_bytes": 2554624784, "write_bytes": 80240640},
+    "lmhead": {"source_sha256": "66116eeb3d8d15e79902f0a68a20d49b198f95fa93dd7d3e027afc10588cde3c", "fetch_bytes": 274890407, "write_bytes": 322560},
 }
 
 
 # kernel families of a decode step of the 0.5B-class model at 64 rows: launches per step, and the kernels behind them
-B64_FAMILIES = {"setup": 1, "prep": 25, "qkv": 24, "attention": 24, "oproj": 24, "gateup": 24, "down": 24, "lmhead": 1, "tail_merge": 1}
+B64_FAMILIES = {"setup": 1, "layers": 1, "prep": 1, "lmhead": 1, "tail_merge": 1}
 B1_FAMILIES = {"setup": 1, "layers": 1, "prep": 1, "lmhead": 1, "tail_merge": 1}
 B1_KERNELS = {"setup": "flow_setup_kernel", "layers": "flow_kernel<1,64>", "prep": "prep_kernel (final norm)", "lmhead": "gemm_kernel<2,14,EpiLmHead>", "tail_merge": "tail_final_kernel"}
-B64_KERNELS = {"setup": "setup_embed_kernel", "prep": "prep_kernel", "qkv": "gemm_kernel<2,14,EpiQkv>", "attention": "attn_rows_kernel<64>",
-               "oproj": "gemm_kernel<2,14,EpiResidualNorm>", "gateup": "gemm22_kernel<28,EpiSwiglu>", "down": "gemm22_kernel<28,EpiPartial>",
-               "lmhead": "gemm22_kernel<28,EpiLmHead>", "tail_merge": "tail_final_kernel"}
+B64_KERNELS = {"setup": "flow_rows_setup_kernel", "layers": "flow_rows_kernel<64,4,4,2,6,16>", "prep": "prep_kernel (final norm)", "lmhead": "gemm22_kernel<28,EpiLmHead>",
+               "tail_merge": "tail_final_kernel"}
 
 
 def family_bytes(s, rows, attention_bytes):
     """Algorithmic bytes of ONE launch of each kernel family: each weight matrix once, each sequence's keys and values of one
     layer once (attention_bytes, given), new keys/values written; activations count as on-chip (0 for the kernels that only move them)."""
     d, qw, kvw, F = s.d_model, s.n_q_heads * s.head_dim, s.n_kv_heads * s.head_dim, s.d_ffn
-    return {"setup": 0, "prep": 0, "tail_merge": 0,
-            "qkv": 2 * (qw + 2 * kvw) * d + rows * 2 * kvw * 2, "attention": attention_bytes, "oproj": 2 * d * qw,
-            "gateup": 2 * 2 * F * d, "down": 2 * d * F, "lmhead": 2 * (s.vocab + s.router_hidden) * d,
+    return {"setup": 0, "prep": 0, "tail_merge": 0, "lmhead": 2 * (s.vocab + s.router_hidden) * d,
             "layers": s.n_layers * (2 * (qw + 2 * kvw) * d + 2 * d * qw + 2 * 3 * F * d + rows * 2 * kvw * 2 + attention_bytes)}
 
 
