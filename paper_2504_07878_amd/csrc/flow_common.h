@@ -1,4 +1,4 @@
-// What the kernels that run a whole decode step in one launch share (flow_kernels.hip, flow_f32_kernels.hip): words that tell by themselves that they are
+// What the kernels that run a whole decode step in one launch share (flow_kernels.hip, flow_rows_kernels.hip, flow_f32_kernels.hip): words that tell by themselves that they are
 // there, and how a task waits for them.
 #pragma once
 #include "mfma_common.h"

@@ -598,6 +598,10 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
     };
     auto rows = [&](auto dh) {
         constexpr int DH = decltype(dh)::value;
+        // Tasks as small as keep the links of a layer, of which two or three are under way, to about the 256 workgroups: smaller ones queue, larger ones take longer each. us a step,
+        // as here / smaller / larger. 16 rows after 200 to 600 keys, gate/up of 5, 4, 6 groups: 476 / 514 / 479, FFN output of 8, 16 rows: 476 / 510. 32 rows after 128 to 700,
+        // gate/up of 16 rows by 8, 10 groups: 558 / 587 / 557, q|k|v of 1 group: 605, FFN output of 8 rows: 618. 64 rows after 128 to 1024, gate/up of 6, 5, 7, 8 groups: 763 / 781 /
+        // 762, 784, of 16 rows by 8 groups: 888, q|k|v of 2, 6: 768 / 784, output projection of 7: 793.
         if (R <= 16) go(flow_rows_kernel<DH, 1, 2, 1, 5, 8>, 1, 2, 1, 5, 8);
         else if (R <= 32) go(flow_rows_kernel<DH, 2, 2, 2, 5, 16>, 2, 2, 2, 5, 16);
         else go(flow_rows_kernel<DH, 4, 4, 2, 6, 16>, 4, 4, 2, 6, 16);

@@ -25,8 +25,8 @@ def small(dtype=synth.BF16):
 
 @pytest.mark.parametrize("page,B", [(32, 3), (64, 3), (64, 21), (128, 70), (32, 70)])
 def test_paged_prefill_decode_and_catch_up(tr, tro, page, B):
-    """Ragged prompts, decode steps and a catch-up step on every kernel family (3 rows: all layers in one launch; 21:
-    matrix-core GEMMs; 70: the row attention kernel), pages of 32 to 128 positions."""
+    """Ragged prompts, decode steps and a catch-up step on every kernel family (3 and 21 rows: all layers in one
+    launch; 70: the row attention kernel), pages of 32 to 128 positions."""
     s, w = small()
     max_seq = 260
     g = tr.Model(s.asdict(), w, B, max_seq, kv_page=page); o = tro.Model(s.asdict(), w, B, max_seq)

@@ -528,7 +528,7 @@ def test_decode_steps_fed_from_device_memory(tr, tro, tiny_weights, dtype):
 def test_decode_step_replayed_from_a_captured_graph(tr, B):
     """A device-fed decode step enqueues kernels only (no allocation, no host copy, no memset), so it can be captured into a
     HIP graph. Every replay, with eager work of the same model and synchronisations in between, must give the bits of the
-    eager step it was captured from (2 and 8 rows: all layers in one launch; 12 rows: a launch per product, with exchange counters)."""
+    eager step it was captured from (all layers in one launch: 2 and 8 rows, 12 rows with their own kernels)."""
     s = synth.TINY.with_(name="graph", dtype=synth.BF16, kv_dtype=synth.BF16, vocab=5003)
     w = synth.make_weights(s, SEED + 41, std=0.05, bias_std=0.05, gain_std=0.1)
     g = tr.Model(s.asdict(), w, B, 1200)
