@@ -52,6 +52,10 @@ struct FlowRowsArgs {
 };
 static_assert(sizeof(FlowRowsArgs) <= 4096, "kernel arguments");
 
+// What values whose squares add up to sq (with others of their row) are handed on by: where that overflows, the row's 1/rms is 0 and they count for 0. Handed on as they are,
+// their products with the gain or with a weight could be infinite, and infinity times 0 is a NaN. (Infinities become NaNs here.)
+__device__ __forceinline__ float flow_rows_by(float sq) { return sq < INFINITY ? 1.f : 0.f; }
+
 // QU, OU: groups of 16 weight rows of a q|k|v and of an output projection task; PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
 template <int DH, int QU, int OU, int PAIR, int GU, int DR>
 struct FlowRows : FlowAttention<FlowRows<DH, QU, OU, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
@@ -157,8 +161,9 @@ struct FlowRows : FlowAttention<FlowRows<DH, QU, OU, PAIR, GU, DR>, DH, 256, 2, 
         sq = flow_sum4(sq);
         if (!on) return;
         uint32_t h0, h1, l0, l1;
-        split_hi_lo(v.x * __uint_as_float(gain.x << 16), v.y * __uint_as_float(gain.x & 0xffff0000u), h0, l0);
-        split_hi_lo(v.z * __uint_as_float(gain.y << 16), v.w * __uint_as_float(gain.y & 0xffff0000u), h1, l1);
+        const f32x4 n = v * flow_rows_by(sq);
+        split_hi_lo(n.x * __uint_as_float(gain.x << 16), n.y * __uint_as_float(gain.x & 0xffff0000u), h0, l0);
+        split_hi_lo(n.z * __uint_as_float(gain.y << 16), n.w * __uint_as_float(gain.y & 0xffff0000u), h1, l1);
         const uint32_t at = at_group(p, rg, a.D.d) + (unit >> 1) * 2048 + ((2 * (unit & 1) + (o & 1)) * 16 + row) * 16 + (o >> 1) * 8;
         flow_store_pair(buf, at, h0, h1);
         flow_store_pair(buf, at + 1024, l0, l1);
@@ -469,7 +474,8 @@ __global__ __launch_bounds__(256) void flow_rows_setup_kernel(FlowRowsSetup a, i
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t ui = i == 0 ? u.x : i == 1 ? u.y : i == 2 ? u.z : u.w, gi = i == 0 ? g.x : i == 1 ? g.y : i == 2 ? g.z : g.w;
                     v[2 * i] = __uint_as_float(ui << 16); v[2 * i + 1] = __uint_as_float(ui & 0xffff0000u);
-                    n[2 * i] = v[2 * i] * __uint_as_float(gi << 16); n[2 * i + 1] = v[2 * i + 1] * __uint_as_float(gi & 0xffff0000u);
+                    n[2 * i] = v[2 * i] * flow_rows_by(v[2 * i] * v[2 * i]) * __uint_as_float(gi << 16);
+                    n[2 * i + 1] = v[2 * i + 1] * flow_rows_by(v[2 * i + 1] * v[2 * i + 1]) * __uint_as_float(gi & 0xffff0000u);
                     sq = fmaf(v[2 * i], v[2 * i], sq); sq = fmaf(v[2 * i + 1], v[2 * i + 1], sq);
                 }
                 uint4 hi, lo;

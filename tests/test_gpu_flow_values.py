@@ -13,18 +13,18 @@ GATED = synth.TINY.with_(name="gated", n_layers=1, d_model=256, n_q_heads=2, n_k
                          dtype=synth.BF16, kv_dtype=synth.BF16)
 
 
-def gated_step(gates, rows, x0=16.0):
-    """rows of hidden (before the final norm) of a decode step whose 255 gates are given (bf16 values)"""
+def gated_step(gates, rows, x0=16.0, gain=1.0):
+    """rows of hidden (before the final norm) of a decode step whose 255 gates (at a gain of 1) are given (bf16 values)"""
     from paper_2504_07878_amd import tokroute as tr
     s, bf = GATED, lambda *shape: torch.zeros(shape, dtype=torch.bfloat16)   # noqa: E731
-    w = {"tok_emb": bf(s.vocab, s.d_model), "final_norm": bf(s.d_model) + 1, "l0.ln1": bf(s.d_model) + 1, "l0.ln2": bf(s.d_model) + 1, "l0.wq": bf(128, s.d_model),
+    w = {"tok_emb": bf(s.vocab, s.d_model), "final_norm": bf(s.d_model) + 1, "l0.ln1": bf(s.d_model) + gain, "l0.ln2": bf(s.d_model) + gain, "l0.wq": bf(128, s.d_model),
          "l0.wk": bf(64, s.d_model), "l0.wv": bf(64, s.d_model), "l0.wo": bf(s.d_model, 128), "l0.wg": bf(s.d_ffn, s.d_model), "l0.wu": bf(s.d_ffn, s.d_model),
          "l0.wd": bf(s.d_model, s.d_ffn)}
     w["tok_emb"][:, 0] = x0
     w["l0.wg"][:255, 0] = torch.tensor(gates, dtype=torch.float64).bfloat16() / 16
     w["l0.wu"][:, 0] = 1 / 16
     w["l0.wd"][1 + torch.arange(255), torch.arange(255)] = 1
-    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, 8, 64, hidden_tap=tr.PRE_FINAL_NORM)
+    g = tr.Model(s.asdict(), {k: v.cuda() for k, v in w.items()}, max(rows, 8), 64, hidden_tap=tr.PRE_FINAL_NORM)
     g.prefill(list(range(rows)), [[3, 4]] * rows)
     out = g.decode_step(list(range(rows)), np.arange(rows, dtype=np.int32)).cpu()
     return out.hidden.astype(np.float64)
@@ -69,6 +69,24 @@ def test_rows_whose_sum_of_squares_overflows(rows):
     want = np.zeros_like(got)
     want[:, 0] = 2.0 ** 70
     assert np.array_equal(got, want), got
+
+
+@pytest.mark.parametrize("rows", [9, 17, 64])
+@pytest.mark.parametrize("x0,gain", [(2.0 ** 64, 1.0), (2.0 ** 70, 2.0 ** 60), (2.0 ** 120, 2.0 ** 8), (-255 * 2.0 ** 120, 3.0)])
+def test_rows_whose_values_leave_the_range_with_their_gain(rows, x0, gain):
+    """1/rms is 0: neither a value's product with its gain nor a sum of such products may make a NaN of the row."""
+    got = gated_step(np.linspace(-400, 400, 255), rows, x0=x0, gain=gain)
+    want = np.zeros_like(got)
+    want[:, 0] = x0
+    assert np.array_equal(got, want), got
+
+
+@pytest.mark.parametrize("rows", [9, 17, 64])
+def test_rows_whose_sum_of_squares_just_fits(rows):
+    """The largest value whose square is finite: its row's 1/rms is 2^-60 and the gates are what they always are."""
+    t = torch.tensor(np.linspace(-6, 6, 255)).bfloat16().double().numpy()
+    got, want = gated_step(t, rows, x0=255 * 2.0 ** 56)[:, 1:], silu(t)
+    assert (np.abs(got - want) <= 1e-5 * np.abs(want)).all(), np.abs(got - want).max()
 
 
 @pytest.mark.parametrize("rows", [1, 2, 4, 8])
