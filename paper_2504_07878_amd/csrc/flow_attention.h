@@ -192,43 +192,39 @@ struct FlowAttention {
 #pragma unroll
         for (int p = 0; p < NP; ++p) { const uint32_t w = flow_part(O0, O1); flow_store_pair(f.buf, at + p * plane, w); }
     }
-    // the parts of a row and kv head put together
-    __device__ __forceinline__ void merge(int l, int r, int g) const
+    // the parts of `heads` heads of a row put together, two dims a thread (at most 1024)
+    __device__ __forceinline__ void merge(int l, int r, int head, int heads) const
     {
+        static_assert(2 * 64 * W >= 1024, "");
         const F &f = self();
         const auto &a = f.a;
         const auto buf = f.buf;
-        const int G = a.D.G, parts = parts_of(a.pos[r]);
-        if (parts == 1) return;
+        const int parts = parts_of(a.pos[r]), k = 2 * (int)threadIdx.x, d = k % DH;
+        if (parts == 1 || k >= heads * DH) return;
+        const uint32_t at_p = (a.o_ap + l * a.s_ap + (r * a.D.Hq + head + k / DH) * a.P * PSTR) * 4, at_o = f.out_of(l, r, 0) + (head * DH + k) * 2, plane = flow_now(f.plane());
+        flow_gate(buf, f.merge_gate(l, r), f.wait());
+        float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f;
+        for (int c0 = 0; c0 < parts; c0 += 4) {
+            FlowPiece<u32x2, 4> ml, po;
 #pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const int t = threadIdx.x + i * 64 * W, h = t / (DH / 2), d = 2 * (t % (DH / 2));
-            if (h >= G) break;   // (whole wavefronts)
-            const uint32_t at_p = (a.o_ap + l * a.s_ap + (r * a.D.Hq + g * G + h) * a.P * PSTR) * 4, at_o = f.out_of(l, r, g), plane = flow_now(f.plane());
-            flow_gate(buf, f.merge_gate(l, r), f.wait());
-            float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f;
-            for (int c0 = 0; c0 < parts; c0 += 4) {
-                FlowPiece<u32x2, 4> ml, po;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    ml.off[c] = c0 + c < parts ? at_p + ((c0 + c) * PSTR + DH) * 4 : BUFFER_NOWHERE;
-                    po.off[c] = c0 + c < parts ? at_p + ((c0 + c) * PSTR + d) * 4 : BUFFER_NOWHERE;
-                }
-                flow_poll(buf, f.wait(), ml, po);
-                float m = M;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) m = c0 + c < parts ? fmaxf(m, __uint_as_float(ml.v[0][c].x)) : m;
-                const float old = __expf(M - m);   // 0 the first time
-                L *= old; O0 *= old; O1 *= old; M = m;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float by = c0 + c < parts ? __expf(__uint_as_float(ml.v[0][c].x) - m) : 0.f;
-                    L = fmaf(__uint_as_float(ml.v[0][c].y), by, L);
-                    O0 = fmaf(__uint_as_float(po.v[0][c].x), by, O0); O1 = fmaf(__uint_as_float(po.v[0][c].y), by, O1);
-                }
+            for (int c = 0; c < 4; ++c) {
+                ml.off[c] = c0 + c < parts ? at_p + ((c0 + c) * PSTR + DH) * 4 : BUFFER_NOWHERE;
+                po.off[c] = c0 + c < parts ? at_p + ((c0 + c) * PSTR + d) * 4 : BUFFER_NOWHERE;
             }
-            attention_out(f, at_o + (h * DH + d) * 2, plane, O0, O1, L);
+            flow_poll(buf, f.wait(), ml, po);
+            float m = M;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) m = c0 + c < parts ? fmaxf(m, __uint_as_float(ml.v[0][c].x)) : m;
+            const float old = __expf(M - m);   // 0 the first time
+            L *= old; O0 *= old; O1 *= old; M = m;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float by = c0 + c < parts ? __expf(__uint_as_float(ml.v[0][c].x) - m) : 0.f;
+                L = fmaf(__uint_as_float(ml.v[0][c].y), by, L);
+                O0 = fmaf(__uint_as_float(po.v[0][c].x), by, O0); O1 = fmaf(__uint_as_float(po.v[0][c].y), by, O1);
+            }
         }
+        attention_out(f, at_o, plane, O0, O1, L);
     }
 };
 

@@ -437,7 +437,7 @@ __global__ __launch_bounds__(64 * FLOW_WAVES, 2) void flow_kernel(FlowArgs args)
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
         else if ((i -= a.nQ) < a.nA) f.attention(l, i / (a.D.Hkv * a.P), (i / a.P) % a.D.Hkv, i % a.P);
-        else if ((i -= a.nA) < a.nM) { f.merge(l, i / a.D.Hkv, i % a.D.Hkv); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
+        else if ((i -= a.nA) < a.nM) { f.merge(l, i / a.D.Hkv, i % a.D.Hkv * a.D.G, a.D.G); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
         else if ((i -= a.nM) < a.nO) f.oproj(l, i);
         else if ((i -= a.nO) < a.nG) f.gateup(l, i);
         else f.down(l, i - a.nG);

@@ -44,7 +44,7 @@ struct FlowRowsArgs {
     // xa, pa, sa: a layer's input: residual rows, times the norm's gain as operands, sums of squares; x1, p1, s1: the same behind the output projection; q, kvn: query, new
     // key and value; ap: attention of parts of a context; at: attention; h: FFN activations as operands; out: the last layer's rows
     uint32_t o_xa, o_pa, o_sa, o_x1, o_p1, o_s1, o_q, o_kvn, o_ap, o_at, o_h, o_out, s_in, s_q, s_kvn, s_ap, s_at, s_h;
-    int nQ, nA, nM, nO, nG, nD;       // tasks of a layer
+    int nQ, nA, nM, nO, nG, nD;       // tasks of a layer (nM: rows whose contexts are in parts)
     int uG;                           // groups of 8 gate and 8 up rows of a layer
     int *ticket, *given_up;           // next task; set when a wait was given up
     // the parts of all rows' contexts, row + 256 * part: first parts of the rows, those of several parts first, then the other parts
@@ -440,7 +440,7 @@ __global__ __launch_bounds__(64 * FR_W, 2) void flow_rows_kernel(FlowRowsArgs ar
         int i = t - l * per_layer;
         if (i < a.nQ) f.qkv(l, i);
         else if ((i -= a.nQ) < a.nA) { const uint32_t p = a.part[i / a.D.Hkv]; f.attention(l, p & 0xff, i % a.D.Hkv, p >> 8); }
-        else if ((i -= a.nA) < a.nM) { f.merge(l, a.part[i / a.D.Hkv] & 0xff, i % a.D.Hkv); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
+        else if ((i -= a.nA) < a.nM) { f.merge(l, a.part[i] & 0xff, 0, a.D.Hq); __syncthreads(); }   // (not all of its wavefronts have something to wait for)
         else if ((i -= a.nM) < a.nO) f.oproj(l, i);
         else if ((i -= a.nO) < a.nG) f.gateup(l, i);
         else f.template down<DR>(l, i - a.nG);
@@ -554,6 +554,10 @@ size_t flow_rows_floats(const Dims &D, int max_rows)
     return most;
 }
 
+// FLOW_ROWS_PARTS is what the table of parts has room for: the launch is still the faster one there. 6 layers, all rows after as many keys, a launch per link / here: 896 columns with
+// 2 kv heads, 9 rows after 16 keys 206 / 117 us, 64 after 3071 374 / 307; 128-wide heads, 64 rows after 1023 326 / 235; 256 columns with 16 kv heads, 64 rows after 769 481 / 431,
+// after 2312 886 / 879 (a merge per kv head and not per row: 498, 946), 9 rows after 21503 1215 / 991. Not so only where 14 to 16 rows of 1024 key columns all have more than 9000 keys
+// (3900 of 128-wide heads) and both are bound by the cache: 16 rows after 12287 987 / 1012; with contexts of 1500 to 12287 809 / 636.
 bool flow_rows_takes(const Dims &D, int R, const int *poss)
 {
     int U, P;
@@ -598,7 +602,7 @@ float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R,
     }
     auto go = [&](auto kern, int qu, int ou, int pair, int gu, int dr) {
         a.nG16 = (R + 15) / 16; a.nPair = (a.nG16 + pair - 1) / pair; a.uG = D.F / 8;
-        a.nQ = (D.qw + 2 * D.kvw) / 16 / qu * a.nG16; a.nA = n_parts * D.Hkv; a.nM = n_split * D.Hkv; a.nO = (D.d / 16 + ou - 1) / ou * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
+        a.nQ = (D.qw + 2 * D.kvw) / 16 / qu * a.nG16; a.nA = n_parts * D.Hkv; a.nM = n_split; a.nO = (D.d / 16 + ou - 1) / ou * a.nG16; a.nD = D.d / 16 * ((R + dr - 1) / dr);
         a.nG = (a.uG + gu - 1) / gu * a.nPair;
         hipLaunchKernelGGL(kern, dim3(256), dim3(64 * FR_W), 0, s, a);
     };

@@ -24,6 +24,8 @@ def bf16(rng, shape):
     ("narrow", dict(d_model=32, n_q_heads=2, d_ffn=5408), 32, [0, 31, 32, 255] * 8, 0),                    # FFN columns past one round; one step of columns
     ("odd_groups", dict(d_model=896, d_ffn=4864, n_q_heads=14, n_kv_heads=2), 37, [64, 100, 1, 513] * 10, 64),
     ("wide_heads", dict(head_dim=128, n_q_heads=4, n_kv_heads=2, d_ffn=96), 41, [0, 1, 32, 255, 256, 257, 600, 1000] * 6, 0),
+    ("heads_of_16_keys", dict(n_q_heads=16, n_kv_heads=16), 20, [769, 1537, 768, 2310, 31] * 5, 0),       # a merge of all 16 heads; of all 8
+    ("wide_heads_of_8_keys", dict(head_dim=128, n_q_heads=8, n_kv_heads=8), 49, [257, 256, 769, 1000, 3] * 10, 32),
     ("one_part", {}, 10, [768, 767, 513, 512, 1] * 3, 0),                                                  # the longest contexts of one part, ..
     ("one_part_wide", dict(head_dim=128, n_q_heads=4, n_kv_heads=2), 50, [256, 255, 0, 33] * 13, 64),      # .. of 128-wide heads
     ("all", dict(d_model=480, d_ffn=1120), 64, [1537, 2300] + [5 * i for i in range(62)], 0),
