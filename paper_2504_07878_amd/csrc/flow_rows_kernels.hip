@@ -554,6 +554,16 @@ size_t flow_rows_floats(const Dims &D, int max_rows)
     return most;
 }
 
+// A wavefront takes its share of an FFN output in rounds of FR_NSD steps (5120 columns in all), one after another; from the third or fourth round on a launch per link is faster, which
+// splits these columns over workgroups. 4 layers after 23 keys, launch per link / here: 896 columns, FFN of 9728 64 rows 1.05, 16 rows 1.41; FFN of 12288 64 rows 0.95, 33 rows 1.00, 32 rows
+// 1.10, 16 rows 1.26; of 15360 0.88, 0.94, 1.04, 1.21; 512 columns, 12288: 0.93, 1.02, 1.02, 1.18; 256 columns, 9728: 1.06, 1.13, 1.08, 1.27; 12288: 0.92, 1.00, 0.97, 1.12; 128 columns, 16384: 0.78,
+// 0.80, 0.83, 0.97; 896 columns, 20480: 0.81, 0.92, 0.96, 1.13.
+static bool flow_rows_ffn(const Dims &D, int R)
+{
+    const int round = 32 * FR_W * FR_NSD;
+    return D.F <= round * (2 + (R <= 16) + (R <= 32 && D.d >= 512));
+}
+
 // FLOW_ROWS_PARTS is what the table of parts has room for: the launch is still the faster one there. 6 layers, all rows after as many keys, a launch per link / here: 896 columns with
 // 2 kv heads, 9 rows after 16 keys 206 / 117 us, 64 after 3071 374 / 307; 128-wide heads, 64 rows after 1023 326 / 235; 256 columns with 16 kv heads, 64 rows after 769 481 / 431,
 // after 2312 886 / 879 (a merge per kv head and not per row: 498, 946), 9 rows after 21503 1215 / 991. Not so only where 14 to 16 rows of 1024 key columns all have more than 9000 keys
@@ -561,7 +571,7 @@ size_t flow_rows_floats(const Dims &D, int max_rows)
 bool flow_rows_takes(const Dims &D, int R, const int *poss)
 {
     int U, P;
-    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && flow_rows_split(D, R, poss, &U, &P) && flow_rows_floats(D, R) < (size_t)1 << 29;
+    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && flow_rows_ffn(D, R) && flow_rows_split(D, R, poss, &U, &P) && flow_rows_floats(D, R) < (size_t)1 << 29;
 }
 
 void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,

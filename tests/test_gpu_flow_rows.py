@@ -59,6 +59,34 @@ def test_steps(name, shape, rows, lens, page):
     assert exempt <= 2
 
 
+def in_one_launch(model, step):
+    """Whether a call ran its layers in one launch; its result."""
+    from paper_2504_07878_amd import tokroute as tr
+    model.profile_select(tr.KERNEL_FAMILIES.index("layers"))
+    model.profile_enable(True)
+    out = step()
+    n = model.profile_read()[2]
+    model.profile_enable(False)
+    return n == 1, out
+
+
+@pytest.mark.parametrize("d_model,d_ffn,rows,one", [(256, 10240, 17, True), (256, 10272, 17, False), (512, 10272, 32, True), (512, 10272, 33, False), (512, 15392, 32, False),
+                                                    (256, 15360, 16, True), (256, 15392, 16, False), (512, 20480, 9, True), (512, 20512, 9, False)])
+def test_wide_ffns_keep_a_launch_per_link(d_model, d_ffn, rows, one):
+    """Past two rounds of 5120 FFN columns (one more up to 16 rows, one more up to 32 rows of 512 columns) the FFN output of one launch is slower than a launch per link."""
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name="ffn", **{**BASE, **dict(d_model=d_model, d_ffn=d_ffn, n_layers=1)})
+    w = synth.make_weights(s, SEED + 9, std=0.05)
+    g, o = tr.Model(s.asdict(), w, rows, 8), tro.Model(s.asdict(), w, rows, 8)
+    slots, toks = list(range(rows)), synth.prompt_tokens(SEED, "ffn", rows, s.vocab)
+    for m in (g, o):
+        m.prefill(slots, [toks[i:i + 1] for i in range(rows)])
+    was, go = in_one_launch(g, lambda: g.decode_step(slots, toks, want_logits=True).cpu())
+    assert was == one
+    assert compare_outputs(go, o.decode_step(slots, toks, want_logits=True), s.dtype, s.threshold, f"FFN of {d_ffn}") <= 1
+
+
 @pytest.mark.parametrize("rows", [9, 64])
 def test_nans_end_the_step(rows):
     from paper_2504_07878_amd import tokroute as tr
