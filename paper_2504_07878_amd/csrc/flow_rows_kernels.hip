@@ -506,18 +506,18 @@ static int flow_rows_most(int R) { return FLOW_ROWS_PARTS / R; }
 // rule below, which splits from 257 keys on: 16 rows after 200 to 600 keys 476 us a step and 490, 32 after 128 to 700 559 and 577, 64 after 128 to 512 709 and 744.
 // Else the smallest parts that make no more tasks than can be under way while their queries are computed; false: more parts than there is room for. Blocks per wavefront
 // 1 / 2 / 3: 16 rows after 100 to 1900 keys 542 / 512 / 540 us, 32 rows after 128 to 1024 616 / 590 / 594, 64 rows 834 / 765 / 771.
-static bool flow_rows_split(const Dims &D, int R, const int *poss, int *U, int *P)
+static bool flow_rows_split(const Dims &D, int R, const int *poss, FlowRowsPlan *p)
 {
     const int umax = D.dh == 64 ? FR_U<64> : FR_U<128>, longest = *std::max_element(poss, poss + R);
-    *P = 1;
-    for (*U = 1; *U <= umax; ++*U)
-        if (flow_rows_parts(longest, *U) == 1) return true;
-    for (*U = 1;; ++*U) {
-        *P = flow_rows_parts(longest, *U);
+    p->P = 1;
+    for (p->U = 1; p->U <= umax; ++p->U)
+        if (flow_rows_parts(longest, p->U) == 1) return true;
+    for (p->U = 1;; ++p->U) {
+        p->P = flow_rows_parts(longest, p->U);
         int tasks = 0;
-        for (int r = 0; r < R; ++r) tasks += flow_rows_parts(poss[r], *U) * D.Hkv;
-        if (*P <= flow_rows_most(R) && (tasks <= (R <= 32 ? 128 : 256) || *U == umax)) return true;
-        if (*U == umax) return false;
+        for (int r = 0; r < R; ++r) tasks += flow_rows_parts(poss[r], p->U) * D.Hkv;
+        if (p->P <= flow_rows_most(R) && (tasks <= (R <= 32 ? 128 : 256) || p->U == umax)) return true;
+        if (p->U == umax) return false;
     }
 }
 
@@ -544,16 +544,6 @@ static size_t flow_rows_layout(const Dims &D, int R, int P, FlowRowsArgs &a, siz
     return at;
 }
 
-size_t flow_rows_floats(const Dims &D, int max_rows)
-{
-    if (max_rows <= FLOW_MAX_ROWS) return 0;
-    size_t first, filled;
-    FlowRowsArgs a;
-    size_t most = 0;
-    for (int R = FLOW_MAX_ROWS + 1; R <= std::min(max_rows, FLOW_ROWS_MAX); ++R) most = std::max(most, flow_rows_layout(D, R, flow_rows_most(R), a, &first, &filled));
-    return most;
-}
-
 // A wavefront takes its share of an FFN output in rounds of FR_NSD steps (5120 columns in all), one after another; from the third or fourth round on a launch per link is faster, which
 // splits these columns over workgroups. 4 layers after 23 keys, launch per link / here: 896 columns, FFN of 9728 64 rows 1.05, 16 rows 1.41; FFN of 12288 64 rows 0.95, 33 rows 1.00, 32 rows
 // 1.10, 16 rows 1.26; of 15360 0.88, 0.94, 1.04, 1.21; 512 columns, 12288: 0.93, 1.02, 1.02, 1.18; 256 columns, 9728: 1.06, 1.13, 1.08, 1.27; 12288: 0.92, 1.00, 0.97, 1.12; 128 columns, 16384: 0.78,
@@ -564,23 +554,42 @@ static bool flow_rows_ffn(const Dims &D, int R)
     return D.F <= round * (2 + (R <= 16) + (R <= 32 && D.d >= 512));
 }
 
+constexpr size_t FR_MOST_WORDS = (size_t)1 << 29;   // 32-bit offsets in bytes
+
+size_t flow_rows_floats(const Dims &D, int max_rows)
+{
+    size_t most = 0, first, filled;
+    FlowRowsArgs a;
+    for (int R = FLOW_MAX_ROWS + 1; R <= std::min(max_rows, FLOW_ROWS_MAX); ++R) {
+        if (!flow_rows_ffn(D, R)) continue;
+        for (int P = std::min(flow_rows_most(R), flow_rows_parts(D.max_seq - 1, 1)); P > 0; --P) {   // (a row's own key is in no block)
+            const size_t n = flow_rows_layout(D, R, P, a, &first, &filled);
+            if (n >= FR_MOST_WORDS) continue;
+            most = std::max(most, n);
+            break;
+        }
+    }
+    return most;
+}
+
 // FLOW_ROWS_PARTS is what the table of parts has room for: the launch is still the faster one there. 6 layers, all rows after as many keys, a launch per link / here: 896 columns with
 // 2 kv heads, 9 rows after 16 keys 206 / 117 us, 64 after 3071 374 / 307; 128-wide heads, 64 rows after 1023 326 / 235; 256 columns with 16 kv heads, 64 rows after 769 481 / 431,
 // after 2312 886 / 879 (a merge per kv head and not per row: 498, 946), 9 rows after 21503 1215 / 991. Not so only where 14 to 16 rows of 1024 key columns all have more than 9000 keys
 // (3900 of 128-wide heads) and both are bound by the cache: 16 rows after 12287 987 / 1012; with contexts of 1500 to 12287 809 / 636.
-bool flow_rows_takes(const Dims &D, int R, const int *poss)
+bool flow_rows_takes(const Dims &D, int R, const int *poss, FlowRowsPlan *p)
 {
-    int U, P;
-    return R > FLOW_MAX_ROWS && R <= FLOW_ROWS_MAX && flow_rows_ffn(D, R) && flow_rows_split(D, R, poss, &U, &P) && flow_rows_floats(D, R) < (size_t)1 << 29;
+    if (R <= FLOW_MAX_ROWS || R > FLOW_ROWS_MAX || !flow_rows_ffn(D, R) || !flow_rows_split(D, R, poss, p)) return false;
+    FlowRowsArgs a;
+    size_t first, filled;
+    return flow_rows_layout(D, R, p->P, a, &first, &filled) < FR_MOST_WORDS;
 }
 
-void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,
+void launch_flow_rows_setup(hipStream_t s, const Dims &D, const FlowRowsPlan &plan, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,
                             const int *dev_toks, int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket)
 {
-    FlowRowsArgs a{};
+    FlowRowsArgs a;
     size_t first, filled;
-    flow_rows_split(D, R, poss, &a.U, &a.P);
-    flow_rows_layout(D, R, a.P, a, &first, &filled);
+    flow_rows_layout(D, R, plan.P, a, &first, &filled);
     FlowRowsSetup su{};
     for (int i = 0; i < R; ++i) { su.slot[i] = slots[i]; su.tok[i] = toks ? toks[i] : 0; su.pos[i] = poss[i]; }
     const uint32_t skip = (uint32_t)(first / 4), n_fill = (uint32_t)(filled / 4);   // 16-byte words
@@ -589,11 +598,11 @@ void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, c
                        reinterpret_cast<uint4 *>(buf), n_fill, skip, ticket);
 }
 
-float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
+float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowRowsPlan &plan, const FlowModel &m, int R, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up)
 {
     FlowRowsArgs a{};
     size_t first, filled;
-    flow_rows_split(D, R, poss, &a.U, &a.P);
+    a.U = plan.U; a.P = plan.P;
     const size_t n = flow_rows_layout(D, R, a.P, a, &first, &filled);
     a.wt = m.wt; a.wt_stride = m.wt_stride; a.wt_qkv = (uint32_t)m.wt_qkv; a.wt_o = (uint32_t)m.wt_o; a.wt_gu = (uint32_t)m.wt_gu; a.wt_d = (uint32_t)m.wt_d;
     a.bias = m.bias; a.bias_stride = m.bias_stride;

@@ -564,7 +564,7 @@ int run_layers(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, bool embed = true
 
 // A decode step of few rows (flow_takes, flow_rows_takes): row set-up, embedding and all layers. Returns the rows of the residual stream; *pending partial sums are
 // still to be added.
-float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, float **partials, int *pending)
+float *run_flow(tr_ctx *ctx, hipStream_t s, const FlowRowsPlan &plan, int R, int max_ctx, const int *slots, const int *toks, const int *poss, const int *dev_toks, float **partials, int *pending)
 {
     const Layout &L = ctx->lay;
     float *buf = ctx->at<float>(L.flow_buf);
@@ -573,13 +573,13 @@ float *run_flow(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *slots
     {
         Bracket br(ctx, s, TR_KERNEL_SETUP);
         if (few) launch_flow_setup(s, ctx->D, ctx->tok_emb, R, max_ctx, slots, toks, poss, dev_toks, d_slot, d_tok, d_pos, buf, ticket);
-        else launch_flow_rows_setup(s, ctx->D, ctx->tok_emb, ctx->layers[0].ln1, R, slots, toks, poss, dev_toks, d_slot, d_tok, d_pos, buf, ticket);
+        else launch_flow_rows_setup(s, ctx->D, plan, ctx->tok_emb, ctx->layers[0].ln1, R, slots, toks, poss, dev_toks, d_slot, d_tok, d_pos, buf, ticket);
     }
     const FlowModel m{ctx->wt(0, 0), L.wt_layer_stride, L.wt_qkv, L.wt_o, L.wt_gu, L.wt_d, ctx->bias(0), L.bias_stride / 4, ctx->layers.data(),
                       ctx->ws + L.kc, ctx->ws + L.vc, L.k_layer_bytes, L.v_layer_bytes, ctx->at<float2>(L.rope)};
     Bracket br(ctx, s, TR_KERNEL_LAYERS);
     *pending = few ? FLOW_KQ : 0;
-    return few ? launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up, partials) : launch_flow_rows(s, ctx->D, m, R, poss, d_slot, d_pos, buf, ticket, given_up);
+    return few ? launch_flow(s, ctx->D, m, R, max_ctx, d_slot, d_pos, buf, ticket, given_up, partials) : launch_flow_rows(s, ctx->D, plan, m, R, poss, d_slot, d_pos, buf, ticket, given_up);
 }
 
 // The routing tail on n rows of the residual stream x starting at row0. `pending` split-K partials part[pending][part_M][d] (rows indexed
@@ -647,10 +647,11 @@ bool run_step_of_few(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *
 {
     const Dims &D = ctx->D;
     const Layout &L = ctx->lay;
-    if (L.flow && (flow_takes(D, R, max_ctx) || flow_rows_takes(D, R, poss))) {
+    FlowRowsPlan plan{};
+    if (L.flow && (flow_takes(D, R, max_ctx) || flow_rows_takes(D, R, poss, &plan))) {
         float *part = nullptr;
         int pending;
-        float *x = run_flow(ctx, s, R, max_ctx, slots, toks, poss, dev_toks, &part, &pending);
+        float *x = run_flow(ctx, s, plan, R, max_ctx, slots, toks, poss, dev_toks, &part, &pending);
         run_tail(ctx, s, t, x, 0, pending, R, part);
         return true;
     }

@@ -236,11 +236,12 @@ void launch_flow_setup(hipStream_t s, const Dims &D, const void *tok_emb, int R,
 float *launch_flow(hipStream_t s, const Dims &D, const FlowModel &m, int R, int max_ctx, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up, float **partials);
 // the same for 9 to 64 rows (flow_rows_kernels.hip); gain: of the first layer's first norm; the rows come complete
 constexpr int FLOW_ROWS_MAX = 64, FLOW_ROWS_PARTS = 256;   // parts of all rows' contexts
-size_t flow_rows_floats(const Dims &D, int max_rows);
-bool flow_rows_takes(const Dims &D, int R, const int *poss);
-void launch_flow_rows_setup(hipStream_t s, const Dims &D, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,
+size_t flow_rows_floats(const Dims &D, int max_rows);   // as many as flow_rows_takes may ask for with contexts of up to D.max_seq
+struct FlowRowsPlan { int U, P; };   // blocks of 32 keys per wavefront; most parts of a row's context
+bool flow_rows_takes(const Dims &D, int R, const int *poss, FlowRowsPlan *plan);
+void launch_flow_rows_setup(hipStream_t s, const Dims &D, const FlowRowsPlan &plan, const void *tok_emb, const void *gain, int R, const int *slots, const int *toks, const int *poss,
                             const int *dev_toks, int *d_slot, int *d_tok, int *d_pos, float *buf, int *ticket);
-float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowModel &m, int R, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up);
+float *launch_flow_rows(hipStream_t s, const Dims &D, const FlowRowsPlan &plan, const FlowModel &m, int R, const int *poss, const int *d_slot, const int *d_pos, float *buf, int *ticket, int *given_up);
 // the same for fp32 models of up to 4 rows, with the LM head's slices and the router's first layer (flow_f32_kernels.hip)
 constexpr int FLOW32_MAX_ROWS = 4, FLOW32_MAX_LAYERS = 24;
 struct Flow32Model {
