@@ -70,6 +70,31 @@ def in_one_launch(model, step):
     return n == 1, out
 
 
+@pytest.mark.parametrize("shape,rows,longest,page", [({}, 64, 3072, 0), (dict(head_dim=128, n_q_heads=4, n_kv_heads=2), 64, 1024, 32), ({}, 16, 12288, 64), ({}, 9, 21504, 0)])
+def test_limit_of_parts(shape, rows, longest, page):
+    """256 parts of contexts in one launch at most (rows x parts of the longest): a step at the limit, 28 parts of 9 rows among them, and the next one, a launch per link."""
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name="limit", **{**BASE, **shape})
+    w = synth.make_weights(s, SEED + 9, std=0.05)
+    lens = [longest, longest - 1, longest // 2 + 1] + [1 + 37 * i for i in range(rows - 3)]
+    g, o = tr.Model(s.asdict(), w, rows, longest + 2, kv_page=page), tro.Model(s.asdict(), w, rows, longest + 2)
+    rng = synth.rng(SEED, "limit")
+    (kf, kb), (vf, vb) = (bf16(rng, (s.n_layers, s.n_kv_heads, longest, s.head_dim)) for _ in range(2))
+    for b, m in enumerate(lens):
+        g.load_kv(b, *(tr.to_device(np.ascontiguousarray(c[:, :, :m]), s.kv_dtype) for c in (kb, vb)))
+        o.load_kv(b, *(np.ascontiguousarray(c[:, :, :m]) for c in (kf, vf)))
+    slots, toks = list(range(rows)), synth.prompt_tokens(SEED, "limit", rows, s.vocab)
+    exempt = 0
+    for one in (True, False):
+        was, go = in_one_launch(g, lambda: g.decode_step(slots, toks, want_logits=True).cpu())
+        oo = o.decode_step(slots, toks, want_logits=True)
+        assert was == one
+        exempt += compare_outputs(go, oo, s.dtype, s.threshold, f"{rows} rows after {longest} keys, in one launch: {one}")
+        toks = oo.token.copy()
+    assert exempt <= 2
+
+
 @pytest.mark.parametrize("d_model,d_ffn,rows,one", [(256, 10240, 17, True), (256, 10272, 17, False), (512, 10272, 32, True), (512, 10272, 33, False), (512, 15392, 32, False),
                                                     (256, 15360, 16, True), (256, 15392, 16, False), (512, 20480, 9, True), (512, 20512, 9, False)])
 def test_wide_ffns_keep_a_launch_per_link(d_model, d_ffn, rows, one):

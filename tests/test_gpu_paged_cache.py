@@ -18,8 +18,8 @@ def tr():
     return tokroute
 
 
-def small(dtype=synth.BF16):
-    s = synth.TINY.with_(dtype=dtype, kv_dtype=synth.BF16)
+def small(dtype=synth.BF16, d_model=synth.TINY.d_model):
+    s = synth.TINY.with_(dtype=dtype, kv_dtype=synth.BF16, d_model=d_model)
     return s, synth.make_weights(s, SEED + 21, std=0.05, bias_std=0.05, gain_std=0.1)
 
 
@@ -48,10 +48,10 @@ def test_paged_prefill_decode_and_catch_up(tr, tro, page, B):
         assert g.seq_len(slot) == o.seq_len(slot) == lens[i] + 3 + len(segs[i])
 
 
-@pytest.mark.parametrize("B,ctx", [(3, 1200), (12, 2300)])
-def test_paged_long_contexts(tr, tro, B, ctx):
-    """Contexts of many pages: rows split into parts, in one launch (3 rows) and in launches with a merge."""
-    s, w = small()
+@pytest.mark.parametrize("B,ctx,d_model", [(3, 1200, 256), (12, 2300, 256), (12, 2300, 240)])
+def test_paged_long_contexts(tr, tro, B, ctx, d_model):
+    """Contexts of many pages: rows split into parts, in one launch and, with a width that is no multiple of 32, in launches whose last workgroup merges."""
+    s, w = small(d_model=d_model)
     max_seq = ctx + 8
     g = tr.Model(s.asdict(), w, B, max_seq, kv_page=64); o = tro.Model(s.asdict(), w, B, max_seq)
     lens = [ctx - 37 * i for i in range(B)]

@@ -524,12 +524,13 @@ def test_decode_steps_fed_from_device_memory(tr, tro, tiny_weights, dtype):
     assert np.array_equal(ya.logits, yb.logits)
 
 
-@pytest.mark.parametrize("B", [2, 8, 12])
-def test_decode_step_replayed_from_a_captured_graph(tr, B):
+@pytest.mark.parametrize("B,d_model", [(2, 256), (8, 256), (12, 256), (12, 240)])
+def test_decode_step_replayed_from_a_captured_graph(tr, B, d_model):
     """A device-fed decode step enqueues kernels only (no allocation, no host copy, no memset), so it can be captured into a
     HIP graph. Every replay, with eager work of the same model and synchronisations in between, must give the bits of the
-    eager step it was captured from (all layers in one launch: 2 and 8 rows, 12 rows with their own kernels)."""
-    s = synth.TINY.with_(name="graph", dtype=synth.BF16, kv_dtype=synth.BF16, vocab=5003)
+    eager step it was captured from (all layers in one launch: 2 and 8 rows, 12 rows with their own kernels; a width that is no
+    multiple of 32: a launch per product, attention with exchange counters)."""
+    s = synth.TINY.with_(name="graph", d_model=d_model, dtype=synth.BF16, kv_dtype=synth.BF16, vocab=5003)
     w = synth.make_weights(s, SEED + 41, std=0.05, bias_std=0.05, gain_std=0.1)
     g = tr.Model(s.asdict(), w, B, 1200)
     prompts = [synth.prompt_tokens(SEED, f"graph.p{i}", 900 + 37 * i if i == 0 else 5 + 23 * i, s.vocab) for i in range(B)]   # one row long enough for several attention parts
@@ -605,8 +606,9 @@ def test_exchanges_between_workgroups_give_the_same_bits_every_time(tr):
     several workgroups; the router's hidden units split over the workgroups of a row), each repeated a few hundred times:
     every repetition must reproduce the first result bit for bit. Stops at the first difference."""
     REPS = 300
-    # (1) attention: 64 rows of a bf16 model with contexts of up to ~2000 keys, i.e. up to three parts per (row, kv head)
-    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
+    # (1) attention: 64 rows of a bf16 model with contexts of up to ~2000 keys, i.e. two parts per (row, kv head); with a width that is no multiple of 32 its
+    # layers are a launch per product
+    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16, d_model=240)
     w = synth.make_weights(s, SEED + 9, std=0.05)
     B, ctx = 64, 2000
     g = tr.Model(s.asdict(), w, B, ctx + 4)
