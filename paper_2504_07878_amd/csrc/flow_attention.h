@@ -20,21 +20,21 @@ __device__ __forceinline__ uint4 flow_part(float (&v)[8])
     return u;
 }
 template <class T> __device__ __forceinline__ bf16x8 flow_bf(T u) { return __builtin_bit_cast(bf16x8, u); }
-template <int DH, int W> struct FlowAttentionLds { float o[W][8][DH + 4]; f32x4 m[8][W / 4], l[8][W / 4]; };
+template <int DH> struct FlowAttentionLds { float o[FLOW_WAVES][8][DH + 4]; f32x4 m[8][FLOW_WAVES / 4], l[8][FLOW_WAVES / 4]; };
 
 // K8: bytes from 8 dims to the next 8 of a query, key or value that is handed on; NP: parts of the attention output. F says where they lie (q_at, kvn_at, vn_behind, out_of,
 // plane) and which word shows that the link before is on its way (attention_gate, merge_gate).
-// W: wavefronts of a workgroup; UMAX: most blocks of 32 keys a wavefront takes.
-template <class F, int DH, int K8, int NP, int W, int UMAX>
+// UMAX: most blocks of 32 keys a wavefront takes.
+template <class F, int DH, int K8, int NP, int UMAX>
 struct FlowAttention {
     static constexpr int KS = DH / 32, DT = DH / 16;
     static constexpr int PSTR = DH + 4;
-    static constexpr int ROUNDS = (8 * DH / 2 + 64 * W - 1) / (64 * W);   // two dims of a head per thread
+    static_assert(8 * DH / 2 <= 64 * FLOW_WAVES, "two dims of a head per thread");
     __device__ __forceinline__ const F &self() const { return static_cast<const F &>(*this); }
 
-    // Parts of a row's context: blocks of 32 keys cached before this step, W U to a part
-    __device__ __forceinline__ int parts_of(int pos) const { const int n = W * self().a.U; return max(1, ((pos + 31) / 32 + n - 1) / n); }
-    // Part c of the keys of one row and kv head: wavefront w takes the blocks W U c + w + W i. The row's own key and value join in the last part, as a block of one.
+    // Parts of a row's context: blocks of 32 keys cached before this step, FLOW_WAVES U to a part
+    __device__ __forceinline__ int parts_of(int pos) const { const int n = FLOW_WAVES * self().a.U; return max(1, ((pos + 31) / 32 + n - 1) / n); }
+    // Part c of the keys of one row and kv head: wavefront w takes the blocks FLOW_WAVES U c + w + FLOW_WAVES i. The row's own key and value join in the last part, as a block of one.
     __device__ __forceinline__ void attention(int l, int r, int g, int c) const
     {
         const F &f = self();
@@ -43,7 +43,7 @@ struct FlowAttention {
         const auto buf = f.buf;
         const int wave = f.wave, lane = f.lane, col = f.col, o = f.o;
         const int G = flow_now(a.D.G);
-        const int pos = a.pos[r], slot = a.slot[r], nblk = (pos + 31) / 32, parts = parts_of(pos), b0 = c * W * a.U + wave;
+        const int pos = a.pos[r], slot = a.slot[r], nblk = (pos + 31) / 32, parts = parts_of(pos), b0 = c * FLOW_WAVES * a.U + wave;
         if (c >= parts) return;   // uniform over the workgroup
         const int ulen = kv_unit_len(a.D), uvts = kv_unit_vts(a.D);
         const bf16_t *kc = reinterpret_cast<const bf16_t *>(a.kc + (size_t)l * a.k_layer), *vc = reinterpret_cast<const bf16_t *>(a.vc + (size_t)l * a.v_layer);
@@ -52,7 +52,7 @@ struct FlowAttention {
         const int krow = 8 * (col >> 2) + (col & 3);   // row `col` of tile t holds key krow + 4 t: the probabilities come out as operands
 #pragma unroll
         for (int i = 0; i < UMAX; ++i) {
-            const int b = b0 + W * i;
+            const int b = b0 + FLOW_WAVES * i;
             if (i >= a.U || b >= nblk) break;
             nb = i + 1;
             const int t = 32 * b, last = pos - 1 - t;   // keys from the row's own on: the last one again
@@ -67,7 +67,7 @@ struct FlowAttention {
 #pragma unroll
             for (int d = 0; d < DT; ++d) vr[i][d] = *reinterpret_cast<const uint4 *>(vp + d * 16 * 32);
         }
-        const bool own = c == parts - 1 && wave == nblk % W;   // uniform over the wavefront
+        const bool own = c == parts - 1 && wave == nblk % FLOW_WAVES;   // uniform over the wavefront
         FlowPiece<u32x4, KS> qhm, ql, kn;
         FlowPiece<uint32_t, DT> vn;
         const uint32_t at_q = f.q_at(l, r, g * G + min(col & 7, G - 1)) + o * K8, at_n = f.kvn_at(l, r, g), at_v = at_n + f.vn_behind();
@@ -97,7 +97,7 @@ struct FlowAttention {
 #pragma unroll
         for (int i = 0; i < UMAX; ++i) {
             if (i >= nb) break;
-            const int t = 32 * (b0 + W * i);
+            const int t = 32 * (b0 + FLOW_WAVES * i);
 #pragma unroll
             for (int tt = 0; tt < 2; ++tt) {
                 const f32x4 c0 = scores([&](int s) { return kr[i][tt][s]; });
@@ -163,26 +163,23 @@ struct FlowAttention {
             reinterpret_cast<float *>(&lds.att.l[lane])[wave] = any ? sum : 0.f;
         }
         __syncthreads();
+        const int h = threadIdx.x / (DH / 2), d = 2 * (threadIdx.x % (DH / 2));
+        if (h >= G) return;
+        float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f, mw[FLOW_WAVES], lw[FLOW_WAVES];
 #pragma unroll
-        for (int i = 0; i < ROUNDS; ++i) {
-            const int t = threadIdx.x + i * 64 * W, h = t / (DH / 2), d = 2 * (t % (DH / 2));
-            if (h >= G) break;
-            float M = -INFINITY, L = 0.f, O0 = 0.f, O1 = 0.f, mw[W], lw[W];
+        for (int w = 0; w < FLOW_WAVES; ++w) { mw[w] = lds.att.m[h][w >> 2][w & 3]; lw[w] = lds.att.l[h][w >> 2][w & 3]; M = fmaxf(M, mw[w]); }
 #pragma unroll
-            for (int w = 0; w < W; ++w) { mw[w] = lds.att.m[h][w >> 2][w & 3]; lw[w] = lds.att.l[h][w >> 2][w & 3]; M = fmaxf(M, mw[w]); }
-#pragma unroll
-            for (int w = 0; w < W; ++w) {
-                const float by = __expf(mw[w] - M);
-                const float2 ow = *reinterpret_cast<const float2 *>(&lds.att.o[w][h][d]);
-                const bool none = mw[w] == -INFINITY;   // a wavefront without keys: its sums are whatever the LDS held
-                L = fmaf(lw[w], by, L);
-                O0 = none ? O0 : fmaf(ow.x, by, O0); O1 = none ? O1 : fmaf(ow.y, by, O1);
-            }
-            if (parts > 1) {
-                flow_store(buf, at_p + h * p_head + d * 4, O0, O1);
-                if (d == 0) flow_store(buf, at_p + h * p_head + DH * 4, M, L);
-            } else attention_out(f, at_o + (h * DH + d) * 2, o_plane, O0, O1, L);
+        for (int w = 0; w < FLOW_WAVES; ++w) {
+            const float by = __expf(mw[w] - M);
+            const float2 ow = *reinterpret_cast<const float2 *>(&lds.att.o[w][h][d]);
+            const bool none = mw[w] == -INFINITY;   // a wavefront without keys: its sums are whatever the LDS held
+            L = fmaf(lw[w], by, L);
+            O0 = none ? O0 : fmaf(ow.x, by, O0); O1 = none ? O1 : fmaf(ow.y, by, O1);
         }
+        if (parts > 1) {
+            flow_store(buf, at_p + h * p_head + d * 4, O0, O1);
+            if (d == 0) flow_store(buf, at_p + h * p_head + DH * 4, M, L);
+        } else attention_out(f, at_o + (h * DH + d) * 2, o_plane, O0, O1, L);
     }
     // two dims of the attention output as operand parts
     __device__ __forceinline__ void attention_out(const F &f, uint32_t at, uint32_t plane, float O0, float O1, float L) const
@@ -195,7 +192,7 @@ struct FlowAttention {
     // the parts of `heads` heads of a row put together, two dims a thread (at most 1024)
     __device__ __forceinline__ void merge(int l, int r, int head, int heads) const
     {
-        static_assert(2 * 64 * W >= 1024, "");
+        static_assert(2 * 64 * FLOW_WAVES >= 1024, "");
         const F &f = self();
         const auto &a = f.a;
         const auto buf = f.buf;

@@ -52,7 +52,7 @@ struct FlowArgs {
 
 // RC: rows the operands are laid out for (1, 2, 4, 8); a.R of them exist
 template <int RC, int DH>
-struct Flow : FlowAttention<Flow<RC, DH>, DH, 16, RC <= 4 ? 3 : 2, FLOW_WAVES, DH == 64 ? 3 : 1> {
+struct Flow : FlowAttention<Flow<RC, DH>, DH, 16, RC <= 4 ? 3 : 2, DH == 64 ? 3 : 1> {
     static constexpr int NP = RC <= 4 ? 3 : 2;            // parts
     static constexpr int NC = NP * RC;                     // columns of a stored operand: part * RC + row
     static constexpr int PV = RC == 1 ? 2 : 4;             // columns of a piece: what a lane brings of a row at a time
@@ -69,7 +69,7 @@ struct Flow : FlowAttention<Flow<RC, DH>, DH, 16, RC <= 4 ? 3 : 2, FLOW_WAVES, D
             f32x4 red[FLOW_WAVES][FLOW_UNITS][4][NC | 1];  // sums of a wavefront's share (odd: no bank conflicts)
             float ss[RC][FLOW_WAVES];                      // sums of squares of a wavefront's share
         } g;
-        FlowAttentionLds<DH, FLOW_WAVES> att;
+        FlowAttentionLds<DH> att;
     };
     const FlowArgs &a;
     Lds &lds;

@@ -1,4 +1,4 @@
-// All layers of a decode step of 9 to 64 rows in ONE launch (bf16 models of up to 1024 columns, bf16 cache).
+// All layers of a decode step of 9 to 64 rows in ONE launch (bf16 models of up to 896 columns, bf16 cache).
 //
 // The tasks, the way outputs are handed on and the order that lets the launch end are those of flow_kernels.hip. What differs is the work of a task: with this many rows a
 // compute unit is bound by the activations it has to fetch (229 KB for 64 rows of 896 columns as hi and lo parts), so a task takes 16 rows (gate and up: 16 or 32) and few
@@ -19,7 +19,7 @@
 
 namespace tr {
 
-constexpr int FR_W = 8;        // wavefronts of a workgroup
+constexpr int FR_W = FLOW_WAVES;   // wavefronts of a workgroup
 constexpr int FR_NS = 4;       // steps of 32 columns per wavefront: up to 1024 columns
 constexpr int FR_NSO = 4;      // of the output projection: up to 1024
 constexpr int FR_NSD = 20;     // of the FFN output, per round: 5120 columns
@@ -58,11 +58,11 @@ __device__ __forceinline__ float flow_rows_by(float sq) { return sq < INFINITY ?
 
 // QU, OU: groups of 16 weight rows of a q|k|v and of an output projection task; PAIR: groups of 16 rows of a gate/up task; GU: its groups of 8 gate and 8 up rows; DR: rows of an FFN output task (16 or 8)
 template <int DH, int QU, int OU, int PAIR, int GU, int DR>
-struct FlowRows : FlowAttention<FlowRows<DH, QU, OU, PAIR, GU, DR>, DH, 256, 2, FR_W, FR_U<DH>> {
+struct FlowRows : FlowAttention<FlowRows<DH, QU, OU, PAIR, GU, DR>, DH, 256, 2, FR_U<DH>> {
     static constexpr int MOST = PAIR * GU;
     union Lds {
         struct { f32x4 red[FR_W][MOST][64]; float ss[PAIR][FR_W][16]; } g;
-        FlowAttentionLds<DH, FR_W> att;
+        FlowAttentionLds<DH> att;
     };
     static_assert(PAIR == 1 || PAIR == 2, "");
     static_assert(MOST >= QU && MOST >= OU, "");

@@ -60,9 +60,9 @@ struct Layout {
     size_t flow_buf, flow_ticket, given_up;
 };
 
-// Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists (and the step is not one launch, run_step_of_few, which takes
-// 0.32 to 0.51 ms from 1 to 8 rows). Measured decode step of the 0.5B-class model (context 256): 0.64 ms at 1 row and 0.69 at 2 on the streaming kernels, which then
-// climb to 1.15 (3 rows), 1.26 (4) and 1.40 (8); 0.81 to 0.83 from 3 to 8 rows on the kernels for these, 0.93 from 9 to 32 on the others.
+// Up to this many rows the streaming GEMV kernels are used where the matrix-core path exists and the step is not one launch (run_step_of_few: 0.32 to 0.51 ms from 1 to
+// 8 rows of the 0.5B-class model, 0.44 to 0.76 from 9 to 64). A launch per link, its decode step at context 256: 0.64 ms at 1 row and 0.69 at 2 on the streaming
+// kernels, which then climb to 1.15 (3 rows), 1.26 (4) and 1.40 (8); 0.81 to 0.83 from 3 to 8 rows on the kernels for these, 0.93 from 9 to 32 on the others.
 constexpr int GEMV_MAX_ROWS = 2;
 
 // The matrix-core kernels keep 896 columns of K per workgroup resident, and the layers with a non-linear
