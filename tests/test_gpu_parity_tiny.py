@@ -188,7 +188,7 @@ def test_tiny_run_twice_is_bit_identical(tr, tiny_weights):
 
 @pytest.mark.parametrize("B", [9, 33, 70, 256])
 def test_small_bf16_model_on_the_matrix_core_path(tr, tro, B):
-    """bf16 weights and 3 or more rows take the MFMA kernels: batches of 9 (one column block), 33 (two) and 70 (two row
+    """bf16 weights and 3 or more rows take the MFMA kernels: batches of 9 and 33 (steps in one launch), 70 (two row
     groups) and 256 (four row groups, the LM head's XCD-aware placement), ragged prompts up to several 64-row groups,
     non-zero biases, non-unit gains."""
     s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
@@ -211,12 +211,12 @@ def test_small_bf16_model_on_the_matrix_core_path(tr, tro, B):
         assert g.seq_len(slot) == lens[i] + 4 and cnt[slot][0] == 5
 
 
-@pytest.mark.parametrize("B,ctx", [(3, 1200), (1, 4500), (12, 2300), (40, 900)])
-def test_small_bf16_model_long_contexts(tr, tro, B, ctx):
-    """Long loaded caches with a bf16 KV cache: several parts of a row's context (1 and 3 rows: tasks of one launch; 12 and 40 rows: merged by
-    a separate kernel or the batched merge), three blocks of keys a wavefront past 4096 positions, contexts of very
+@pytest.mark.parametrize("B,ctx,d_model", [(3, 1200, 256), (1, 4500, 256), (12, 2300, 256), (40, 900, 256), (12, 2300, 240), (40, 900, 240)])
+def test_small_bf16_model_long_contexts(tr, tro, B, ctx, d_model):
+    """Long loaded caches with a bf16 KV cache: several parts of a row's context (tasks of one launch; with a width that is no multiple of 32, merged by
+    the workgroup that finishes last), three blocks of keys a wavefront past 4096 positions, contexts of very
     different lengths in one call, and decoding right up to the last position of the cache (max_seq not a multiple of 32)."""
-    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
+    s = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16, d_model=d_model)
     w = synth.make_weights(s, SEED + 4, std=0.05, bias_std=0.05, gain_std=0.1)
     max_seq = ctx + 3
     g = tr.Model(s.asdict(), w, B, max_seq); o = tro.Model(s.asdict(), w, B, max_seq)
