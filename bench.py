@@ -408,8 +408,8 @@ def measured_traffic(family):
 # run (see profiles/); bytes per launch, per kernel family, with the hash of the kernel sources they were taken on.
 TRAFFIC = {
     # all 24 layers: 12 times the launch of the 2-layer model
-    "layers": {"source_sha256": "66116eeb3d8d15e79902f0a68a20d49b198f95fa93dd7d3e027afc10588cde3c", "fetch_bytes": 2554624784, "write_bytes": 80240640},
-    "lmhead": {"source_sha256": "66116eeb3d8d15e79902f0a68a20d49b198f95fa93dd7d3e027afc10588cde3c", "fetch_bytes": 274890407, "write_bytes": 322560},
+    "layers": {"source_sha256": "e816debad0d7bfeaf48faf65112a955fc71997c88ba7439e7cd99ea39c28227e", "fetch_bytes": 2468735736, "write_bytes": 80202240},
+    "lmhead": {"source_sha256": "e816debad0d7bfeaf48faf65112a955fc71997c88ba7439e7cd99ea39c28227e", "fetch_bytes": 274891830, "write_bytes": 322560},
 }
 
 

@@ -9,7 +9,7 @@
 //   * Work is split over workgroups by rows and features alone, so no sum is put together by a task of its own: the 8 wavefronts of a task share K and add up through the LDS.
 //     Only long contexts are split (flow_rows_split), merged by tasks of their own.
 // What bounds it: five or six hand-overs a layer and the rows that each task brings from the L2; 64 rows take 28 us a layer where their bytes take 10 at the copy rate.
-// 0.5B-class model, a launch per link / here: 64 rows after 128 to 1024 keys 1132 / 763 us a step.
+// 0.5B-class model, a launch per link / here: 64 rows after 128 to 1024 keys 1132 / 760 us a step.
 #include "flow_attention.h"
 #include <algorithm>
 #include <numeric>
@@ -575,7 +575,8 @@ size_t flow_rows_floats(const Dims &D, int max_rows)
 // FLOW_ROWS_PARTS is what the table of parts has room for: the launch is still the faster one there. 6 layers, all rows after as many keys, a launch per link / here: 896 columns with
 // 2 kv heads, 9 rows after 16 keys 206 / 117 us, 64 after 3071 374 / 307; 128-wide heads, 64 rows after 1023 326 / 235; 256 columns with 16 kv heads, 64 rows after 769 481 / 431,
 // after 2312 886 / 879 (a merge per kv head and not per row: 498, 946), 9 rows after 21503 1215 / 991. Not so only where 14 to 16 rows of 1024 key columns all have more than 9000 keys
-// (3900 of 128-wide heads) and both are bound by the cache: 16 rows after 12287 987 / 1012; with contexts of 1500 to 12287 809 / 636.
+// (3900 of 128-wide heads) and both are bound by the cache: 16 rows after 12287 987 / 1012, with contexts of 1500 to 12287 809 / 636; and for 64 rows of 32 columns with two rounds
+// of the FFN output (0.97 after 23 keys, 1.03 after 253).
 bool flow_rows_takes(const Dims &D, int R, const int *poss, FlowRowsPlan *p)
 {
     if (R <= FLOW_MAX_ROWS || R > FLOW_ROWS_MAX || !flow_rows_ffn(D, R) || !flow_rows_split(D, R, poss, p)) return false;
