@@ -214,6 +214,12 @@ int tr_tail_noalloc(tr_ctx *ctx, void *hip_stream, int32_t n, const float *x, co
 int tr_set_threshold(tr_ctx *ctx, float threshold);
 int tr_set_mode(tr_ctx *ctx, int32_t mode);
 
+/* Whether work of other streams is to run beside this context's steps (0, the default, or 1); applies to calls made afterwards. A decode
+ * step in one launch holds every compute unit until it ends, so that a chain of kernels on another stream gets little further than
+ * between two steps. With 1 steps keep a launch per link and share the GPU (infrastructure; a step alone takes longer that way). Steps of
+ * 3 and 4 rows and fp32 models stay as they are: a launch per link would carry fewer bits of their activations, or gain nothing. */
+int tr_set_shared(tr_ctx *ctx, int32_t shared);
+
 /* Host-side sequence state (infrastructure; the paper's request only carries the position as "token_index",
  * Figure 5). tr_seq_len: number of cached tokens of a slot (0 for a slot never filled). tr_seq_truncate rolls a
  * slot back to its first new_len tokens, 0 <= new_len <= length (a paged cache gives the freed pages back):

@@ -252,6 +252,7 @@ struct tr_ctx {
     int32_t *scatter = nullptr;
     float threshold;
     int mode;
+    bool shared = false;    // tr_set_shared
     std::string err;
     // kernel timing: while enabled, ONE launch of the selected kernel family per call is bracketed by events (the launches of
     // the family take turns from call to call, so that every layer is sampled)
@@ -648,7 +649,10 @@ bool run_step_of_few(tr_ctx *ctx, hipStream_t s, int R, int max_ctx, const int *
     const Dims &D = ctx->D;
     const Layout &L = ctx->lay;
     FlowRowsPlan plan{};
-    if (L.flow && (flow_takes(D, R, max_ctx) || flow_rows_takes(D, R, poss, &plan))) {
+    // Beside another stream's work (tr_set_shared) a launch per link: the launch holds all registers of every compute unit. Steps of the 0.5B-class
+    // model beside 6-row steps of the 7B-class one, each again and again, in one launch / a launch per link: 64 rows 0.78 / 3.1 ms and 37.5 / 4.0 ms a step of the large
+    // model (alone 0.72 / 1.05 and 3.6), 8 rows 0.50 / 2.5 and 21.4 / 3.9; two models of 64 rows each 1.40 / 1.29 ms a step. (3 and 4 rows: 24 bits against 16.)
+    if (L.flow && (!ctx->shared || R == 3 || R == 4) && (flow_takes(D, R, max_ctx) || flow_rows_takes(D, R, poss, &plan))) {
         float *part = nullptr;
         int pending;
         float *x = run_flow(ctx, s, plan, R, max_ctx, slots, toks, poss, dev_toks, &part, &pending);
@@ -932,6 +936,14 @@ int tr_set_mode(tr_ctx *ctx, int32_t mode)
     if (!ctx) return TR_ERR_INVALID_ARG;
     if (mode != TR_JOINT && mode != TR_SMALL_ONLY) return fail(ctx, TR_ERR_INVALID_ARG, "tr_set_mode: unknown mode");
     ctx->mode = mode;
+    return TR_OK;
+}
+
+int tr_set_shared(tr_ctx *ctx, int32_t shared)
+{
+    if (!ctx) return TR_ERR_INVALID_ARG;
+    if (shared != 0 && shared != 1) return fail(ctx, TR_ERR_INVALID_ARG, "tr_set_shared: 0 or 1");
+    ctx->shared = shared != 0;
     return TR_OK;
 }
 

@@ -59,7 +59,7 @@ def generate_overlapped(slm, llm, prompts, max_new: int):
 
     The large model runs on a stream of its own, one call at a time, on every sequence that is waiting when the previous call
     has finished (prefill for a sequence's first call, catch-up segments afterwards); the small model steps the sequences that
-    are not waiting. What a sequence emits does not depend on the schedule (each of its positions is still the small model's
+    are not waiting, while a call of the large model is under way with steps that leave it compute units (Model.set_shared). What a sequence emits does not depend on the schedule (each of its positions is still the small model's
     token unless the router flags it, and the large model's otherwise), only the order in which the sequences advance does.
     Returns (tokens, routed) like `generate`.
     """
@@ -93,7 +93,7 @@ def generate_overlapped(slm, llm, prompts, max_new: int):
             else:
                 emit(b, out.token[i], False)
 
-    start = torch.cuda.current_stream()
+    start, was_shared = torch.cuda.current_stream(), slm.shared
     s_small.wait_stream(start); s_large.wait_stream(start)
     with torch.cuda.stream(s_small):
         take(list(range(B)), slm.prefill(list(range(B)), prompts).cpu(NEEDED, stream_only=True))
@@ -122,7 +122,9 @@ def generate_overlapped(slm, llm, prompts, max_new: int):
             pending = []
         run = [b for b in range(B) if running[b]]
         if run:
+            slm.set_shared(was_shared or inflight is not None)
             with torch.cuda.stream(s_small):
                 take(run, slm.decode_step(run, next_tok[run]).cpu(NEEDED, stream_only=True))
+    slm.set_shared(was_shared)
     start.wait_stream(s_small); start.wait_stream(s_large)
     return tokens, routed

@@ -24,7 +24,7 @@ POST_FINAL_NORM, PRE_FINAL_NORM = 0, 1
 KERNEL_FAMILIES = ("setup", "prep", "qkv", "attention", "oproj", "gateup", "down", "lmhead", "tail_merge", "qkv_attention", "layers")   # TR_KERNEL_*
 
 EXPORTS = ["tr_workspace_bytes", "tr_create", "tr_destroy", "tr_prefill", "tr_decode_step", "tr_decode_step_dev", "tr_decode_step_active", "tr_extend", "tr_tail", "tr_tail_noalloc", "tr_set_threshold",
-           "tr_set_mode", "tr_seq_len", "tr_seq_truncate", "tr_seq_fork", "tr_seq_load_kv", "tr_counters_ptr", "tr_profile_enable", "tr_profile_select",
+           "tr_set_mode", "tr_set_shared", "tr_seq_len", "tr_seq_truncate", "tr_seq_fork", "tr_seq_load_kv", "tr_counters_ptr", "tr_profile_enable", "tr_profile_select",
            "tr_profile_read", "tr_profile_chain", "tr_last_error"]
 
 
@@ -73,6 +73,7 @@ def load_library():
         L.tr_tail_noalloc.argtypes = [vp, vp, i32, vp, C.POINTER(tr_out)]
         L.tr_set_threshold.argtypes = [vp, f32]
         L.tr_set_mode.argtypes = [vp, i32]
+        L.tr_set_shared.argtypes = [vp, i32]
         L.tr_seq_len.argtypes = [vp, i32, C.POINTER(i32)]
         L.tr_seq_truncate.argtypes = [vp, i32, i32]
         L.tr_seq_fork.argtypes = [vp, vp, i32, i32]
@@ -166,6 +167,7 @@ class Model:
             raise TokrouteError(ERR_SHAPE, "tr_workspace_bytes", "(configuration not supported)")
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=device)
         self._h = C.c_void_p()
+        self.shared = False
         rc = self.lib.tr_create(C.byref(self.cfg), C.byref(w), self.workspace.data_ptr(), nbytes, C.byref(self._h))
         if rc:
             raise TokrouteError(rc, "tr_create")
@@ -263,6 +265,11 @@ class Model:
 
     def set_mode(self, m):
         self._check(self.lib.tr_set_mode(self._h, int(m)), "tr_set_mode")
+
+    def set_shared(self, shared):
+        """Whether other streams' work is to run beside this model's steps (False at first)."""
+        self._check(self.lib.tr_set_shared(self._h, int(bool(shared))), "tr_set_shared")
+        self.shared = bool(shared)
 
     def seq_len(self, slot):
         v = C.c_int32()

@@ -70,6 +70,26 @@ def in_one_launch(model, step):
     return n == 1, out
 
 
+@pytest.mark.parametrize("rows,one", [(2, False), (3, True), (4, True), (8, False), (9, False), (64, False)])
+def test_steps_beside_other_streams_keep_a_launch_per_link(rows, one):
+    from oracle import tro
+    from paper_2504_07878_amd import tokroute as tr
+    s = synth.TINY.with_(name="shared", **BASE)
+    w = synth.make_weights(s, SEED + 9, std=0.05)
+    g, o = tr.Model(s.asdict(), w, 64, 8), tro.Model(s.asdict(), w, 64, 8)
+    slots, toks = list(range(rows)), synth.prompt_tokens(SEED, "shared", rows, s.vocab)
+    for m in (g, o):
+        m.prefill(slots, [toks[i:i + 1] for i in range(rows)])
+    exempt = 0
+    for shared in (False, True, False):
+        g.set_shared(shared)
+        assert g.lib.tr_set_shared(g._h, 2) == tr.ERR_INVALID_ARG
+        was, go = in_one_launch(g, lambda: g.decode_step(slots, toks, want_logits=True).cpu())
+        assert was == (one or not shared)
+        exempt += compare_outputs(go, o.decode_step(slots, toks, want_logits=True), s.dtype, s.threshold, f"{rows} rows, shared {shared}")
+    assert exempt <= 1
+
+
 @pytest.mark.parametrize("shape,rows,longest,page", [({}, 64, 3072, 0), (dict(head_dim=128, n_q_heads=4, n_kv_heads=2), 64, 1024, 32), ({}, 16, 12288, 64), ({}, 9, 21504, 0)])
 def test_limit_of_parts(shape, rows, longest, page):
     """256 parts of contexts in one launch at most (rows x parts of the longest): a step at the limit, 28 parts of 9 rows among them, and the next one, a launch per link."""

@@ -66,3 +66,31 @@ def test_joint_decoding_matches_the_plain_loop(tr, tro, dtype, overlapped):
     cnt = slm.counters()
     for b in range(B):
         assert cnt[b][0] == max_new and cnt[b][1] >= routed[b, 1:].sum()      # one small-model step per emitted token
+
+
+def test_overlapped_schedule_leaves_the_large_model_compute_units(tr):
+    """Steps beside a call of the large model share the GPU with it, others do not. The model is left as it was."""
+    from paper_2504_07878_amd import joint
+    shape = synth.TINY.with_(dtype=synth.BF16, kv_dtype=synth.BF16)
+    w = synth.make_weights(shape, SEED + 10, std=0.05)
+    slm, llm = (tr.Model(shape.asdict(), w, 12, 128, **kw) for kw in (dict(), dict(route_policy=tr.POLICY_CONFIDENCE)))
+    calls = []
+
+    def noted(model, name, what):
+        call = getattr(model, name)
+        setattr(model, name, lambda *a, **k: (calls.append(what()), call(*a, **k))[1])
+
+    noted(slm, "decode_step", lambda: ("step", slm.shared))
+    noted(llm, "prefill", lambda: ("large", None))
+    noted(llm, "extend", lambda: ("large", None))
+    prompts = [synth.prompt_tokens(SEED, f"beside.{b}", 9, shape.vocab) for b in range(12)]
+    scores = np.sort(np.concatenate([slm.prefill(list(range(12)), prompts).cpu().score]))
+    for threshold, shared in ((0.0, False), (float(scores[6]), True)):   # nothing routed; about half
+        calls.clear()
+        slm.set_threshold(threshold)
+        joint.generate_overlapped(slm, llm, prompts, 12)
+        steps = [c for c in calls if c[0] == "step"]
+        assert steps and any(c[1] for c in steps) == shared
+        if shared:   # six of the prompts' tokens are the large model's: the other sequences go on beside it
+            assert calls[0][0] == "large" and calls[1] == ("step", True)
+        assert not slm.shared
